@@ -320,8 +320,8 @@ int mpm_mlp_grad(void* state_dev, const float* samples_dev, int64_t n, int32_t b
                  float* grad_out_dev, double* loss_out_host, void* stream);
 /* mpm_mlp_grad for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
- * the per-sample scratch is a static device array of the library, sized for
- * MPM_MLP_NOALLOC_MAX_BATCH records (2.2 MB, held by each device the
+ * the scratch is a static device array of the library, sized for
+ * MPM_MLP_NOALLOC_MAX_BATCH records (1.7 MB, held by each device the
  * library runs on until the process ends), instead of a caller buffer.
  * min(n, batch) above the maximum returns MPM_EWORKSPACE and does nothing.
  * The call allocates nothing.  Every call on one device shares that

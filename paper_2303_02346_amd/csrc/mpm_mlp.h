@@ -68,13 +68,11 @@ struct MlpScratch {
 };
 
 // Forward of the 64 samples held by the lanes of one wavefront (lane l holds
-// sample l).  Every lane must call it.  Optionally returns the BF16-rounded
-// hidden activations of the lane's sample (as the next layer consumed them).
+// sample l).  Every lane must call it.
 // Matrix-core layout of v_mfma_f32_16x16x16_bf16 (a 16-sample row block):
 //   A[row = l % 16][k = 4 (l / 16) + q], B[k = 4 (l / 16) + q][col = l % 16],
 //   D[row = 4 (l / 16) + q][col = l % 16],  q = 0..3.
-__device__ inline void mlp_wave_forward(const MlpBlob& W, const float* x, float* y, MlpScratch& S,
-                                        float* h1_out = nullptr, float* h2_out = nullptr) {
+__device__ inline void mlp_wave_forward(const MlpBlob& W, const float* x, float* y, MlpScratch& S) {
   const int l = __lane_id();
   const int lr = l & 15, lg = l >> 4;
   float xn[MLP_IN];
@@ -117,13 +115,6 @@ __device__ inline void mlp_wave_forward(const MlpBlob& W, const float* x, float*
     for (int kt = 0; kt < 4; kt++)
 #pragma unroll
       for (int q = 0; q < 4; q++) a2[kt][q] = (short)S.h[lr * MLP_HROW + 16 * kt + 4 * lg + q];
-    if (h1_out) {
-      // the lane's own sample, if it lies in this row block
-      if ((l >> 4) == rb) {
-#pragma unroll
-        for (int k = 0; k < MLP_H; k++) h1_out[k] = bf2f(S.h[(l & 15) * MLP_HROW + k]);
-      }
-    }
     wave_lds_sync();
     f32x4_t c2[4];
 #pragma unroll
@@ -154,12 +145,6 @@ __device__ inline void mlp_wave_forward(const MlpBlob& W, const float* x, float*
     for (int kt = 0; kt < 4; kt++)
 #pragma unroll
       for (int q = 0; q < 4; q++) a3[kt][q] = (short)S.h[lr * MLP_HROW + 16 * kt + 4 * lg + q];
-    if (h2_out) {
-      if ((l >> 4) == rb) {
-#pragma unroll
-        for (int k = 0; k < MLP_H; k++) h2_out[k] = bf2f(S.h[(l & 15) * MLP_HROW + k]);
-      }
-    }
     f32x4_t c3 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kt = 0; kt < 4; kt++) {

@@ -1,17 +1,18 @@
 // Training and batch inference of the learned cone-return closure
 // (6 -> 64 -> 64 -> 3 MLP, ReLU).  The forward runs on the matrix cores in
-// BF16 with FP32 accumulation (mlp_wave_forward); the backward and Adam run
+// BF16 with FP32 accumulation; the backward (FP32 matrix cores) and Adam run
 // in FP32.  Loss: mean squared error of the normalised outputs.
 //
 // State layout (device, caller-owned, mpm_mlp_state_bytes()):
 //   params  FP32 [MLP_NPARAM]   master weights W1 b1 W2 b2 W3 b3 (row-major [out][in])
 //   adam_m  FP32 [MLP_NPARAM]
 //   adam_v  FP32 [MLP_NPARAM]
-//   grad    FP32 [MLP_NPARAM]
+//   grad    FP32 [MLP_NPARAM]   sums of the normalisation statistics (initialisation only)
 //   misc    FP64 [8]            loss accumulator, step count
 //   blob    MlpBlob             inference copy (normalisation, FP32 biases, BF16 weights)
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <string.h>
 #include <mutex>
@@ -43,14 +44,15 @@ MlpLayout mlp_layout() {
   return L;
 }
 constexpr int SAMPLE = MLP_IN + MLP_OUT;   // floats per logged sample
-// per-sample backward scratch: xn 6, dy 3 (slots 6..8), pad, h1 64, h2 64,
-// dh1 64, dh2 64 (from slot 12)
-constexpr int HDR = 12;
-constexpr int SCR = HDR + 4 * MLP_H;
 }  // namespace
 
-// normalisation statistics (mean, std) of the 9 sample columns, FP64 sums
-__global__ void k_mlp_stats(const float* __restrict__ samples, long long n, double* __restrict__ acc) {
+// normalisation statistics (mean, std) of the 9 sample columns, FP64 sums:
+// reduced over the workgroup before the atomics, of which there are then 18
+// per workgroup (18 per wavefront of 256 workgroups took 113 us for 131072
+// samples, all of it the queue at the 18 addresses)
+__global__ __launch_bounds__(1024) void k_mlp_stats(const float* __restrict__ samples, long long n,
+                                                    double* __restrict__ acc) {
+  __shared__ double s_w[16][2 * SAMPLE];
   double s[SAMPLE], q[SAMPLE];
 #pragma unroll
   for (int c = 0; c < SAMPLE; c++) { s[c] = 0.0; q[c] = 0.0; }
@@ -58,10 +60,19 @@ __global__ void k_mlp_stats(const float* __restrict__ samples, long long n, doub
 #pragma unroll
     for (int c = 0; c < SAMPLE; c++) { double v = samples[i * SAMPLE + c]; s[c] += v; q[c] += v * v; }
   }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int c = 0; c < SAMPLE; c++) {
+#pragma unroll
     for (int off = 32; off > 0; off >>= 1) { s[c] += __shfl_xor(s[c], off); q[c] += __shfl_xor(q[c], off); }
-    if ((threadIdx.x & 63) == 0) { atomicAdd(acc + c, s[c]); atomicAdd(acc + SAMPLE + c, q[c]); }
+    if (lane == 0) { s_w[wv][c] = s[c]; s_w[wv][SAMPLE + c] = q[c]; }
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * SAMPLE) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; w++) t += s_w[w][threadIdx.x];
+    atomicAdd(acc + threadIdx.x, t);
   }
 }
 
@@ -105,136 +116,423 @@ __global__ void k_mlp_publish(const float* __restrict__ p, MlpBlob* __restrict__
   }
 }
 
-// Forward (matrix cores) and per-sample backward of a batch.  One sample
-// per thread, 256 threads; samples i0 .. i0 + nb - 1 (indices wrap at n).
-// Writes the per-sample activations and adjoints to scr for the weight
-// gradient kernel and adds the batch loss to misc[0].
-__global__ __launch_bounds__(256) void k_mlp_batch(const MlpBlob* __restrict__ blob, const float* __restrict__ samples,
-                                                   long long n, long long i0, int nb, float* __restrict__ scr,
-                                                   double* __restrict__ misc, float* __restrict__ y_out) {
-  __shared__ MlpBlob W;
-  __shared__ MlpScratch S[4];
-  {
-    const uint32_t* src = (const uint32_t*)blob;
-    uint32_t* dst = (uint32_t*)&W;
-    for (int q = threadIdx.x; q < (int)(sizeof(MlpBlob) / 4); q += 256) dst[q] = src[q];
+// ---------------------------------------------------------------------------
+// The network on 16 samples per wavefront (the row block of one 16x16 MFMA
+// tile; lane (lr, lg) = (lane % 16, lane / 16)), every weight fragment in
+// registers: 24 fragments of 4 BF16 values, loaded once per wavefront with
+// 8-byte loads and used for every row block it works through.  (Staging the
+// 13 KB of weights in LDS for each workgroup instead costs the staging and
+// 16-way bank conflicts: the rows are 128 bytes.)
+// ---------------------------------------------------------------------------
+struct MlpFrag {
+  bf16x4_t w1[4], w2[4][4], w3[4];   // [16-output tile]([16-input tile])
+  float b1[4], b2[4], b3;
+};
+
+__device__ __forceinline__ bf16x4_t load_frag(const uint16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  union { uint2 u; bf16x4_t b; } c;
+  c.u = v;
+  return c.b;
+}
+
+__device__ __forceinline__ void load_frags(const MlpBlob* __restrict__ W, int lr, int lg, MlpFrag& F) {
+  static_assert(offsetof(MlpBlob, W1) % 8 == 0 && offsetof(MlpBlob, W2) % 8 == 0 && offsetof(MlpBlob, W3) % 8 == 0,
+                "8-byte fragment loads");
+#pragma unroll
+  for (int nt = 0; nt < 4; nt++) {
+    F.w1[nt] = load_frag(W->W1 + (16 * nt + lr) * MLP_K1 + 4 * lg);
+    F.w3[nt] = load_frag(W->W3 + lr * MLP_H + 16 * nt + 4 * lg);
+    F.b1[nt] = W->b1[16 * nt + lr];
+    F.b2[nt] = W->b2[16 * nt + lr];
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) F.w2[nt][kt] = load_frag(W->W2 + (16 * nt + lr) * MLP_H + 16 * kt + 4 * lg);
   }
-  __syncthreads();
-  const int b = blockIdx.x * 256 + threadIdx.x;        // sample slot in the batch
+  F.b3 = W->b3[lr];
+}
+
+// LDS row stride of a sample's 64 activations: rows stay 16-byte aligned and
+// begin 4 banks apart
+constexpr int HS = 68;
+
+// One layer's input fragments from the wavefront's 16 LDS rows (the values are
+// already rounded to BF16, so the upper half is exact).
+__device__ __forceinline__ void frags_from_rows(const float* H, int lr, int lg, bf16x4_t* a) {
+#pragma unroll
+  for (int kt = 0; kt < 4; kt++) {
+    const float4 v = *reinterpret_cast<const float4*>(H + lr * HS + 16 * kt + 4 * lg);
+    a[kt][0] = (short)(__float_as_uint(v.x) >> 16);
+    a[kt][1] = (short)(__float_as_uint(v.y) >> 16);
+    a[kt][2] = (short)(__float_as_uint(v.z) >> 16);
+    a[kt][3] = (short)(__float_as_uint(v.w) >> 16);
+  }
+}
+
+// Forward of the wavefront's 16 samples: x = the 6 inputs of sample lr (every
+// lane of a sample's group holds them).  H1, H2: the wavefront's LDS rows,
+// left with the BF16-rounded activations; h1, h2: the same in the lane's
+// accumulator places (sample 4 lg + q, unit 16 nt + lr); Y: 16 rows of 4 floats,
+// left with the normalised outputs.
+__device__ __forceinline__ void mlp_rows16(const MlpBlob* __restrict__ W, const MlpFrag& F, const float* xn, int lr,
+                                           int lg, float* H1, float* H2, float* Y, f32x4_t* h1, f32x4_t* h2) {
+  bf16x4_t a1;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    float v = lg == 0 ? xn[q] : (lg == 1 && q < 2 ? xn[(4 + q) % MLP_IN] : 0.f);
+    a1[q] = (short)f2bf(v);
+  }
+#pragma unroll
+  for (int nt = 0; nt < 4; nt++) {
+    f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, F.w1[nt], c, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      h1[nt][q] = bf2f(f2bf(fmaxf(c[q] + F.b1[nt], 0.f)));
+      H1[(4 * lg + q) * HS + 16 * nt + lr] = h1[nt][q];
+    }
+  }
+  wave_lds_sync();
+  bf16x4_t a[4];
+  frags_from_rows(H1, lr, lg, a);
+#pragma unroll
+  for (int nt = 0; nt < 4; nt++) {
+    f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[kt], F.w2[nt][kt], c, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      h2[nt][q] = bf2f(f2bf(fmaxf(c[q] + F.b2[nt], 0.f)));
+      H2[(4 * lg + q) * HS + 16 * nt + lr] = h2[nt][q];
+    }
+  }
+  wave_lds_sync();
+  frags_from_rows(H2, lr, lg, a);
+  f32x4_t c3 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < 4; kt++) c3 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[kt], F.w3[kt], c3, 0, 0, 0);
+  if (lr < MLP_OUT) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) Y[(4 * lg + q) * 4 + lr] = c3[q] + F.b3;
+  }
+  wave_lds_sync();
+}
+
+// Denormalised outputs of one sample, shifted equally onto the inputs' trace.
+__device__ __forceinline__ void mlp_outputs(const MlpBlob* __restrict__ W, const float* x, const float* Yrow, float* y) {
+#pragma unroll
+  for (int o = 0; o < MLP_OUT; o++) y[o] = Yrow[o] * W->out_std[o] + W->out_mean[o];
+  const float dtr = ((x[0] + x[1] + x[2]) - (y[0] + y[1] + y[2])) * (1.f / 3.f);
+#pragma unroll
+  for (int o = 0; o < MLP_OUT; o++) y[o] += dtr;
+}
+
+// Batch inference, one wavefront per 16 records at a time.
+__global__ __launch_bounds__(256) void k_mlp_predict(const MlpBlob* __restrict__ W, const float* __restrict__ samples,
+                                                     long long n, float* __restrict__ y_out) {
+  __shared__ __align__(16) float sH[4][2][16 * HS];
+  __shared__ __align__(16) float sY[4][16 * 4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
+  MlpFrag F;
+  load_frags(W, lr, lg, F);
+  for (long long r0 = ((long long)blockIdx.x * 4 + wv) * 16; r0 < n; r0 += (long long)gridDim.x * 64) {
+    const bool has = r0 + lr < n;
+    const float* rec = samples + (has ? r0 + lr : r0) * SAMPLE;
+    float x[MLP_IN], xn[MLP_IN];
+#pragma unroll
+    for (int c = 0; c < MLP_IN; c++) x[c] = rec[c];
+#pragma unroll
+    for (int c = 0; c < MLP_IN; c++) xn[c] = (x[c] - W->in_mean[c]) / W->in_std[c];
+    f32x4_t h1[4], h2[4];
+    mlp_rows16(W, F, xn, lr, lg, sH[wv][0], sH[wv][1], sY[wv], h1, h2);
+    if (lg == 0 && has) {
+      float y[MLP_OUT];
+      mlp_outputs(W, x, sY[wv] + 4 * lr, y);
+#pragma unroll
+      for (int c = 0; c < MLP_OUT; c++) y_out[(r0 + lr) * MLP_OUT + c] = y[c];
+    }
+    wave_lds_sync();
+  }
+}
+
+// A batch's gradient takes two launches: k_mlp_batch (forward and input
+// gradients per sample) and k_mlp_update (weight gradients, and in training
+// the Adam step and the published copy).  Both run their FP32 products on the
+// matrix cores: v_mfma_f32_16x16x4f32 adds its four products to the
+// accumulator as a chain of FMAs in the order of the contraction index, so a
+// weight's gradient is the sequential FP32 sum over the samples of each of 16
+// slices of the batch, the slices added in FP64 and rounded once.  At a batch of
+// 4096 the work is 140 MFLOP (1 us at the FP32 rate); the time is the latency
+// of the two launches' chains.  One thread per sample with scalar products,
+// then one thread per weight and slice reading every sample's stored
+// activations with float atomics, took 66 + 96 us per batch (and 10 us for Adam
+// and the copy in launches of their own); these take 10 + 14 us.
+//
+// Per-sample scratch of a batch of nb, structure of arrays.  Units are grouped
+// by 16 (a matrix tile's edge), so that a wavefront of k_mlp_update reads four
+// samples' 16 values of a group as 256 contiguous bytes.
+struct BatchScratch {
+  float* d1;        // [4][nb][16] adjoints of the first hidden layer's sums
+  float* d2;        // [4][nb][16] of the second's
+  float* x;         // [nb][12] normalised inputs (6), 1, 0, adjoint of the output (3), 0
+  uint16_t* h1;     // [4][nb][16] BF16 activations
+  uint16_t* h2;
+  double* loss;     // [ceil(nb / 16)] per wavefront
+};
+constexpr int XS = 12;
+constexpr size_t SCR_BYTES = 2 * MLP_H * 4 + XS * 4 + 2 * MLP_H * 2;   // per sample, without the loss
+static_assert(SCR_BYTES % 16 == 0, "alignment of the arrays");
+__host__ __device__ constexpr size_t scratch_bytes(size_t nb) { return nb * SCR_BYTES + (nb + 15) / 16 * 8; }
+__host__ __device__ inline BatchScratch scratch_of(void* base, size_t nb) {
+  char* p = (char*)base;
+  BatchScratch S;
+  S.d1 = (float*)p; p += nb * MLP_H * 4;
+  S.d2 = (float*)p; p += nb * MLP_H * 4;
+  S.x = (float*)p; p += nb * XS * 4;
+  S.h1 = (uint16_t*)p; p += nb * MLP_H * 2;
+  S.h2 = (uint16_t*)p; p += nb * MLP_H * 2;
+  S.loss = (double*)p;
+  return S;
+}
+
+// Forward and input gradients of the batch (samples i0 .. i0 + nb - 1,
+// wrapping at n), 16 samples per wavefront, one row block each, so that a batch
+// of 4096 has 256 wavefronts (two per workgroup).
+constexpr int BATCH_NT = 128;
+__global__ __launch_bounds__(BATCH_NT) void k_mlp_batch(const MlpBlob* __restrict__ W, const float* __restrict__ samples,
+                                                        long long n, long long i0, int nb, void* scr) {
+  constexpr int NW = BATCH_NT / 64;
+  __shared__ __align__(16) float sH1[NW][16 * HS], sH2[NW][16 * HS];
+  __shared__ __align__(16) float sY[NW][16 * 4], sD[NW][16 * 4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
+  const int base = (blockIdx.x * NW + wv) * 16;
+  if (base >= nb) return;
+  const BatchScratch S = scratch_of(scr, (size_t)nb);
+  const int b = base + lr;                       // the sample of the lane's group
   const bool has = b < nb;
-  long long si = (i0 + (has ? b : 0)) % n;
-  float x[MLP_IN], t[MLP_OUT];
+  long long si = i0 + (has ? b : base);
+  if (si >= n) si -= n;                          // (i0 < n and nb <= n)
+  float x[MLP_IN], xn[MLP_IN], t[MLP_OUT];
 #pragma unroll
   for (int c = 0; c < MLP_IN; c++) x[c] = samples[si * SAMPLE + c];
 #pragma unroll
   for (int c = 0; c < MLP_OUT; c++) t[c] = samples[si * SAMPLE + MLP_IN + c];
-  float* rec = scr ? scr + (size_t)(has ? b : 0) * SCR : nullptr;
-  float* h1 = rec ? rec + HDR : nullptr;
-  float* h2 = rec ? rec + HDR + MLP_H : nullptr;
-  float* dh1 = rec ? rec + HDR + 2 * MLP_H : nullptr;
-  float* dh2 = rec ? rec + HDR + 3 * MLP_H : nullptr;
-  float y[MLP_OUT];
-  // all lanes run the wavefront forward; lanes without a sample write to a
-  // dummy row that is never read (slot 0 is overwritten by its owner below)
-  __shared__ float s_dummy[2 * MLP_H * 4];
-  float* h1o = !scr ? nullptr : (has ? h1 : s_dummy + (threadIdx.x >> 6) * 2 * MLP_H);
-  float* h2o = !scr ? nullptr : (has ? h2 : s_dummy + (threadIdx.x >> 6) * 2 * MLP_H + MLP_H);
-  mlp_wave_forward(W, x, y, S[threadIdx.x >> 6], h1o, h2o);
-  if (y_out && has) {
+  MlpFrag F;
+  load_frags(W, lr, lg, F);
+  // W2 for dh1 = dh2 W2: rows 4 k + lg, tile nt's column lr standing for input
+  // 4 lr + nt, so that a row's four tiles are one 8-byte load
+  bf16x4_t wb[16];
 #pragma unroll
-    for (int c = 0; c < MLP_OUT; c++) y_out[(size_t)b * MLP_OUT + c] = y[c];
-  }
+  for (int k = 0; k < 16; k++) wb[k] = load_frag(W->W2 + (4 * k + lg) * MLP_H + 4 * lr);
+  float w3[4][MLP_OUT];
+#pragma unroll
+  for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+    for (int c = 0; c < MLP_OUT; c++) w3[nt][c] = bf2f(W->W3[c * MLP_H + 16 * nt + lr]);
+#pragma unroll
+  for (int c = 0; c < MLP_IN; c++) xn[c] = (x[c] - W->in_mean[c]) / W->in_std[c];
+  float* H1 = sH1[wv];
+  float* H2 = sH2[wv];
+  f32x4_t h1[4], h2[4];
+  mlp_rows16(W, F, xn, lr, lg, H1, H2, sY[wv], h1, h2);
   double loss = 0.0;
-  if (has && rec) {
+  {
     // normalised error of the trace-projected output y; the adjoint of the
     // network's normalised output yn goes back through the projection
     // y = P(yn * std + mean), P(u) = u + (tr x - sum u) / 3
-    float g[MLP_OUT], dy[MLP_OUT], gs = 0.f;
+    float y[MLP_OUT], g[MLP_OUT], dy[MLP_OUT], gs = 0.f;
+    mlp_outputs(W, x, sY[wv] + 4 * lr, y);
 #pragma unroll
     for (int c = 0; c < MLP_OUT; c++) {
-      const float yn = (y[c] - W.out_mean[c]) / W.out_std[c];
-      const float tn = (t[c] - W.out_mean[c]) / W.out_std[c];
+      const float yn = (y[c] - W->out_mean[c]) / W->out_std[c];
+      const float tn = (t[c] - W->out_mean[c]) / W->out_std[c];
       const float e = yn - tn;
       loss += (double)e * e;
-      g[c] = 2.f * e / (float)(MLP_OUT * nb) / W.out_std[c];   // dL/dy
+      g[c] = 2.f * e / (float)(MLP_OUT * nb) / W->out_std[c];   // dL/dy
       gs += g[c];
     }
 #pragma unroll
-    for (int c = 0; c < MLP_OUT; c++) dy[c] = (g[c] - gs * (1.f / 3.f)) * W.out_std[c];
-#pragma unroll
-    for (int c = 0; c < MLP_IN; c++) rec[c] = (x[c] - W.in_mean[c]) / W.in_std[c];
-    // dh2 = W3^T dy masked by ReLU; dh1 = W2^T dh2 masked by ReLU (BF16 weights)
-    float g2[MLP_H];
-#pragma unroll
-    for (int k = 0; k < MLP_H; k++) {
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < MLP_OUT; c++) s += bf2f(W.W3[c * MLP_H + k]) * dy[c];
-      g2[k] = h2[k] > 0.f ? s : 0.f;
-      dh2[k] = g2[k];
-    }
-    for (int j = 0; j < MLP_H; j++) {
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < MLP_H; i++) s += bf2f(W.W2[i * MLP_H + j]) * g2[i];
-      dh1[j] = h1[j] > 0.f ? s : 0.f;
-    }
-#pragma unroll
-    for (int c = 0; c < MLP_OUT; c++) rec[MLP_IN + c] = dy[c];
+    for (int c = 0; c < MLP_OUT; c++) dy[c] = (g[c] - gs * (1.f / 3.f)) * W->out_std[c];
+    if (!has || lg != 0) loss = 0.0;
+    if (lg == 0) *reinterpret_cast<float4*>(sD[wv] + 4 * lr) = make_float4(dy[0], dy[1], dy[2], 0.f);
+    if (has && lg < 3)
+      *reinterpret_cast<float4*>(S.x + (size_t)b * XS + 4 * lg) =
+          lg == 0 ? make_float4(xn[0], xn[1], xn[2], xn[3])
+                  : (lg == 1 ? make_float4(xn[4], xn[5], 1.f, 0.f) : make_float4(dy[0], dy[1], dy[2], 0.f));
   }
+  wave_lds_sync();
+  // dh2 = W3^T dy masked by ReLU (BF16 weights), over the H2 rows in LDS (the
+  // third layer has read them)
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const float4 d = *reinterpret_cast<const float4*>(sD[wv] + 4 * (4 * lg + q));
+    const int bq = base + 4 * lg + q;
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++) {
+      float v = 0.f;
+      v += w3[nt][0] * d.x;
+      v += w3[nt][1] * d.y;
+      v += w3[nt][2] * d.z;
+      v = h2[nt][q] > 0.f ? v : 0.f;
+      H2[(4 * lg + q) * HS + 16 * nt + lr] = v;
+      if (bq < nb) {
+        const size_t o = ((size_t)nt * nb + bq) * 16 + lr;
+        S.d2[o] = v;
+        S.h1[o] = (uint16_t)(__float_as_uint(h1[nt][q]) >> 16);
+        S.h2[o] = (uint16_t)(__float_as_uint(h2[nt][q]) >> 16);
+      }
+    }
+  }
+  wave_lds_sync();
+  f32x4_t d1[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; nt++) d1[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 16; k++) {
+    const float a = H2[lr * HS + 4 * k + lg];
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+      d1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bf2f((uint16_t)wb[k][nt]), d1[nt], 0, 0, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int bq = base + 4 * lg + q;
+    const float4 h = *reinterpret_cast<const float4*>(H1 + (4 * lg + q) * HS + 4 * lr);
+    if (bq < nb)
+      *reinterpret_cast<float4*>(S.d1 + ((size_t)(lr >> 2) * nb + bq) * 16 + 4 * (lr & 3)) =
+          make_float4(h.x > 0.f ? d1[0][q] : 0.f, h.y > 0.f ? d1[1][q] : 0.f, h.z > 0.f ? d1[2][q] : 0.f,
+                      h.w > 0.f ? d1[3][q] : 0.f);
+  }
+#pragma unroll
   for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
-  if ((threadIdx.x & 63) == 0 && misc) atomicAdd(misc, loss / (double)(MLP_OUT * nb));
+  if (lane == 0) S.loss[base / 16] = loss / (double)(MLP_OUT * nb);
 }
 
-// Weight gradients: each thread owns one parameter and sums its term over a
-// slice of the batch; slices are combined with atomic adds into grad.
-__global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ scr, int nb, int slices, float* __restrict__ grad) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= MLP_NPARAM) return;
-  const int sl = blockIdx.y;
-  const int b0 = (int)((long long)nb * sl / slices), b1 = (int)((long long)nb * (sl + 1) / slices);
-  float acc = 0.f;
-  // decode the parameter
-  int kind, i = 0, j = 0;
-  if (p < OFF_B1) { kind = 0; i = p / MLP_IN; j = p % MLP_IN; }
-  else if (p < OFF_W2) { kind = 1; i = p - OFF_B1; }
-  else if (p < OFF_B2) { kind = 2; i = (p - OFF_W2) / MLP_H; j = (p - OFF_W2) % MLP_H; }
-  else if (p < OFF_W3) { kind = 3; i = p - OFF_B2; }
-  else if (p < OFF_B3) { kind = 4; i = (p - OFF_W3) / MLP_H; j = (p - OFF_W3) % MLP_H; }
-  else { kind = 5; i = p - OFF_B3; }
-  for (int b = b0; b < b1; b++) {
-    const float* r = scr + (size_t)b * SCR;
-    switch (kind) {
-      case 0: acc += r[HDR + 2 * MLP_H + i] * r[j]; break;              // dh1_i * xn_j
-      case 1: acc += r[HDR + 2 * MLP_H + i]; break;
-      case 2: acc += r[HDR + 3 * MLP_H + i] * r[HDR + j]; break;        // dh2_i * h1_j
-      case 3: acc += r[HDR + 3 * MLP_H + i]; break;
-      case 4: acc += r[MLP_IN + i] * r[HDR + MLP_H + j]; break;         // dy_i * h2_j
-      default: acc += r[MLP_IN + i]; break;
+// One 16 x 16 tile of weight gradients over the samples b0 .. b1 - 1, as a
+// sequential chain: acc += A^T B with A the tile's 16 adjoint values of a
+// sample and B its 16 input values.
+//   AD: A = d[b][lr] of one unit group (row stride 16), else the output adjoint (x row, 8 ..)
+//   BH: B = h[b][lr] of one unit group (BF16), else the inputs and the 1 (x row, 0 ..)
+template <bool AD, bool BH>
+__device__ __forceinline__ f32x4_t wgrad_chain(const float* __restrict__ d, const uint16_t* __restrict__ h,
+                                               const float* __restrict__ x, int b0, int b1, int lr, int lg) {
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  auto av = [&](int b) { return AD ? d[(size_t)b * 16 + lr] : (lr < MLP_OUT ? x[(size_t)b * XS + 8 + lr] : 0.f); };
+  auto bv = [&](int b) { return BH ? bf2f(h[(size_t)b * 16 + lr]) : (lr <= MLP_IN ? x[(size_t)b * XS + lr] : 0.f); };
+  // operands loaded 16 products ahead: one group is in flight while the other
+  // is multiplied
+  int b = b0;
+  constexpr int U = 16;
+  float a[2][U], c[2][U];
+  auto load = [&](int s, int at) {
+#pragma unroll
+    for (int u = 0; u < U; u++) { a[s][u] = av(at + 4 * u + lg); c[s][u] = bv(at + 4 * u + lg); }
+  };
+  auto mul = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < U; u++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][u], c[s][u], acc, 0, 0, 0);
+  };
+  if (b + 4 * U <= b1) {
+    load(0, b);
+    for (; b + 12 * U <= b1; b += 8 * U) {
+      load(1, b + 4 * U);
+      mul(0);
+      load(0, b + 8 * U);
+      mul(1);
+    }
+    if (b + 8 * U <= b1) {
+      load(1, b + 4 * U);
+      mul(0);
+      mul(1);
+      b += 8 * U;
+    } else {
+      mul(0);
+      b += 4 * U;
     }
   }
-  atomicAdd(grad + p, acc);
+  for (; b < b1; b += 4) {
+    const bool ok = b + lg < b1;
+    const float at = ok ? av(b + lg) : 0.f, ct = ok ? bv(b + lg) : 0.f;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(at, ct, acc, 0, 0, 0);
+  }
+  return acc;
 }
 
-// Adam (Kingma and Ba 2015) on the FP32 master weights; clears the gradient.
-__global__ void k_mlp_adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, float* __restrict__ g,
-                           float lr, float b1, float b2, float eps, float c1, float c2) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= MLP_NPARAM) return;
-  float gi = g[i];
+// Place of parameter i in the inference blob.
+__device__ __forceinline__ void publish_param(MlpBlob* __restrict__ blob, int i, float v) {
+  if (i < OFF_B1) blob->W1[(i / MLP_IN) * MLP_K1 + i % MLP_IN] = f2bf(v);
+  else if (i < OFF_W2) blob->b1[i - OFF_B1] = v;
+  else if (i < OFF_B2) blob->W2[i - OFF_W2] = f2bf(v);
+  else if (i < OFF_W3) blob->b2[i - OFF_B2] = v;
+  else if (i < OFF_B3) blob->W3[i - OFF_W3] = f2bf(v);
+  else blob->b3[i - OFF_B3] = v;
+}
+
+// Weight gradients of the batch, one 16 x 16 tile per workgroup and one of 16
+// slices of the samples per wavefront; the slices meet in LDS.  Tiles 0..15: dW2; 16..19: dW1 with db1 as the column of ones; 20..23: db2;
+// 24..27: dW3; 28: db3, which also sums the loss into misc[0] (first: stores it).
+// With ADAM the step (Kingma and Ba 2015) on the FP32 master weights and their
+// copy in the blob follow in the same launch; else the gradient goes to grad.
+constexpr int SLICES = 16, UPDATE_TILES = 29;
+template <bool ADAM>
+__global__ __launch_bounds__(64 * SLICES) void k_mlp_update(void* scr, int nb, float* __restrict__ grad,
+                                                            double* __restrict__ misc, int first, float* __restrict__ p,
+                                                            float* __restrict__ m, float* __restrict__ v,
+                                                            MlpBlob* __restrict__ blob, float lr, float b1, float b2,
+                                                            float eps, float c1, float c2) {
+  __shared__ float sG[SLICES][256];
+  const BatchScratch S = scratch_of(scr, (size_t)nb);
+  const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, lc = lane & 15, lg = lane >> 4;
+  const int tile = blockIdx.x;
+  const int s0 = (int)((long long)nb * sl / SLICES), s1 = (int)((long long)nb * (sl + 1) / SLICES);
+  const size_t grp = (size_t)nb * 16;      // one group of 16 units
+  f32x4_t acc;
+  if (tile < 16) acc = wgrad_chain<true, true>(S.d2 + (tile >> 2) * grp, S.h1 + (tile & 3) * grp, nullptr, s0, s1, lc, lg);
+  else if (tile < 20) acc = wgrad_chain<true, false>(S.d1 + (tile - 16) * grp, nullptr, S.x, s0, s1, lc, lg);
+  else if (tile < 24) acc = wgrad_chain<true, false>(S.d2 + (tile - 20) * grp, nullptr, S.x, s0, s1, lc, lg);
+  else if (tile < 28) acc = wgrad_chain<false, true>(nullptr, S.h2 + (tile - 24) * grp, S.x, s0, s1, lc, lg);
+  else acc = wgrad_chain<false, false>(nullptr, nullptr, S.x, s0, s1, lc, lg);
+#pragma unroll
+  for (int q = 0; q < 4; q++) sG[sl][(4 * lg + q) * 16 + lc] = acc[q];
+  if (tile == 28 && sl == SLICES - 1) {
+    double l = 0.0;
+    for (int r = lane; r < (nb + 15) / 16; r += 64) l += S.loss[r];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+    if (lane == 0) misc[0] = first ? l : misc[0] + l;
+  }
+  __syncthreads();
+  const int tid = threadIdx.x;
+  if (tid >= 256) return;
+  const int r = tid >> 4, c = tid & 15;    // row (adjoint unit) and column (input unit) of the tile
+  int i = -1;
+  if (tile < 16) i = OFF_W2 + (16 * (tile >> 2) + r) * MLP_H + 16 * (tile & 3) + c;
+  else if (tile < 20) { if (c < MLP_IN) i = OFF_W1 + (16 * (tile - 16) + r) * MLP_IN + c; else if (c == MLP_IN) i = OFF_B1 + 16 * (tile - 16) + r; }
+  else if (tile < 24) { if (c == MLP_IN) i = OFF_B2 + 16 * (tile - 20) + r; }
+  else if (tile < 28) { if (r < MLP_OUT) i = OFF_W3 + r * MLP_H + 16 * (tile - 24) + c; }
+  else if (r < MLP_OUT && c == MLP_IN) i = OFF_B3 + r;
+  if (i < 0) return;
+  double gs = 0.0;
+#pragma unroll
+  for (int q = 0; q < SLICES; q++) gs += (double)sG[q][tid];
+  const float gi = (float)gs;
+  if (!ADAM) {
+    grad[i] = gi;
+    return;
+  }
   float mi = b1 * m[i] + (1.f - b1) * gi;
   float vi = b2 * v[i] + (1.f - b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  g[i] = 0.f;
+  const float w = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[i] = w;
+  publish_param(blob, i, w);
 }
 
-// Per-sample backward scratch of mpm_mlp_grad_noalloc: at most
-// MPM_MLP_NOALLOC_MAX_BATCH samples of SCR floats (2.2 MB), one copy per
-// device for the life of the process.  Host code never passes this name to
-// a kernel: it uses the address hipGetSymbolAddress returns for the device.
-static __device__ __align__(256) float scratch[MPM_MLP_NOALLOC_MAX_BATCH * SCR];
+// Per-sample scratch of mpm_mlp_grad_noalloc for at most
+// MPM_MLP_NOALLOC_MAX_BATCH samples (1.7 MB), one copy per device for the
+// life of the process.  Host code never passes this name to a kernel: it uses
+// the address hipGetSymbolAddress returns for the device.
+static __device__ __align__(256) char scratch[scratch_bytes(MPM_MLP_NOALLOC_MAX_BATCH)];
 
 }  // namespace mpm
 
@@ -264,7 +562,7 @@ size_t mpm_mlp_state_bytes(void) { return mlp_layout().total; }
 
 size_t mpm_mlp_scratch_bytes(int32_t batch) {
   if (batch < 1) return 0;
-  return al((size_t)batch * SCR * sizeof(float));
+  return al(scratch_bytes((size_t)batch));
 }
 
 int mpm_mlp_init(void* state_dev, const float* samples_dev, int64_t n, const float* init_params, uint64_t seed,
@@ -296,7 +594,7 @@ int mpm_mlp_init(void* state_dev, const float* samples_dev, int64_t n, const flo
   if (rc == MPM_OK) {
     // the statistics need 18 doubles: accumulate in the (still zero) gradient block
     double* acc = (double*)(st + L.grad);
-    k_mlp_stats<<<256, 256, 0, s>>>((const float*)samples_dev, n, acc);
+    k_mlp_stats<<<(unsigned)(n < 64 * 1024 ? (n + 1023) / 1024 : 64), 1024, 0, s>>>((const float*)samples_dev, n, acc);
     k_mlp_stats_final<<<1, 64, 0, s>>>(acc, n, (MlpBlob*)(st + L.blob));
     if (hipMemsetAsync(st + L.grad, 0, al(MLP_NPARAM * 4), s) != hipSuccess) rc = MPM_EHIP;
     k_mlp_publish<<<32, 256, 0, s>>>((const float*)(st + L.params), (MlpBlob*)(st + L.blob));
@@ -305,39 +603,34 @@ int mpm_mlp_init(void* state_dev, const float* samples_dev, int64_t n, const flo
   return rc;
 }
 
-// Gradient of the batch loss (samples i0 .. i0 + nb - 1) into the state's
-// gradient block (added), the loss into misc[0] (added).
-static void batch_grad(char* st, const float* samples, long long n, long long i0, int nb, float* scr, hipStream_t s) {
-  MlpLayout L = mlp_layout();
-  k_mlp_batch<<<(nb + 255) / 256, 256, 0, s>>>((const MlpBlob*)(st + L.blob), samples, n, i0, nb, scr,
-                                              (double*)(st + L.misc), nullptr);
-  dim3 grid((MLP_NPARAM + 255) / 256, 16);
-  k_mlp_wgrad<<<grid, 256, 0, s>>>(scr, nb, 16, (float*)(st + L.grad));
+// Forward and input gradients of the batch (samples i0 .. i0 + nb - 1) into scr.
+static void batch_forward(const char* st, const float* samples, long long n, long long i0, int nb, void* scr,
+                          hipStream_t s) {
+  constexpr int per = BATCH_NT / 4;   // samples of a workgroup
+  k_mlp_batch<<<(nb + per - 1) / per, BATCH_NT, 0, s>>>((const MlpBlob*)(st + mlp_layout().blob), samples, n, i0, nb, scr);
 }
 
 // Loss and gradient of the first nb records with the per-sample scratch scr
 // (shared by mpm_mlp_grad and mpm_mlp_grad_noalloc).
-static int grad_impl(void* state_dev, const float* samples_dev, int64_t n, int nb, float* scr, float* grad_out_dev,
+static int grad_impl(void* state_dev, const float* samples_dev, int64_t n, int nb, void* scr, float* grad_out_dev,
                      double* loss_out_host, hipStream_t s) {
   MlpLayout L = mlp_layout();
   char* st = (char*)state_dev;
-  if (hipMemsetAsync(st + L.grad, 0, al(MLP_NPARAM * 4), s) != hipSuccess) return MPM_EHIP;
-  if (hipMemsetAsync(st + L.misc, 0, 64, s) != hipSuccess) return MPM_EHIP;
-  batch_grad(st, samples_dev, n, 0, nb, scr, s);
-  if (hipMemcpyAsync(grad_out_dev, st + L.grad, sizeof(float) * MLP_NPARAM, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return MPM_EHIP;
+  batch_forward(st, samples_dev, n, 0, nb, scr, s);
+  k_mlp_update<false><<<UPDATE_TILES, 64 * SLICES, 0, s>>>(scr, nb, grad_out_dev, (double*)(st + L.misc), 1, nullptr,
+                                                          nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
   double loss = 0.0;
   if (hipMemcpyAsync(&loss, st + L.misc, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return MPM_EHIP;
   if (hipStreamSynchronize(s) != hipSuccess) return MPM_EHIP;
   if (loss_out_host) *loss_out_host = loss;
-  return hipok(hipMemsetAsync(st + L.grad, 0, al(MLP_NPARAM * 4), s));
+  return hipok(hipGetLastError());
 }
 
 int mpm_mlp_grad(void* state_dev, const float* samples_dev, int64_t n, int32_t batch, void* scratch_dev,
                  float* grad_out_dev, double* loss_out_host, void* stream) {
   if (!state_dev || !samples_dev || n < 1 || batch < 1 || !scratch_dev || !grad_out_dev) return MPM_EINVAL;
   const int nb = (int)(n < batch ? n : batch);
-  return grad_impl(state_dev, samples_dev, n, nb, (float*)scratch_dev, grad_out_dev, loss_out_host, (hipStream_t)stream);
+  return grad_impl(state_dev, samples_dev, n, nb, scratch_dev, grad_out_dev, loss_out_host, (hipStream_t)stream);
 }
 
 int mpm_mlp_grad_noalloc(void* state_dev, const float* samples_dev, int64_t n, int32_t batch, float* grad_out_dev,
@@ -347,7 +640,7 @@ int mpm_mlp_grad_noalloc(void* state_dev, const float* samples_dev, int64_t n, i
   if (nb > MPM_MLP_NOALLOC_MAX_BATCH) return MPM_EWORKSPACE;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return MPM_EHIP;
-  float* scr = (float*)noalloc_scratch(dev);
+  void* scr = noalloc_scratch(dev);
   if (!scr) return MPM_EHIP;
   return grad_impl(state_dev, samples_dev, n, (int)nb, scr, grad_out_dev, loss_out_host, (hipStream_t)stream);
 }
@@ -370,15 +663,14 @@ int mpm_mlp_train(void* state_dev, const float* samples_dev, int64_t n, int32_t 
   const int nb = (int)(n < batch ? n : batch);
   const long long steps_per_epoch = (n + nb - 1) / nb;
   for (int ep = 0; ep < epochs; ep++) {
-    if (hipMemsetAsync(st + L.misc, 0, sizeof(double), s) != hipSuccess) return MPM_EHIP;
     const long long offset = (long long)(rng() % (unsigned long long)n);
     for (long long k = 0; k < steps_per_epoch; k++) {
-      batch_grad(st, samples_dev, n, (offset + k * nb) % n, nb, (float*)scratch_dev, s);
+      batch_forward(st, samples_dev, n, (offset + k * nb) % n, nb, scratch_dev, s);
       t_adam += 1.0;
       float c1 = (float)(1.0 - pow((double)b1, t_adam)), c2 = (float)(1.0 - pow((double)b2, t_adam));
-      k_mlp_adam<<<(MLP_NPARAM + 255) / 256, 256, 0, s>>>((float*)(st + L.params), (float*)(st + L.m), (float*)(st + L.v),
-                                                          (float*)(st + L.grad), lr, b1, b2, eps, c1, c2);
-      k_mlp_publish<<<32, 256, 0, s>>>((const float*)(st + L.params), (MlpBlob*)(st + L.blob));
+      k_mlp_update<true><<<UPDATE_TILES, 64 * SLICES, 0, s>>>(
+          scratch_dev, nb, nullptr, (double*)(st + L.misc), k == 0 ? 1 : 0, (float*)(st + L.params), (float*)(st + L.m),
+          (float*)(st + L.v), (MlpBlob*)(st + L.blob), lr, b1, b2, eps, c1, c2);
     }
     double loss = 0.0;
     if (hipMemcpyAsync(&loss, st + L.misc, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return MPM_EHIP;
@@ -395,15 +687,10 @@ int mpm_mlp_predict(const void* state_dev, const float* x_dev, int64_t n, float*
   hipStream_t s = (hipStream_t)stream;
   MlpLayout L = mlp_layout();
   const char* st = (const char*)state_dev;
-  // x_dev holds n samples of 6 inputs; run the batch kernel over them as
-  // 9-float records is not possible, so rows are read with stride 6 via a
-  // strided view: the batch kernel reads SAMPLE floats per sample, hence the
-  // inputs are expected in 9-float records (targets ignored)
-  for (long long i0 = 0; i0 < n; i0 += 1 << 20) {
-    int nb = (int)((n - i0) < (1 << 20) ? (n - i0) : (1 << 20));
-    k_mlp_batch<<<(nb + 255) / 256, 256, 0, s>>>((const MlpBlob*)(st + L.blob), x_dev + i0 * SAMPLE, nb, 0, nb, nullptr,
-                                                nullptr, y_dev + i0 * MLP_OUT);
-  }
+  // (the records are those of the training set, 9 floats each; the targets are
+  // not read)
+  const long long blocks = (n + 63) / 64;
+  k_mlp_predict<<<(unsigned)(blocks < 2048 ? blocks : 2048), 256, 0, s>>>((const MlpBlob*)(st + L.blob), x_dev, n, y_dev);
   return hipok(hipStreamSynchronize(s));
 }
 

@@ -140,3 +140,71 @@ def test_training_and_closure_in_the_simulator():
     # benchmark trains on 10M): it takes over most cone-case returns at the
     # residual tolerance, where an untrained one is nearly always rejected
     assert shares["trained"] >= 0.6 and shares["untrained"] <= 0.1
+
+
+def bf16(a):
+    return a.float().bfloat16().double()
+
+
+def emulated_loss_and_grad(params, norm, rec):
+    """The network's loss and parameter gradient in FP64 with the BF16
+    roundings the matrix cores' inputs take (normalised inputs, weights and
+    hidden activations; the roundings carry the gradient unchanged)."""
+    t = lambda a: torch.as_tensor(np.asarray(a), dtype=torch.float64)
+    ste = lambda a: a + (bf16(a.detach()) - a.detach())
+    p = t(params).requires_grad_()
+    W1, b1, W2, b2, W3, b3 = torch.split(p, [384, 64, 4096, 64, 192, 3])
+    W1, W2, W3 = ste(W1.view(64, 6)), ste(W2.view(64, 64)), ste(W3.view(3, 64))
+    x, y = t(rec[:, :6]), t(rec[:, 6:])
+    h = ste(((x - t(norm["in_mean"])) / t(norm["in_std"])).float().double())
+    h = ste(torch.relu(h @ W1.T + b1))
+    h = ste(torch.relu(h @ W2.T + b2))
+    m, s = t(norm["out_mean"]), t(norm["out_std"])
+    o = (h @ W3.T + b3) * s + m
+    o = o + ((x[:, :3].sum(1) - o.sum(1)) / 3.0)[:, None]
+    loss = (((o - y) / s) ** 2).mean()
+    loss.backward()
+    return float(loss.detach()), p.grad.numpy()
+
+
+@pytest.mark.parametrize("nb", [1, 15, 16, 17, 63, 64, 65, 700, 16384, 16385, 20011])
+def test_gradient_batch_edges_vs_emulation(nb):
+    """Ragged 16-sample tiles and slices of the batch (empty ones below 16),
+    up to several rounds of workgroups, against FP64 with the same roundings.  An activation
+    near a rounding tie (about 1 in 1e4) may round the other way after FP32
+    sums, 2^-8 of one unit of one sample: bounded by 2^-8 / sqrt(nb) of the
+    gradient, beside FP32 rounding."""
+    from paper_2303_02346_amd.closure import MLP
+    rec = synthetic_records(max(nb, 2), seed=20 + nb)
+    dev = torch.from_numpy(rec).cuda()
+    net = MLP()
+    net.init(dev, seed=nb)
+    loss, g = net.grad(dev, batch=nb)
+    p, norm, _ = net.params()
+    L, gr = emulated_loss_and_grad(p, norm, rec[:nb])
+    e = rel(g.double().cpu().numpy(), gr)
+    say(f"  nb {nb}: loss {loss:.8f} emulation {L:.8f}; gradient rel err {e:.2e}")
+    tol = 2.0 ** -8 / np.sqrt(nb) + 1e-5
+    assert abs(loss - L) <= 2 * tol * L
+    assert e <= tol
+
+
+def test_training_publishes_its_weights_and_repeats_exactly():
+    """After training, the inference copy is the BF16 rounding of the master
+    weights, and a second run from the same start gives the same bits (fixed
+    summation order), with a batch that leaves a ragged block and wraps."""
+    from paper_2303_02346_amd.closure import MLP
+    rec = torch.from_numpy(synthetic_records(5003, seed=9)).cuda()
+    runs = []
+    for _ in range(2):
+        net = MLP()
+        net.init(rec, seed=2)
+        hist = net.train(rec, epochs=2, batch=777, lr=1e-3, seed=3)
+        p, _, pb = net.params()
+        runs.append((hist, p, net.predict(rec).cpu().numpy()))
+        w = np.r_[0:384, 448:4544, 4608:4800]
+        assert np.array_equal(pb[w], torch.from_numpy(p[w]).bfloat16().float().numpy())
+        assert hist[1] < hist[0]
+    assert runs[0][0] == runs[1][0]
+    assert np.array_equal(runs[0][1], runs[1][1])
+    assert np.array_equal(runs[0][2], runs[1][2])
