@@ -62,7 +62,7 @@ template <int NT>
 __global__ __launch_bounds__(NT, 3) void k_g2p_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
   constexpr int NW = NT / 64;
   constexpr int NQ = 3;   // velocity adjoint components
-  __shared__ float4 s_v[VT_NODES];
+  __shared__ float4 s_v[VT_LDS];
   __shared__ float s_tile[NQ * TILE_NODES];
   __shared__ int s_itile[NQ * TILE_NODES];
   __shared__ int s_lo[3], s_hi[3];
@@ -78,10 +78,7 @@ __global__ __launch_bounds__(NT, 3) void k_g2p_adj_tiled(AdjArgs A, StepParams P
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
-    for (int q = tid; q < VT_NODES; q += NT) {
-      const int qi = q / (VT * VT), qj = (q / VT) % VT, qk = q % VT;
-      s_v[q] = stage_node(A.vgrid, g, sc, ox - 1 + qi, oy - 1 + qj, oz - 1 + qk);
-    }
+    stage_window<NT>(s_v, A.vgrid, g, sc, bx, by, bz, tid);
     for (int q = tid; q < NQ * TILE_NODES; q += NT) { s_tile[q] = 0.f; s_itile[q] = 0; }
     if (tid < 3) { s_lo[tid] = 1 << 20; s_hi[tid] = -(1 << 20); }
     __syncthreads();
@@ -329,7 +326,7 @@ __global__ __launch_bounds__(REDO_NT) void k_g2p_adj_redo(AdjArgs A, StepParams 
           loc[(i * 3 + jj) * 3 + k] = stage_node(A.vgrid, g, sc, S.base[0] + i, S.base[1] + jj, S.base[2] + k);
     const int l0[3] = {0, 0, 0};
     float vn[3], Bi[9], B[9];
-    g2p_gather<3>(loc, l0, S, vn, Bi);
+    g2p_gather<3, 9>(loc, l0, S, vn, Bi);
 #pragma unroll
     for (int a = 0; a < 3; a++)
 #pragma unroll
@@ -351,7 +348,7 @@ __global__ __launch_bounds__(REDO_NT) void k_g2p_adj_redo(AdjArgs A, StepParams 
       for (int b = 0; b < 3; b++) Ad[a * 3 + b] = P.dx * Bb[a * 3 + b];
       c0[a] = vbt[a] - (Ad[a * 3] * S.f[0] + Ad[a * 3 + 1] * S.f[1] + Ad[a * 3 + 2] * S.f[2]);
     }
-    weight_grad_sum<false, 3>(loc, l0, S, c0, Ad, 0.f, X, nullptr, nullptr);
+    weight_grad_sum<false, 3, 9>(loc, l0, S, c0, Ad, 0.f, X, nullptr, nullptr);
     float* ab = A.abar;
 #pragma unroll
     for (int a = 0; a < 3; a++) {
@@ -473,9 +470,9 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
 // returns false, before doing anything, for a solid whose F is
 // ill-conditioned (s2 < s0/4) or whose FP32 sweeps do not converge.
 // FP64 = true: the stress and its adjoint from FP64 SVDs, for the particles
-// the FP32 pass returned (k_p2g_adj_redo).  The tile holds E^3 nodes, lv is
-// the stencil's first node in it.
-template <bool FP64, int E>
+// the FP32 pass returned (k_p2g_adj_redo).  lv is the stencil's
+// first node in the tile of strides ROW and PLANE.
+template <bool FP64, int ROW, int PLANE>
 MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState& st, const float4* tile,
                              const int* lv, const Stencil& S, int j) {
   const int N = A.N;
@@ -515,7 +512,7 @@ MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState
       for (int b = 0; b < 3; b++) Ad[a * 3 + b] = P.dx * Am[a * 3 + b];
       c0[a] = mvp[a] - (Ad[a * 3] * S.f[0] + Ad[a * 3 + 1] * S.f[1] + Ad[a * 3 + 2] * S.f[2]);
     }
-    weight_grad_sum<true, E>(tile, lv, S, c0, Ad, M.mass, X, G0, Gi);
+    weight_grad_sum<true, ROW, PLANE>(tile, lv, S, c0, Ad, M.mass, X, G0, Gi);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
       vb[a] = M.mass * G0[a];
@@ -542,7 +539,7 @@ MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState
 
 template <int NT>
 __global__ __launch_bounds__(NT) void k_p2g_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
-  __shared__ float4 s_g[VT_NODES];
+  __shared__ float4 s_g[VT_LDS];
   const int tid = threadIdx.x;
   const int N = A.N;
   const PState st = packed_state(A.st.f, N);
@@ -552,10 +549,7 @@ __global__ __launch_bounds__(NT) void k_p2g_adj_tiled(AdjArgs A, StepParams P, F
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
-    for (int q = tid; q < VT_NODES; q += NT) {
-      const int qi = q / (VT * VT), qj = (q / VT) % VT, qk = q % VT;
-      s_g[q] = stage_node(A.mmvb, g, sc, ox - 1 + qi, oy - 1 + qj, oz - 1 + qk);
-    }
+    stage_window<NT>(s_g, A.mmvb, g, sc, bx, by, bz, tid);
     __syncthreads();
     const int start = ent.y, count = ent.z;
     for (int c0 = 0; c0 < count; c0 += NT) {
@@ -566,7 +560,7 @@ __global__ __launch_bounds__(NT) void k_p2g_adj_tiled(AdjArgs A, StepParams P, F
       if (!stencil_setup(x, P, S)) continue;   // reported by the G2P adjoint
       int lv[3] = {S.base[0] - (ox - 1), S.base[1] - (oy - 1), S.base[2] - (oz - 1)};
       if (lv[0] < 0 || lv[1] < 0 || lv[2] < 0 || lv[0] > VT - 3 || lv[1] > VT - 3 || lv[2] > VT - 3) continue;
-      if (!p2g_adj_particle<false, VT>(A, P, st, s_g, lv, S, j)) {
+      if (!p2g_adj_particle<false, VT_ROW, VT_PLANE>(A, P, st, s_g, lv, S, j)) {
         const uint32_t r = atomicAdd(A.redo_n, 1u);
         A.redo[r] = make_uint2((uint32_t)j, (uint32_t)ent.x);
       }
@@ -599,7 +593,7 @@ __global__ __launch_bounds__(REDO_NT) void k_p2g_adj_redo(AdjArgs A, StepParams 
         for (int k = 0; k < 3; k++)
           loc[(i * 3 + jj) * 3 + k] = stage_node(A.mmvb, g, sc, S.base[0] + i, S.base[1] + jj, S.base[2] + k);
     const int l0[3] = {0, 0, 0};
-    p2g_adj_particle<true, 3>(A, P, st, loc, l0, S, j);
+    p2g_adj_particle<true, 3, 9>(A, P, st, loc, l0, S, j);
   }
 }
 

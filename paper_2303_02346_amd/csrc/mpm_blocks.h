@@ -123,9 +123,9 @@ __device__ inline uint32_t wave_rank(uint32_t* counts, uint32_t key, bool valid,
 
 __device__ inline void load_state(const PBuf& b, int N, int j, float* x, float* v, float* C, float* F, float& J) {
 #pragma unroll
-  for (int a = 0; a < 3; a++) { x[a] = b.f[a * (size_t)N + j]; v[a] = b.f[(3 + a) * (size_t)N + j]; }
+  for (int a = 0; a < 3; a++) { x[a] = row32(b.f, a, N, 4u * (uint32_t)j); v[a] = row32(b.f, 3 + a, N, 4u * (uint32_t)j); }
 #pragma unroll
-  for (int k = 0; k < 9; k++) C[k] = b.f[(6 + k) * (size_t)N + j];
+  for (int k = 0; k < 9; k++) C[k] = row32(b.f, 6 + k, N, 4u * (uint32_t)j);
 }
 
 }  // namespace mpm

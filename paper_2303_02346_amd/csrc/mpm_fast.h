@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include <vector>
 #include "mpm_internal.h"
 
@@ -23,6 +24,12 @@ constexpr int TILE = 10;                     // P2G tile edge (nodes): block +-2
 constexpr int TILE_NODES = TILE * TILE * TILE;
 constexpr int VT = 8;                        // G2P velocity tile edge
 constexpr int VT_NODES = VT * VT * VT;
+// LDS strides of the velocity tile (16-byte words): a block's 64 cells then
+// start in each of the 8 bank groups equally often (with strides 8 and 64 the
+// bank group followed z alone and half of the banks were idle)
+constexpr int VT_ROW = VT;
+constexpr int VT_PLANE = VT * VT + 4;
+constexpr int VT_LDS = VT * VT_PLANE;
 // Tile slots per block key: the forward lists a block of more than two
 // chunks twice, and the second workgroup publishes its tile in slot
 // key + n_keys (the adjoint uses slot key only).
@@ -36,6 +43,16 @@ struct PBuf {
   uint32_t* rank; // rank within that key
   uint8_t* mat;
 };
+
+// Element at byte offset `off` (4 x the index, which is below 2^30) of row k of
+// rows of N words, or of an array: a wavefront-uniform base and a 32-bit lane
+// offset, which a load or store takes as they are (64-bit lane addresses cost
+// two vector instructions and two registers each).
+template <typename T> __device__ __forceinline__ T& at32(T* p, uint32_t off) {
+  using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return *reinterpret_cast<T*>(reinterpret_cast<B*>(p) + off);
+}
+__device__ __forceinline__ float& row32(float* f, int k, int N, uint32_t off) { return at32(f + (size_t)k * N, off); }
 
 // A captured call (graph mode).
 struct FastGraph {

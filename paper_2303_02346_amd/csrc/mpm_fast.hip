@@ -23,6 +23,7 @@
 // MPM_ERR_TILE, the CFL > 1 condition).
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include <vector>
 #include "mpm_fast.h"
 #include "mpm_blocks.h"
@@ -440,6 +441,11 @@ __global__ __launch_bounds__(256) void k_gather_out(PBuf X, PState u, const MatD
 // ---------------------------------------------------------------------------
 // particle kernel
 // ---------------------------------------------------------------------------
+// multiplier m with r / d = (r m) >> 20 for r d < 2^19 (2^20 / d < m <= 2^20 / d + 2)
+__device__ __forceinline__ uint32_t div_mul(int d) {
+  return (uint32_t)(1048576.f * __builtin_amdgcn_rcpf((float)d)) + 2u;
+}
+
 enum { MODE_P2G = 0, MODE_FUSED = 1, MODE_G2P = 2 };
 
 struct PartArgs {
@@ -468,20 +474,24 @@ struct PartArgs {
   unsigned long long* log_count;
   unsigned long long log_cap;
   uint32_t* map_out;                   // (records) output row of each input row, or nullptr
+  int write_vc;                        // fused: also write v and C (rows the next fused step does not read)
 };
 
 enum { FEAT_NONE = 0, FEAT_LOG = 1, FEAT_CLOSURE = 2 };
 
 // The fused kernel (MODE 1 without the closure features) in 256-thread
-// workgroups runs fastest held to three wavefronts per SIMD (168 VGPRs and a
-// few spills): 65.5 us per config-2 step against 69.5 us at two (231 VGPRs)
-// and 81.7 us at four.  In 512-thread workgroups the same bound made the
-// 1e5-particle 64^3 step slower (66 against 62 us), so they keep two.  The
-// separate P2G (MODE 0, 190 VGPRs unbounded) gains from the same bound too:
-// the rigid-body step at config-2 size 0.126 -> 0.121 ms.  The learned-
-// closure variant (FP64 return, network on the matrix cores) held to two
-// wavefronts per SIMD keeps its accumulators in VGPRs (256, a few spills)
-// instead of running at one (0.76 -> 0.57 ms per config-5 step).
+// workgroups runs fastest held to three wavefronts per SIMD (168 VGPRs, the
+// main pass without spills): 37.6 us for a step of 250k particles on 128^3 and
+// 430 us for 3.8M on 64 grids of 64^3, against 41.6 and 508 at two and 39.8
+// and 430 at four.  It took 46.4 and 567 us while the FP64 redo ran inline, the
+// rows were addressed with 64-bit lane addresses and per-thread values were
+// computed ahead of the entry loop: together 50 registers a lane spilled, 30 MB
+// of scratch writes per launch at 250k.  In 512-thread workgroups the same
+// bound made the 1e5-particle 64^3 step slower, so they keep two.  The separate
+// P2G (MODE 0) gains from the same bound too: the rigid-body step at 250k
+// 0.126 -> 0.121 ms.  The learned-closure variant (network on the matrix
+// cores) held to two wavefronts per SIMD keeps its accumulators in VGPRs
+// instead of running at one (0.76 -> 0.57 ms per step of 1M particles).
 template <int MODE, int NT, int FEAT>
 __global__ __launch_bounds__(NT, (NT == 256 && ((MODE == 1 && FEAT == FEAT_NONE) || MODE == 0))
                                      ? 3
@@ -496,18 +506,26 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
     for (int q = threadIdx.x; q < (int)(sizeof(MlpBlob) / 4); q += NT) dstw[q] = src[q];
     __syncthreads();
   }
-  __shared__ float s_tile[4 * TILE_NODES];
-  __shared__ int s_itile[4 * TILE_NODES];
-  __shared__ float4 s_v[VT_NODES];
+  __shared__ float4 s_tile[TILE_NODES];
+  __shared__ __align__(16) int s_itile[4 * TILE_NODES];
+  __shared__ float4 s_v[VT_LDS];
   __shared__ float s_red[NW * 4];     // per-wave bound sums of the chunk
   __shared__ uint32_t s_ired[NW];      // per-wave box bits of the chunk
-  const int tid = threadIdx.x;
   const int N = A.N;
   const uint32_t n_list = A.list_n[0];
   // step stamp: per-call epoch (advanced by the import) and step within the call
   const uint32_t stamp = (A.gen[0] << 16) | A.step_id;
   for (uint32_t e = blockIdx.x; e < n_list; e += gridDim.x) {
-    const int4 ent = A.list[e];
+    // (the thread index is opaque to the entry loop, so that what follows from
+    // it is not computed ahead of the loop and spilled across it)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    int4 ent = A.list[e];
+    // (one entry per workgroup: its decoding runs on the scalar unit)
+    ent.x = __builtin_amdgcn_readfirstlane(ent.x);
+    ent.y = __builtin_amdgcn_readfirstlane(ent.y);
+    ent.z = __builtin_amdgcn_readfirstlane(ent.z);
+    ent.w = __builtin_amdgcn_readfirstlane(ent.w);
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
@@ -519,42 +537,51 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
     float px[3] = {0, 0, 0}, pF[9], pJ = 1.f;
     int pm = 0;
     uint32_t pkey = 0, prank = 0;
+    auto load_inputs = [&](int jn) {
+      const uint32_t off = 4u * (uint32_t)jn;
+#pragma unroll
+      for (int a = 0; a < 3; a++) px[a] = row32(A.in.f, a, N, off);
+#pragma unroll
+      for (int k = 0; k < 9; k++) pF[k] = row32(A.in.f, 15 + k, N, off);
+      pJ = row32(A.in.f, 24, N, off);
+      pm = A.in.mat[(uint32_t)jn];
+      if (MODE != MODE_P2G) { pkey = at32(A.in.key, off); prank = at32(A.in.rank, off); }
+    };
     auto prefetch = [&](int c0n) {
       const int jn = start + c0n + tid;
-      if (c0n + tid < count && jn < N) {
-#pragma unroll
-        for (int a = 0; a < 3; a++) px[a] = A.in.f[a * (size_t)N + jn];
-#pragma unroll
-        for (int k = 0; k < 9; k++) pF[k] = A.in.f[(15 + k) * (size_t)N + jn];
-        pJ = A.in.f[24 * (size_t)N + jn];
-        pm = A.in.mat[jn];
-        if (MODE != MODE_P2G) { pkey = A.in.key[jn]; prank = A.in.rank[jn]; }
-      }
+      if (c0n + tid < count && jn < N) load_inputs(jn);
     };
     prefetch(0);
     // ---- stage grid velocities of nodes [4b-1, 4b+7) for G2P
-    if (MODE != MODE_P2G) {
-      for (int q = tid; q < VT_NODES; q += NT) {
-        int qi = q / (VT * VT), qj = (q / VT) % VT, qk = q % VT;
-        int gx = ox - 1 + qi, gy = oy - 1 + qj, gz = oz - 1 + qk;
-        float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gx >= 0 && gy >= 0 && gz >= 0 && gx < g.n && gy < g.n && gz < g.n) {
-          uint32_t kk = block_key(g, sc, gx >> 2, gy >> 2, gz >> 2);
-          val = A.vgrid[(size_t)kk * 64 + (((gx & 3) << 4) | ((gy & 3) << 2) | (gz & 3))];
-        }
-        s_v[q] = val;
-      }
-    }
-    if (MODE != MODE_G2P) {
-      for (int q = tid; q < 4 * TILE_NODES; q += NT) { s_tile[q] = 0.f; s_itile[q] = 0; }
-
+    if (MODE != MODE_P2G) stage_window<NT>(s_v, A.vgrid, g, sc, bx, by, bz, tid);
+    if (MODE != MODE_G2P && e == blockIdx.x) {
+      // the integer tile starts at zero; every flush leaves it so
+      for (int r = tid; r < TILE_NODES; r += NT) reinterpret_cast<int4*>(s_itile)[r] = make_int4(0, 0, 0, 0);
     }
     __syncthreads();
+    const size_t slot = (size_t)(uint32_t)ent.x + (size_t)ent.w * (size_t)A.n_keys;   // the entry's tile slot
+    float4* tile_out = reinterpret_cast<float4*>(A.tiles + slot * 4 * TILE_NODES);
     // the tile's non-zero box over all chunks (every thread keeps the same copy)
     int blo[3] = {1 << 20, 1 << 20, 1 << 20}, bhi[3] = {-(1 << 20), -(1 << 20), -(1 << 20)};
-    for (int c0 = 0; c0 < count; c0 += NT) {
+    // One pass over a chunk's particles (the lanes with `on` set).  The main pass
+    // (RETRY false) works in FP32; lanes whose FP32 result is ill-conditioned
+    // set `defer` and contribute nothing, and the pass returns whether any lane
+    // of the workgroup did (the same for every lane; in the G2P mode, which has
+    // no barriers, of the wavefront).  Those lanes are then done by a second
+    // pass in FP64.  As a pass of its own the FP64 arithmetic leaves the main
+    // pass's registers alone: inline, every particle's live values were
+    // spilled around it (200 B a lane, about 1 GB of scratch traffic per launch
+    // of 3.8M particles).  Sample logging runs only the FP64 pass: its records
+    // are the exact FP64 return.  last: the flush publishes the tile
+    // (unless lanes were deferred).
+    auto pass = [&](auto retry, int c0, const bool on, bool& defer, bool last) -> bool {
+      constexpr bool RETRY = decltype(retry)::value;
       const int j = start + c0 + tid;
-      const bool has = (c0 + tid) < count && j < N;
+      const bool has = on;
+      bool any_deferred = false;
+      if (RETRY) {
+        if (has) load_inputs(j);
+      }
       float x[3] = {px[0], px[1], px[2]}, v[3] = {0, 0, 0}, C[9], F[9], J = pJ;
 #pragma unroll
       for (int k = 0; k < 9; k++) { F[k] = pF[k]; C[k] = 0.f; }
@@ -565,7 +592,7 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
       uint32_t dst = 0;
       if (has) {
         if (MODE == MODE_P2G) load_state(A.in, N, j, x, v, C, F, J);
-        else dst = A.offsets[pkey] + prank;
+        else dst = at32(A.offsets, 4u * pkey) + prank;
       }
       const MatDev& M = P.mats[m];
       const bool liquid = M.kind == KIND_LIQUID;
@@ -606,43 +633,38 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
             fin = fin && isfinite(J);
           } else if (elastic_update_kind(M.kind)) {
             float Fn[9];
-            matmul(Md, F, Fn);
+            matmul_fma(Md, F, Fn);
 #pragma unroll
             for (int k = 0; k < 9; k++) F[k] = Fn[k];
           } else {
-            // plastic solids: FP32 SVD and return map, redone in FP64 for an
-            // ill-conditioned trial state (or an unconverged sweep).  Sample
-            // logging keeps the FP64 SVD throughout: its records are the
-            // exact FP64 return
+            // plastic solids: SVD and return map (and for the fused mode the
+            // Hencky stress, from the same SVD)
+            using T = std::conditional_t<RETRY, double, float>;
             float Fn[9];
-            PlasticStep<float> R;
-            int st = FEAT != FEAT_LOG ? plastic_step<float, MODE == MODE_FUSED>(Md, F, M, Fn, tau, R) : PLASTIC_RETRY;
-            if (st == PLASTIC_RETRY) {
-              PlasticStep<double> R2;
-              st = plastic_step<double, MODE == MODE_FUSED>(Md, F, M, Fn, tau, R2);
-              R.cse = R2.cse;
-#pragma unroll
-              for (int k = 0; k < 9; k++) { R.U[k] = (float)R2.U[k]; R.V[k] = (float)R2.V[k]; }
-#pragma unroll
-              for (int a = 0; a < 3; a++) { R.e[a] = (float)R2.e[a]; R.ep[a] = (float)R2.ep[a]; }
-            }
-#pragma unroll
-            for (int k = 0; k < 9; k++) F[k] = Fn[k];
-            if (st == PLASTIC_SIGMA) {
-              atomicOr(P.err, ERR_SAND_SIGMA);
+            PlasticStep<T> R;
+            const int st = plastic_step<T, MODE == MODE_FUSED>(Md, F, M, Fn, tau, R);
+            if (!RETRY && st == PLASTIC_RETRY) {
+              defer = true;
               ok = false;
             } else {
-              have_tau = MODE == MODE_FUSED && M.kind != KIND_BOX;
-              if (FEAT != FEAT_NONE && M.kind == KIND_SAND && R.cse == 2) {
-                cone = true;
 #pragma unroll
-                for (int a = 0; a < 3; a++) { xin[a] = R.e[a]; eex[a] = R.ep[a]; }
-                xin[3] = M.alpha;
-                xin[4] = M.coh;
-                xin[5] = M.kappa;
-                if (FEAT == FEAT_CLOSURE) {
+              for (int k = 0; k < 9; k++) F[k] = Fn[k];
+              if (st == PLASTIC_SIGMA) {
+                atomicOr(P.err, ERR_SAND_SIGMA);
+                ok = false;
+              } else {
+                have_tau = MODE == MODE_FUSED && M.kind != KIND_BOX;
+                if (FEAT != FEAT_NONE && M.kind == KIND_SAND && R.cse == 2) {
+                  cone = true;
 #pragma unroll
-                  for (int k = 0; k < 9; k++) { Uk[k] = R.U[k]; Vk[k] = R.V[k]; }
+                  for (int a = 0; a < 3; a++) { xin[a] = (float)R.e[a]; eex[a] = (float)R.ep[a]; }
+                  xin[3] = M.alpha;
+                  xin[4] = M.coh;
+                  xin[5] = M.kappa;
+                  if (FEAT == FEAT_CLOSURE) {
+#pragma unroll
+                    for (int k = 0; k < 9; k++) { Uk[k] = (float)R.U[k]; Vk[k] = (float)R.V[k]; }
+                  }
                 }
               }
             }
@@ -653,28 +675,36 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
           }
 #pragma unroll
           for (int k = 0; k < 9; k++) fin = fin && isfinite(C[k]);
-          if (!fin) { atomicOr(P.err, ERR_NONFINITE); ok = false; }
+          if (!fin && !defer) { atomicOr(P.err, ERR_NONFINITE); ok = false; }
         }
         // write the particle to its slot in the output buffer
-        if (dst < (uint32_t)N) {
-          PBuf& O = A.out;
+        if (defer) {
+          // (its FP64 pass writes it)
+        } else if (dst < (uint32_t)N) {
+          const PBuf& O = A.out;
+          const uint32_t off = 4u * dst;
 #pragma unroll
-          for (int a = 0; a < 3; a++) { O.f[a * (size_t)N + dst] = x[a]; O.f[(3 + a) * (size_t)N + dst] = v[a]; }
+          for (int a = 0; a < 3; a++) row32(O.f, a, N, off) = x[a];
+          // the next step's G2P replaces v and C: the fused kernel writes them
+          // only where the state is read otherwise (checkpoints, records)
+          if (MODE == MODE_G2P || A.write_vc) {
 #pragma unroll
-          for (int k = 0; k < 9; k++) O.f[(6 + k) * (size_t)N + dst] = C[k];
-          if (liquid) O.f[24 * (size_t)N + dst] = J;
+            for (int a = 0; a < 3; a++) row32(O.f, 3 + a, N, off) = v[a];
+#pragma unroll
+            for (int k = 0; k < 9; k++) row32(O.f, 6 + k, N, off) = C[k];
+          }
+          if (liquid) row32(O.f, 24, N, off) = J;
           else {
 #pragma unroll
-            for (int k = 0; k < 9; k++) O.f[(15 + k) * (size_t)N + dst] = F[k];
+            for (int k = 0; k < 9; k++) row32(O.f, 15 + k, N, off) = F[k];
           }
-          O.id[dst] = A.in.id[j];
+          at32(O.id, off) = at32(A.in.id, 4u * (uint32_t)j);
           O.mat[dst] = (uint8_t)m;
-          if (A.map_out) A.map_out[j] = dst;
+          if (A.map_out) at32(A.map_out, 4u * (uint32_t)j) = dst;
         } else {
           ok = false;
         }
       }
-      if (MODE == MODE_G2P && c0 + NT < count) prefetch(c0 + NT);
       if (FEAT == FEAT_LOG) {
         // append the exact cone-case samples, one counter atomic per wavefront
         const unsigned long long m = __ballot(cone);
@@ -753,11 +783,21 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
         }
         float Am[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, mvp[3] = {0, 0, 0}, bnd[4] = {0, 0, 0, 0};
         if (ok) {
-          if (liquid) stress_liquid(J, C, M, tau);
-          else if (!have_tau && !stress_solid_fast(F, M, tau)) atomicOr(P.err, ERR_SAND_SIGMA);
+          if (liquid) {
+            stress_liquid(J, C, M, tau);
+          } else if (!have_tau) {
+            if (RETRY) {
+              if (!stress_solid(F, M, tau)) atomicOr(P.err, ERR_SAND_SIGMA);
+            } else if (!stress_solid_fp32(F, M, tau)) {
+              defer = true;
+              ok = false;
+            }
+          }
+        }
+        if (ok) {
           const float scl = -P.dt * M.vol * 4.f * P.inv_dx * P.inv_dx;
 #pragma unroll
-          for (int k = 0; k < 9; k++) Am[k] = scl * tau[k] + M.mass * C[k];
+          for (int k = 0; k < 9; k++) Am[k] = fmaf(scl, tau[k], M.mass * C[k]);
 #pragma unroll
           for (int a = 0; a < 3; a++) {
             mvp[a] = M.mass * v[a];
@@ -784,7 +824,7 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
         // bit per occupied stencil origin and axis (bit lb_a of byte a; lb
         // is at most TILE - 3 = 7), so that one OR gives it.
         const uint32_t obits = ok ? ((1u << lb[0]) | (1u << (8 + lb[1])) | (1u << (16 + lb[2]))) : 0u;
-        const uint32_t wbits = wave_or(obits);
+        const uint32_t wbits = wave_or(obits | (defer ? 1u << 31 : 0u));
         float wb[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) wb[q] = wave_sum(bnd[q]);
@@ -798,34 +838,36 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
         // every thread derives the chunk's scales and box from the waves'
         // partial results (no second barrier); the previous chunk's flush,
         // which ran after its scatter barrier, is complete here as well
+        // (all on the scalar unit: every lane holds the same sums)
         float sc[4], isc[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
           float T = 0.f;
 #pragma unroll
           for (int w = 0; w < NW; w++) T += s_red[w * 4 + q];
-          T *= 0.421875f;
-          if (!isfinite(T)) {
+          int tb = __builtin_amdgcn_readfirstlane(__float_as_int(T * 0.421875f));
+          if ((tb & 0x7f800000) == 0x7f800000) {
             if (tid == 0) atomicOr(P.err, ERR_NONFINITE);
-            T = 1.f;
+            tb = 0x3f800000;
           }
-          int e = 0;
-          frexpf(T > 0.f ? T : 1.f, &e);
-          e = max(e, -90);
-          sc[q] = ldexpf(1.f, 30 - e);
-          isc[q] = ldexpf(1.f, e - 30);
+          // 2^(30 - e) and its inverse for T = m 2^e, m in [1/2, 1), e >= -90; e = 1 for T = 0
+          const int e = tb == 0 ? 1 : max((tb >> 23) - 126, -90);
+          sc[q] = __int_as_float((157 - e) << 23);
+          isc[q] = __int_as_float((e + 97) << 23);
         }
-        int clo[3], chi[3];
+        int olo[3], ohi[3];   // the box before this chunk
         {
           uint32_t cb = 0;
 #pragma unroll
           for (int w = 0; w < NW; w++) cb |= s_ired[w];
+          cb = (uint32_t)__builtin_amdgcn_readfirstlane((int)cb);
+          any_deferred = !RETRY && (cb >> 31) != 0u;
 #pragma unroll
           for (int a = 0; a < 3; a++) {
             const uint32_t ab = (cb >> (8 * a)) & 0xffu;
-            clo[a] = ab ? __ffs(ab) - 1 : 1 << 20;
-            chi[a] = ab ? 31 - __clz(ab) : -(1 << 20);
-            if (clo[a] <= chi[a]) { blo[a] = min(blo[a], clo[a]); bhi[a] = max(bhi[a], chi[a]); }
+            olo[a] = blo[a];
+            ohi[a] = bhi[a];
+            if (ab) { blo[a] = min(blo[a], __ffs(ab) - 1); bhi[a] = max(bhi[a], 31 - __clz(ab)); }
           }
         }
         if (ok) {
@@ -864,57 +906,82 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
             }
           }
         }
-        if (c0 + NT < count) prefetch(c0 + NT);
+        if (!RETRY && !any_deferred && c0 + NT < count) prefetch(c0 + NT);
         __syncthreads();
         {
-          // flush the chunk's box into the float tile and clear the integers
-          // (the next chunk scatters only after its bound barrier)
-          if (clo[0] <= chi[0]) {
-            const int ex = chi[0] - clo[0] + 3, ey = chi[1] - clo[1] + 3, ez = chi[2] - clo[2] + 3;
-            const int cnt = ex * ey * ez;
+          // Flush: the entry's box so far (the stencils of every chunk up to this
+          // one) is walked, its integers read and cleared and added to the float
+          // tile, where the box so far held before this chunk; the last chunk's
+          // sums go straight to global memory, where a node's (m, mv) is one
+          // 16-byte word, so a one-chunk entry never touches the float tile.
+          // The walk divides by the box's extents with multipliers (exact for
+          // r d < 2^19): about 7 instructions a node against 60 for three integer
+          // divisions.  (Walking all 1000 nodes instead, with no index
+          // arithmetic at all, made the kernel 10 to 20% slower: it is the LDS
+          // traffic that the flush costs.)
+          const bool pub = last && !any_deferred;
+          if (blo[0] <= bhi[0]) {
+            const int ey = bhi[1] - blo[1] + 3, ez = bhi[2] - blo[2] + 3, eyz = ey * ez;
+            const int cnt = (bhi[0] - blo[0] + 3) * eyz;
+            const uint32_t m1 = div_mul(eyz), m2 = div_mul(ez);
             for (int r = tid; r < cnt; r += NT) {
-              int qq = ((clo[0] + r / (ey * ez)) * TILE + clo[1] + (r / ez) % ey) * TILE + clo[2] + r % ez;
+              const int i = (int)(((uint32_t)r * m1) >> 20), rem = r - i * eyz;
+              const int jj = (int)(((uint32_t)rem * m2) >> 20), k = rem - jj * ez;
+              const int qi = blo[0] + i, qj = blo[1] + jj, qk = blo[2] + k;
+              const int q = (qi * TILE + qj) * TILE + qk;
+              float4 val = make_float4((float)s_itile[q] * isc[0], (float)s_itile[TILE_NODES + q] * isc[1],
+                                       (float)s_itile[2 * TILE_NODES + q] * isc[2],
+                                       (float)s_itile[3 * TILE_NODES + q] * isc[3]);
 #pragma unroll
-              for (int c = 0; c < 4; c++) {
-                int iv = s_itile[c * TILE_NODES + qq];
-                if (iv != 0) {
-                  s_tile[c * TILE_NODES + qq] += (float)iv * isc[c];
-                  s_itile[c * TILE_NODES + qq] = 0;
-                }
+              for (int c = 0; c < 4; c++) s_itile[c * TILE_NODES + q] = 0;
+              if (qi >= olo[0] && qi <= ohi[0] + 2 && qj >= olo[1] && qj <= ohi[1] + 2 && qk >= olo[2] && qk <= ohi[2] + 2) {
+                const float4 o = s_tile[q];
+                val.x += o.x; val.y += o.y; val.z += o.z; val.w += o.w;
               }
+              if (pub) tile_out[q] = val;
+              else s_tile[q] = val;
             }
           }
         }
         if (MODE == MODE_FUSED) {
           uint32_t r = rank_finish(WR, A.touched, A.n_touched, (uint32_t)A.n_keys);
-          if (has && dst < (uint32_t)N) { A.out.key[dst] = nkey; A.out.rank[dst] = counted ? r : 0u; }
-          // a particle that could not be counted keeps a valid (key 0) slot
-          if (has && !counted && dst < (uint32_t)N) {
-            uint32_t r0 = atomicAdd(&A.counts[0], 1u);
-            if (r0 == 0u) touch_key(0u, A.touched, A.n_touched, (uint32_t)A.n_keys);
-            A.out.key[dst] = 0u;
-            A.out.rank[dst] = r0;
+          if (has && !defer && dst < (uint32_t)N) {
+            at32(A.out.key, 4u * dst) = nkey;
+            at32(A.out.rank, 4u * dst) = counted ? r : 0u;
+            // a particle that could not be counted keeps a valid (key 0) slot
+            if (!counted) {
+              uint32_t r0 = atomicAdd(&A.counts[0], 1u);
+              if (r0 == 0u) touch_key(0u, A.touched, A.n_touched, (uint32_t)A.n_keys);
+              A.out.key[dst] = 0u;
+              A.out.rank[dst] = r0;
+            }
           }
         }
+      } else if (!RETRY) {
+        any_deferred = __ballot(defer) != 0ull;
+      }
+      return any_deferred;
+    };
+    for (int c0 = 0; c0 < count; c0 += NT) {
+      const bool has = c0 + tid < count && start + c0 + tid < N;
+      const bool last = c0 + NT >= count;
+      bool defer = false;
+      if (FEAT == FEAT_LOG && MODE != MODE_P2G) {
+        pass(std::true_type{}, c0, has, defer, last);
+      } else if (pass(std::false_type{}, c0, has, defer, last)) {
+        bool none = false;
+        pass(std::true_type{}, c0, defer, none, last);
+        if (c0 + NT < count) prefetch(c0 + NT);
+      } else if (MODE == MODE_G2P && c0 + NT < count) {
+        prefetch(c0 + NT);
       }
     }
-    __syncthreads();
+    if (MODE == MODE_G2P) __syncthreads();   // (the velocity tile is staged anew for the next entry)
     if (MODE != MODE_G2P) {
-      // ---- publish the tile's non-zero box and mark the blocks it touches
+      // ---- mark the blocks the published tile touches
       const int lo0 = blo[0], lo1 = blo[1], lo2 = blo[2];
       const int hi0 = bhi[0] + 2, hi1 = bhi[1] + 2, hi2 = bhi[2] + 2;
-      const uint32_t bkey = (uint32_t)ent.x;
-      const size_t slot = (size_t)bkey + (size_t)ent.w * (size_t)A.n_keys;   // the entry's tile slot
       if (lo0 <= hi0 - 2) {
-        const int ex = hi0 - lo0 + 1, ey = hi1 - lo1 + 1, ez = hi2 - lo2 + 1;
-        const int cnt = ex * ey * ez;
-        // in global memory a node's (m, mv) is one 16-byte word
-        float4* T = reinterpret_cast<float4*>(A.tiles + slot * 4 * TILE_NODES);
-        for (int r = tid; r < cnt; r += NT) {
-          int qi = lo0 + r / (ey * ez), qj = lo1 + (r / ez) % ey, qk = lo2 + r % ez;
-          int q = (qi * TILE + qj) * TILE + qk;
-          T[q] = make_float4(s_tile[q], s_tile[TILE_NODES + q], s_tile[2 * TILE_NODES + q], s_tile[3 * TILE_NODES + q]);
-        }
         if (tid == 0) {
           int packed = lo0 | (lo1 << 4) | (lo2 << 8) | (hi0 << 12) | (hi1 << 16) | (hi2 << 20);
           A.tile_box[slot] = make_int2(packed, (int)stamp);
@@ -941,12 +1008,11 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
             if (tid == 0) base = atomicAdd(A.cl_count, (uint32_t)__popcll(wm));
             base = __shfl(base, 0);
             // a block is claimed once per step, so at most n_keys keys arrive
-            const uint32_t slot = base + (uint32_t)__popcll(wm & ((1ull << tid) - 1ull));
-            if (won && slot < (uint32_t)A.n_keys) A.cl_list[slot] = nk;
+            const uint32_t at = base + (uint32_t)__popcll(wm & ((1ull << tid) - 1ull));
+            if (won && at < (uint32_t)A.n_keys) A.cl_list[at] = nk;
           }
         }
       }
-      __syncthreads();
     }
   }
 }
@@ -1272,6 +1338,7 @@ static void enqueue_call(FastPath& f, const StepParams& P, const PState& user, i
   A.log_count = f.log_count;
   A.log_cap = f.log_cap;
   A.map_out = nullptr;
+  A.write_vc = 0;
   // Bookkeeping: `rd` is the list describing buf[cur] (the buffer the next
   // particle kernel reads); `wr` is the list describing the order in which
   // the current offsets place particles (the buffer the next kernel writes).
@@ -1293,11 +1360,13 @@ static void enqueue_call(FastPath& f, const StepParams& P, const PState& user, i
     if (step == 0) {
       k_particles<MODE_P2G, NT, FEAT_NONE><<<f.part_wgs, NT, 0, s>>>(A, P, g);
     } else {
+      const bool ckpt = f.ck_k > 0 && (f.ck_t0 + step) % f.ck_k == 0;
+      A.write_vc = ckpt ? 1 : 0;
       if (ev) hipEventRecord((*ev)[2 * ei], s);
       k_particles<MODE_FUSED, NT, FEAT><<<f.part_wgs, NT, 0, s>>>(A, P, g);
       if (ev) { hipEventRecord((*ev)[2 * ei + 1], s); ei++; }
       // the state at time t0 + step now sits in the output buffer
-      if (f.ck_k > 0 && (f.ck_t0 + step) % f.ck_k == 0) {
+      if (ckpt) {
         PState ck = packed_state((float*)(f.ck_base + (size_t)((f.ck_t0 + step) / f.ck_k) * f.ck_stride), N);
         export_state(f, A.out, ck, P.mats, s);
       }
@@ -1465,6 +1534,7 @@ void fast_fused(FastPath& f, const StepParams& P, const SortedState& in, const S
   A.cl_list = out.cl_list ? out.cl_list : f.cl_list;
   A.cl_count = out.cl_count ? out.cl_count : f.cl_count;
   A.map_out = map;
+  A.write_vc = 1;
   k_particles<MODE_FUSED, 256, FEAT_NONE><<<f.part_wgs, 256, 0, s>>>(A, P, f.g);
 }
 

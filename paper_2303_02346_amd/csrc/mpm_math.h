@@ -21,6 +21,17 @@ template <typename T> MPM_DI void matmul(const T* A, const T* B, T* C) {
 #pragma unroll
     for (int j = 0; j < 3; j++) C[i * 3 + j] = A[i * 3] * B[j] + A[i * 3 + 1] * B[3 + j] + A[i * 3 + 2] * B[6 + j];
 }
+// C = A B with a fixed choice of the fused products (left to itself the compiler
+// chooses by the order in which the operands happen to be computed, so that two
+// kernels, or two branches of one, can round the same product differently)
+MPM_DI double t_fma(double a, double b, double c) { return fma(a, b, c); }
+MPM_DI float t_fma(float a, float b, float c) { return fmaf(a, b, c); }
+template <typename T> MPM_DI void matmul_fma(const T* A, const T* B, T* C) {
+#pragma unroll
+  for (int i = 0; i < 3; i++)
+#pragma unroll
+    for (int j = 0; j < 3; j++) C[i * 3 + j] = t_fma(A[i * 3 + 2], B[6 + j], t_fma(A[i * 3], B[j], A[i * 3 + 1] * B[3 + j]));
+}
 // C = A B^T
 template <typename T> MPM_DI void matmul_nt(const T* A, const T* B, T* C) {
 #pragma unroll
@@ -105,7 +116,8 @@ template <typename T> MPM_DI void jacobi_rotate(T* A, T* V, int p, int q) {
 // diagonal (eigenvalues then exact to about 1e-24 relative where separated,
 // 1e-12 where they nearly coincide).  In FP32 they stop at 1e-7, the
 // rounding level, within at most 6 sweeps.  Returns whether that happened.
-template <typename T> MPM_DI bool svd3(const T* F, T* U, T* s, T* V) {
+// FIXED: the products F V are fused in a fixed choice (see matmul_fma).
+template <typename T, bool FIXED = false> MPM_DI bool svd3(const T* F, T* U, T* s, T* V) {
   constexpr bool dbl = sizeof(T) == 8;
   constexpr int max_sweeps = dbl ? 12 : 6;
   const T tol2 = dbl ? T(1e-24) : T(1e-14);
@@ -140,7 +152,17 @@ template <typename T> MPM_DI bool svd3(const T* F, T* U, T* s, T* V) {
     for (int k = 0; k < 3; k++) V[k * 3 + 2] = -V[k * 3 + 2];
   }
   T B[9];
-  matmul(F, V, B);
+  if (FIXED) {
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+      const T f0 = F[i * 3], f1 = F[i * 3 + 1], f2 = F[i * 3 + 2];
+      B[i * 3] = t_fma(f2, V[6], t_fma(f1, V[3], f0 * V[0]));
+      B[i * 3 + 1] = t_fma(f2, V[7], t_fma(f0, V[1], f1 * V[4]));
+      B[i * 3 + 2] = t_fma(f2, V[8], t_fma(f1, V[5], f0 * V[2]));
+    }
+  } else {
+    matmul(F, V, B);
+  }
   T b0[3] = {B[0], B[3], B[6]}, b1[3] = {B[1], B[4], B[7]}, b2[3] = {B[2], B[5], B[8]};
   // norms and normalisations from one reciprocal square root each
   const T q0 = b0[0] * b0[0] + b0[1] * b0[1] + b0[2] * b0[2];
@@ -190,6 +212,15 @@ template <typename T> MPM_DI void usv(const T* U, const T* g, const T* V, T* out
 #pragma unroll
     for (int j = 0; j < 3; j++)
       out[i * 3 + j] = U[i * 3] * g[0] * V[j * 3] + U[i * 3 + 1] * g[1] * V[j * 3 + 1] + U[i * 3 + 2] * g[2] * V[j * 3 + 2];
+}
+
+// usv with a fixed choice of the fused products (see matmul_fma)
+template <typename T> MPM_DI void usv_fma(const T* U, const T* g, const T* V, T* out) {
+#pragma unroll
+  for (int i = 0; i < 3; i++)
+#pragma unroll
+    for (int j = 0; j < 3; j++)
+      out[i * 3 + j] = t_fma(U[i * 3 + 2] * g[2], V[j * 3 + 2], t_fma(U[i * 3 + 1] * g[1], V[j * 3 + 1], U[i * 3] * g[0] * V[j * 3]));
 }
 
 // Adjoint of an isotropic map Phi(F) = U diag(g(s)) V^T.  Given Phibar,

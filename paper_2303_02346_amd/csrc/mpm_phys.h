@@ -132,13 +132,13 @@ MPM_DI bool stress_solid(const float* Ff, const MatDev& M, float* tau) {
   return stress_solid_usv(F, U, s, V, M, tau);
 }
 
-// The solid stress with an FP32 SVD, redone in FP64 when F is
-// ill-conditioned (s2 < s0/4) or the FP32 sweeps do not converge.
-// Returns false when a Hencky solid has a singular value that is not positive.
-MPM_DI bool stress_solid_fast(const float* Ff, const MatDev& M, float* tau) {
+// The solid stress with an FP32 SVD.  Returns false, without output, when F is
+// ill-conditioned (s2 < s0/4) or the FP32 sweeps do not converge: the caller
+// takes stress_solid.
+MPM_DI bool stress_solid_fp32(const float* Ff, const MatDev& M, float* tau) {
   float U[9], s[3], V[9];
   const bool conv = svd3(Ff, U, s, V);
-  if (!conv || !(s[2] > 0.25f * s[0])) return stress_solid(Ff, M, tau);
+  if (!conv || !(s[2] > 0.25f * s[0])) return false;
   if (corotated_kind(M.kind)) {
     float R[9], D[9], T[9];
     matmul_nt(U, V, R);
@@ -340,9 +340,9 @@ MPM_DI int plastic_step(const float* Md, const float* Fin, const MatDev& M, floa
     T Mdd[9], Fd[9];
 #pragma unroll
     for (int k = 0; k < 9; k++) { Mdd[k] = (T)Md[k]; Fd[k] = (T)Fin[k]; }
-    matmul(Mdd, Fd, Ft);
+    matmul_fma(Mdd, Fd, Ft);
   }
-  const bool conv = svd3(Ft, R.U, s, R.V);
+  const bool conv = svd3<T, true>(Ft, R.U, s, R.V);
   if (!dbl && (!conv || !(s[2] > T(0.25) * s[0]))) return PLASTIC_RETRY;
   R.cse = 0;
   if (!(s[2] > T(0))) {
@@ -370,7 +370,8 @@ MPM_DI int plastic_step(const float* Md, const float* Fin, const MatDev& M, floa
     T gg[3], Fn[9];
 #pragma unroll
     for (int a = 0; a < 3; a++) gg[a] = t_exp(R.ep[a]);
-    usv(R.U, gg, R.V, Fn);
+    if (TAU) usv_fma(R.U, gg, R.V, Fn);
+    else usv(R.U, gg, R.V, Fn);
 #pragma unroll
     for (int k = 0; k < 9; k++) Fo[k] = (float)Fn[k];
   }

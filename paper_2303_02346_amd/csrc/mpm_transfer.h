@@ -1,7 +1,8 @@
 // Sums over the 27 nodes of a particle's quadratic B-spline stencil, read
-// from a tile of E^3 nodes staged in LDS (E = VT for a block's velocity
-// tile, 3 for one particle's own stencil; lb = the stencil's first node in
-// the tile), shared by the forward and adjoint transfer kernels.
+// from a tile of nodes staged in LDS (a block's 8^3 velocity tile with the
+// padded strides VT_ROW and VT_PLANE, or one particle's own 3^3 stencil; lb =
+// the stencil's first node in the tile), shared by the forward and adjoint
+// transfer kernels.
 //
 // Both sums run over z inside y inside x, so that each partial sum is
 // weighted once by the outer weights (w = wx wy wz factorises); the loads of
@@ -10,14 +11,49 @@
 // rather than 27 bounds the register count).
 #pragma once
 #include <hip/hip_runtime.h>
+#include "mpm_blocks.h"
 #include "mpm_fast.h"
 #include "mpm_phys.h"
 
 namespace mpm {
 
+// A block's 8^3 window of node values (nodes 4 b - 1 .. 4 b + 6 per axis; zero
+// outside the grid) from a block-layout array into LDS, by NT threads.  The
+// window spans three blocks per axis, whose key parts are wavefront-uniform:
+// spreading each node's own block coordinates cost about 45 vector
+// instructions a node.
+template <int NT>
+__device__ __forceinline__ void stage_window(float4* __restrict__ tile, const float4* __restrict__ src,
+                                             const FastGeom& g, int sc, int bx, int by, int bz, int tid) {
+  const uint32_t base = (uint32_t)sc << (3 * g.kb);
+  const uint32_t kx[3] = {spread3(bx - 1) << 2, spread3(bx) << 2, spread3(bx + 1) << 2};
+  const uint32_t ky[3] = {spread3(by - 1) << 1, spread3(by) << 1, spread3(by + 1) << 1};
+  const uint32_t kz[3] = {spread3(bz - 1), spread3(bz), spread3(bz + 1)};
+  constexpr int R = (VT_NODES + NT - 1) / NT;
+  float4 val[R];
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int q = tid + r * NT;
+    const int qi = q / (VT * VT), qj = (q / VT) % VT, qk = q % VT;
+    const int gx = 4 * bx - 1 + qi, gy = 4 * by - 1 + qj, gz = 4 * bz - 1 + qk;
+    val[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (q < VT_NODES && gx >= 0 && gy >= 0 && gz >= 0 && gx < g.n && gy < g.n && gz < g.n) {
+      // window node 0 lies in the block before, 1..4 in the block, 5..7 after
+      const uint32_t kk = base | (qi == 0 ? kx[0] : (qi < 5 ? kx[1] : kx[2])) |
+                          (qj == 0 ? ky[0] : (qj < 5 ? ky[1] : ky[2])) | (qk == 0 ? kz[0] : (qk < 5 ? kz[1] : kz[2]));
+      val[r] = src[(size_t)kk * 64 + ((((qi + 3) & 3) << 4) | (((qj + 3) & 3) << 2) | ((qk + 3) & 3))];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int q = tid + r * NT;
+    if (q < VT_NODES) tile[(q / (VT * VT)) * VT_PLANE + ((q / VT) % VT) * VT_ROW + q % VT] = val[r];
+  }
+}
+
 // G2P gather: vn = sum_i w_i v_i and Bi = sum_i w_i v_i idx_i^T with idx_i
 // in {0,1,2}^3 the node's offset in the stencil (v_i = the tile's xyz).
-template <int E = VT>
+template <int ROW = VT_ROW, int PLANE = VT_PLANE>
 __device__ __forceinline__ void g2p_gather(const float4* __restrict__ s_v, const int* lb, const Stencil& S,
                                            float* vn, float* Bi) {
 #pragma unroll
@@ -30,7 +66,7 @@ __device__ __forceinline__ void g2p_gather(const float4* __restrict__ s_v, const
     float p0[3] = {0, 0, 0}, pj[3] = {0, 0, 0}, pk[3] = {0, 0, 0};
 #pragma unroll
     for (int jj = 0; jj < 3; jj++) {
-      const float4* row = s_v + ((lb[0] + i) * E + lb[1] + jj) * E + lb[2];
+      const float4* row = s_v + (lb[0] + i) * PLANE + (lb[1] + jj) * ROW + lb[2];
       const float4 g0 = row[0], g1 = row[1], g2 = row[2];
       // r = sum_k w_k v_k, rk = sum_k k w_k v_k along z
       const float r[3] = {S.w[2][0] * g0.x + wz1 * g1.x + wz2 * g2.x, S.w[2][0] * g0.y + wz1 * g1.y + wz2 * g2.y,
@@ -63,7 +99,7 @@ __device__ __forceinline__ void g2p_gather(const float4* __restrict__ s_v, const
 // adjoint of the node's momentum, mom = mvp + A (x_i - x_p), or of the G2P
 // terms v_i (vbt + Bb (x_i - x_p)), written as c0 + Ad idx).  With WANT_G it
 // also returns G0 = sum_i w_i g_i.xyz and Gi = sum_i w_i g_i.xyz idx_i^T.
-template <bool WANT_G, int E = VT>
+template <bool WANT_G, int ROW = VT_ROW, int PLANE = VT_PLANE>
 __device__ __forceinline__ void weight_grad_sum(const float4* __restrict__ tile, const int* lb, const Stencil& S,
                                                 const float* c0, const float* Ad, float mw, float* X, float* G0,
                                                 float* Gi) {
@@ -84,7 +120,7 @@ __device__ __forceinline__ void weight_grad_sum(const float4* __restrict__ tile,
     float p0[3] = {0, 0, 0}, pj[3] = {0, 0, 0}, pk[3] = {0, 0, 0};
 #pragma unroll
     for (int jj = 0; jj < 3; jj++) {
-      const float4* row = tile + ((lb[0] + i) * E + lb[1] + jj) * E + lb[2];
+      const float4* row = tile + (lb[0] + i) * PLANE + (lb[1] + jj) * ROW + lb[2];
       const float4 g[3] = {row[0], row[1], row[2]};
       float m2[3];
 #pragma unroll

@@ -475,3 +475,24 @@ def test_records_of_every_step_vs_oracle():
     with pytest.raises(_lib.MpmError) as e:
         sim.log_samples(buf, count)
     assert e.value.status == _lib.MPM_ESTATE
+
+
+@pytest.mark.parametrize("threads,share", [(128, 2), (256, 0), (256, 1), (256, 2), (512, 2)])
+def test_deferred_particles_over_several_chunks_vs_oracle(threads, share):
+    """Blocks of several chunks whose ill-conditioned solids are left to the
+    chunk's FP64 pass: the tile box and the float tile grow over both passes
+    of every chunk, and the last pass publishes (every launch shape, blocks
+    shared by two workgroups and not).  Tolerances: those of the
+    ill-conditioned gradient test's forward state."""
+    from parity import ill_conditioned_solids
+    sc = scenes.tiny(n_particles=4001, n_grid=16, steps=4, seed=7,
+                     kinds=(scenes.ELASTIC, scenes.LIQUID, scenes.SAND, scenes.VONMISES, scenes.BOX))
+    n_ill = ill_conditioned_solids(sc, 0)
+    assert n_ill > 1000
+    sim = sim_of(sc)
+    sim.set_option(2, threads)
+    sim.set_option(7, share)
+    sim.step(sc.horizon)
+    say(f"{n_ill} ill-conditioned of {sc.n} particles, {threads} threads, share {share}")
+    compare_states(sim.state_numpy(), oracle_state(sc, sc.horizon), liquid_mask(sc), tol_x=1e-6, tol=1e-4,
+                   tol_FJ=1e-5, n_grid=sc.n_grid)
