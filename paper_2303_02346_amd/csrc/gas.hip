@@ -1229,6 +1229,7 @@ struct gas_ctx {
   bool stats;
   double last_res;
   int last_err_bits;
+  HostWord err_host;
   KernelTimer t_adv, t_smooth;
 };
 
@@ -1423,8 +1424,7 @@ void gas_adjoint_step(gas_ctx* c, const gas_state& st, const gas_state& an, cons
 
 // Waits for the call's work; reads (and clears) the device error word.
 int sync_ok(gas_ctx* c) {
-  int bits = 0;
-  if (hipMemcpyAsync(&bits, c->ws + c->L.err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+  if (hipMemcpyAsync(c->err_host.p, c->ws + c->L.err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
     return MPM_EHIP;
   if (hipStreamSynchronize(c->stream) != hipSuccess) return MPM_EHIP;
   if (hipGetLastError() != hipSuccess) return MPM_EHIP;
@@ -1435,7 +1435,7 @@ int sync_ok(gas_ctx* c) {
     if (hipMemcpy(&r, c->ws + c->L.resout, sizeof(double), hipMemcpyDeviceToHost) != hipSuccess) return MPM_EHIP;
     c->last_res = r;
   }
-  if (bits) {
+  if (const int bits = *c->err_host.p) {
     c->last_err_bits = bits;
     if (hipMemsetAsync(c->ws + c->L.err, 0, sizeof(int), c->stream) != hipSuccess) return MPM_EHIP;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return MPM_EHIP;
@@ -1515,7 +1515,17 @@ int gas_create(const gas_desc* d, void* workspace_dev, size_t ws_bytes, void* st
       }
     }
   }
-  if (hipStreamSynchronize(c->stream) != hipSuccess || hipGetLastError() != hipSuccess) { delete c; return MPM_EHIP; }
+  // the emitter's pose at t = 0: its slot is written here only
+  double pose0[POSE_DOUBLES];
+  for (int k = 0; k < 3; k++) pose0[k] = c->d.emit_pos0[k];
+  for (int k = 0; k < 9; k++) pose0[3 + k] = c->d.emit_rot0[k];
+  if (!c->err_host.create() ||
+      hipMemcpyAsync(c->ws + c->L.pose, pose0, sizeof(pose0), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+      hipStreamSynchronize(c->stream) != hipSuccess || hipGetLastError() != hipSuccess) {
+    c->err_host.destroy();
+    delete c;
+    return MPM_EHIP;
+  }
   *out = c;
   return MPM_OK;
 }
@@ -1525,12 +1535,7 @@ int gas_set_state(gas_ctx* c, const gas_state* st) {
   c->user = *st;
   c->has_state = true;
   c->t = 0;
-  double pose0[POSE_DOUBLES];
-  for (int k = 0; k < 3; k++) pose0[k] = c->d.emit_pos0[k];
-  for (int k = 0; k < 9; k++) pose0[3 + k] = c->d.emit_rot0[k];
-  if (hipMemcpyAsync(c->ws + c->L.pose, pose0, sizeof(pose0), hipMemcpyHostToDevice, c->stream) != hipSuccess)
-    return MPM_EHIP;
-  return sync_ok(c);
+  return MPM_OK;
 }
 
 int gas_set_actions(gas_ctx* c, int32_t t0, int32_t n, const float* actions_dev) {
@@ -1666,6 +1671,7 @@ int gas_destroy(gas_ctx* c) {
   if (!c) return MPM_EINVAL;
   c->t_adv.destroy();
   c->t_smooth.destroy();
+  c->err_host.destroy();
   delete c;
   return MPM_OK;
 }

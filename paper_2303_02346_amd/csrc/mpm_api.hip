@@ -173,6 +173,7 @@ struct mpm_ctx {
   size_t state_bytes;
   FastPath fast;
   KernelTimer timer;
+  HostWord err_host;
   bool plain_adjoint;
   RigidCtx rigid;           // n_bodies = 0: no rigid bodies
   // captured calls (graph mode), keyed by their start, steps, pointers and
@@ -277,12 +278,11 @@ static float4* G(mpm_ctx* c, size_t off) { return (float4*)(c->ws + off); }
 // Read and clear the device error word; the call's only host synchronisation.
 static int finish(mpm_ctx* c) {
   int* err = (int*)(c->ws + c->L.err);
-  int host = 0;
-  if (hipMemcpyAsync(&host, err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return MPM_EHIP;
+  if (hipMemcpyAsync(c->err_host.p, err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return MPM_EHIP;
   if (hipStreamSynchronize(c->stream) != hipSuccess) return MPM_EHIP;
   if (hipGetLastError() != hipSuccess) return MPM_EHIP;
   c->timer.collect();
-  if (host) {
+  if (const int host = *c->err_host.p) {
     c->last_err_bits = host;
     if (hipMemsetAsync(err, 0, sizeof(int), c->stream) != hipSuccess) return MPM_EHIP;
     return MPM_EDOMAIN;
@@ -372,7 +372,16 @@ int mpm_create(const mpm_desc* d, void* workspace_dev, size_t ws_bytes, void* st
   if (d->scene_offsets) for (int s = 0; s <= S; s++) offs[s] = d->scene_offsets[s];
   else { offs[0] = 0; offs[1] = d->n_particles; }
   int rc = MPM_OK;
-  if (hipMemcpyAsync(c->ws + L.mats, c->mats.data(), 256 * sizeof(MatDev), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+  // the collider's pose at t = 0: its slot is written here only (the steps
+  // write the slots that follow)
+  std::vector<double> pose0((size_t)S * POSE_DOUBLES);
+  for (int s = 0; s < S; s++) {
+    for (int k = 0; k < 3; k++) pose0[s * POSE_DOUBLES + k] = c->cyl_pos0[3 * s + k];
+    for (int k = 0; k < 9; k++) pose0[s * POSE_DOUBLES + 3 + k] = c->cyl_rot0[9 * s + k];
+  }
+  if (!c->err_host.create() ||
+      hipMemcpyAsync(c->ws + L.pose, pose0.data(), pose0.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+      hipMemcpyAsync(c->ws + L.mats, c->mats.data(), 256 * sizeof(MatDev), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
       hipMemcpyAsync(c->ws + L.offs, offs.data(), (S + 1) * sizeof(int64_t), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
       hipMemcpyAsync(c->ws + L.cyl_radius, c->cyl_radius.data(), S * sizeof(float), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
       hipMemsetAsync(c->ws + L.err, 0, 64, c->stream) != hipSuccess)
@@ -392,7 +401,7 @@ int mpm_create(const mpm_desc* d, void* workspace_dev, size_t ws_bytes, void* st
     if (hipMemsetAsync(c->ws + L.cstats, 0, 64, c->stream) != hipSuccess) rc = MPM_EHIP;
   }
   if (rc == MPM_OK && hipStreamSynchronize(c->stream) != hipSuccess) rc = MPM_EHIP;
-  if (rc != MPM_OK) { delete c; return rc; }
+  if (rc != MPM_OK) { c->err_host.destroy(); delete c; return rc; }
   *out = c;
   return MPM_OK;
 }
@@ -406,27 +415,18 @@ int mpm_set_state(mpm_ctx* c, const mpm_state* st) {
   c->user = *st;
   c->has_state = true;
   c->t = 0;
-  int S = c->d.n_scenes;
-  std::vector<double> pose0((size_t)S * POSE_DOUBLES);
-  for (int s = 0; s < S; s++) {
-    for (int k = 0; k < 3; k++) pose0[s * POSE_DOUBLES + k] = c->cyl_pos0[3 * s + k];
-    for (int k = 0; k < 9; k++) pose0[s * POSE_DOUBLES + 3 + k] = c->cyl_rot0[9 * s + k];
-  }
-  if (hipMemcpyAsync(c->ws + c->L.pose, pose0.data(), pose0.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess)
-    return MPM_EHIP;
-  int rstat = 0;
   if (c->rigid.n_bodies > 0) {
     // rest shapes of the rigid bodies from this state
     StepParams P = make_params(c);
+    int rstat = 0;
     rigid_setup(c->rigid, P, user_pstate(st, c->d.n_particles), c->stream);
-    if (hipMemcpyAsync(&rstat, c->rigid.status, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+    if (hipMemcpyAsync(&rstat, c->rigid.status, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+        hipStreamSynchronize(c->stream) != hipSuccess)
       return MPM_EHIP;
-  }
-  // pose0 and rstat are host temporaries: wait for the copies
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return MPM_EHIP;
-  if (rstat) {
-    c->has_state = false;
-    return MPM_EINVAL;
+    if (rstat) {
+      c->has_state = false;
+      return MPM_EINVAL;
+    }
   }
   return MPM_OK;
 }
@@ -1058,6 +1058,7 @@ int mpm_destroy(mpm_ctx* c) {
   for (auto& g : c->bgraphs) destroy_call_graph(g);
   for (auto& g : c->rgraphs) destroy_call_graph(g);
   c->timer.destroy();
+  c->err_host.destroy();
   fast_destroy(c->fast);
   delete c;
   return MPM_OK;

@@ -119,6 +119,17 @@ struct KernelTimer {
   }
 };
 
+// A device error word's copy in pinned host memory: read after a stream has been
+// waited for, without the staged (and blocking) copy that pageable memory takes.
+struct HostWord {
+  int* p = nullptr;
+  bool create() { return hipHostMalloc((void**)&p, sizeof(int), hipHostMallocDefault) == hipSuccess; }
+  void destroy() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+  }
+};
+
 // ---- launch wrappers (mpm_kernels.hip) ----
 void launch_pose(int n_scenes, int t0, int n, float dt, const float* act, double* pose, hipStream_t s);
 void launch_zero(void* p, size_t bytes, hipStream_t s);   // fills floor(bytes / 16) 16-byte words

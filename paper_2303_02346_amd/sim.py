@@ -15,6 +15,7 @@ import numpy as np
 import torch
 
 from . import _lib
+from . import scenes as scenes_mod
 from .scenes import Scene, concat_scenes
 
 STATE_ROWS = 25   # x(3) v(3) C(9) F(9) J(1), each row of length N
@@ -94,6 +95,11 @@ class Simulator:
         self.buf = torch.zeros(STATE_ROWS, self.N, dtype=torch.float32, device=self.device)
         self.mat = torch.from_numpy(arrs["mat"].astype(np.uint8)).to(self.device)
         self._init_arrays = arrs
+        # the scenes' initial state as the buffer holds it, uploaded once:
+        # converting the host arrays for every rollout took longer than the
+        # rollout (6 ms at 250k particles)
+        self._buf0 = torch.from_numpy(self._host_state(arrs)).to(self.device)
+        self._rigid = any(m.kind == scenes_mod.RIGID for m in mats)
         self.actions = torch.zeros(self.horizon, self.S, 6, dtype=torch.float32, device=self.device)
         acts = np.zeros((self.horizon, self.S, 6))
         for s, sc in enumerate(self.scenes):
@@ -174,10 +180,7 @@ class Simulator:
                              self.mat.data_ptr() if with_mat else None)
 
     # ---- calls -------------------------------------------------------------
-    def load(self, arrs=None):
-        """Copy initial particle arrays (host, float64 from the scene
-        generator) into the device state, FP32."""
-        a = self._init_arrays if arrs is None else arrs
+    def _host_state(self, a) -> np.ndarray:
         N = self.N
         host = np.empty((STATE_ROWS, N), np.float32)
         host[0:3] = a["x"].T
@@ -185,7 +188,12 @@ class Simulator:
         host[6:15] = a["C"].reshape(N, 9).T
         host[15:24] = a["F"].reshape(N, 9).T
         host[24] = a["J"]
-        self.buf.copy_(torch.from_numpy(host))
+        return host
+
+    def load(self, arrs=None):
+        """Copy initial particle arrays (host, float64 from the scene
+        generator) into the device state, FP32; the scenes' own by default."""
+        self.buf.copy_(self._buf0 if arrs is None else torch.from_numpy(self._host_state(arrs)))
 
     def reset(self, arrs=None):
         self.load(arrs)
@@ -193,7 +201,8 @@ class Simulator:
         self.set_actions(self.actions)
 
     def set_state(self):
-        self._sync_in()
+        if self._rigid:          # (rest shapes are taken from the state on the library's stream)
+            self._sync_in()
         self._state = self.state_struct()
         _lib.check(_lib.lib().mpm_set_state(self.ctx, ctypes.byref(self._state)), "mpm_set_state", self.ctx)
 

@@ -218,3 +218,40 @@ def test_gas_long_axes_vs_oracle():
     sim.step(3)
     say(f"  pressure residual {sim.residual():.2e}")
     compare(sim.state_numpy(), G.rollout_scene(sc, steps=3))
+
+
+def test_initial_states_are_loaded_again():
+    """Loads in a row (the staging memory is reused), one field replaced, a
+    field of the wrong size refused; and a particle scene's own state restored
+    by a reset after steps and after another state was loaded."""
+    from paper_2303_02346_amd.gas import GasSim
+    from paper_2303_02346_amd.sim import Simulator
+    sc = scenes.gas_room(n=(16, 24, 12), steps=2)
+    sim = GasSim(sc)
+    for k in range(3):
+        sc.u = sc.u + 0.25 * k          # (the scene's current fields are read)
+        sim.reset()
+        u, v, w, s = (t.cpu().numpy() for t in sim.split(sim.buf))
+        for got, ref in ((u, sc.u), (v, sc.v), (w, sc.w), (s, sc.s)):
+            assert np.array_equal(got, ref.astype(np.float32))
+        sim.step(2)
+    other = np.random.default_rng(0).random(sc.w.shape)
+    sim.load(w=other)
+    assert np.array_equal(sim.split(sim.buf)[2].cpu().numpy(),
+                          other.astype(np.float32))
+    with pytest.raises(RuntimeError):
+        sim.load(w=other[:-1])
+    p = scenes.tiny(n_particles=300, steps=4, seed=3)
+    ps = Simulator(p)
+    first = ps.buf.clone()
+    arrs = {k: np.array(getattr(p, k)) for k in ("x", "v", "C", "F", "J")}
+    arrs["v"] = arrs["v"] + 0.1
+    for _ in range(2):
+        ps.step(4)
+        assert not torch.equal(ps.buf, first)
+        ps.reset()
+        assert torch.equal(ps.buf, first)
+        ps.reset(arrs)
+        assert torch.equal(ps.v, torch.from_numpy(arrs["v"].T.astype(np.float32)).cuda())
+        ps.reset()
+        assert torch.equal(ps.buf, first)
