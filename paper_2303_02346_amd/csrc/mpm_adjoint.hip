@@ -13,10 +13,6 @@
 //                         the particle update, and the scatter of the
 //                         velocity adjoint into a fixed-point LDS tile whose
 //                         non-zero box is published (no global float atomics)
-//   k_g2p_adj_redo        the particles whose plastic-return adjoint is
-//                         ill-conditioned in FP32, listed by the kernel
-//                         above: the same steps with the FP64 adjoint, the
-//                         scatter added to the published tiles
 //   k_grid_adj_tiled      per node of the blocks claimed in the recompute:
 //                         sum of the 27 neighbouring tiles, then the adjoint
 //                         of the node update (walls, contact, gravity,
@@ -25,14 +21,23 @@
 //   k_p2g_adj_tiled       one workgroup per occupied block: the P2G adjoint
 //                         gathered from an LDS copy of the node adjoints,
 //                         through the stress adjoint
-//   k_p2g_adj_redo        the solids whose F is ill-conditioned in FP32,
-//                         listed by the kernel above: the same with FP64 SVDs.
-// The FP64 paths run in kernels of their own so that their register demand
-// does not set the occupancy of the common FP32 path.
+// Particles whose FP32 plastic-return or stress adjoint is ill-conditioned are
+// done by a second pass in FP64 in the same workgroup, which only workgroups
+// that hold such a particle run (kernels of their own over a list of those
+// particles cost 2 x 5 us a step with empty lists).
+// Both particle kernels are bound by latency at the few wavefronts that their
+// registers allow, so they are kept free of spills: held to two wavefronts per
+// SIMD they take 40.5 and 29.6 us at 250k particles on 128^3 (half of them
+// sand), to three 52.3 and 46.7 (the SVD's and the FP64 pass's live values are
+// then spilled).  They took 46.7 and 46.1 us, and 10 us for the FP64 lists,
+// with 64-bit row addresses, bound sums through LDS shuffles and four
+// barriers a chunk, integer divisions in the flush, and v and C adjoint rows
+// that the first kernel zeroed and the second added to.
 // The adjoint of s_{t+1} is read through the row map that the segment's sort
 // recorded, so no separate permutation pass is needed.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include "mpm_adjoint.h"
 #include "mpm_blocks.h"
 #include "mpm_math.h"
@@ -41,107 +46,118 @@
 
 namespace mpm {
 
-namespace {
-
-__device__ inline float4 stage_node(const float4* __restrict__ src, const FastGeom& g, int sc, int gx, int gy, int gz) {
-  if (gx < 0 || gy < 0 || gz < 0 || gx >= g.n || gy >= g.n || gz >= g.n) return make_float4(0.f, 0.f, 0.f, 0.f);
-  uint32_t kk = block_key(g, sc, gx >> 2, gy >> 2, gz >> 2);
-  return src[(size_t)kk * 64 + (((gx & 3) << 4) | ((gy & 3) << 2) | (gz & 3))];
-}
-
-}  // namespace
 
 // ---------------------------------------------------------------------------
 // Adjoint of G2P and of the particle update; scatter of the grid velocity
 // adjoint.  Writes the direct part of the state adjoint of s_t (x, F, J; the
-// v and C adjoints of s_t come only through P2G and are added later).
+// v and C adjoints of s_t come only through P2G, whose adjoint writes them).
 // ---------------------------------------------------------------------------
-// (three workgroups per CU; the FP64 plastic-return adjoint runs in
-// k_g2p_adj_redo, so that its registers do not count here)
 template <int NT>
-__global__ __launch_bounds__(NT, 3) void k_g2p_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
+__global__ __launch_bounds__(NT, 2) void k_g2p_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
   constexpr int NW = NT / 64;
   constexpr int NQ = 3;   // velocity adjoint components
   __shared__ float4 s_v[VT_LDS];
-  __shared__ float s_tile[NQ * TILE_NODES];
-  __shared__ int s_itile[NQ * TILE_NODES];
-  __shared__ int s_lo[3], s_hi[3];
-  __shared__ float s_red[NW * NQ], s_scale[2 * NQ];
-  __shared__ int s_ired[NW * 6 + 6];
-  const int tid = threadIdx.x;
+  __shared__ float4 s_tile[TILE_NODES];
+  __shared__ __align__(16) int s_itile[NQ * TILE_NODES];
+  __shared__ float s_red[NW * NQ];
+  __shared__ uint32_t s_ired[NW];
   const int N = A.N;
-  const PState st = packed_state(A.st.f, N);
   const uint32_t n_list = A.list_n[0];
   const uint32_t stamp = (A.gen[0] << 16) | A.sid;
   for (uint32_t e = blockIdx.x; e < n_list; e += gridDim.x) {
-    const int4 ent = A.list[e];
+    // (opaque to the entry loop, and the entry decoded on the scalar unit: see k_particles)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    int4 ent = A.list[e];
+    ent.x = __builtin_amdgcn_readfirstlane(ent.x);
+    ent.y = __builtin_amdgcn_readfirstlane(ent.y);
+    ent.z = __builtin_amdgcn_readfirstlane(ent.z);
+    ent.w = __builtin_amdgcn_readfirstlane(ent.w);
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
-    stage_window<NT>(s_v, A.vgrid, g, sc, bx, by, bz, tid);
-    for (int q = tid; q < NQ * TILE_NODES; q += NT) { s_tile[q] = 0.f; s_itile[q] = 0; }
-    if (tid < 3) { s_lo[tid] = 1 << 20; s_hi[tid] = -(1 << 20); }
-    __syncthreads();
     const int start = ent.y, count = ent.z;
-    for (int c0 = 0; c0 < count; c0 += NT) {
-      const int j = start + c0 + tid;
-      const bool has = (c0 + tid) < count && j < N;
-      bool ok = has;
-      float x[3] = {0, 0, 0};
-      int m = 0;
-      if (has) {
+    // position, material and next row are loaded one chunk ahead
+    float px[3] = {0, 0, 0};
+    int pm = 0;
+    uint32_t pn = 0;
+    auto load_inputs = [&](int jn) {
+      const uint32_t off = 4u * (uint32_t)jn;
 #pragma unroll
-        for (int a = 0; a < 3; a++) x[a] = st.x[a * (size_t)N + j];
-        m = A.st.mat[j];
+      for (int a = 0; a < 3; a++) px[a] = row32(A.st.f, a, N, off);
+      pm = A.st.mat[(uint32_t)jn];
+      pn = at32(A.map, off);
+    };
+    auto prefetch = [&](int c0n) {
+      const int jn = start + c0n + tid;
+      if (c0n + tid < count && jn < N) load_inputs(jn);
+    };
+    prefetch(0);
+    stage_window<NT>(s_v, A.vgrid, g, sc, bx, by, bz, tid);
+    if (e == blockIdx.x) {
+      // the integer tile starts at zero; every flush leaves it so
+      for (int r = tid; r < NQ * TILE_NODES / 4; r += NT) reinterpret_cast<int4*>(s_itile)[r] = make_int4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    const size_t slot = (size_t)(uint32_t)ent.x + (size_t)ent.w * (size_t)g.n_keys;   // the entry's tile slot
+    float4* tile_out = reinterpret_cast<float4*>(A.tiles + slot * 4 * TILE_NODES);
+    int blo[3] = {1 << 20, 1 << 20, 1 << 20}, bhi[3] = {-(1 << 20), -(1 << 20), -(1 << 20)};
+    // One pass over a chunk, as in k_particles: the main pass takes the FP32
+    // plastic-return adjoint, and lanes where that is ill-conditioned are done
+    // by a second pass (RETRY) in FP64.
+    auto pass = [&](auto retry, int c0, const bool has, bool& defer, bool last) -> bool {
+      constexpr bool RETRY = decltype(retry)::value;
+      const int j = start + c0 + tid;
+      const uint32_t off = 4u * (uint32_t)j;
+      if (RETRY) {
+        if (has) load_inputs(j);
       }
-      const MatDev& M = P.mats[m];
+      const float x[3] = {px[0], px[1], px[2]};
+      const uint32_t jn = has ? pn : 0u;
+      const MatDev& M = P.mats[has ? pm : 0];
+      bool ok = has;
       Stencil S;
       int lb[3] = {0, 0, 0}, lv[3] = {0, 0, 0};
       if (ok) {
         const bool in_grid = stencil_setup(x, P, S);
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-          lv[a] = S.base[a] - ((a == 0 ? ox : a == 1 ? oy : oz) - 1);
-          lb[a] = S.base[a] - ((a == 0 ? ox : a == 1 ? oy : oz) - 2);
-        }
-        const bool in_tile = lv[0] >= 0 && lv[1] >= 0 && lv[2] >= 0 && lv[0] <= VT - 3 && lv[1] <= VT - 3 &&
-                             lv[2] <= VT - 3 && lb[0] <= TILE - 3 && lb[1] <= TILE - 3 && lb[2] <= TILE - 3;
+        lv[0] = S.base[0] - (ox - 1); lv[1] = S.base[1] - (oy - 1); lv[2] = S.base[2] - (oz - 1);
+        // (inside the velocity window, the stencil is inside the tile: lb = lv + 1)
+        const bool in_tile = lv[0] >= 0 && lv[1] >= 0 && lv[2] >= 0 && lv[0] <= VT - 3 && lv[1] <= VT - 3 && lv[2] <= VT - 3;
         if (!in_grid) { atomicOr(P.err, ERR_OUTSIDE); ok = false; }
-        else if (!in_tile) { atomicOr(P.err, ERR_TILE); ok = false; }
-        else if (A.map[j] >= (uint32_t)N) { atomicOr(P.err, ERR_TILE); ok = false; }
+        else if (!in_tile || jn >= (uint32_t)N) { atomicOr(P.err, ERR_TILE); ok = false; }
+#pragma unroll
+        for (int a = 0; a < 3; a++) lb[a] = lv[a] + 1;
       }
       float vbt[3] = {0, 0, 0}, Bb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, bnd[NQ] = {0, 0, 0};
-      float vn[3], xb[3], Fbo[9], Jbo = 0.f;
-      bool defer = false;
       if (ok) {
         // G2P recomputed from the staged velocities
-        float Bi[9];
+        float vn[3], Bi[9], B[9], Fbo[9], Jbo = 0.f;
         g2p_gather(s_v, lv, S, vn, Bi);
-        float B[9];
 #pragma unroll
         for (int a = 0; a < 3; a++)
 #pragma unroll
           for (int b = 0; b < 3; b++) B[a * 3 + b] = P.dx * (Bi[a * 3 + b] - vn[a] * S.f[b]);
-        // adjoint of s_{t+1}, row jn of the next state's order
-        const uint32_t jn = A.map[j];
+        // adjoint of s_{t+1}, row jn of the next state's order, and the F or J of s_t
+        float xb[3], vb[3], Cb[9], Fb[9], F[9], J = 0.f;
         const float* an = A.abar_next;
-        float vb[3], Cb[9], Fb[9];
+        const uint32_t offn = 4u * jn;
 #pragma unroll
-        for (int a = 0; a < 3; a++) { xb[a] = an[a * (size_t)N + jn]; vb[a] = an[(3 + a) * (size_t)N + jn]; }
+        for (int a = 0; a < 3; a++) { xb[a] = row32(an, a, N, offn); vb[a] = row32(an, 3 + a, N, offn); }
 #pragma unroll
-        for (int k = 0; k < 9; k++) { Cb[k] = an[(6 + k) * (size_t)N + jn]; Fb[k] = an[(15 + k) * (size_t)N + jn]; }
-        const float Jb = an[24 * (size_t)N + jn];
-        defer = !particle_update_adjoint<ADJ_FP32>(x, vn, B, M, P, st, j, xb, vb, Cb, Fb, Jb, vbt, Bb, Fbo, Jbo);
-      }
-      if (defer) {
-        // listed for the FP64 pass; it stays in the tile box, scatters nothing here
-        const uint32_t r = atomicAdd(A.redo_n, 1u);
-        A.redo[r] = make_uint2((uint32_t)j, (uint32_t)ent.x);
-      } else if (ok) {
-        // position adjoint through the weights and the node offsets:
-        // xo = xb + sum_i grad w_i (v_i . (vbt + Bb (x_i - x_p))) - Bb^T vn
-        float xo[3];
-        {
+        for (int k = 0; k < 9; k++) { Cb[k] = row32(an, 6 + k, N, offn); Fb[k] = row32(an, 15 + k, N, offn); }
+        const float Jb = row32(an, 24, N, offn);
+        if (M.kind == KIND_LIQUID) {
+          J = row32(A.st.f, 24, N, off);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 9; k++) F[k] = row32(A.st.f, 15 + k, N, off);
+        }
+        defer = !particle_update_adjoint<RETRY ? ADJ_FP64 : ADJ_FP32>(vn, B, M, P, F, J, xb, vb, Cb, Fb, Jb, vbt, Bb, Fbo, Jbo);
+        if (defer) {
+          ok = false;   // (the second pass does it)
+        } else {
+          // position adjoint through the weights and the node offsets:
+          // xo = xb + sum_i grad w_i (v_i . (vbt + Bb (x_i - x_p))) - Bb^T vn
           float c0[3], Ad[9], X[3];
 #pragma unroll
           for (int a = 0; a < 3; a++) {
@@ -152,232 +168,145 @@ __global__ __launch_bounds__(NT, 3) void k_g2p_adj_tiled(AdjArgs A, StepParams P
           weight_grad_sum<false>(s_v, lv, S, c0, Ad, 0.f, X, nullptr, nullptr);
 #pragma unroll
           for (int a = 0; a < 3; a++)
-            xo[a] = xb[a] + P.inv_dx * X[a] - (Bb[a] * vn[0] + Bb[3 + a] * vn[1] + Bb[6 + a] * vn[2]);
-        }
-        float* ab = A.abar;
+            row32(A.abar, a, N, off) = xb[a] + P.inv_dx * X[a] - (Bb[a] * vn[0] + Bb[3 + a] * vn[1] + Bb[6 + a] * vn[2]);
 #pragma unroll
-        for (int a = 0; a < 3; a++) { ab[a * (size_t)N + j] = xo[a]; ab[(3 + a) * (size_t)N + j] = 0.f; }
+          for (int k = 0; k < 9; k++) row32(A.abar, 15 + k, N, off) = Fbo[k];
+          row32(A.abar, 24, N, off) = Jbo;
 #pragma unroll
-        for (int k = 0; k < 9; k++) { ab[(6 + k) * (size_t)N + j] = 0.f; ab[(15 + k) * (size_t)N + j] = Fbo[k]; }
-        ab[24 * (size_t)N + j] = Jbo;
+          for (int a = 0; a < 3; a++)
+            bnd[a] = fabsf(vbt[a]) + 1.5f * P.dx * (fabsf(Bb[a * 3]) + fabsf(Bb[a * 3 + 1]) + fabsf(Bb[a * 3 + 2]));
+          if (!isfinite(bnd[0] + bnd[1] + bnd[2])) {
+            atomicOr(P.err, ERR_NONFINITE);
+            ok = false;
 #pragma unroll
-        for (int a = 0; a < 3; a++)
-          bnd[a] = fabsf(vbt[a]) + 1.5f * P.dx * (fabsf(Bb[a * 3]) + fabsf(Bb[a * 3 + 1]) + fabsf(Bb[a * 3 + 2]));
-        if (!isfinite(bnd[0] + bnd[1] + bnd[2])) {
-          atomicOr(P.err, ERR_NONFINITE);
-          ok = false;
-#pragma unroll
-          for (int a = 0; a < NQ; a++) bnd[a] = 0.f;
+            for (int a = 0; a < NQ; a++) bnd[a] = 0.f;
+          }
         }
       } else if (has) {
         // a particle outside the grid carries no adjoint (the call reports it)
-        float* ab = A.abar;
 #pragma unroll
-        for (int k = 0; k < STATE_FLOATS; k++) ab[k * (size_t)N + j] = 0.f;
+        for (int a = 0; a < 3; a++) row32(A.abar, a, N, off) = 0.f;
+#pragma unroll
+        for (int k = 15; k < STATE_FLOATS; k++) row32(A.abar, k, N, off) = 0.f;
       }
       // chunk-wide bound sums and box, as in the forward P2G
-      int clo[3], chi[3];
+      const uint32_t obits = ok ? ((1u << lb[0]) | (1u << (8 + lb[1])) | (1u << (16 + lb[2]))) : 0u;
+      const uint32_t wbits = wave_or(obits | (defer ? 1u << 31 : 0u));
+      float wb[NQ];
 #pragma unroll
-      for (int a = 0; a < 3; a++) { clo[a] = ok ? lb[a] : 1 << 20; chi[a] = ok ? lb[a] : -(1 << 20); }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int q = 0; q < NQ; q++) bnd[q] += __shfl_xor(bnd[q], off);
-#pragma unroll
-        for (int a = 0; a < 3; a++) { clo[a] = min(clo[a], __shfl_xor(clo[a], off)); chi[a] = max(chi[a], __shfl_xor(chi[a], off)); }
-      }
+      for (int q = 0; q < NQ; q++) wb[q] = wave_sum(bnd[q]);
       const int wv = tid >> 6;
       if ((tid & 63) == 0) {
 #pragma unroll
-        for (int q = 0; q < NQ; q++) s_red[wv * NQ + q] = bnd[q];
-#pragma unroll
-        for (int a = 0; a < 3; a++) { s_ired[wv * 6 + a] = clo[a]; s_ired[wv * 6 + 3 + a] = chi[a]; }
+        for (int q = 0; q < NQ; q++) s_red[wv * NQ + q] = wb[q];
+        s_ired[wv] = wbits;
       }
       __syncthreads();
-      if (tid == 0) {
+      float sc[NQ], isc[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; q++) {
-          float T = 0.f;
+      for (int q = 0; q < NQ; q++) {
+        float T = 0.f;
 #pragma unroll
-          for (int w = 0; w < NW; w++) T += s_red[w * NQ + q];
-          T *= 0.421875f;   // largest weight of one node, (3/4)^3
-          if (!isfinite(T)) { atomicOr(P.err, ERR_NONFINITE); T = 1.f; }
-          int ex = 0;
-          frexpf(T > 0.f ? T : 1.f, &ex);
-          ex = max(ex, -90);
-          s_scale[q] = ldexpf(1.f, 30 - ex);
-          s_scale[NQ + q] = ldexpf(1.f, ex - 30);
+        for (int w = 0; w < NW; w++) T += s_red[w * NQ + q];
+        // 0.421875: the largest weight of one node, (3/4)^3
+        int tb = __builtin_amdgcn_readfirstlane(__float_as_int(T * 0.421875f));
+        if ((tb & 0x7f800000) == 0x7f800000) {
+          if (tid == 0) atomicOr(P.err, ERR_NONFINITE);
+          tb = 0x3f800000;
         }
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-          int lo = s_ired[a], hi = s_ired[3 + a];
-#pragma unroll
-          for (int w = 1; w < NW; w++) { lo = min(lo, s_ired[w * 6 + a]); hi = max(hi, s_ired[w * 6 + 3 + a]); }
-          s_ired[NW * 6 + a] = lo;
-          s_ired[NW * 6 + 3 + a] = hi;
-          if (lo <= hi) { s_lo[a] = min(s_lo[a], lo); s_hi[a] = max(s_hi[a], hi); }
-        }
+        const int ex = tb == 0 ? 1 : max((tb >> 23) - 126, -90);
+        sc[q] = __int_as_float((157 - ex) << 23);
+        isc[q] = __int_as_float((ex + 97) << 23);
       }
-      __syncthreads();
-      if (ok && !defer) {
+      int olo[3], ohi[3];   // the box before this chunk
+      uint32_t cb = 0;
+#pragma unroll
+      for (int w = 0; w < NW; w++) cb |= s_ired[w];
+      cb = (uint32_t)__builtin_amdgcn_readfirstlane((int)cb);
+      const bool any_deferred = !RETRY && (cb >> 31) != 0u;
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        const uint32_t ab = (cb >> (8 * a)) & 0xffu;
+        olo[a] = blo[a];
+        ohi[a] = bhi[a];
+        if (ab) { blo[a] = min(blo[a], __ffs(ab) - 1); bhi[a] = max(bhi[a], 31 - __clz(ab)); }
+      }
+      if (ok) {
         // c_a(node) = w (vbt_a + sum_b Bb_ab (idx_b - f_b) dx), scaled
         float c0[3], Ad[9];
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-          const float sa = s_scale[a];
+          const float sa = sc[a];
 #pragma unroll
           for (int b = 0; b < 3; b++) Ad[a * 3 + b] = sa * P.dx * Bb[a * 3 + b];
           c0[a] = sa * vbt[a] - (Ad[a * 3] * S.f[0] + Ad[a * 3 + 1] * S.f[1] + Ad[a * 3 + 2] * S.f[2]);
         }
         int* T = s_itile + (lb[0] * TILE + lb[1]) * TILE + lb[2];
 #pragma unroll
-        for (int i = 0; i < 3; i++)
+        for (int i = 0; i < 3; i++) {
+          float m1[3];
+#pragma unroll
+          for (int a = 0; a < 3; a++) m1[a] = c0[a] + (float)i * Ad[a * 3];
 #pragma unroll
           for (int jj = 0; jj < 3; jj++) {
             const float wxy = S.w[0][i] * S.w[1][jj];
+            float m2[3];
+#pragma unroll
+            for (int a = 0; a < 3; a++) m2[a] = m1[a] + (float)jj * Ad[a * 3 + 1];
 #pragma unroll
             for (int k = 0; k < 3; k++) {
               const float w = wxy * S.w[2][k];
               const int q = (i * TILE + jj) * TILE + k;
 #pragma unroll
               for (int a = 0; a < 3; a++)
-                atomicAdd(&T[a * TILE_NODES + q],
-                          __float2int_rn(w * (c0[a] + (float)i * Ad[a * 3] + (float)jj * Ad[a * 3 + 1] + (float)k * Ad[a * 3 + 2])));
-            }
-          }
-      }
-      __syncthreads();
-      {
-        const int lo0 = s_ired[NW * 6], lo1 = s_ired[NW * 6 + 1], lo2 = s_ired[NW * 6 + 2];
-        const int hi0 = s_ired[NW * 6 + 3], hi1 = s_ired[NW * 6 + 4], hi2 = s_ired[NW * 6 + 5];
-        if (lo0 <= hi0) {
-          const int ex = hi0 - lo0 + 3, ey = hi1 - lo1 + 3, ez = hi2 - lo2 + 3;
-          const int cnt = ex * ey * ez;
-          for (int r = tid; r < cnt; r += NT) {
-            const int qq = ((lo0 + r / (ey * ez)) * TILE + lo1 + (r / ez) % ey) * TILE + lo2 + r % ez;
-#pragma unroll
-            for (int c = 0; c < NQ; c++) {
-              const int iv = s_itile[c * TILE_NODES + qq];
-              if (iv != 0) {
-                s_tile[c * TILE_NODES + qq] += (float)iv * s_scale[NQ + c];
-                s_itile[c * TILE_NODES + qq] = 0;
-              }
+                atomicAdd(&T[a * TILE_NODES + q], __float2int_rn(w * (m2[a] + (float)k * Ad[a * 3 + 2])));
             }
           }
         }
       }
+      if (!RETRY && !any_deferred && c0 + NT < count) prefetch(c0 + NT);
       __syncthreads();
-    }
-    // publish the tile's non-zero box (rows 0..2 of the block's tile slot)
-    const int lo0 = s_lo[0], lo1 = s_lo[1], lo2 = s_lo[2];
-    const int hi0 = s_hi[0] + 2, hi1 = s_hi[1] + 2, hi2 = s_hi[2] + 2;
-    const uint32_t bkey = (uint32_t)ent.x;
-    if (lo0 <= hi0 - 2) {
-      const int ex = hi0 - lo0 + 1, ey = hi1 - lo1 + 1, ez = hi2 - lo2 + 1;
-      const int cnt = ex * ey * ez;
-      float* T = A.tiles + (size_t)bkey * 4 * TILE_NODES;
-      for (int r = tid; r < cnt; r += NT) {
-        const int q = ((lo0 + r / (ey * ez)) * TILE + lo1 + (r / ez) % ey) * TILE + lo2 + r % ez;
+      // flush: see k_particles
+      const bool pub = last && !any_deferred;
+      if (blo[0] <= bhi[0]) {
+        const int ey = bhi[1] - blo[1] + 3, ez = bhi[2] - blo[2] + 3, eyz = ey * ez;
+        const int cnt = (bhi[0] - blo[0] + 3) * eyz;
+        const uint32_t m1 = div_mul(eyz), m2 = div_mul(ez);
+        for (int r = tid; r < cnt; r += NT) {
+          const int i = (int)(((uint32_t)r * m1) >> 20), rem = r - i * eyz;
+          const int jj = (int)(((uint32_t)rem * m2) >> 20), k = rem - jj * ez;
+          const int qi = blo[0] + i, qj = blo[1] + jj, qk = blo[2] + k;
+          const int q = (qi * TILE + qj) * TILE + qk;
+          float4 val = make_float4((float)s_itile[q] * isc[0], (float)s_itile[TILE_NODES + q] * isc[1],
+                                   (float)s_itile[2 * TILE_NODES + q] * isc[2], 0.f);
 #pragma unroll
-        for (int c = 0; c < NQ; c++) T[c * TILE_NODES + q] = s_tile[c * TILE_NODES + q];
-      }
-      if (tid == 0) {
-        const int packed = lo0 | (lo1 << 4) | (lo2 << 8) | (hi0 << 12) | (hi1 << 16) | (hi2 << 20);
-        A.tile_box[bkey] = make_int2(packed, (int)stamp);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// The FP64 pass of the G2P adjoint over the particles k_g2p_adj_tiled listed:
-// each thread stages its particle's 27 stencil nodes in LDS and repeats the
-// steps above with the FP64 plastic-return adjoint; its velocity-adjoint
-// scatter goes into the block's published tile with float atomics (the
-// listed particles were kept inside the tile's box).
-// ---------------------------------------------------------------------------
-constexpr int REDO_NT = 64, REDO_WGS = 256;
-
-__global__ __launch_bounds__(REDO_NT) void k_g2p_adj_redo(AdjArgs A, StepParams P, FastGeom g) {
-  __shared__ float4 s_loc[REDO_NT * 27];
-  float4* loc = s_loc + threadIdx.x * 27;
-  const int N = A.N;
-  const PState st = packed_state(A.st.f, N);
-  const uint32_t n = A.redo_n[0];
-  for (uint32_t e = blockIdx.x * REDO_NT + threadIdx.x; e < n; e += gridDim.x * REDO_NT) {
-    const uint2 r = A.redo[e];
-    const int j = (int)r.x;
-    int sc, bx, by, bz;
-    key_decode(g, r.y, sc, bx, by, bz);
-    float x[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) x[a] = st.x[a * (size_t)N + j];
-    const MatDev& M = P.mats[A.st.mat[j]];
-    Stencil S;
-    stencil_setup(x, P, S);   // inside the grid and the tile: checked when listed
-    const int lb[3] = {S.base[0] - (4 * bx - 2), S.base[1] - (4 * by - 2), S.base[2] - (4 * bz - 2)};
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-      for (int jj = 0; jj < 3; jj++)
-#pragma unroll
-        for (int k = 0; k < 3; k++)
-          loc[(i * 3 + jj) * 3 + k] = stage_node(A.vgrid, g, sc, S.base[0] + i, S.base[1] + jj, S.base[2] + k);
-    const int l0[3] = {0, 0, 0};
-    float vn[3], Bi[9], B[9];
-    g2p_gather<3, 9>(loc, l0, S, vn, Bi);
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-      for (int b = 0; b < 3; b++) B[a * 3 + b] = P.dx * (Bi[a * 3 + b] - vn[a] * S.f[b]);
-    const uint32_t jn = A.map[j];
-    const float* an = A.abar_next;
-    float xb[3], vb[3], Cb[9], Fb[9];
-#pragma unroll
-    for (int a = 0; a < 3; a++) { xb[a] = an[a * (size_t)N + jn]; vb[a] = an[(3 + a) * (size_t)N + jn]; }
-#pragma unroll
-    for (int k = 0; k < 9; k++) { Cb[k] = an[(6 + k) * (size_t)N + jn]; Fb[k] = an[(15 + k) * (size_t)N + jn]; }
-    const float Jb = an[24 * (size_t)N + jn];
-    float vbt[3], Bb[9], Fbo[9], Jbo;
-    particle_update_adjoint<ADJ_FP64>(x, vn, B, M, P, st, j, xb, vb, Cb, Fb, Jb, vbt, Bb, Fbo, Jbo);
-    float c0[3], Ad[9], X[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-#pragma unroll
-      for (int b = 0; b < 3; b++) Ad[a * 3 + b] = P.dx * Bb[a * 3 + b];
-      c0[a] = vbt[a] - (Ad[a * 3] * S.f[0] + Ad[a * 3 + 1] * S.f[1] + Ad[a * 3 + 2] * S.f[2]);
-    }
-    weight_grad_sum<false, 3, 9>(loc, l0, S, c0, Ad, 0.f, X, nullptr, nullptr);
-    float* ab = A.abar;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-      ab[a * (size_t)N + j] = xb[a] + P.inv_dx * X[a] - (Bb[a] * vn[0] + Bb[3 + a] * vn[1] + Bb[6 + a] * vn[2]);
-      ab[(3 + a) * (size_t)N + j] = 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < 9; k++) { ab[(6 + k) * (size_t)N + j] = 0.f; ab[(15 + k) * (size_t)N + j] = Fbo[k]; }
-    ab[24 * (size_t)N + j] = Jbo;
-    bool fin = true;
-#pragma unroll
-    for (int k = 0; k < 9; k++) fin = fin && isfinite(Ad[k]);
-    if (!(fin && isfinite(c0[0] + c0[1] + c0[2]))) { atomicOr(P.err, ERR_NONFINITE); continue; }
-    float* T = A.tiles + (size_t)r.y * 4 * TILE_NODES + (lb[0] * TILE + lb[1]) * TILE + lb[2];
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-      for (int jj = 0; jj < 3; jj++) {
-        const float wxy = S.w[0][i] * S.w[1][jj];
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-          const float w = wxy * S.w[2][k];
-          const int q = (i * TILE + jj) * TILE + k;
-#pragma unroll
-          for (int a = 0; a < 3; a++)
-            atomicAdd(&T[a * TILE_NODES + q],
-                      w * (c0[a] + (float)i * Ad[a * 3] + (float)jj * Ad[a * 3 + 1] + (float)k * Ad[a * 3 + 2]));
+          for (int c = 0; c < NQ; c++) s_itile[c * TILE_NODES + q] = 0;
+          if (qi >= olo[0] && qi <= ohi[0] + 2 && qj >= olo[1] && qj <= ohi[1] + 2 && qk >= olo[2] && qk <= ohi[2] + 2) {
+            const float4 o = s_tile[q];
+            val.x += o.x; val.y += o.y; val.z += o.z;
+          }
+          if (pub) tile_out[q] = val;
+          else s_tile[q] = val;
         }
       }
+      return any_deferred;
+    };
+    for (int c0 = 0; c0 < count; c0 += NT) {
+      const bool has = c0 + tid < count && start + c0 + tid < N;
+      const bool last = c0 + NT >= count;
+      bool defer = false;
+      if (pass(std::false_type{}, c0, has, defer, last)) {
+        bool none = false;
+        pass(std::true_type{}, c0, defer, none, last);
+        if (c0 + NT < count) prefetch(c0 + NT);
+      }
+    }
+    // the published tile's box
+    if (blo[0] <= bhi[0] && tid == 0) {
+      const int packed = blo[0] | (blo[1] << 4) | (blo[2] << 8) | ((bhi[0] + 2) << 12) | ((bhi[1] + 2) << 16) |
+                         ((bhi[2] + 2) << 20);
+      A.tile_box[slot] = make_int2(packed, (int)stamp);
+    }
   }
 }
 
@@ -399,18 +328,19 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
     int sc, cx, cy, cz;
     key_decode(g, key, sc, cx, cy, cz);
     {
+      // (tile sums as in k_grid: lanes 32..58 hold the neighbours' second slots)
       int2 nbox = make_int2(0, 0);
       uint32_t nkey = 0;
-      if (lane < 27) {
-        const int sx = cx + lane / 9 - 1, sy = cy + (lane / 3) % 3 - 1, sz = cz + lane % 3 - 1;
+      const int dl = lane < 32 ? lane : lane - 32;
+      if (dl < 27) {
+        const int sx = cx + dl / 9 - 1, sy = cy + (dl / 3) % 3 - 1, sz = cz + dl % 3 - 1;
         if (sx >= 0 && sy >= 0 && sz >= 0 && sx < g.nb && sy < g.nb && sz < g.nb) {
-          nkey = block_key(g, sc, sx, sy, sz);
+          nkey = block_key(g, sc, sx, sy, sz) + (lane < 32 ? 0u : (uint32_t)g.n_keys);
           nbox = A.tile_box[nkey];
           if ((uint32_t)nbox.y != stamp) nbox.y = 0;
         }
       }
       const int gx = 4 * cx + li, gy = 4 * cy + lj, gz = 4 * cz + lk;
-      // branch-free over the 27 neighbours (see k_grid)
       float vb[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int dd = 0; dd < 27; dd++) {
@@ -423,11 +353,28 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
         const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
         const bool in = valid && qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2;
         const int q = in ? (qi * TILE + qj) * TILE + qk : 0;
-        const float* T = A.tiles + (size_t)(in ? kk : 0u) * 4 * TILE_NODES;
-        const float t0 = T[q], t1 = T[TILE_NODES + q], t2 = T[2 * TILE_NODES + q];
-        vb[0] += in ? t0 : 0.f;
-        vb[1] += in ? t1 : 0.f;
-        vb[2] += in ? t2 : 0.f;
+        const float4 tv = reinterpret_cast<const float4*>(A.tiles + (size_t)(in ? kk : 0u) * 4 * TILE_NODES)[q];
+        vb[0] += in ? tv.x : 0.f;
+        vb[1] += in ? tv.y : 0.f;
+        vb[2] += in ? tv.z : 0.f;
+      }
+      unsigned long long m1 = __ballot(lane >= 32 && nbox.y != 0);
+      while (m1) {
+        const int src = __ffsll((long long)m1) - 1;
+        m1 &= m1 - 1ull;
+        const int dd = src - 32;
+        const int bxv = __shfl(nbox.x, src);
+        const uint32_t kk = __shfl(nkey, src);
+        const int sx = cx + dd / 9 - 1, sy = cy + (dd / 3) % 3 - 1, sz = cz + dd % 3 - 1;
+        const int qi = gx - (4 * sx - 2), qj = gy - (4 * sy - 2), qk = gz - (4 * sz - 2);
+        const int lo0 = bxv & 15, lo1 = (bxv >> 4) & 15, lo2 = (bxv >> 8) & 15;
+        const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
+        if (qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2) {
+          const float4 tv = reinterpret_cast<const float4*>(A.tiles + (size_t)kk * 4 * TILE_NODES)[(qi * TILE + qj) * TILE + qk];
+          vb[0] += tv.x;
+          vb[1] += tv.y;
+          vb[2] += tv.z;
+        }
       }
       const size_t node = (size_t)key * 64 + lane;
       const float4 gm = A.mmv[node];
@@ -448,9 +395,7 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
       for (int q = 0; q < ACC_DOUBLES; q++) any |= (loc[q] != 0.f);
       if (__ballot(any)) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-          for (int q = 0; q < ACC_DOUBLES; q++) loc[q] += __shfl_xor(loc[q], off);
+        for (int q = 0; q < ACC_DOUBLES; q++) loc[q] = wave_sum(loc[q]);
         if (lane == 0) {
           double* dst = acc_t + (size_t)sc * ACC_DOUBLES;
 #pragma unroll
@@ -463,32 +408,27 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
 }
 
 // ---------------------------------------------------------------------------
-// Adjoint of P2G: gather of the node adjoints, through the stress adjoint;
-// added to the state adjoint of s_t.
+// Adjoint of P2G: gather of the node adjoints, through the stress adjoint.
+// Writes the v and C rows of the state adjoint of s_t and adds to its x and F
+// or J rows.
 // ---------------------------------------------------------------------------
-// One particle.  FP64 = false: the stress and its adjoint from one FP32 SVD;
-// returns false, before doing anything, for a solid whose F is
-// ill-conditioned (s2 < s0/4) or whose FP32 sweeps do not converge.
+// One particle of row offset off.  FP64 = false: the stress and its adjoint
+// from one FP32 SVD; returns false, before writing anything, for a solid whose
+// F is ill-conditioned (s2 < s0/4) or whose FP32 sweeps do not converge.
 // FP64 = true: the stress and its adjoint from FP64 SVDs, for the particles
-// the FP32 pass returned (k_p2g_adj_redo).  lv is the stencil's
-// first node in the tile of strides ROW and PLANE.
-template <bool FP64, int ROW, int PLANE>
-MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState& st, const float4* tile,
-                             const int* lv, const Stencil& S, int j) {
+// the FP32 pass returned.  lv is the stencil's first node in the tile.
+template <bool FP64>
+MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const MatDev& M, const float4* tile, const int* lv,
+                             const Stencil& S, uint32_t off, const float* v, const float* C) {
   const int N = A.N;
-  const MatDev& M = P.mats[A.st.mat[j]];
   const bool liquid = M.kind == KIND_LIQUID;
-  float Ff[9], U[9], sv[3], V[9], tau[9];
-  const float Jv = st.J[j];
-  float C[9];
-#pragma unroll
-  for (int k = 0; k < 9; k++) C[k] = st.C[k * (size_t)N + j];
+  float Ff[9], U[9], sv[3], V[9], tau[9], Jv = 0.f;
   if (liquid) {
-    if (FP64) return true;
+    Jv = row32(A.st.f, 24, N, off);
     stress_liquid(Jv, C, M, tau);
   } else {
 #pragma unroll
-    for (int k = 0; k < 9; k++) Ff[k] = st.F[k * (size_t)N + j];
+    for (int k = 0; k < 9; k++) Ff[k] = row32(A.st.f, 15 + k, N, off);
     if (FP64) {
       stress_solid(Ff, M, tau);
     } else {
@@ -496,14 +436,13 @@ MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState
       stress_solid_usv(Ff, U, sv, V, M, tau);
     }
   }
-  float v[3] = {st.v[j], st.v[(size_t)N + j], st.v[2 * (size_t)N + j]};
   float Am[9];
   const float scl = -P.dt * M.vol * 4.f * P.inv_dx * P.inv_dx;
 #pragma unroll
   for (int k = 0; k < 9; k++) Am[k] = scl * tau[k] + M.mass * C[k];
   const float mvp[3] = {M.mass * v[0], M.mass * v[1], M.mass * v[2]};
   // node adjoints gathered: mom_i = mvp + Am (x_i - x_p) = c0 + Ad idx_i
-  float vb[3], Ab[9], xb[3];
+  float Ab[9];
   {
     float c0[3], Ad[9], X[3], G0[3], Gi[9];
 #pragma unroll
@@ -512,40 +451,49 @@ MPM_DI bool p2g_adj_particle(const AdjArgs& A, const StepParams& P, const PState
       for (int b = 0; b < 3; b++) Ad[a * 3 + b] = P.dx * Am[a * 3 + b];
       c0[a] = mvp[a] - (Ad[a * 3] * S.f[0] + Ad[a * 3 + 1] * S.f[1] + Ad[a * 3 + 2] * S.f[2]);
     }
-    weight_grad_sum<true, ROW, PLANE>(tile, lv, S, c0, Ad, M.mass, X, G0, Gi);
+    weight_grad_sum<true>(tile, lv, S, c0, Ad, M.mass, X, G0, Gi);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-      vb[a] = M.mass * G0[a];
+      row32(A.abar, 3 + a, N, off) = M.mass * G0[a];
 #pragma unroll
       for (int b = 0; b < 3; b++) Ab[a * 3 + b] = P.dx * (Gi[a * 3 + b] - G0[a] * S.f[b]);
-      xb[a] = P.inv_dx * X[a] - (Am[a] * G0[0] + Am[3 + a] * G0[1] + Am[6 + a] * G0[2]);
+      row32(A.abar, a, N, off) += P.inv_dx * X[a] - (Am[a] * G0[0] + Am[3 + a] * G0[1] + Am[6 + a] * G0[2]);
     }
   }
-  float taub[9], Cb[9], Fb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  float taub[9], Cb[9];
 #pragma unroll
   for (int k = 0; k < 9; k++) { taub[k] = scl * Ab[k]; Cb[k] = M.mass * Ab[k]; }
-  float Jb = 0.f;
-  if (liquid) stress_liquid_adjoint(Jv, C, M, taub, Jb, Cb);
-  else if (FP64) stress_solid_adjoint(Ff, M, taub, Fb);
-  else stress_solid_adjoint_usv(Ff, U, sv, V, M, taub, Fb);
-  float* ab = A.abar;
+  if (liquid) {
+    const float Jo = row32(A.abar, 24, N, off);
+    float Jb = 0.f;
+    stress_liquid_adjoint(Jv, C, M, taub, Jb, Cb);
+    row32(A.abar, 24, N, off) = Jo + Jb;
+  } else {
+    float Fo[9], Fb[9];
 #pragma unroll
-  for (int a = 0; a < 3; a++) { ab[a * (size_t)N + j] += xb[a]; ab[(3 + a) * (size_t)N + j] += vb[a]; }
+    for (int k = 0; k < 9; k++) { Fo[k] = row32(A.abar, 15 + k, N, off); Fb[k] = 0.f; }
+    if (FP64) stress_solid_adjoint(Ff, M, taub, Fb);
+    else stress_solid_adjoint_usv(Ff, U, sv, V, M, taub, Fb);
 #pragma unroll
-  for (int k = 0; k < 9; k++) { ab[(6 + k) * (size_t)N + j] += Cb[k]; ab[(15 + k) * (size_t)N + j] += Fb[k]; }
-  ab[24 * (size_t)N + j] += Jb;
+    for (int k = 0; k < 9; k++) row32(A.abar, 15 + k, N, off) = Fo[k] + Fb[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; k++) row32(A.abar, 6 + k, N, off) = Cb[k];
   return true;
 }
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_p2g_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
+__global__ __launch_bounds__(NT, 2) void k_p2g_adj_tiled(AdjArgs A, StepParams P, FastGeom g) {
   __shared__ float4 s_g[VT_LDS];
-  const int tid = threadIdx.x;
   const int N = A.N;
-  const PState st = packed_state(A.st.f, N);
   const uint32_t n_list = A.list_n[0];
   for (uint32_t e = blockIdx.x; e < n_list; e += gridDim.x) {
-    const int4 ent = A.list[e];
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    int4 ent = A.list[e];
+    ent.x = __builtin_amdgcn_readfirstlane(ent.x);
+    ent.y = __builtin_amdgcn_readfirstlane(ent.y);
+    ent.z = __builtin_amdgcn_readfirstlane(ent.z);
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
@@ -554,46 +502,32 @@ __global__ __launch_bounds__(NT) void k_p2g_adj_tiled(AdjArgs A, StepParams P, F
     const int start = ent.y, count = ent.z;
     for (int c0 = 0; c0 < count; c0 += NT) {
       const int j = start + c0 + tid;
-      if ((c0 + tid) >= count || j >= N) continue;
-      float x[3] = {st.x[j], st.x[(size_t)N + j], st.x[2 * (size_t)N + j]};
-      Stencil S;
-      if (!stencil_setup(x, P, S)) continue;   // reported by the G2P adjoint
-      int lv[3] = {S.base[0] - (ox - 1), S.base[1] - (oy - 1), S.base[2] - (oz - 1)};
-      if (lv[0] < 0 || lv[1] < 0 || lv[2] < 0 || lv[0] > VT - 3 || lv[1] > VT - 3 || lv[2] > VT - 3) continue;
-      if (!p2g_adj_particle<false, VT_ROW, VT_PLANE>(A, P, st, s_g, lv, S, j)) {
-        const uint32_t r = atomicAdd(A.redo_n, 1u);
-        A.redo[r] = make_uint2((uint32_t)j, (uint32_t)ent.x);
-      }
+      // FP32 for every lane, then FP64 for those it returned
+      auto pass = [&](auto fp64, bool on) -> bool {
+        constexpr bool FP64 = decltype(fp64)::value;
+        if (!on) return false;
+        const uint32_t off = 4u * (uint32_t)j;
+        float x[3], v[3], C[9];
+#pragma unroll
+        for (int a = 0; a < 3; a++) { x[a] = row32(A.st.f, a, N, off); v[a] = row32(A.st.f, 3 + a, N, off); }
+#pragma unroll
+        for (int k = 0; k < 9; k++) C[k] = row32(A.st.f, 6 + k, N, off);
+        const MatDev& M = P.mats[A.st.mat[(uint32_t)j]];
+        Stencil S;
+        const bool in_grid = stencil_setup(x, P, S);
+        const int lv[3] = {S.base[0] - (ox - 1), S.base[1] - (oy - 1), S.base[2] - (oz - 1)};
+        if (!in_grid || lv[0] < 0 || lv[1] < 0 || lv[2] < 0 || lv[0] > VT - 3 || lv[1] > VT - 3 || lv[2] > VT - 3) {
+          // no adjoint; reported by the G2P adjoint
+#pragma unroll
+          for (int k = 3; k < 15; k++) row32(A.abar, k, N, off) = 0.f;
+          return false;
+        }
+        return !p2g_adj_particle<FP64>(A, P, M, s_g, lv, S, off, v, C);
+      };
+      const bool defer = pass(std::false_type{}, (c0 + tid) < count && j < N);
+      if (__ballot(defer)) pass(std::true_type{}, defer);
     }
     __syncthreads();
-  }
-}
-
-// The FP64 pass of the P2G adjoint over the solids k_p2g_adj_tiled listed:
-// each thread stages its particle's 27 stencil nodes in LDS.
-__global__ __launch_bounds__(REDO_NT) void k_p2g_adj_redo(AdjArgs A, StepParams P, FastGeom g) {
-  __shared__ float4 s_loc[REDO_NT * 27];
-  float4* loc = s_loc + threadIdx.x * 27;
-  const int N = A.N;
-  const PState st = packed_state(A.st.f, N);
-  const uint32_t n = A.redo_n[0];
-  for (uint32_t e = blockIdx.x * REDO_NT + threadIdx.x; e < n; e += gridDim.x * REDO_NT) {
-    const uint2 r = A.redo[e];
-    const int j = (int)r.x;
-    int sc, bx, by, bz;
-    key_decode(g, r.y, sc, bx, by, bz);
-    float x[3] = {st.x[j], st.x[(size_t)N + j], st.x[2 * (size_t)N + j]};
-    Stencil S;
-    stencil_setup(x, P, S);   // inside the grid and the block's tile: checked when listed
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-      for (int jj = 0; jj < 3; jj++)
-#pragma unroll
-        for (int k = 0; k < 3; k++)
-          loc[(i * 3 + jj) * 3 + k] = stage_node(A.mmvb, g, sc, S.base[0] + i, S.base[1] + jj, S.base[2] + k);
-    const int l0[3] = {0, 0, 0};
-    p2g_adj_particle<true, 3, 9>(A, P, st, loc, l0, S, j);
   }
 }
 
@@ -620,7 +554,6 @@ static inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1
 
 void launch_g2p_adj_tiled(const AdjArgs& A, const StepParams& P, const FastGeom& g, int n_wgs, hipStream_t s) {
   k_g2p_adj_tiled<256><<<n_wgs, 256, 0, s>>>(A, P, g);
-  k_g2p_adj_redo<<<REDO_WGS, REDO_NT, 0, s>>>(A, P, g);
 }
 void launch_grid_adj_tiled(const AdjArgs& A, const StepParams& P, const FastGeom& g, int n_wgs, const double* pose_t,
                            const float* act_t, double* acc_t, hipStream_t s) {
@@ -628,7 +561,6 @@ void launch_grid_adj_tiled(const AdjArgs& A, const StepParams& P, const FastGeom
 }
 void launch_p2g_adj_tiled(const AdjArgs& A, const StepParams& P, const FastGeom& g, int n_wgs, hipStream_t s) {
   k_p2g_adj_tiled<256><<<n_wgs, 256, 0, s>>>(A, P, g);
-  k_p2g_adj_redo<<<REDO_WGS, REDO_NT, 0, s>>>(A, P, g);
 }
 __global__ __launch_bounds__(256) void k_row_map(const uint32_t* __restrict__ prev_id, const uint32_t* __restrict__ pos,
                                                  int N, uint32_t* __restrict__ map) {

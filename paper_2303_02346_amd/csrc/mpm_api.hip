@@ -52,7 +52,6 @@ struct Layout {
   size_t mats, offs, pscene, cyl_radius, err, mmv, vgrid, vbar, mmvb, pose, act, acc, ckpt, seg, adj0, adj1, scratch;
   size_t fast, cstats;
   size_t tmp, mmvb_blk;   // tiled adjoint: G2P output, node adjoints of (mv, m)
-  size_t redo_n, redo;    // tiled adjoint: FP64-pass counters (two per step) and list
   SortedRec rec, tmp_rec;
   // rigid bodies: rest offsets, material -> body table, body constants,
   // sums, per-step projection records, adjoint terms, set-up sums, status
@@ -127,14 +126,12 @@ Layout plan(const mpm_desc* d) {
     L.seg = take(plain_seg > tiled_seg ? plain_seg : tiled_seg);
     L.tmp = take(L.tmp_rec.bytes);
     L.mmvb_blk = take(n_keys * 64 * sizeof(float4));
-    L.redo_n = take(2 * T * sizeof(uint32_t));
-    L.redo = take(N * sizeof(uint2));
     L.adj0 = take(st);
     L.adj1 = take(st);
   } else {
     L.n_ckpt = 0;
     L.vbar = L.mmvb = L.acc = L.ckpt = L.seg = L.adj0 = L.adj1 = 0;
-    L.tmp = L.mmvb_blk = L.redo_n = L.redo = 0;
+    L.tmp = L.mmvb_blk = 0;
     L.rec = L.tmp_rec = SortedRec{};
   }
   L.n_bodies = count_bodies(d);
@@ -648,8 +645,6 @@ static void adjoint_step(mpm_ctx* c, const StepParams& P, const SortedState& Si,
   A.cl_count = Si.cl_count;
   A.mmv = Si.mmv;
   A.mmvb = G(c, c->L.mmvb_blk);
-  A.redo = (uint2*)(c->ws + c->L.redo);
-  A.redo_n = (uint32_t*)(c->ws + c->L.redo_n) + 2 * t;
   // the adjoint of the rigid projection turns the body rows of the adjoint
   // of s_{t+1} into the adjoint of the G2P output
   if (rrec)
@@ -658,7 +653,6 @@ static void adjoint_step(mpm_ctx* c, const StepParams& P, const SortedState& Si,
   launch_g2p_adj_tiled(A, P, f.g, f.part_wgs, s);
   launch_grid_adj_tiled(A, P, f.g, f.grid_wgs, pose_at(c, t), act_at(c, t), acc + (size_t)t * c->d.n_scenes * ACC_DOUBLES,
                         s);
-  A.redo_n += 1;
   launch_p2g_adj_tiled(A, P, f.g, f.part_wgs, s);
   PState tsw = a_cur; a_cur = a_nxt; a_nxt = tsw;
 }
@@ -778,7 +772,6 @@ static int enqueue_backward(mpm_ctx* c, const mpm_state* grad_T, float* grad_act
   launch_zero(acc, align_up((size_t)T * S * ACC_DOUBLES * sizeof(double)), s);
   int n_seg = k > 0 ? (T + k - 1) / k : 0;
   if (!c->plain_adjoint) {
-    launch_zero(c->ws + c->L.redo_n, align_up(2 * (size_t)T * sizeof(uint32_t)), s);
     int rc = k > 0 ? backward_tiled(c, P, a_cur, a_nxt, acc) : backward_records(c, P, a_cur, a_nxt, acc);
     if (rc != MPM_OK) return rc;
     n_seg = 0;

@@ -53,6 +53,7 @@ template <typename T> __device__ __forceinline__ T& at32(T* p, uint32_t off) {
   return *reinterpret_cast<T*>(reinterpret_cast<B*>(p) + off);
 }
 __device__ __forceinline__ float& row32(float* f, int k, int N, uint32_t off) { return at32(f + (size_t)k * N, off); }
+__device__ __forceinline__ const float& row32(const float* f, int k, int N, uint32_t off) { return at32(f + (size_t)k * N, off); }
 
 // A captured call (graph mode).
 struct FastGraph {

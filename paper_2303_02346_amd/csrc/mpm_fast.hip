@@ -441,11 +441,6 @@ __global__ __launch_bounds__(256) void k_gather_out(PBuf X, PState u, const MatD
 // ---------------------------------------------------------------------------
 // particle kernel
 // ---------------------------------------------------------------------------
-// multiplier m with r / d = (r m) >> 20 for r d < 2^19 (2^20 / d < m <= 2^20 / d + 2)
-__device__ __forceinline__ uint32_t div_mul(int d) {
-  return (uint32_t)(1048576.f * __builtin_amdgcn_rcpf((float)d)) + 2u;
-}
-
 enum { MODE_P2G = 0, MODE_FUSED = 1, MODE_G2P = 2 };
 
 struct PartArgs {

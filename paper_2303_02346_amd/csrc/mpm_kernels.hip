@@ -252,8 +252,13 @@ __global__ __launch_bounds__(256) void k_g2p_adj_plain(PState st, PState bn, PSt
 #pragma unroll
   for (int k = 0; k < 9; k++) { Cb[k] = bn.C[k * N + p]; Fb[k] = bn.F[k * N + p]; }
   Jb = bn.J[p];
-  float vbt[3], Bb[9], Fbo[9], Jbo;
-  particle_update_adjoint(x, vn, B, M, P, st, p, xb, vb, Cb, Fb, Jb, vbt, Bb, Fbo, Jbo);
+  float vbt[3], Bb[9], Fbo[9], Jbo, F[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, J = 0.f;
+  if (M.kind == KIND_LIQUID) J = st.J[p];
+  else {
+#pragma unroll
+    for (int k = 0; k < 9; k++) F[k] = st.F[k * N + p];
+  }
+  particle_update_adjoint(vn, B, M, P, F, J, xb, vb, Cb, Fb, Jb, vbt, Bb, Fbo, Jbo);
   // scatter to grid and weight/position gradients
   float xo[3] = {xb[0], xb[1], xb[2]};
 #pragma unroll

@@ -539,8 +539,8 @@ MPM_DI bool plastic_adjoint(const float* Md, const float* F, const MatDev& M, co
   return true;
 }
 
-// Adjoint of particle_update.  Inputs: the output adjoints (xb, vb, Cb, Fb,
-// Jb).  Outputs: vbt = adjoint of vn, Bb = adjoint of B, Fbo/Jbo = adjoint of
+// Adjoint of particle_update.  Inputs: the input state's F (read for a solid)
+// and J (for a liquid), the output adjoints (xb, vb, Cb, Fb, Jb).  Outputs: vbt = adjoint of vn, Bb = adjoint of B, Fbo/Jbo = adjoint of
 // the input F/J.  The direct x term (x' = x + ...) is left to the caller.
 // PREC selects the precision of the plastic-return adjoint: ADJ_AUTO takes
 // the FP32 adjoint and redoes an ill-conditioned one in FP64; ADJ_FP32
@@ -549,10 +549,9 @@ MPM_DI bool plastic_adjoint(const float* Md, const float* F, const MatDev& M, co
 // takes the FP64 adjoint.  Returns true otherwise.
 enum { ADJ_AUTO = 0, ADJ_FP32 = 1, ADJ_FP64 = 2 };
 template <int PREC = ADJ_AUTO>
-MPM_DI bool particle_update_adjoint(const float* x, const float* vn, const float* B, const MatDev& M, const StepParams& P,
-                                    const PState& in, int p, const float* xb, const float* vb, const float* Cb,
+MPM_DI bool particle_update_adjoint(const float* vn, const float* B, const MatDev& M, const StepParams& P,
+                                    const float* F, float J, const float* xb, const float* vb, const float* Cb,
                                     const float* Fb, float Jb, float* vbt, float* Bb, float* Fbo, float& Jbo) {
-  const int N = in.N;
   const float d4 = 4.f * P.inv_dx * P.inv_dx;
 #pragma unroll
   for (int a = 0; a < 3; a++) vbt[a] = vb[a] + P.dt * xb[a];
@@ -564,7 +563,6 @@ MPM_DI bool particle_update_adjoint(const float* x, const float* vn, const float
     Cbt[k] = Cb[k];
   }
   if (M.kind == KIND_LIQUID) {
-    float J = in.J[p];
     float dM = det3(Md);
     Jbo = Jb * dM;
     float K[9];
@@ -573,9 +571,7 @@ MPM_DI bool particle_update_adjoint(const float* x, const float* vn, const float
     for (int k = 0; k < 9; k++) { Cbt[k] += Jb * J * P.dt * K[k]; Fbo[k] = Fb[k]; }
   } else {
     Jbo = Jb;
-    float F[9], Ftb[9];
-#pragma unroll
-    for (int k = 0; k < 9; k++) F[k] = in.F[k * N + p];
+    float Ftb[9];
     if (elastic_update_kind(M.kind)) {
 #pragma unroll
       for (int k = 0; k < 9; k++) Ftb[k] = Fb[k];

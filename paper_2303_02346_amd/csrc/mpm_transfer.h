@@ -17,6 +17,11 @@
 
 namespace mpm {
 
+// multiplier m with r / d = (r m) >> 20 for r d < 2^19 (2^20 / d < m <= 2^20 / d + 2)
+__device__ __forceinline__ uint32_t div_mul(int d) {
+  return (uint32_t)(1048576.f * __builtin_amdgcn_rcpf((float)d)) + 2u;
+}
+
 // A block's 8^3 window of node values (nodes 4 b - 1 .. 4 b + 6 per axis; zero
 // outside the grid) from a block-layout array into LDS, by NT threads.  The
 // window spans three blocks per axis, whose key parts are wavefront-uniform:

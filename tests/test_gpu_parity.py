@@ -496,3 +496,30 @@ def test_deferred_particles_over_several_chunks_vs_oracle(threads, share):
     say(f"{n_ill} ill-conditioned of {sc.n} particles, {threads} threads, share {share}")
     compare_states(sim.state_numpy(), oracle_state(sc, sc.horizon), liquid_mask(sc), tol_x=1e-6, tol=1e-4,
                    tol_FJ=1e-5, n_grid=sc.n_grid)
+
+
+@pytest.mark.parametrize("ckpt", [0, 3])
+def test_gradient_deferred_particles_over_several_chunks_vs_oracle(ckpt):
+    """The same blocks through the tiled adjoint, records kept and recomputed:
+    the FP64 second passes of several chunks and the velocity-adjoint tile
+    that grows over them.  Tolerances: those of the ill-conditioned gradient
+    test."""
+    from parity import ill_conditioned_solids
+    sc = scenes.tiny(n_particles=4001, n_grid=16, steps=4, seed=7,
+                     kinds=(scenes.ELASTIC, scenes.LIQUID, scenes.SAND, scenes.VONMISES, scenes.BOX))
+    assert ill_conditioned_solids(sc, 0) > 1000
+    sim = sim_of(sc, requires_grad=True, ckpt_every=ckpt)
+    sim.step(sc.horizon)
+    loss, g = sim.loss_blob(sc.target_mu, sc.target_sigma)
+    ga, g0 = sim.backward(g[0:3], torch.zeros_like(g[0:3]), want_grad0=True)
+    p = O.params_from_scene(sc)
+    st0 = O.state_from_scene(sc, requires_grad=True)
+    acts = torch.tensor(sc.actions, dtype=torch.float64, requires_grad=True)
+    st = O.rollout(sc, state=st0, params=p, actions=acts)
+    O.blob_loss(st["x"], p.kind == O.LIQUID, torch.tensor(sc.target_mu, dtype=torch.float64), sc.target_sigma).backward()
+    e = {"actions": rel(ga[:, 0].double().cpu().numpy(), acts.grad.numpy()),
+         "x": rel(g0[0:3].T.double().cpu().numpy(), st0["x"].grad.numpy()),
+         "v": rel(g0[3:6].T.double().cpu().numpy(), st0["v"].grad.numpy()),
+         "C": rel(g0[6:15].T.double().cpu().numpy().reshape(-1, 3, 3), st0["C"].grad.numpy())}
+    say(f"deferred particles, ckpt {ckpt}: " + " ".join(f"{k} {v:.2e}" for k, v in e.items()))
+    assert max(e.values()) <= 1e-4
