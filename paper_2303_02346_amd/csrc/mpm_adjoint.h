@@ -17,7 +17,7 @@ struct AdjArgs {
   float* abar;               // adjoint of s_t in s_t's order, packed 25 x N
   const float4* vgrid;       // updated node velocities of step t (block layout)
   float* tiles;              // per-block tile slots (velocity-adjoint tiles)
-  int2* tile_box;
+  int4* tile_box;
   const uint32_t* gen;       // stamp epoch
   uint32_t sid;              // stamp step id of the velocity-adjoint tiles
   const uint32_t* cl_list;   // blocks claimed by the recompute of step t

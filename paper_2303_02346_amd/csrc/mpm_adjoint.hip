@@ -99,8 +99,8 @@ __global__ __launch_bounds__(NT, 2) void k_g2p_adj_tiled(AdjArgs A, StepParams P
       for (int r = tid; r < NQ * TILE_NODES / 4; r += NT) reinterpret_cast<int4*>(s_itile)[r] = make_int4(0, 0, 0, 0);
     }
     __syncthreads();
-    const size_t slot = (size_t)(uint32_t)ent.x + (size_t)ent.w * (size_t)g.n_keys;   // the entry's tile slot
-    float4* tile_out = reinterpret_cast<float4*>(A.tiles + slot * 4 * TILE_NODES);
+    const EntrySub es = entry_sub((uint32_t)ent.x, ent.w, g.n_keys);
+    float4* tile_out = reinterpret_cast<float4*>(A.tiles + (size_t)es.slot * 4 * TILE_NODES);
     int blo[3] = {1 << 20, 1 << 20, 1 << 20}, bhi[3] = {-(1 << 20), -(1 << 20), -(1 << 20)};
     // One pass over a chunk, as in k_particles: the main pass takes the FP32
     // plastic-return adjoint, and lanes where that is ill-conditioned are done
@@ -301,11 +301,12 @@ __global__ __launch_bounds__(NT, 2) void k_g2p_adj_tiled(AdjArgs A, StepParams P
         if (c0 + NT < count) prefetch(c0 + NT);
       }
     }
-    // the published tile's box
-    if (blo[0] <= bhi[0] && tid == 0) {
-      const int packed = blo[0] | (blo[1] << 4) | (blo[2] << 8) | ((bhi[0] + 2) << 12) | ((bhi[1] + 2) << 16) |
-                         ((bhi[2] + 2) << 20);
-      A.tile_box[slot] = make_int2(packed, (int)stamp);
+    // the published tile's box (an empty tile still says that the block has further ones)
+    if (tid == 0 && (blo[0] <= bhi[0] || es.extra > 0)) {
+      const int hi[3] = {bhi[0] + 2, bhi[1] + 2, bhi[2] + 2};
+      A.tile_box[(size_t)(uint32_t)ent.x * NSUB + es.s] =
+          make_int4(blo[0] <= bhi[0] ? box_word(blo, hi, es.extra) : (BOX_EMPTY | (es.extra << 24)), (int)stamp,
+                    (int)es.slot, 0);
     }
   }
 }
@@ -328,54 +329,10 @@ __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P,
     int sc, cx, cy, cz;
     key_decode(g, key, sc, cx, cy, cz);
     {
-      // (tile sums as in k_grid: lanes 32..58 hold the neighbours' second slots)
-      int2 nbox = make_int2(0, 0);
-      uint32_t nkey = 0;
-      const int dl = lane < 32 ? lane : lane - 32;
-      if (dl < 27) {
-        const int sx = cx + dl / 9 - 1, sy = cy + (dl / 3) % 3 - 1, sz = cz + dl % 3 - 1;
-        if (sx >= 0 && sy >= 0 && sz >= 0 && sx < g.nb && sy < g.nb && sz < g.nb) {
-          nkey = block_key(g, sc, sx, sy, sz) + (lane < 32 ? 0u : (uint32_t)g.n_keys);
-          nbox = A.tile_box[nkey];
-          if ((uint32_t)nbox.y != stamp) nbox.y = 0;
-        }
-      }
       const int gx = 4 * cx + li, gy = 4 * cy + lj, gz = 4 * cz + lk;
-      float vb[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-      for (int dd = 0; dd < 27; dd++) {
-        const int bxv = __shfl(nbox.x, dd);
-        const int valid = __shfl(nbox.y, dd);
-        const uint32_t kk = __shfl(nkey, dd);
-        const int sx = cx + dd / 9 - 1, sy = cy + (dd / 3) % 3 - 1, sz = cz + dd % 3 - 1;
-        const int qi = gx - (4 * sx - 2), qj = gy - (4 * sy - 2), qk = gz - (4 * sz - 2);
-        const int lo0 = bxv & 15, lo1 = (bxv >> 4) & 15, lo2 = (bxv >> 8) & 15;
-        const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
-        const bool in = valid && qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2;
-        const int q = in ? (qi * TILE + qj) * TILE + qk : 0;
-        const float4 tv = reinterpret_cast<const float4*>(A.tiles + (size_t)(in ? kk : 0u) * 4 * TILE_NODES)[q];
-        vb[0] += in ? tv.x : 0.f;
-        vb[1] += in ? tv.y : 0.f;
-        vb[2] += in ? tv.z : 0.f;
-      }
-      unsigned long long m1 = __ballot(lane >= 32 && nbox.y != 0);
-      while (m1) {
-        const int src = __ffsll((long long)m1) - 1;
-        m1 &= m1 - 1ull;
-        const int dd = src - 32;
-        const int bxv = __shfl(nbox.x, src);
-        const uint32_t kk = __shfl(nkey, src);
-        const int sx = cx + dd / 9 - 1, sy = cy + (dd / 3) % 3 - 1, sz = cz + dd % 3 - 1;
-        const int qi = gx - (4 * sx - 2), qj = gy - (4 * sy - 2), qk = gz - (4 * sz - 2);
-        const int lo0 = bxv & 15, lo1 = (bxv >> 4) & 15, lo2 = (bxv >> 8) & 15;
-        const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
-        if (qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2) {
-          const float4 tv = reinterpret_cast<const float4*>(A.tiles + (size_t)kk * 4 * TILE_NODES)[(qi * TILE + qj) * TILE + qk];
-          vb[0] += tv.x;
-          vb[1] += tv.y;
-          vb[2] += tv.z;
-        }
-      }
+      float4 tsum = make_float4(0.f, 0.f, 0.f, 0.f);
+      sum_tiles(g, sc, cx, cy, cz, lane, A.tile_box, A.tiles, stamp, tsum);
+      const float vb[3] = {tsum.x, tsum.y, tsum.z};
       const size_t node = (size_t)key * 64 + lane;
       const float4 gm = A.mmv[node];
       float loc[ACC_DOUBLES];

@@ -42,7 +42,7 @@ SortedRec sorted_rec(size_t N, size_t n_keys, bool with_grid) {
   r.rank = take(N * 4);
   r.mat = take(N);
   r.map = take(N * 4);
-  r.list = take(n_keys * 16);
+  r.list = take(n_keys * TILE_SLOTS * 16);
   r.list_n = take(16);
   r.bytes = o;
   return r;
@@ -180,7 +180,7 @@ struct mpm_ctx {
   struct CallGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    int t0 = 0, n = 0, part_wgs = 0, grid_wgs = 0;
+    int t0 = 0, n = 0, part_wgs = 0, grid_wgs = 0, share_chunks = 0;
     const void* ptr[11] = {};
     unsigned long long n_ep = 0;   // stamp epochs one call advances
   };
@@ -205,7 +205,8 @@ static int graph_call(mpm_ctx* c, std::vector<mpm_ctx::CallGraph>& cache, const 
   hipStream_t s = c->stream;
   mpm_ctx::CallGraph* G = nullptr;
   for (auto& g : cache) {
-    bool same = g.exec && g.t0 == key.t0 && g.n == key.n && g.part_wgs == key.part_wgs && g.grid_wgs == key.grid_wgs;
+    bool same = g.exec && g.t0 == key.t0 && g.n == key.n && g.part_wgs == key.part_wgs && g.grid_wgs == key.grid_wgs &&
+                g.share_chunks == key.share_chunks;
     for (int q = 0; q < 11 && same; q++) same = g.ptr[q] == key.ptr[q];
     if (same) G = &g;
   }
@@ -229,7 +230,7 @@ static int graph_call(mpm_ctx* c, std::vector<mpm_ctx::CallGraph>& cache, const 
   } else {
     if ((f.calls & 0xffffull) + G->n_ep >= 0x10000ull) {
       launch_zero(f.claim, (size_t)f.g.n_keys * 4, s);
-      launch_zero(f.tile_box, (size_t)f.g.n_keys * NSUB * 8, s);
+      launch_zero(f.tile_box, (size_t)f.g.n_keys * NSUB * 16, s);
     }
     f.calls += G->n_ep;
   }
@@ -470,7 +471,7 @@ static void rigid_tiled_run(mpm_ctx* c, const StepParams& P, const PState& us, i
   const PBuf tmp = f.buf[1];
   const RigidRows rows{packed_state(tmp.f, N), tmp.mat, tmp.id};
   // (the forward's sorts scan only the keys they counted)
-  fast_sort_user(f, P, us, R0, s, true);
+  fast_sort_user(f, P, us, R0, s, true, true);
   for (int t = t0; t < t0 + n; t++) {
     const uint32_t sid = fast_next_sid(f);
     fast_p2g(f, P, R0, sid, s);
@@ -519,6 +520,7 @@ int mpm_step(mpm_ctx* c, int32_t n_steps) {
       key.t0 = c->t;
       key.n = n_steps;
       key.part_wgs = c->fast.part_wgs;
+      key.share_chunks = c->fast.share_chunks;
       key.grid_wgs = c->fast.grid_wgs;
       const void* ptr[6] = {us.x, us.v, us.C, us.F, us.J, P.mat};
       for (int q = 0; q < 6; q++) key.ptr[q] = ptr[q];
@@ -689,7 +691,7 @@ static int backward_tiled(mpm_ctx* c, const StepParams& P, PState& a_cur, PState
     // recompute: block-sorted records of s_ts .. s_{te-1}, each with its step's grid
     PState ck = packed_state((float*)(c->ws + c->L.ckpt + (size_t)seg * c->state_bytes), N);
     SortedState S0 = sorted_state(c, c->L.seg);
-    fast_sort_user(f, P, ck, S0, s, true);   // (the padded import counters: the touched scan)
+    fast_sort_user(f, P, ck, S0, s, true, true);   // (the padded import counters: the touched scan)
     // record of step t (record 1 keeps record 0's order: the first fused
     // step places its output by the import's offsets)
     auto rec = [&](int t) {
@@ -826,6 +828,7 @@ int mpm_step_backward(mpm_ctx* c, const mpm_state* grad_T, float* grad_actions_d
     mpm_ctx::CallGraph key;
     key.n = c->t;
     key.part_wgs = f.part_wgs;
+    key.share_chunks = f.share_chunks;
     key.grid_wgs = f.grid_wgs;
     const void* ptr[11] = {grad_T->x, grad_T->v, grad_T->C, grad_T->F, grad_T->J, grad_actions_dev,
                            grad_0 ? grad_0->x : nullptr, grad_0 ? grad_0->v : nullptr, grad_0 ? grad_0->C : nullptr,

@@ -58,6 +58,29 @@ __device__ __forceinline__ float wave_sum(float x) {
          (__int_as_float(__builtin_amdgcn_readlane(xi, 32)) + __int_as_float(__builtin_amdgcn_readlane(xi, 48)));
 }
 
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  int v = (int)x;
+  v += dpp::mov<dpp::kSwap1>(v);
+  v += dpp::mov<dpp::kSwap2>(v);
+  v += dpp::mov<dpp::kHalfMirror>(v);
+  v += dpp::mov<dpp::kMirror>(v);
+  return (uint32_t)(__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
+                    __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
+  int v = (int)x;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1, :2, :4, :8 (zeros shifted in)
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  const int r0 = __builtin_amdgcn_readlane(v, 15), r1 = __builtin_amdgcn_readlane(v, 31),
+            r2 = __builtin_amdgcn_readlane(v, 47);
+  const int row = __lane_id() >> 4;
+  return (uint32_t)(v + (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0));
+}
+
 __device__ __forceinline__ uint32_t wave_or(uint32_t x) {
   int v = (int)x;
   v |= dpp::mov<dpp::kSwap1>(v);

@@ -30,10 +30,32 @@ constexpr int VT_NODES = VT * VT * VT;
 constexpr int VT_ROW = VT;
 constexpr int VT_PLANE = VT * VT + 4;
 constexpr int VT_LDS = VT * VT_PLANE;
-// Tile slots per block key: the forward lists a block of more than two
-// chunks twice, and the second workgroup publishes its tile in slot
-// key + n_keys (the adjoint uses slot key only).
-constexpr int NSUB = 2;
+// A block may be shared by up to NSUB workgroups (list entries), each of which
+// publishes a tile of its own: entry 0 in slot key, the others in slots that
+// the scan assigns from the n_keys slots after those.  Word w of an entry:
+// its number (bits 0..2), the block's entries minus one (3..5), and its first
+// extra slot minus n_keys (6..).  The box of entry s of a key is at
+// tile_box[key * NSUB + s].
+constexpr int NSUB = 6;
+constexpr int TILE_SLOTS = 2;   // tile slots per key
+struct EntrySub {
+  int s, extra;
+  uint32_t slot;
+};
+__host__ __device__ inline EntrySub entry_sub(uint32_t key, int w, int n_keys) {
+  EntrySub r;
+  r.s = w & 7;
+  r.extra = (w >> 3) & 7;
+  r.slot = r.s == 0 ? key : (uint32_t)n_keys + (uint32_t)(w >> 6) + (uint32_t)(r.s - 1);
+  return r;
+}
+// A published box: the tile's node range as two packed corners (4 bits per
+// axis) with the block's further entries in bits 24.., the stamp of the step
+// that wrote it, and the tile's slot.
+__host__ __device__ inline int box_word(const int* lo, const int* hi, int extra) {
+  return lo[0] | (lo[1] << 4) | (lo[2] << 8) | (hi[0] << 12) | (hi[1] << 16) | (hi[2] << 20) | (extra << 24);
+}
+constexpr int BOX_EMPTY = 0xfff;   // lo 15, hi 0
 
 // Particle buffer: packed state (25 rows of N floats) plus bookkeeping.
 struct PBuf {
@@ -86,13 +108,13 @@ struct FastPath {
   uint32_t* cpad;          // the import's key counters, 64 bytes apart
   uint32_t *counts, *offsets;
   uint32_t *touched, *n_touched;   // keys counted in the current step, in first-touch order
-  int4* list[3];           // occupied-block lists (rotating; up to NSUB entries per key)
+  int4* list[3];           // occupied-block lists (rotating; TILE_SLOTS n_keys rows)
   uint32_t* list_n;        // [3]
   uint32_t* claim;         // per-block stamp: which step last updated the block
   uint32_t* cl_list;       // keys of the blocks claimed in the current step
   uint32_t* cl_count;      // [2]: claims of odd and even step ids
-  int2* tile_box;          // {packed lo/hi, stamp} per tile slot
-  float* tiles;            // NSUB n_keys slots of 4 TILE_NODES floats (forward: a float4 (m, mv) per node)
+  int4* tile_box;          // {packed box, stamp, tile slot} per key and entry (NSUB n_keys)
+  float* tiles;            // TILE_SLOTS n_keys slots of 4 TILE_NODES floats (forward: a float4 (m, mv) per node)
   float4* vgrid;           // n_keys x 64
   uint32_t* gen;           // device per-call epoch of the step stamps
   int* t0_dev;             // device clock at the start of the call
@@ -131,7 +153,7 @@ struct FastPath {
 // keeps one per step of a checkpoint segment).
 struct SortedState {
   PBuf b;                  // f (25 x N), id (user index), key, rank, mat
-  int4* list;              // occupied blocks {key, offset, count, 0}
+  int4* list;              // occupied blocks {key, offset, count, w} (see NSUB; TILE_SLOTS n_keys rows)
   uint32_t* list_n;
   // the step's grid, kept for the adjoint (block layout; NULL = the path's
   // shared arrays): updated velocities and masses, node momenta and masses,
@@ -159,10 +181,11 @@ void fast_destroy(FastPath& f);
 // under step id `sid` (from fast_next_sid), the grid update of step t (with
 // st.mmv, also the node momenta and masses), and G2P into `out` in the same
 // row order.  The sorts scan the keys they counted; the blocks are listed in
-// key (Morton) order unless `touched` is set: then in first-touch order.
+// key (Morton) order unless `touched` is set: then in first-touch order, shared
+// by several workgroups as in the forward path if `share` is set too.
 uint32_t fast_next_sid(FastPath& f);
 void fast_sort_user(FastPath& f, const StepParams& P, const PState& user, SortedState& out, hipStream_t s,
-                    bool touched = false);
+                    bool touched = false, bool share = false);
 void fast_sort_next(FastPath& f, const StepParams& P, const SortedState& prev, const PBuf& next, SortedState& out,
                     uint32_t* map, hipStream_t s, bool touched = false);
 void fast_p2g(FastPath& f, const StepParams& P, const SortedState& st, uint32_t sid, hipStream_t s);
@@ -176,7 +199,7 @@ void fast_g2p(FastPath& f, const StepParams& P, const SortedState& st, const PBu
 // `sid` and its block claims into out's claim list; the keys of the new
 // positions are counted for the next scan.  fast_grid_scan is fast_grid that
 // also clears the claim counter cl_zero and, with scan_list, scans those
-// counts into scan_list (each block listed once).
+// counts into scan_list.
 void fast_fused(FastPath& f, const StepParams& P, const SortedState& in, const SortedState& out, uint32_t* map,
                 uint32_t sid, hipStream_t s);
 void fast_grid_scan(FastPath& f, const StepParams& P, const SortedState& st, uint32_t sid, int t,

@@ -73,139 +73,171 @@ __global__ __launch_bounds__(256) void k_import_keys(PState u, StepParams P, Fas
 }
 
 // Exclusive scan of the counts of the touched keys -> their offsets, the
-// list of occupied keys {key, offset, count, sub}, and the counts and the
+// list of occupied blocks {key, offset, count, w}, and the counts and the
 // touched counter cleared.  Run by one workgroup of NT threads.  The
 // particles of the blocks follow the order in which their keys were first
-// touched; only contiguity matters.  With split_nt > 0 a block of more than
-// max_chunks chunks of split_nt particles is listed twice, sub 0 with the
-// first ceil(chunks / 2) chunks and sub 1 with the rest, so that two
-// workgroups share it (each publishes its own tile slot); with fill_slots >
-// 0 as well, blocks of two chunks are split too (the first ones in touch
-// order, at most one added entry in 16) while the list has fewer entries
-// than fill_slots, the particle kernel's resident workgroups.  Entries of
-// two or more chunks (of split_nt
-// particles, else of order_nt; none if both are 0) are listed before those
-// of one: the particle kernels' workgroups are dispatched round-robin over
-// the CUs, so each CU then receives about as many chunks as the others, the
-// longest first.
+// touched; only contiguity matters.
+//
+// With split_nt > 0 a block may be shared by several workgroups (entries of
+// split_nt-particle chunks; word w: see NSUB).  While the entries of all
+// blocks, each shared by one workgroup per chunk up to NSUB, are no more than
+// fill_slots, the particle kernel's resident workgroups, every block is shared
+// that way: the kernel then takes the time of one chunk (1e5 particles on
+// 64^3, 208 blocks of up to 5 chunks: 33.4 -> 20.3 us; 78k on 101^3, 455 of up
+// to 2: 30.2 -> 22.2).  Otherwise a block of more than max_chunks chunks is
+// shared by two, and blocks of two chunks while the list is shorter than
+// fill_slots (the first ones in touch order, at most one added entry in 16:
+// the tiles added cost the grid kernel more than they save here).
+// Entries of two or more chunks (of split_nt particles, else of order_nt; none
+// if both are 0) are listed before those of one: the particle kernels'
+// workgroups are dispatched round-robin over the CUs, so each CU then receives
+// about as many chunks as the others, the longest first.
+//
+// A thread holds KT consecutive keys of a tile of NT KT; of a list that fits
+// one tile the keys and counts are read once, and before the number of keys is
+// known (two dependent round trips; three and three again for the second pass
+// before, when the scan set the length of that step's grid kernel: 13.4 us for
+// the 208 blocks above, now 9.5).
 template <int NT>
 __device__ void scan_touched(uint32_t* __restrict__ counts, uint32_t* __restrict__ offsets,
                              const uint32_t* __restrict__ touched, uint32_t* __restrict__ n_touched,
                              int4* __restrict__ list, uint32_t* __restrict__ list_n, int n_keys, int stride = 1,
                              int split_nt = 0, int max_chunks = 2, int order_nt = 0, int fill_slots = 0) {
-  constexpr int NW = NT / 64;
-  __shared__ uint32_t s_sum[NW], s_big[NW], s_sm[NW], s_cand[NW];
-  __shared__ uint32_t s_run, s_runbig, s_runsm, s_runcand, s_nbig, s_nent, s_ncand;
+  constexpr int NW = NT / 64, KT = 4, TILE_KEYS = NT * KT;
+  __shared__ uint32_t s_tot[5], s_a[NW], s_b[NW], s_c[NW];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const uint32_t n = min(n_touched[0], (uint32_t)n_keys);
-  // the chunks of a key with c particles, whether it is split by size, and
-  // whether it may be split to fill the resident workgroups
-  const uint32_t cs = (uint32_t)(split_nt > 0 ? split_nt : order_nt);
-  auto chunks = [&](uint32_t c) { return cs > 0 ? (c + cs - 1) / cs : 0u; };
-  auto size_split = [&](uint32_t nch) { return split_nt > 0 && nch > (uint32_t)max_chunks; };
-  auto fill_candidate = [&](uint32_t nch) { return fill_slots > 0 && split_nt > 0 && nch == 2u && !size_split(nch); };
-  // its entries' classes (two or more chunks: big)
-  auto classes = [&](uint32_t nch, bool valid, bool sp, uint32_t& ch0, bool& big0, bool& big1) {
-    ch0 = sp ? (nch + 1) / 2 : nch;
-    big0 = valid && ch0 >= 2u;
-    big1 = sp && (nch - ch0) >= 2u;
+  uint32_t key[KT], c[KT];
+  auto load_tile = [&](uint32_t i0, uint32_t n) {
+#pragma unroll
+    for (int q = 0; q < KT; q++) {
+      const uint32_t i = i0 + (uint32_t)(t * KT + q);
+      key[q] = i < n ? touched[i] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < KT; q++) c[q] = counts[(size_t)min(key[q], (uint32_t)n_keys - 1u) * stride];
   };
-  if (t == 0) { s_run = 0; s_runbig = 0; s_runsm = 0; s_runcand = 0; s_nbig = 0; s_nent = 0; s_ncand = 0; }
+  if (t < 5) s_tot[t] = 0u;
+  // (rows past the number of touched keys are stale: their counts are dropped)
+  load_tile(0u, (uint32_t)n_keys);
+  const uint32_t n = min(n_touched[0], (uint32_t)n_keys);
+  const uint32_t cs = (uint32_t)(split_nt > 0 ? split_nt : order_nt);
+  auto chunks = [&](uint32_t cc) { return cs > 0 ? (cc + cs - 1) / cs : 0u; };
+  auto size_split = [&](uint32_t nch) { return split_nt > 0 && nch > (uint32_t)max_chunks && nch > 1u; };
+  auto fill_candidate = [&](uint32_t nch) { return fill_slots > 0 && split_nt > 0 && nch == 2u && !size_split(nch); };
+  // entries of two or more chunks among ns entries of nch chunks (entry s has
+  // nch / ns chunks, and one more for s < nch % ns)
+  auto big_entries = [&](uint32_t nch, uint32_t ns) -> uint32_t {
+    const uint32_t b = nch / ns;
+    return b >= 2u ? ns : (b == 1u ? nch - ns : 0u);
+  };
   __syncthreads();
   if (cs > 0) {
-    // first pass: the entries (big ones, all) and the fill candidates
-    uint32_t nb = 0, ne = 0, nc = 0;
-    for (uint32_t i = t; i < n; i += NT) {
-      const uint32_t nch = chunks(counts[(size_t)touched[i] * stride]);
-      const bool sp = size_split(nch);
-      uint32_t ch0;
-      bool b0, b1;
-      classes(nch, true, sp, ch0, b0, b1);
-      nb += (b0 ? 1u : 0u) + (b1 ? 1u : 0u);
-      ne += sp ? 2u : 1u;
-      nc += fill_candidate(nch) ? 1u : 0u;
-    }
+    // totals: entries, big ones and fill candidates by the second rule; entries and big ones by the first
+    uint32_t v[5] = {0, 0, 0, 0, 0};
+    for (uint32_t i0 = 0; i0 < n; i0 += TILE_KEYS) {
+      if (i0 > 0) load_tile(i0, n);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      nb += __shfl_xor(nb, off);
-      ne += __shfl_xor(ne, off);
-      nc += __shfl_xor(nc, off);
-    }
-    if (lane == 0) {
-      atomicAdd(&s_nbig, nb);
-      atomicAdd(&s_nent, ne);
-      atomicAdd(&s_ncand, nc);
-    }
-    __syncthreads();
-  }
-  // the first `fill` candidates are split: each turns one big entry into two
-  // of one chunk.  At most one entry in 16 is added (every split adds a
-  // second tile slot that the grid kernel reads one at a time)
-  const uint32_t fill = (fill_slots > 0 && (uint32_t)fill_slots > s_nent)
-                            ? min(min((uint32_t)fill_slots - s_nent, s_ncand), s_nent / 16u)
-                            : 0u;
-  const uint32_t nbig = s_nbig - fill;
-  for (uint32_t c0 = 0; c0 < n; c0 += NT) {
-    const uint32_t i = c0 + t;
-    const bool valid = i < n;
-    uint32_t key = 0, c = 0;
-    if (valid) { key = touched[i]; c = counts[(size_t)key * stride]; }
-    const uint32_t nch = valid ? chunks(c) : 0u;
-    const bool cand = valid && fill_candidate(nch);
-    uint32_t icand = cand ? 1u : 0u;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t o = __shfl_up(icand, off);
-      if (lane >= off) icand += o;
-    }
-    if (lane == 63) s_cand[wv] = icand;
-    __syncthreads();
-    uint32_t wcand = s_runcand, totcand = s_runcand;
-#pragma unroll
-    for (int q = 0; q < NW; q++) {
-      if (q < wv) wcand += s_cand[q];
-      totcand += s_cand[q];
-    }
-    const bool sp = valid && (size_split(nch) || (cand && wcand + icand - 1u < fill));
-    uint32_t ch0;
-    bool big0, big1;
-    classes(nch, valid, sp, ch0, big0, big1);
-    const uint32_t eb = (big0 ? 1u : 0u) + (big1 ? 1u : 0u);
-    const uint32_t es = (valid ? 1u : 0u) + (sp ? 1u : 0u) - eb;
-    uint32_t is = c, ib = eb, ism = es;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t o = __shfl_up(is, off), o2 = __shfl_up(ib, off), o3 = __shfl_up(ism, off);
-      if (lane >= off) { is += o; ib += o2; ism += o3; }
-    }
-    if (lane == 63) { s_sum[wv] = is; s_big[wv] = ib; s_sm[wv] = ism; }
-    __syncthreads();
-    uint32_t woff = s_run, tot = s_run, wb = s_runbig, totb = s_runbig, wsm = s_runsm, totsm = s_runsm;
-#pragma unroll
-    for (int q = 0; q < NW; q++) {
-      if (q < wv) { woff += s_sum[q]; wb += s_big[q]; wsm += s_sm[q]; }
-      tot += s_sum[q];
-      totb += s_big[q];
-      totsm += s_sm[q];
-    }
-    if (valid) {
-      const uint32_t o = woff + is - c;
-      uint32_t pb = wb + ib - eb, ps = nbig + wsm + ism - es;
-      offsets[key] = o;
-      counts[(size_t)key * stride] = 0u;
-      if (sp) {
-        const uint32_t c1 = ch0 * (uint32_t)split_nt;
-        list[big0 ? pb++ : ps++] = make_int4((int)key, (int)o, (int)c1, 0);
-        list[big1 ? pb : ps] = make_int4((int)key, (int)(o + c1), (int)(c - c1), 1);
-      } else {
-        list[big0 ? pb : ps] = make_int4((int)key, (int)o, (int)c, 0);
+      for (int q = 0; q < KT; q++) {
+        if (i0 + (uint32_t)(t * KT + q) >= n) continue;
+        const uint32_t nch = chunks(c[q]), ns = size_split(nch) ? 2u : 1u;
+        const uint32_t nf = min(max(nch, 1u), (uint32_t)NSUB);
+        v[0] += ns;
+        v[1] += big_entries(nch, ns);
+        v[2] += fill_candidate(nch) ? 1u : 0u;
+        v[3] += nf;
+        v[4] += big_entries(nch, nf);
       }
     }
-    __syncthreads();
-    if (t == 0) { s_run = tot; s_runbig = totb; s_runsm = totsm; s_runcand = totcand; }
+#pragma unroll
+    for (int q = 0; q < 5; q++) {
+      v[q] = wave_sum_u32(v[q]);
+      if (lane == 0 && v[q]) atomicAdd(&s_tot[q], v[q]);
+    }
     __syncthreads();
   }
-  if (t == 0) { list_n[0] = s_runbig + s_runsm; n_touched[0] = 0u; }
+  const uint32_t n_ent = s_tot[0], n_full = s_tot[3];
+  const bool full = split_nt > 0 && fill_slots > 0 && n_full <= (uint32_t)fill_slots && n_full - n <= (uint32_t)n_keys;
+  // the first `fill` candidates are split: each turns one big entry into two of one chunk
+  const uint32_t fill = (!full && fill_slots > 0 && (uint32_t)fill_slots > n_ent)
+                            ? min(min((uint32_t)fill_slots - n_ent, s_tot[2]), n_ent / 16u)
+                            : 0u;
+  const uint32_t nbig = full ? s_tot[4] : s_tot[1] - fill;
+  uint32_t run = 0, run_e = 0, run_b = 0, run_c = 0;   // particles, entries, big entries, candidates before this tile
+  for (uint32_t i0 = 0; i0 < n; i0 += TILE_KEYS) {
+    if (n > TILE_KEYS) load_tile(i0, n);
+    uint32_t ns[KT], nch[KT];
+    uint32_t cand_before = 0;
+    if (fill > 0) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int q = 0; q < KT; q++)
+        mine += (i0 + (uint32_t)(t * KT + q) < n && fill_candidate(chunks(c[q]))) ? 1u : 0u;
+      const uint32_t inc = wave_scan_u32(mine);
+      if (lane == 63) s_c[wv] = inc;
+      __syncthreads();
+      cand_before = run_c + inc - mine;
+#pragma unroll
+      for (int w = 0; w < NW; w++) {
+        if (w < wv) cand_before += s_c[w];
+        run_c += s_c[w];
+      }
+    }
+    uint32_t sum = 0, ent = 0, big = 0;
+#pragma unroll
+    for (int q = 0; q < KT; q++) {
+      const bool valid = i0 + (uint32_t)(t * KT + q) < n;
+      nch[q] = valid ? chunks(c[q]) : 0u;
+      bool two = size_split(nch[q]);
+      if (fill > 0 && valid && fill_candidate(nch[q])) {
+        two = cand_before < fill;
+        cand_before++;
+      }
+      ns[q] = !valid ? 0u : (full ? min(max(nch[q], 1u), (uint32_t)NSUB) : (two ? 2u : 1u));
+      if (valid) {
+        sum += c[q];
+        ent += ns[q];
+        big += big_entries(nch[q], ns[q]);
+      }
+    }
+    // (a thread has at most KT NSUB entries, so both counts of a tile fit 16 bits)
+    const uint32_t both = ent | (big << 16);
+    const uint32_t isum = wave_scan_u32(sum), iboth = wave_scan_u32(both);
+    if (lane == 63) { s_a[wv] = isum; s_b[wv] = iboth; }
+    __syncthreads();
+    uint32_t o = run + isum - sum, pe = iboth - both, tb = 0;
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      const uint32_t a = s_a[w], b = s_b[w];
+      if (w < wv) { o += a; pe += b; }
+      run += a;
+      tb += b;
+    }
+    uint32_t pb = run_b + (pe >> 16), pa = run_e + (pe & 0xffffu);   // big entries and entries before this thread's
+    run_e += tb & 0xffffu;
+    run_b += tb >> 16;
+#pragma unroll
+    for (int q = 0; q < KT; q++) {
+      const uint32_t i = i0 + (uint32_t)(t * KT + q);
+      if (i >= n) continue;
+      offsets[key[q]] = o;
+      counts[(size_t)key[q] * stride] = 0u;
+      // small entries before = entries before - big ones; extra slots before = entries - keys
+      const uint32_t base = nch[q] / ns[q], rem = nch[q] - base * ns[q];
+      const int wbase = (int)(((ns[q] - 1u) << 3) | ((ns[q] > 1u ? pa - i : 0u) << 6));
+      uint32_t left = c[q];
+      for (uint32_t s = 0; s < ns[q]; s++) {
+        const uint32_t ch = base + (s < rem ? 1u : 0u);
+        const uint32_t cc = s + 1u == ns[q] ? left : ch * cs;
+        const uint32_t at = ch >= 2u ? pb++ : nbig + (pa - pb);
+        list[at] = make_int4((int)key[q], (int)o, (int)cc, wbase | (int)s);
+        pa++;
+        o += cc;
+        left -= cc;
+      }
+    }
+    if (n > TILE_KEYS) __syncthreads();
+  }
+  if (t == 0) { list_n[0] = run_e; n_touched[0] = 0u; }
 }
 
 // Dense variant: exclusive scan of all counts -> offsets, the list of
@@ -453,7 +485,7 @@ struct PartArgs {
   uint32_t* touched;           // keys counted in this step (first touch appends)
   uint32_t* n_touched;
   float* tiles;
-  int2* tile_box;
+  int4* tile_box;
   int n_keys;
   uint32_t* claim;             // per-block stamp of the step that claimed it
   uint32_t* cl_list;           // keys of the blocks claimed in this step
@@ -554,8 +586,8 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
       for (int r = tid; r < TILE_NODES; r += NT) reinterpret_cast<int4*>(s_itile)[r] = make_int4(0, 0, 0, 0);
     }
     __syncthreads();
-    const size_t slot = (size_t)(uint32_t)ent.x + (size_t)ent.w * (size_t)A.n_keys;   // the entry's tile slot
-    float4* tile_out = reinterpret_cast<float4*>(A.tiles + slot * 4 * TILE_NODES);
+    const EntrySub es = entry_sub((uint32_t)ent.x, ent.w, A.n_keys);
+    float4* tile_out = reinterpret_cast<float4*>(A.tiles + (size_t)es.slot * 4 * TILE_NODES);
     // the tile's non-zero box over all chunks (every thread keeps the same copy)
     int blo[3] = {1 << 20, 1 << 20, 1 << 20}, bhi[3] = {-(1 << 20), -(1 << 20), -(1 << 20)};
     // One pass over a chunk's particles (the lanes with `on` set).  The main pass
@@ -978,8 +1010,8 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
       const int hi0 = bhi[0] + 2, hi1 = bhi[1] + 2, hi2 = bhi[2] + 2;
       if (lo0 <= hi0 - 2) {
         if (tid == 0) {
-          int packed = lo0 | (lo1 << 4) | (lo2 << 8) | (hi0 << 12) | (hi1 << 16) | (hi2 << 20);
-          A.tile_box[slot] = make_int2(packed, (int)stamp);
+          const int lo[3] = {lo0, lo1, lo2}, hi[3] = {hi0, hi1, hi2};
+          A.tile_box[(size_t)(uint32_t)ent.x * NSUB + es.s] = make_int4(box_word(lo, hi, es.extra), (int)stamp, (int)es.slot, 0);
         }
         // claim the blocks this tile touches: the first entry to claim a block
         // in this step appends it to the list the grid kernel works through
@@ -1007,6 +1039,9 @@ k_particles(PartArgs A, StepParams P, FastGeom g) {
             if (won && at < (uint32_t)A.n_keys) A.cl_list[at] = nk;
           }
         }
+      } else if (tid == 0 && es.extra > 0) {
+        // (an empty tile still says that the block has further ones)
+        A.tile_box[(size_t)(uint32_t)ent.x * NSUB + es.s] = make_int4(BOX_EMPTY | (es.extra << 24), (int)stamp, (int)es.slot, 0);
       }
     }
   }
@@ -1037,7 +1072,7 @@ struct ScanArgs {
 // kernel (independent of the grid work) and the others do the grid update.
 __global__ __launch_bounds__(256) void k_grid(StepParams P, FastGeom g, const uint32_t* __restrict__ cl_list,
                                               const uint32_t* __restrict__ cl_count, uint32_t* __restrict__ cl_zero,
-                                              const int2* __restrict__ tile_box, const float* __restrict__ tiles,
+                                              const int4* __restrict__ tile_box, const float* __restrict__ tiles,
                                               const uint32_t* __restrict__ gen, uint32_t step_id,
                                               float4* __restrict__ vgrid, const double* __restrict__ pose_base,
                                               const float* __restrict__ act_base, const int* __restrict__ t0_dev,
@@ -1072,60 +1107,10 @@ __global__ __launch_bounds__(256) void k_grid(StepParams P, FastGeom g, const ui
     int sc, cx, cy, cz;
     key_decode(g, key, sc, cx, cy, cz);
     {
-      // lanes 0..26 read the boxes of the 27 neighbours' tiles, lanes 32..58
-      // those of their second slots (blocks shared by two workgroups)
-      int2 nbox = make_int2(0, 0);
-      uint32_t nkey = 0;
-      const int dl = lane < 32 ? lane : lane - 32;
-      if (dl < 27) {
-        const int sx = cx + dl / 9 - 1, sy = cy + (dl / 3) % 3 - 1, sz = cz + dl % 3 - 1;
-        if (sx >= 0 && sy >= 0 && sz >= 0 && sx < g.nb && sy < g.nb && sz < g.nb) {
-          nkey = block_key(g, sc, sx, sy, sz) + (lane < 32 ? 0u : (uint32_t)g.n_keys);
-          nbox = tile_box[nkey];
-          if ((uint32_t)nbox.y != stamp) nbox.y = 0;
-        }
-      }
       const int gx = 4 * cx + li, gy = 4 * cy + lj, gz = 4 * cz + lk;
-      // branch-free over the 27 neighbours so that all tile loads are in
-      // flight together (a lane outside a tile's box reads slot 0 and adds 0)
-      float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int dd = 0; dd < 27; dd++) {
-        const int bxv = __shfl(nbox.x, dd);
-        const int valid = __shfl(nbox.y, dd);
-        const uint32_t kk = __shfl(nkey, dd);
-        const int sx = cx + dd / 9 - 1, sy = cy + (dd / 3) % 3 - 1, sz = cz + dd % 3 - 1;
-        const int qi = gx - (4 * sx - 2), qj = gy - (4 * sy - 2), qk = gz - (4 * sz - 2);
-        const int lo0 = bxv & 15, lo1 = (bxv >> 4) & 15, lo2 = (bxv >> 8) & 15;
-        const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
-        const bool in = valid && qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2;
-        const int q = in ? (qi * TILE + qj) * TILE + qk : 0;
-        const float4 tv = reinterpret_cast<const float4*>(tiles + (size_t)(in ? kk : 0u) * 4 * TILE_NODES)[q];
-        acc.w += in ? tv.x : 0.f;
-        acc.x += in ? tv.y : 0.f;
-        acc.y += in ? tv.z : 0.f;
-        acc.z += in ? tv.w : 0.f;
-      }
-      // the few valid second slots, one at a time
-      unsigned long long m1 = __ballot(lane >= 32 && nbox.y != 0);
-      while (m1) {
-        const int src = __ffsll((long long)m1) - 1;
-        m1 &= m1 - 1ull;
-        const int dd = src - 32;
-        const int bxv = __shfl(nbox.x, src);
-        const uint32_t kk = __shfl(nkey, src);
-        const int sx = cx + dd / 9 - 1, sy = cy + (dd / 3) % 3 - 1, sz = cz + dd % 3 - 1;
-        const int qi = gx - (4 * sx - 2), qj = gy - (4 * sy - 2), qk = gz - (4 * sz - 2);
-        const int lo0 = bxv & 15, lo1 = (bxv >> 4) & 15, lo2 = (bxv >> 8) & 15;
-        const int hi0 = (bxv >> 12) & 15, hi1 = (bxv >> 16) & 15, hi2 = (bxv >> 20) & 15;
-        if (qi >= lo0 && qi <= hi0 && qj >= lo1 && qj <= hi1 && qk >= lo2 && qk <= hi2) {
-          const float4 tv = reinterpret_cast<const float4*>(tiles + (size_t)kk * 4 * TILE_NODES)[(qi * TILE + qj) * TILE + qk];
-          acc.w += tv.x;
-          acc.x += tv.y;
-          acc.y += tv.z;
-          acc.z += tv.w;
-        }
-      }
+      float4 tsum = make_float4(0.f, 0.f, 0.f, 0.f);   // (m, mv)
+      sum_tiles(g, sc, cx, cy, cz, lane, tile_box, tiles, stamp, tsum);
+      const float4 acc = make_float4(tsum.y, tsum.z, tsum.w, tsum.x);
       float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
       if (acc.w > 0.f && gx < g.n && gy < g.n && gz < g.n) {
         int idx[3] = {gx, gy, gz};
@@ -1165,7 +1150,7 @@ static FastLayout fast_plan(int n_grid, int S, int N) {
   FastLayout L;
   size_t o = 0;
   auto take = [&](size_t b) { size_t r = o; o += a256(b); return r; };
-  for (int b = 0; b < 3; b++) L.list[b] = take((size_t)g.n_keys * NSUB * 16);
+  for (int b = 0; b < 3; b++) L.list[b] = take((size_t)g.n_keys * TILE_SLOTS * 16);
   for (int b = 0; b < 2; b++) {
     L.buf_f[b] = take((size_t)STATE_FLOATS * N * 4);
     L.buf_id[b] = take((size_t)N * 4);
@@ -1185,8 +1170,8 @@ static FastLayout fast_plan(int n_grid, int S, int N) {
   L.cl_count = take(16);
   L.touched = take((size_t)g.n_keys * 4);
   L.n_touched = take(16);
-  L.tile_box = take((size_t)g.n_keys * NSUB * 8);
-  L.tiles = take((size_t)g.n_keys * NSUB * 4 * TILE_NODES * 4);
+  L.tile_box = take((size_t)g.n_keys * NSUB * 16);
+  L.tiles = take((size_t)g.n_keys * TILE_SLOTS * 4 * TILE_NODES * 4);
   L.vgrid = take((size_t)g.n_keys * 64 * 16);
   L.gen = take(16);
   L.t0 = take(16);
@@ -1237,7 +1222,7 @@ int fast_init(FastPath& f, char* ws, int n_grid, int n_scenes, int N, hipStream_
   f.cl_count = (uint32_t*)(ws + L.cl_count);
   f.touched = (uint32_t*)(ws + L.touched);
   f.n_touched = (uint32_t*)(ws + L.n_touched);
-  f.tile_box = (int2*)(ws + L.tile_box);
+  f.tile_box = (int4*)(ws + L.tile_box);
   f.tiles = (float*)(ws + L.tiles);
   f.vgrid = (float4*)(ws + L.vgrid);
   f.gen = (uint32_t*)(ws + L.gen);
@@ -1277,7 +1262,7 @@ int fast_init(FastPath& f, char* ws, int n_grid, int n_scenes, int N, hipStream_
   launch_zero(ws + L.claim, a256((size_t)f.g.n_keys * 4), s);
   launch_zero(ws + L.cl_count, 256, s);
   launch_zero(ws + L.n_touched, 256, s);
-  launch_zero(ws + L.tile_box, a256((size_t)f.g.n_keys * NSUB * 8), s);
+  launch_zero(ws + L.tile_box, a256((size_t)f.g.n_keys * NSUB * 16), s);
   launch_zero(ws + L.vgrid, a256((size_t)f.g.n_keys * 64 * 16), s);
   launch_zero(ws + L.gen, 256, s);
   return hipGetLastError() == hipSuccess ? 0 : -3;
@@ -1292,7 +1277,7 @@ __global__ void k_set_word(int* w, int v) { w[0] = v; }
 static void new_epoch(FastPath& f, hipStream_t s) {
   if ((++f.calls & 0xffff) == 0) {
     launch_zero(f.claim, (size_t)f.g.n_keys * 4, s);
-    launch_zero(f.tile_box, (size_t)f.g.n_keys * NSUB * 8, s);
+    launch_zero(f.tile_box, (size_t)f.g.n_keys * NSUB * 16, s);
   }
   f.sid = 0;
 }
@@ -1470,15 +1455,17 @@ uint32_t fast_next_sid(FastPath& f) { return ++f.sid; }
 // workgroup size of the kernels that read the lists of sorted states (the
 // records' forward kernels and the tiled adjoint's)
 constexpr int SORTED_NT = 256;
+static int sorted_slots(const FastPath& f) { return std::min(f.part_wgs, f.fused_slots); }
 
 void fast_sort_user(FastPath& f, const StepParams& P, const PState& user, SortedState& out, hipStream_t s,
-                    bool touched) {
+                    bool touched, bool share) {
   const int N = f.N;
+  share = share && f.share_chunks > 0;
   new_epoch(f, s);
   k_import_keys<<<nblk(N, 256), 256, 0, s>>>(user, P, f.g, f.cpad, f.key_tmp, f.rank_tmp, f.touched, f.n_touched);
   k_scan<<<1, 1024, 0, s>>>(f.cpad, f.offsets, f.touched, f.n_touched, out.list, out.list_n, f.g.n_keys, f.gen,
                             out.cl_count ? out.cl_count : f.cl_count, touched ? SCAN_TOUCHED : SCAN_DENSE,
-                            IMPORT_PAD, 0, 0, SORTED_NT, 0);
+                            IMPORT_PAD, share ? SORTED_NT : 0, f.share_chunks, SORTED_NT, share ? sorted_slots(f) : 0);
   import_permute(f, user, P.mat, out.b, s);
 }
 
@@ -1544,10 +1531,10 @@ void fast_grid_scan(FastPath& f, const StepParams& P, const SortedState& st, uin
   SA.list = scan_list;
   SA.list_n = scan_list_n;
   SA.n_keys = f.g.n_keys;
-  SA.split_nt = 0;       // the adjoint's records list each block once
-  SA.max_chunks = 0;
+  SA.split_nt = f.share_chunks > 0 ? SORTED_NT : 0;
+  SA.max_chunks = f.share_chunks;
   SA.order_nt = SORTED_NT;
-  SA.fill_slots = 0;
+  SA.fill_slots = f.share_chunks > 0 ? sorted_slots(f) : 0;
   const int do_scan = scan_list ? 1 : 0;
   k_grid<<<f.grid_wgs + do_scan, 256, 0, s>>>(P, f.g, st.cl_list ? st.cl_list : f.cl_list,
                                               st.cl_count ? st.cl_count : f.cl_count, cl_zero, f.tile_box, f.tiles,

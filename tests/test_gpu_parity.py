@@ -523,3 +523,34 @@ def test_gradient_deferred_particles_over_several_chunks_vs_oracle(ckpt):
          "C": rel(g0[6:15].T.double().cpu().numpy().reshape(-1, 3, 3), st0["C"].grad.numpy())}
     say(f"deferred particles, ckpt {ckpt}: " + " ".join(f"{k} {v:.2e}" for k, v in e.items()))
     assert max(e.values()) <= 1e-4
+
+
+@pytest.mark.parametrize("n,grid,dt,wgs,share,grad", [(4001, 16, 2e-4, 2048, 2, True), (12001, 32, 2e-4, 64, 2, True),
+                                                      (12001, 32, 2e-4, 64, 1, False), (4001, 16, 2e-4, 64, 0, False),
+                                                      (20001, 128, 5e-5, 2048, 2, False)])
+def test_shared_blocks_vs_oracle(n, grid, dt, wgs, share, grad):
+    """Blocks shared by one workgroup per chunk (up to 7 chunks, more than a
+    block's most entries), by two (a list longer than the workgroups), by
+    none, and more blocks than one tile of the scan holds; forward, and the
+    adjoint over the shared records.  Tolerances: those of the tests above."""
+    sc = scenes.tiny(n_particles=n, n_grid=grid, steps=4, seed=7, dt=dt,
+                     kinds=(scenes.ELASTIC, scenes.LIQUID, scenes.SAND, scenes.VONMISES, scenes.BOX))
+    sim = sim_of(sc, requires_grad=grad, **({"ckpt_every": 0} if grad else {}))
+    sim.set_option(3, wgs)
+    sim.set_option(7, share)
+    sim.step(sc.horizon)
+    compare_states(sim.state_numpy(), oracle_state(sc, sc.horizon), liquid_mask(sc), tol_x=1e-6, tol=1e-4,
+                   tol_FJ=1e-5, n_grid=sc.n_grid)
+    if not grad:
+        return
+    loss, g = sim.loss_blob(sc.target_mu, sc.target_sigma)
+    ga, g0 = sim.backward(g[0:3], torch.zeros_like(g[0:3]), want_grad0=True)
+    p = O.params_from_scene(sc)
+    st0 = O.state_from_scene(sc, requires_grad=True)
+    acts = torch.tensor(sc.actions, dtype=torch.float64, requires_grad=True)
+    st = O.rollout(sc, state=st0, params=p, actions=acts)
+    O.blob_loss(st["x"], p.kind == O.LIQUID, torch.tensor(sc.target_mu, dtype=torch.float64), sc.target_sigma).backward()
+    ea = rel(ga[:, 0].double().cpu().numpy(), acts.grad.numpy())
+    ex = rel(g0[0:3].T.double().cpu().numpy(), st0["x"].grad.numpy())
+    say(f"  shared blocks, {wgs} workgroups: actions {ea:.2e} dL/dx0 {ex:.2e}")
+    assert ea <= 1e-4 and ex <= 1e-4
