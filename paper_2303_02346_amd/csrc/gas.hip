@@ -641,141 +641,233 @@ __global__ __launch_bounds__(BOTTOM_THREADS) void k_bottom(BottomArgs B) {
 // transforms.  Each axis transform is a dense contraction with an n x n
 // matrix: out[k] = sum_i M[i][k] in[i] along the axis.
 // ---------------------------------------------------------------------------
-// The contraction runs on the matrix cores in FP32 (v_mfma_f32_16x16x4f32):
-// a workgroup of four wavefronts takes XB = 64 lines and XK outputs along the
-// axis, each wavefront 16 lines x XK outputs as XK / 16 tiles of 16 x 16;
-// input chunks of XI values and the matching XI x XK block of the matrix are
-// staged in LDS with every global load of a chunk issued before the first
-// LDS write (float4 loads: every axis length and line count is a multiple
-// of 4).
-constexpr int XB = 64;
+// The basis is even or odd about the middle of the axis (column k has the
+// parity of k), so each transform is two contractions with half as many terms:
+// the even outputs from in[i] + in[n - 1 - i], the odd ones from the
+// differences (and the inverse from even and odd inputs, its outputs i and
+// n - 1 - i the sum and the difference of the two).  They run on the matrix
+// cores in FP32 (v_mfma_f32_16x16x4f32), 16 outputs of one parity x 16 lines a
+// tile.  A wavefront takes 16 C lines and a tile of outputs of both parities at
+// a time; the wavefronts of a workgroup share the lines.  Nothing goes through
+// LDS: the matrix is laid out once in the order in which lanes hold it, and the
+// terms are taken in an order (i = 16 s + 4 lr + t) in which a lane's terms are
+// contiguous in memory along z, and its lines along y and x, so that every load
+// and store moves 8 or 16 bytes a lane.  The last forward pass (x), the
+// division by the eigenvalues and the first inverse pass are one launch, the
+// coefficients in LDS between them.  At 128^3: 8.0 and 12.1 us forward and back along z, 8.0
+// and 7.5 along y, 12.4 for both along x (a pass's floor: 16.8 MB at the rate of a
+// large copy, 3.2 us; at two wavefronts per SIMD the latency of the loads ahead
+// of 64 products is the rest).  Full-length contractions staged through LDS,
+// every line chunk read eight times, took 14 us each.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct AxisArgs {
   const float* in;
   float* out;
-  const float* M;        // n x n, row = input index
+  const float4* M;       // the pass's matrix, in fragments (see gas_create)
+  const float4* M2;      // AXIS_BOTH: the inverse's
   int n;                 // length of the transformed axis
   int A, B;              // layout [A][n][B]; inner transform (B == 1): A lines of n contiguous values
-  // optional division by the 3-D eigenvalue (the last forward pass, along x):
-  // out index k = kx, line index b = ky * nz + kz
+  // division of the outputs by the 3-D eigenvalue (along x; NULL: none); output index k = kx, line index b = ky * nz + kz
   const float* lx;
   const float* ly;
   const float* lz;
   int nz;
 };
 
-template <bool INNER, int XK, int XI>
+enum { AXIS_FWD = 0, AXIS_INV = 1, AXIS_BOTH = 2 };
+
+// 16-term steps and 16-output tiles of one parity of an axis of n values
+__host__ __device__ inline int axis_steps(int n) { return (n / 2 + 15) / 16; }
+
+template <int C> struct AxisVec;
+template <> struct AxisVec<2> { using T = float2; };
+template <int C> __device__ __forceinline__ float axis_get(const typename AxisVec<C>::T& v, int c) {
+  return reinterpret_cast<const float*>(&v)[c];
+}
+
+// Both parities of output tile m: acc[p][c] = 16 outputs x 16 lines (line tile
+// c).  load(i, t, a): the C values of term i = 16 s + 4 lr + t of the even and
+// the odd contraction.
+template <int C, class Load>
+__device__ __forceinline__ void axis_contract(const float4* __restrict__ M, int S, int m, int lane, Load&& load,
+                                              floatx4 (&acc)[2][C]) {
+#pragma unroll
+  for (int p = 0; p < 2; p++)
+#pragma unroll
+    for (int c = 0; c < C; c++) acc[p][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const float4* Me = M + (size_t)m * S * 64 + lane;
+  const float4* Mo = Me + (size_t)S * S * 64;
+#pragma unroll 2
+  for (int s = 0; s < S; s++) {
+    const float4 fe = Me[s * 64], fo = Mo[s * 64];
+    float e[4][C], o[4][C];
+    load(s, e, o);
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+#pragma unroll
+      for (int c = 0; c < C; c++) {
+        acc[0][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fe)[t], e[t][c], acc[0][c], 0, 0, 0);
+        acc[1][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fo)[t], o[t][c], acc[1][c], 0, 0, 0);
+      }
+  }
+}
+
+template <bool INNER, int KIND, int C>
 __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
-  constexpr int XM = XK / 16;
-  // two accumulator sets over alternate i-steps, added at the end: the same
-  // speed as one, and a shorter rounding chain (pressure residual at 128^3
-  // 1.2e-4 against 1.6e-4)
-  constexpr int NACC = 2;
-  static_assert(XI % (4 * NACC) == 0, "chunk split");
-  constexpr int NS = XB * XI / 1024;      // float4 loads of the input chunk per thread
-  constexpr int NMAT = XI * XK / 1024;    // float4 loads of the matrix block per thread
-  static_assert(XK % 16 == 0 && XI % 16 == 0 && NS >= 1 && NMAT >= 1, "tile shape");
-  static_assert(XK * XB <= XI * (XK + 1), "the output tile reuses the matrix chunk's LDS");
-  __shared__ float sS[XI][XB + 1];       // input chunk, [i][line]
-  __shared__ float sM[XI][XK + 1];       // matrix chunk, [i][k]; reused for the output tile [k][line]
-  float* sO = &sM[0][0];                 // output tile: k * XB + line
-  const int tid = threadIdx.x;
-  // wavefront wv: lines 16 wv .. 16 wv + 15; lane (lr, lc)
-  const int wv = tid >> 6, ln = tid & 63, lr = ln >> 4, lc = ln & 15;
-  const int n = X.n;
-  const int a = INNER ? 0 : (int)blockIdx.y;
-  const int line0 = blockIdx.x * XB;        // first line (INNER: row; OUTER: b)
-  const int nlines = INNER ? X.A : X.B;
-  const int k0 = blockIdx.z * XK;
-  floatx4 acc[NACC][XM];
+  using V = typename AxisVec<C>::T;
+  extern __shared__ __align__(16) float s_coef[];   // AXIS_BOTH: [k][16 C lines]
+  constexpr int LINES = 16 * C;
+  const int lane = threadIdx.x & 63, lr = lane >> 4, lc = lane & 15;
+  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int n = X.n, h = n / 2, S = axis_steps(n);
+  const int line0 = blockIdx.x * LINES;
+  if (INNER) {
+    // line tile c of the lane: row line0 + 16 c + lc
+    const float* in[C];
+    bool on[C];
 #pragma unroll
-  for (int u = 0; u < NACC; u++)
-#pragma unroll
-    for (int m = 0; m < XM; m++) acc[u][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int i0 = 0; i0 < n; i0 += XI) {
-    float4 rs[NS], rm[NMAT];
-#pragma unroll
-    for (int r = 0; r < NS; r++) {
-      const int q = tid + 256 * r;
-      int line, ii;
-      if (INNER) { line = line0 + q / (XI / 4); ii = i0 + 4 * (q % (XI / 4)); }
-      else { ii = i0 + q / (XB / 4); line = line0 + 4 * (q % (XB / 4)); }
-      rs[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (line < nlines && ii < n)
-        rs[r] = INNER ? *(const float4*)(X.in + (size_t)line * n + ii)
-                      : *(const float4*)(X.in + ((size_t)a * n + ii) * X.B + line);
+    for (int c = 0; c < C; c++) {
+      const int line = line0 + 16 * c + lc;
+      on[c] = line < X.A;
+      in[c] = X.in + (size_t)(on[c] ? line : 0) * n;
     }
+    for (int m = wv; m < S; m += nw) {
+      floatx4 acc[2][C];
+      axis_contract<C>(X.M, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
+        const int i = 16 * s + 4 * lr;
+        const bool in_h = i < h;   // (past h the matrix is zero; the loads stay in the row)
+        const int ia = in_h ? (KIND == AXIS_FWD ? i : 2 * i) : 0;
 #pragma unroll
-    for (int r = 0; r < NMAT; r++) {
-      const int q = tid + 256 * r;
-      const int ii = i0 + q / (XK / 4), kk = k0 + 4 * (q % (XK / 4));
-      rm[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ii < n && kk < n) rm[r] = *(const float4*)(X.M + (size_t)ii * n + kk);
-    }
-    __syncthreads();    // the previous chunk's reads are done
+        for (int c = 0; c < C; c++) {
+          const float4 a = *(const float4*)(in[c] + ia);
+          if (KIND == AXIS_FWD) {
+            const float4 b = *(const float4*)(in[c] + (n - 4 - ia));
+            e[0][c] = a.x + b.w; o[0][c] = a.x - b.w;
+            e[1][c] = a.y + b.z; o[1][c] = a.y - b.z;
+            e[2][c] = a.z + b.y; o[2][c] = a.z - b.y;
+            e[3][c] = a.w + b.x; o[3][c] = a.w - b.x;
+          } else {
+            // (an axis of n = 4 mod 8 ends between the two loads)
+            const float4 b = *(const float4*)(in[c] + (ia + 4 < n ? ia + 4 : ia));
+            e[0][c] = a.x; o[0][c] = a.y;
+            e[1][c] = a.z; o[1][c] = a.w;
+            e[2][c] = b.x; o[2][c] = b.y;
+            e[3][c] = b.z; o[3][c] = b.w;
+          }
+        }
+      }, acc);
+      const int kk = 16 * m + 4 * lr;   // the lane's outputs kk .. kk + 3 of each parity (h is even: two or four of them)
+      if (kk >= h) continue;
+      const bool four = kk + 2 < h;
 #pragma unroll
-    for (int r = 0; r < NS; r++) {
-      const int q = tid + 256 * r;
-      if (INNER) {
-        const int b = q / (XI / 4), i = 4 * (q % (XI / 4));
-        sS[i][b] = rs[r].x; sS[i + 1][b] = rs[r].y; sS[i + 2][b] = rs[r].z; sS[i + 3][b] = rs[r].w;
-      } else {
-        const int i = q / (XB / 4), b = 4 * (q % (XB / 4));
-        sS[i][b] = rs[r].x; sS[i][b + 1] = rs[r].y; sS[i][b + 2] = rs[r].z; sS[i][b + 3] = rs[r].w;
+      for (int c = 0; c < C; c++) {
+        if (!on[c]) continue;
+        float* o = X.out + (size_t)(line0 + 16 * c + lc) * n;
+        const floatx4 ev = acc[0][c], od = acc[1][c];
+        if (KIND == AXIS_FWD) {
+          *(float4*)(o + 2 * kk) = make_float4(ev[0], od[0], ev[1], od[1]);
+          if (four) *(float4*)(o + 2 * kk + 4) = make_float4(ev[2], od[2], ev[3], od[3]);
+        } else if (four) {
+          *(float4*)(o + kk) = make_float4(ev[0] + od[0], ev[1] + od[1], ev[2] + od[2], ev[3] + od[3]);
+          *(float4*)(o + n - 4 - kk) = make_float4(ev[3] - od[3], ev[2] - od[2], ev[1] - od[1], ev[0] - od[0]);
+        } else {
+          *(float4*)(o + kk) = make_float4(ev[0] + od[0], ev[1] + od[1], ev[1] - od[1], ev[0] - od[0]);
+        }
       }
     }
+    return;
+  }
+  // line tile c of the lane: column line + c of the [n][B] plane
+  const int line = line0 + C * lc;
+  const bool on = line < X.B;
+  const size_t plane = (size_t)blockIdx.y * n * X.B;
+  const float* in = X.in + plane + (on ? line : 0);
+  float* out = X.out + plane + line;
+  const uint32_t B = (uint32_t)X.B;
+  // forward: terms from memory; outputs to memory (FWD) or to LDS (BOTH)
+  if (KIND != AXIS_INV) {
+    for (int m = wv; m < S; m += nw) {
+      floatx4 acc[2][C];
+      axis_contract<C>(X.M, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
 #pragma unroll
-    for (int r = 0; r < NMAT; r++) {
-      const int q = tid + 256 * r;
-      const int i = q / (XK / 4), k = 4 * (q % (XK / 4));
-      sM[i][k] = rm[r].x; sM[i][k + 1] = rm[r].y; sM[i][k + 2] = rm[r].z; sM[i][k + 3] = rm[r].w;
-    }
-    __syncthreads();
-    // D(16 lines x 16 outputs) += A(16 x 4) B(4 x 16): lane (lr, lc) holds
-    // A[lc][lr] = in[line 16 wv + lc][i + lr] and B[lr][lc] = M[i + lr][16 m + lc]
-#pragma unroll 2
-    for (int i = 0; i < XI; i += 4 * NACC) {
+        for (int t = 0; t < 4; t++) {
+          const int i = 16 * s + 4 * lr + t, ia = i < h ? i : 0;   // (past h the matrix is zero)
+          const V a = *(const V*)(in + (uint32_t)ia * B), b = *(const V*)(in + (uint32_t)(n - 1 - ia) * B);
 #pragma unroll
-      for (int u = 0; u < NACC; u++) {
-        const float av = sS[i + 4 * u + lr][16 * wv + lc];
+          for (int c = 0; c < C; c++) {
+            e[t][c] = axis_get<C>(a, c) + axis_get<C>(b, c);
+            o[t][c] = axis_get<C>(a, c) - axis_get<C>(b, c);
+          }
+        }
+      }, acc);
+      float lyz[C];
+      const bool divide = KIND == AXIS_BOTH || X.lx;
+      if (divide) {
+        const int l = on ? line : 0, ky = l / X.nz, kz = l - ky * X.nz;   // (C divides nz: the lines share ky)
 #pragma unroll
-        for (int m = 0; m < XM; m++)
-          acc[u][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, sM[i + 4 * u + lr][16 * m + lc], acc[u][m], 0, 0, 0);
+        for (int c = 0; c < C; c++) lyz[c] = X.ly[ky] + X.lz[kz + c];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int kk = 16 * m + 4 * lr + r;
+        if (kk >= h) continue;
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+          const int k = 2 * kk + p;
+          V v;
+          float* f = reinterpret_cast<float*>(&v);
+          if (!divide) {
+#pragma unroll
+            for (int c = 0; c < C; c++) f[c] = acc[p][c][r];
+          } else {
+            const float lx = X.lx[k];
+#pragma unroll
+            for (int c = 0; c < C; c++) {
+              const float lam = lx + lyz[c];
+              f[c] = lam != 0.f ? acc[p][c][r] / lam : 0.f;
+            }
+          }
+          if (KIND == AXIS_BOTH) *(V*)(s_coef + k * LINES + C * lc) = v;
+          else if (on) *(V*)(out + (uint32_t)k * B) = v;
+        }
       }
     }
   }
+  if (KIND == AXIS_FWD) return;
+  if (KIND == AXIS_BOTH) __syncthreads();
+  const float4* Mi = KIND == AXIS_BOTH ? X.M2 : X.M;
+  for (int m = wv; m < S; m += nw) {
+    floatx4 acc[2][C];
+    axis_contract<C>(Mi, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
 #pragma unroll
-  for (int u = 1; u < NACC; u++)
-#pragma unroll
-    for (int m = 0; m < XM; m++) acc[0][m] += acc[u][m];
-  __syncthreads();
-  // output tile through LDS ([k][line] in sM), then coalesced stores; lane
-  // (lr, lc) holds D[4 lr + r][lc], r < 4
-#pragma unroll
-  for (int m = 0; m < XM; m++)
-#pragma unroll
-    for (int r = 0; r < 4; r++) sO[(16 * m + lc) * XB + 16 * wv + 4 * lr + r] = acc[0][m][r];
-  __syncthreads();
-  if (INNER) {
-    for (int q = tid; q < XB * XK; q += 256) {
-      const int b = q / XK, k = q % XK;
-      const int line = line0 + b, kk = k0 + k;
-      if (line < nlines && kk < n) X.out[(size_t)line * n + kk] = sO[k * XB + b];
-    }
-  } else {
-    for (int q = tid; q < XB * XK; q += 256) {
-      const int k = q / XB, b = q % XB;
-      const int line = line0 + b, kk = k0 + k;
-      if (line < nlines && kk < n) {
-        float v = sO[k * XB + b];
-        if (X.lx) {
-          const int ky = line / X.nz, kz = line - ky * X.nz;
-          const float lam = X.lx[kk] + X.ly[ky] + X.lz[kz];
-          v = lam != 0.f ? v / lam : 0.f;
+      for (int t = 0; t < 4; t++) {
+        const int i = 16 * s + 4 * lr + t, ia = i < h ? i : 0;
+        V a, b;
+        if (KIND == AXIS_BOTH) {
+          a = *(const V*)(s_coef + 2 * ia * LINES + C * lc);
+          b = *(const V*)(s_coef + (2 * ia + 1) * LINES + C * lc);
+        } else {
+          a = *(const V*)(in + (uint32_t)(2 * ia) * B);
+          b = *(const V*)(in + (uint32_t)(2 * ia + 1) * B);
         }
-        X.out[((size_t)a * n + kk) * X.B + line] = v;
+#pragma unroll
+        for (int c = 0; c < C; c++) { e[t][c] = axis_get<C>(a, c); o[t][c] = axis_get<C>(b, c); }
       }
+    }, acc);
+    if (!on) continue;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = 16 * m + 4 * lr + r;
+      if (i >= h) continue;
+      V a, b;
+#pragma unroll
+      for (int c = 0; c < C; c++) {
+        reinterpret_cast<float*>(&a)[c] = acc[0][c][r] + acc[1][c][r];
+        reinterpret_cast<float*>(&b)[c] = acc[0][c][r] - acc[1][c][r];
+      }
+      *(V*)(out + (uint32_t)i * B) = a;
+      *(V*)(out + (uint32_t)(n - 1 - i) * B) = b;
     }
   }
 }
@@ -1175,8 +1267,9 @@ Layout plan(const gas_desc* d) {
     const int nn[3] = {d->nx, d->ny, d->nz};
     L.spec_tmp = take(nc * 4);
     for (int a = 0; a < 3; a++) {
-      L.dct[a] = take((size_t)nn[a] * nn[a] * 4);
-      L.idct[a] = take((size_t)nn[a] * nn[a] * 4);
+      const size_t st = axis_steps(nn[a]);
+      L.dct[a] = take(2 * st * st * 64 * sizeof(float4));
+      L.idct[a] = take(2 * st * st * 64 * sizeof(float4));
       L.lam[a] = take((size_t)nn[a] * 4);
     }
   }
@@ -1317,17 +1410,14 @@ void mg_solve(gas_ctx* c, float* psi0, float* f0) {
   }
 }
 
-// one transform pass; grid.z splits the n outputs into chunks of XK (16 up to
-// n = 128, 64 above: measured fastest at 64^3, 128^3 and 256^3)
-template <bool INNER>
-void launch_axis(const AxisArgs& X, dim3 grid, hipStream_t s) {
-  if (X.n <= 128) {
-    grid.z = (X.n + 15) / 16;
-    k_axis<INNER, 16, 64><<<grid, 256, 0, s>>>(X);
-  } else {
-    grid.z = (X.n + 63) / 64;
-    k_axis<INNER, 64, 64><<<grid, 256, 0, s>>>(X);
-  }
+// one launch of transforms: 32 lines a workgroup (64 lines, with 16-byte loads
+// along y and x, leave one wavefront per SIMD at 128^3: 9.7 to 11.8 us a pass, 17.1
+// along x)
+template <bool INNER, int KIND, int C = 2>
+void launch_axis(const AxisArgs& X, int lines, int planes, hipStream_t s) {
+  const unsigned nt = 64u * (unsigned)min(4, axis_steps(X.n));
+  const size_t lds = KIND == AXIS_BOTH ? (size_t)X.n * 16 * C * 4 : 0;
+  k_axis<INNER, KIND, C><<<dim3((lines + 16 * C - 1) / (16 * C), planes), nt, lds, s>>>(X);
 }
 
 // A psi = f exactly by the axis transforms (psi0 receives the solution with
@@ -1336,36 +1426,39 @@ void spectral_solve(gas_ctx* c, float* psi0, const float* f0) {
   const GP& P = c->P;
   hipStream_t s = c->stream;
   float* T = (float*)(c->ws + c->L.spec_tmp);
-  const float* Mf[3] = {(const float*)(c->ws + c->L.dct[0]), (const float*)(c->ws + c->L.dct[1]),
-                        (const float*)(c->ws + c->L.dct[2])};
-  const float* Mi[3] = {(const float*)(c->ws + c->L.idct[0]), (const float*)(c->ws + c->L.idct[1]),
-                        (const float*)(c->ws + c->L.idct[2])};
-  const float* lam[3] = {(const float*)(c->ws + c->L.lam[0]), (const float*)(c->ws + c->L.lam[1]),
-                         (const float*)(c->ws + c->L.lam[2])};
+  const float4* Mf[3] = {(const float4*)(c->ws + c->L.dct[0]), (const float4*)(c->ws + c->L.dct[1]),
+                         (const float4*)(c->ws + c->L.dct[2])};
+  const float4* Mi[3] = {(const float4*)(c->ws + c->L.idct[0]), (const float4*)(c->ws + c->L.idct[1]),
+                         (const float4*)(c->ws + c->L.idct[2])};
   const int nx = P.nx, ny = P.ny, nz = P.nz;
-  auto pass = [&](int axis, const float* in, float* out, const float* M, bool divide) {
+  auto args = [&](const float* in, float* out, const float4* M, int n, int A, int B) {
     AxisArgs X = {};
-    X.in = in; X.out = out; X.M = M;
-    if (axis == 2) {
-      X.n = nz; X.A = nx * ny; X.B = 1;
-      launch_axis<true>(X, dim3((X.A + XB - 1) / XB, 1, 1), s);
-      return;
-    }
-    X.n = axis == 0 ? nx : ny;
-    X.A = axis == 0 ? 1 : nx;
-    X.B = axis == 0 ? ny * nz : nz;
-    if (divide) { X.lx = lam[0]; X.ly = lam[1]; X.lz = lam[2]; X.nz = nz; }
-    launch_axis<false>(X, dim3((X.B + XB - 1) / XB, X.A, 1), s);
+    X.in = in; X.out = out; X.M = M; X.n = n; X.A = A; X.B = B;
+    return X;
   };
-  // one event pair around the six back-to-back transforms (read as six
-  // launches): a pair per launch would add its own overhead to each
+  // one event pair around the back-to-back transforms (read as six): a pair
+  // per launch would add its own overhead to each
   c->t_smooth.begin(s);
-  pass(2, f0, T, Mf[2], false);
-  pass(1, T, psi0, Mf[1], false);
-  pass(0, psi0, T, Mf[0], true);
-  pass(0, T, psi0, Mi[0], false);
-  pass(1, psi0, T, Mi[1], false);
-  pass(2, T, psi0, Mi[2], false);
+  launch_axis<true, AXIS_FWD>(args(f0, T, Mf[2], nz, nx * ny, 1), nx * ny, 1, s);
+  launch_axis<false, AXIS_FWD>(args(T, psi0, Mf[1], ny, nx, nz), nz, nx, s);
+  // along x in place: every workgroup has read its lines when it writes them
+  // (with more than 512 values an axis does not fit the 64 KB of a workgroup's
+  // coefficients: two launches)
+  const bool both = nx <= 512;
+  AxisArgs X = args(psi0, both ? psi0 : T, Mf[0], nx, 1, ny * nz);
+  X.M2 = Mi[0];
+  X.lx = (const float*)(c->ws + c->L.lam[0]);
+  X.ly = (const float*)(c->ws + c->L.lam[1]);
+  X.lz = (const float*)(c->ws + c->L.lam[2]);
+  X.nz = nz;
+  if (both) {
+    launch_axis<false, AXIS_BOTH>(X, ny * nz, 1, s);
+  } else {
+    launch_axis<false, AXIS_FWD>(X, ny * nz, 1, s);
+    launch_axis<false, AXIS_INV>(args(T, psi0, Mi[0], nx, 1, ny * nz), ny * nz, 1, s);
+  }
+  launch_axis<false, AXIS_INV>(args(psi0, T, Mi[1], ny, nx, nz), nz, nx, s);
+  launch_axis<true, AXIS_INV>(args(T, psi0, Mi[2], nz, nx * ny, 1), nx * ny, 1, s);
   c->t_smooth.end(s);
 }
 
@@ -1496,13 +1589,23 @@ int gas_create(const gas_desc* d, void* workspace_dev, size_t ws_bytes, void* st
     const int nn[3] = {d->nx, d->ny, d->nz};
     for (int a = 0; a < 3; a++) {
       const int n = nn[a];
-      std::vector<float> C((size_t)n * n), Ci((size_t)n * n), lam(n);
-      for (int i = 0; i < n; i++)
-        for (int k = 0; k < n; k++) {
-          const double v = cos(M_PI * k * (i + 0.5) / n);
-          C[(size_t)i * n + k] = (float)v;
-          Ci[(size_t)k * n + i] = (float)(v * (k == 0 ? 1.0 / n : 2.0 / n));
-        }
+      // as fragments [parity][output tile][step][lane (lr, lc)][t]: term
+      // 16 step + 4 lr + t, output 16 tile + lc of the parity (forward: rows i,
+      // outputs k = 2 kk + parity; inverse: rows k, outputs i); zero past n / 2
+      const int h = n / 2, st = axis_steps(n);
+      std::vector<float> C((size_t)2 * st * st * 256, 0.f), Ci(C.size(), 0.f), lam(n);
+      size_t q = 0;
+      for (int par = 0; par < 2; par++)
+        for (int m = 0; m < st; m++)
+          for (int sp = 0; sp < st; sp++)
+            for (int ln = 0; ln < 64; ln++)
+              for (int tt = 0; tt < 4; tt++, q++) {
+                const int term = 16 * sp + 4 * (ln >> 4) + tt, o = 16 * m + (ln & 15);
+                if (term >= h || o >= h) continue;
+                const int kf = 2 * o + par, ki = 2 * term + par;
+                C[q] = (float)cos(M_PI * kf * (term + 0.5) / n);
+                Ci[q] = (float)(cos(M_PI * ki * (o + 0.5) / n) * (ki == 0 ? 1.0 / n : 2.0 / n));
+              }
       for (int k = 0; k < n; k++) {
         const double sk = sin(M_PI * k / (2.0 * n));
         lam[k] = (float)(-4.0 * sk * sk);

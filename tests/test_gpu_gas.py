@@ -255,3 +255,17 @@ def test_initial_states_are_loaded_again():
         assert torch.equal(ps.v, torch.from_numpy(arrs["v"].T.astype(np.float32)).cuda())
         ps.reset()
         assert torch.equal(ps.buf, first)
+
+
+@pytest.mark.parametrize("n", [(8, 12, 20), (20, 36, 8), (12, 68, 44), (516, 8, 12)])
+def test_gas_axis_tiles_vs_oracle(n):
+    """Axis lengths at the edges of the transform's tiles: halves below one
+    16-output tile, of 4 q + 2 outputs, one past a tile, and an x axis whose
+    coefficients do not fit one workgroup (two launches)."""
+    sc = scenes.gas_room(n=n, steps=2, seed=11, n_scalars=1, translate=True)
+    say(f"gas {n}, 2 steps")
+    sim = gas_sim(sc)
+    sim.enable_stats(True)
+    sim.step(2)
+    say(f"  pressure residual {sim.residual():.2e}")
+    compare(sim.state_numpy(), G.rollout_scene(sc, steps=2))
