@@ -4,7 +4,8 @@
 // Forward step, three launches plus the pressure solve:
 //   k_gas_advect   every grid point of u, v, w and the cells: the velocity
 //                  at the point from its stencils, back-trace, trilinear
-//                  sample, emitter blend (one launch for the four grids)
+//                  sample, emitter blend (one launch for the four grids); the
+//                  scalars are final then
 //   k_gas_div      per cell: divergence of the advected velocity with the
 //                  buoyancy of the y-faces added on the fly and the walls
 //                  closed; right-hand side of the pressure equation
@@ -15,13 +16,12 @@
 //                  multigrid V-cycles (mg_solve: red-black half-sweeps on
 //                  the finest level, tiled full sweeps on the coarser grid
 //                  levels, the levels of at most 4096 cells in one workgroup)
-//   k_gas_final    u = u* - grad psi on the interior faces, walls zero,
-//                  scalars copied
-// Adjoint step: the projection of the adjoint (k_gas_adj_div, the same
-// pressure solve, k_gas_adj_sub; the projector is self-adjoint on
+//   k_gas_final    u = u* - grad psi on the interior faces, walls zero
+// Adjoint step: the projection of the adjoint (the same divergence without
+// buoyancy, pressure solve and subtraction; the projector is self-adjoint on
 // wall-closed fields), then k_gas_adj_advect, which recomputes the
 // back-traces, applies the buoyancy and emitter adjoints and scatters the
-// advection adjoint at the back-traced points with float atomics (lanes
+// advection adjoint at the back-traced points with float atomics (samples
 // merge the corners they share first), and k_gas_adj_ugather, which gathers
 // the adjoint of the grid-point velocities over their stencils; the
 // emitter's pose partials are reduced per wavefront into 128 FP64
@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
+#include <type_traits>
 #include <new>
 #include <vector>
 
@@ -115,8 +116,54 @@ struct GP {
   float kappa, speed;
   float src[MAXK];
   size_t nu, nv, nw, nc;
+  uint32_t mz, mz1;     // multipliers of row_of for rows of nz and nz + 1 points
+  int big;              // an array of 4 GB or more: samples need 64-bit offsets
   int* err;             // device error word (MPM_ERR_NONFINITE)
 };
+
+// Point kernels run one workgroup on 256 U consecutive points of one x plane of
+// one grid, so that the grid, the plane and every array's plane are uniform
+// over the workgroup: a point costs one multiplication for its row instead of
+// three divisions by run-time sizes, and the stencil loads are 32-bit offsets
+// from scalar bases.  U points a thread share the uniform part, about 100
+// scalar instructions (U = 1, and the planes' number by division: k_gas_final
+// 21.8 us at 128^3 against 13.1).  The workgroups go plane by plane (u, v, w,
+// cells of a plane in turn), in xcd_block's order.
+struct PointGrid {
+  uint32_t nb[4], per, mper;   // workgroups of a plane of each grid, of all, and its multiplier for division
+  uint32_t blocks;
+};
+__host__ __device__ inline int plane_points(int q, int ny, int nz) { return q == 1 ? (ny + 1) * nz : (q == 2 ? ny * (nz + 1) : ny * nz); }
+inline PointGrid point_grid(const GP& P, int nq, int u) {
+  PointGrid G = {};
+  for (int q = 0; q < nq; q++) {
+    G.nb[q] = ((uint32_t)plane_points(q, P.ny, P.nz) + 256u * u - 1) / (256u * u);
+    G.per += G.nb[q];
+  }
+  G.blocks = G.per * (uint32_t)(P.nx + 1);
+  G.mper = (uint32_t)((0x100000000ull + G.per - 1) / G.per);
+  return G;
+}
+struct PlaneBlock {
+  int q, i, r0, n;   // grid, plane, first point in the plane, points of the plane (n = 0: past the grid's last plane)
+};
+template <int U>
+__device__ __forceinline__ PlaneBlock plane_block(const GP& P, const PointGrid& G) {
+  uint32_t b = xcd_block();
+  PlaneBlock o;
+  o.i = G.per == 1u ? (int)b : (int)__umulhi(b, G.mper);
+  if ((uint32_t)o.i * G.per > b) o.i--;   // (the multiplier rounds up)
+  b -= (uint32_t)o.i * G.per;
+  o.q = 0;
+#pragma unroll
+  for (int q = 0; q < 3; q++)
+    if (o.q == q && b >= G.nb[q]) { b -= G.nb[q]; o.q = q + 1; }
+  o.n = (o.q == 0 || o.i < P.nx) ? plane_points(o.q, P.ny, P.nz) : 0;
+  o.r0 = (int)b * 256 * U;
+  return o;
+}
+// row of point r in rows of d values, m = ceil(2^32 / d) (exact for r d < 2^32)
+__device__ __forceinline__ int row_of(int r, uint32_t m) { return (int)__umulhi((uint32_t)r, m); }
 
 // grid q: 0 = u (x-faces), 1 = v, 2 = w, 3 = cells
 __device__ inline void gdims(const GP& P, int q, int& d0, int& d1, int& d2) {
@@ -133,19 +180,29 @@ struct Lerp {
   bool cl[3];
 };
 
-__device__ inline Lerp lerp_setup(const GP& P, int q, const float* x) {
+// The sample of grid q at the back-traced point x - dt U of its point (i, j, k).
+// (Here and below the roundings are written out.  A sample's fraction has lost
+// the digits of its coordinate, so what the compiler contracts, which differs
+// from kernel to kernel, changed the velocities' distance from a 64-bit run by
+// a factor of two.)
+__device__ __forceinline__ Lerp lerp_setup(const GP& P, int q, int i, int j, int k, const float* U) {
+#pragma clang fp contract(off)
   int d[3];
   gdims(P, q, d[0], d[1], d[2]);
+  const int n[3] = {i, j, k};
   Lerp L;
   int b[3];
 #pragma unroll
   for (int a = 0; a < 3; a++) {
-    float g = x[a] * P.inv_h - gorigin(q, a);
+    const float o = gorigin(q, a), no = (float)n[a] + o;
+    const float xb = fmaf(no, P.h, -(P.dt * U[a]));
+    float g = fmaf(xb, P.inv_h, -o);
     const float hi = (float)(d[a] - 1);
     L.cl[a] = !(g >= 0.f && g <= hi);        // (also NaN)
     g = fminf(fmaxf(g, 0.f), hi);
-    b[a] = min((int)floorf(g), d[a] - 2);
-    L.f[a] = g - (float)b[a];
+    const float fl = fminf(floorf(g), hi - 1.f);
+    b[a] = (int)fl;
+    L.f[a] = g - fl;
   }
   L.i0 = b[0]; L.j0 = b[1]; L.k0 = b[2];
   return L;
@@ -164,22 +221,6 @@ __device__ inline void cell_of(const Dims& D, size_t g, int& i, int& j, int& k) 
   j = (int)(r - (uint32_t)i * (uint32_t)D.y);
 }
 
-// the 8 corner values
-__device__ inline void lerp_load(const float* __restrict__ F, const Lerp& L, int d1, int d2, float* c) {
-  const float* b = F + gidx(L.i0, L.j0, L.k0, d1, d2);
-  const uint32_t sy = (uint32_t)d2, sx = (uint32_t)d1 * (uint32_t)d2;
-#pragma unroll
-  for (int n = 0; n < 8; n++) c[n] = b[((n >> 2) ? sx : 0u) + (((n >> 1) & 1) ? sy : 0u) + (uint32_t)(n & 1)];
-}
-__device__ inline float lerp_weight(const Lerp& L, int n) {
-  return ((n >> 2) ? L.f[0] : 1.f - L.f[0]) * (((n >> 1) & 1) ? L.f[1] : 1.f - L.f[1]) * ((n & 1) ? L.f[2] : 1.f - L.f[2]);
-}
-__device__ inline float lerp_eval(const float* c, const Lerp& L) {
-  float s = 0.f;
-#pragma unroll
-  for (int n = 0; n < 8; n++) s += lerp_weight(L, n) * c[n];
-  return s;
-}
 // d(sample)/d(fraction) per axis
 __device__ inline void lerp_grad(const float* c, const Lerp& L, float* g) {
   const float fx = L.f[0], fy = L.f[1], fz = L.f[2];
@@ -197,72 +238,73 @@ struct VelPtrs {
   const float* w;
 };
 
-__device__ inline float sample(const GP& P, int q, const float* F, const float* x) {
-  int d0, d1, d2;
-  gdims(P, q, d0, d1, d2);
-  const Lerp L = lerp_setup(P, q, x);
-  float c[8];
-  lerp_load(F, L, d1, d2, c);
-  return lerp_eval(c, L);
+// The velocity at a grid point: the trilinear sample of each component grid
+// there reduces to the point's own value on its own grid and to averages of 2
+// or 4 neighbours on the others (sample fractions 0 or 1/2, clamped at the walls
+// like every sample).  Point (j, k) on plane i of grid Q: the planes' bases are
+// uniform, the offsets in a plane 32-bit.
+__device__ __forceinline__ float ld32(const float* __restrict__ p, uint32_t off) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + 4u * off);
 }
-
-// The velocity at a grid point of grid q: the trilinear sample of each
-// component grid there reduces to the point's own value on its own grid and
-// to averages of 2 or 4 neighbours on the others (sample fractions 0 or 1/2,
-// clamped at the walls like every sample).
-__device__ inline void node_velocity(const GP& P, const VelPtrs& vel, int q, int i, int j, int k, float* U) {
+template <int Q>
+__device__ __forceinline__ void plane_velocity(const GP& P, const VelPtrs& vel, int i, int j, int k, float* U) {
   const int ny = P.ny, nz = P.nz;
-  if (q == 3) {
-    U[0] = 0.5f * (vel.u[gidx(i, j, k, ny, nz)] + vel.u[gidx(i + 1, j, k, ny, nz)]);
-    U[1] = 0.5f * (vel.v[gidx(i, j, k, ny + 1, nz)] + vel.v[gidx(i, j + 1, k, ny + 1, nz)]);
-    U[2] = 0.5f * (vel.w[gidx(i, j, k, ny, nz + 1)] + vel.w[gidx(i, j, k + 1, ny, nz + 1)]);
-  } else if (q == 0) {
+  const size_t pu = (size_t)ny * nz, pv = (size_t)(ny + 1) * nz, pw = (size_t)ny * (nz + 1);
+  const uint32_t z = (uint32_t)nz, o = (uint32_t)(j * nz + k), ow = o + (uint32_t)j;   // rows of nz and of nz + 1
+  if (Q == 3) {
+    const float *u0 = vel.u + i * pu, *v0 = vel.v + i * pv, *w0 = vel.w + i * pw;
+    U[0] = 0.5f * (ld32(u0, o) + ld32(u0 + pu, o));
+    U[1] = 0.5f * (ld32(v0, o) + ld32(v0, o + z));
+    U[2] = 0.5f * (ld32(w0, ow) + ld32(w0, ow + 1));
+  } else if (Q == 0) {
     const int ia = max(i - 1, 0), ib = min(i, P.nx - 1);
-    U[0] = vel.u[gidx(i, j, k, ny, nz)];
-    U[1] = 0.25f * ((vel.v[gidx(ia, j, k, ny + 1, nz)] + vel.v[gidx(ib, j, k, ny + 1, nz)]) +
-                    (vel.v[gidx(ia, j + 1, k, ny + 1, nz)] + vel.v[gidx(ib, j + 1, k, ny + 1, nz)]));
-    U[2] = 0.25f * ((vel.w[gidx(ia, j, k, ny, nz + 1)] + vel.w[gidx(ib, j, k, ny, nz + 1)]) +
-                    (vel.w[gidx(ia, j, k + 1, ny, nz + 1)] + vel.w[gidx(ib, j, k + 1, ny, nz + 1)]));
-  } else if (q == 1) {
-    const int ja = max(j - 1, 0), jb = min(j, ny - 1);
-    U[0] = 0.25f * ((vel.u[gidx(i, ja, k, ny, nz)] + vel.u[gidx(i, jb, k, ny, nz)]) +
-                    (vel.u[gidx(i + 1, ja, k, ny, nz)] + vel.u[gidx(i + 1, jb, k, ny, nz)]));
-    U[1] = vel.v[gidx(i, j, k, ny + 1, nz)];
-    U[2] = 0.25f * ((vel.w[gidx(i, ja, k, ny, nz + 1)] + vel.w[gidx(i, jb, k, ny, nz + 1)]) +
-                    (vel.w[gidx(i, ja, k + 1, ny, nz + 1)] + vel.w[gidx(i, jb, k + 1, ny, nz + 1)]));
+    const float *va = vel.v + ia * pv, *vb = vel.v + ib * pv, *wa = vel.w + ia * pw, *wb = vel.w + ib * pw;
+    U[0] = ld32(vel.u + i * pu, o);
+    U[1] = 0.25f * ((ld32(va, o) + ld32(vb, o)) + (ld32(va, o + z) + ld32(vb, o + z)));
+    U[2] = 0.25f * ((ld32(wa, ow) + ld32(wb, ow)) + (ld32(wa, ow + 1) + ld32(wb, ow + 1)));
+  } else if (Q == 1) {
+    const uint32_t ja = (uint32_t)max(j - 1, 0), jb = (uint32_t)min(j, ny - 1), uk = (uint32_t)k;
+    const float *u0 = vel.u + i * pu, *u1 = u0 + pu, *w0 = vel.w + i * pw;
+    const uint32_t oa = ja * z + uk, ob = jb * z + uk, wa = oa + ja, wb = ob + jb;
+    U[0] = 0.25f * ((ld32(u0, oa) + ld32(u0, ob)) + (ld32(u1, oa) + ld32(u1, ob)));
+    U[1] = ld32(vel.v + i * pv, o);
+    U[2] = 0.25f * ((ld32(w0, wa) + ld32(w0, wb)) + (ld32(w0, wa + 1) + ld32(w0, wb + 1)));
   } else {
-    const int ka = max(k - 1, 0), kb = min(k, nz - 1);
-    U[0] = 0.25f * ((vel.u[gidx(i, j, ka, ny, nz)] + vel.u[gidx(i, j, kb, ny, nz)]) +
-                    (vel.u[gidx(i + 1, j, ka, ny, nz)] + vel.u[gidx(i + 1, j, kb, ny, nz)]));
-    U[1] = 0.25f * ((vel.v[gidx(i, j, ka, ny + 1, nz)] + vel.v[gidx(i, j, kb, ny + 1, nz)]) +
-                    (vel.v[gidx(i, j + 1, ka, ny + 1, nz)] + vel.v[gidx(i, j + 1, kb, ny + 1, nz)]));
-    U[2] = vel.w[gidx(i, j, k, ny, nz + 1)];
+    const uint32_t oa = (uint32_t)(j * nz + max(k - 1, 0)), ob = (uint32_t)(j * nz + min(k, nz - 1));
+    const float *u0 = vel.u + i * pu, *u1 = u0 + pu, *v0 = vel.v + i * pv;
+    U[0] = 0.25f * ((ld32(u0, oa) + ld32(u0, ob)) + (ld32(u1, oa) + ld32(u1, ob)));
+    U[1] = 0.25f * ((ld32(v0, oa) + ld32(v0, ob)) + (ld32(v0, oa + z) + ld32(v0, ob + z)));
+    U[2] = ld32(vel.w + i * pw, ow);
   }
 }
 
-// grid point of flat index g of grid q, and its position
-__device__ inline void point_of(const GP& P, int q, size_t g, int& i, int& j, int& k, float* x) {
-  int d0, d1, d2;
-  gdims(P, q, d0, d1, d2);
-  // (every grid has fewer than 2^32 points: 32-bit divisions)
-  const uint32_t g32 = (uint32_t)g, r = g32 / (uint32_t)d2;
-  k = (int)(g32 - r * (uint32_t)d2);
-  i = (int)(r / (uint32_t)d1);
-  j = (int)(r - (uint32_t)i * (uint32_t)d1);
-  x[0] = ((float)i + gorigin(q, 0)) * P.h;
-  x[1] = ((float)j + gorigin(q, 1)) * P.h;
-  x[2] = ((float)k + gorigin(q, 2)) * P.h;
+// the eight corner values as four z pairs (two adjacent values, 4-byte aligned)
+struct __attribute__((packed, aligned(4))) ZPair {
+  float a, b;
+};
+__device__ __forceinline__ void lerp_pairs(int big, const float* __restrict__ F, const Lerp& L, uint32_t d1, uint32_t d2,
+                                           ZPair* c) {
+  const uint32_t b = ((uint32_t)L.i0 * d1 + (uint32_t)L.j0) * d2 + (uint32_t)L.k0, sx = d1 * d2;
+  const float* row[4] = {F, F + d2, F + sx, F + (size_t)sx + d2};
+  if (big) {
+#pragma unroll
+    for (int n = 0; n < 4; n++) c[n] = *reinterpret_cast<const ZPair*>(row[n] + b);
+  } else {
+#pragma unroll
+    for (int n = 0; n < 4; n++) c[n] = *reinterpret_cast<const ZPair*>(reinterpret_cast<const char*>(row[n]) + 4u * b);
+  }
 }
-
-// which grid a flat index of the concatenated point sets belongs to
-__device__ inline int split_points(const GP& P, size_t& g) {
-  if (g < P.nu) return 0;
-  g -= P.nu;
-  if (g < P.nv) return 1;
-  g -= P.nv;
-  if (g < P.nw) return 2;
-  g -= P.nw;
-  return 3;
+__device__ __forceinline__ float lerp_pairs_eval(const ZPair* c, const Lerp& L) {
+#pragma clang fp contract(off)
+  const float fx[2] = {1.f - L.f[0], L.f[0]}, fy[2] = {1.f - L.f[1], L.f[1]}, fz[2] = {1.f - L.f[2], L.f[2]};
+  float s = 0.f;
+#pragma unroll
+  for (int n = 0; n < 4; n++) {
+    const float w = fx[n >> 1] * fy[n & 1];
+    s = fmaf(w * fz[0], c[n].a, s);
+    s = fmaf(w * fz[1], c[n].b, s);
+  }
+  return s;
 }
 
 struct Pose {
@@ -274,108 +316,159 @@ __device__ inline Pose load_pose(const double* p) {
   for (int k = 0; k < 3; k++) { o.c[k] = (float)p[k]; o.a[k] = (float)p[3 + k * 3 + 1]; }
   return o;
 }
-__device__ inline float emitter_chi(const GP& P, const Pose& E, const float* x) {
-  const float d0 = x[0] - E.c[0], d1 = x[1] - E.c[1], d2 = x[2] - E.c[2];
-  return P.kappa * expf(-(d0 * d0 + d1 * d1 + d2 * d2) * P.s2inv);
+// offset d of point (i, j, k) of grid Q from the emitter, and its blend
+template <int Q>
+__device__ __forceinline__ float emitter_chi(const GP& P, const Pose& E, int i, int j, int k, float* d) {
+#pragma clang fp contract(off)
+  const int n[3] = {i, j, k};
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const float no = (float)n[a] + gorigin(Q, a);
+    d[a] = fmaf(no, P.h, -E.c[a]);
+  }
+  const float r2 = fmaf(d[2], d[2], fmaf(d[0], d[0], d[1] * d[1]));
+  return P.kappa * expf(-r2 * P.s2inv);
 }
 
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
+// One point of grid Q in plane i.  The scalars go straight to the step's output.
+template <int Q>
+__device__ __forceinline__ void advect_point(const GP& P, const VelPtrs& vel, const float* __restrict__ s,
+                                             float* __restrict__ o, const Pose& E, int i, int r) {
+  constexpr bool Z1 = Q == 2;
+  const uint32_t d1 = (uint32_t)(P.ny + (Q == 1)), d2 = (uint32_t)(P.nz + (Q == 2));
+  const int j = row_of(r, Z1 ? P.mz1 : P.mz), k = r - j * (int)d2;
+  float d[3], U[3];
+  plane_velocity<Q>(P, vel, i, j, k, U);
+  const Lerp L = lerp_setup(P, Q, i, j, k, U);
+  const size_t g = (size_t)i * d1 * d2;   // (uniform)
+  if (Q < 3) {
+    ZPair c[4];
+    lerp_pairs(P.big, Q == 0 ? vel.u : (Q == 1 ? vel.v : vel.w), L, d1, d2, c);
+    const float chi = emitter_chi<Q>(P, E, i, j, k, d);
+    const float val = lerp_pairs_eval(c, L);
+    (o + g)[(uint32_t)r] = fmaf(chi, fmaf(P.speed, E.a[Q < 3 ? Q : 0], -val), val);
+  } else {
+    ZPair c[MAXK][4];
+#pragma unroll
+    for (int kk = 0; kk < MAXK; kk++)
+      if (kk < P.K) lerp_pairs(P.big, s + kk * P.nc, L, d1, d2, c[kk]);
+    const float chi = emitter_chi<Q>(P, E, i, j, k, d);
+    bool fin = true;
+#pragma unroll
+    for (int kk = 0; kk < MAXK; kk++) {
+      if (kk >= P.K) break;
+      const float vs = lerp_pairs_eval(c[kk], L), val = fmaf(chi, P.src[kk] - vs, vs);
+      fin = fin && isfinite(val);
+      (o + kk * P.nc + g)[(uint32_t)r] = val;
+    }
+    if (!fin) atomicOr(P.err, ERR_NONFINITE);
+  }
+}
+
+constexpr int ADV_U = 4, DIV_U = 1, FIN_U = 4;
+// (bound by VALU issue: the plane-wise points and the loads of whole z pairs
+// took it from 70.4 to 42 us at 128^3 with two scalars; the
+// arrays it has to read and write take 16)
 __global__ __launch_bounds__(256) void k_gas_advect(GP P, VelPtrs vel, const float* __restrict__ s,
                                                     float* __restrict__ u1, float* __restrict__ v1,
                                                     float* __restrict__ w1, float* __restrict__ s1,
-                                                    const double* __restrict__ pose) {
-  const size_t total = P.nu + P.nv + P.nw + P.nc;
+                                                    const double* __restrict__ pose, PointGrid G) {
+  const PlaneBlock b = plane_block<ADV_U>(P, G);
   const Pose E = load_pose(pose);
-  for (size_t g0 = xcd_block() * (size_t)blockDim.x + threadIdx.x; g0 < total; g0 += (size_t)gridDim.x * blockDim.x) {
-    size_t g = g0;
-    const int q = split_points(P, g);
-    int i, j, k;
-    float x[3];
-    point_of(P, q, g, i, j, k, x);
-    float U[3];
-    node_velocity(P, vel, q, i, j, k, U);
-    const float xb[3] = {x[0] - P.dt * U[0], x[1] - P.dt * U[1], x[2] - P.dt * U[2]};
-    const float chi = emitter_chi(P, E, x);
-    if (q < 3) {
-      const float* F = q == 0 ? vel.u : (q == 1 ? vel.v : vel.w);
-      float val = sample(P, q, F, xb);
-      val += chi * (P.speed * E.a[q] - val);
-      float* O = q == 0 ? u1 : (q == 1 ? v1 : w1);
-      O[g] = val;
-    } else {
-      const Lerp L = lerp_setup(P, 3, xb);
-#pragma unroll
-      for (int kk = 0; kk < MAXK; kk++) {
-        if (kk >= P.K) break;
-        float c[8];
-        lerp_load(s + kk * P.nc, L, P.ny, P.nz, c);
-        float val = lerp_eval(c, L);
-        val += chi * (P.src[kk] - val);
-        s1[kk * P.nc + g] = val;
-      }
-    }
-  }
+  auto points = [&](auto q, float* o) {
+#pragma unroll 1
+    for (int r = b.r0 + (int)threadIdx.x, u = 0; u < ADV_U && r < b.n; u++, r += 256)
+      advect_point<decltype(q)::value>(P, vel, s, o, E, b.i, r);
+  };
+  if (b.q == 0) points(std::integral_constant<int, 0>{}, u1);
+  else if (b.q == 1) points(std::integral_constant<int, 1>{}, v1);
+  else if (b.q == 2) points(std::integral_constant<int, 2>{}, w1);
+  else points(std::integral_constant<int, 3>{}, s1);
 }
 
-// y-face value after buoyancy (interior faces j in [1, ny - 1])
-__device__ inline float buoyant_v(const GP& P, const float* v1, const float* T1, int i, int j, int k) {
-  const float Tf = 0.5f * (T1[gidx(i, j - 1, k, P.ny, P.nz)] + T1[gidx(i, j, k, P.ny, P.nz)]);
-  return v1[gidx(i, j, k, P.ny + 1, P.nz)] + P.dt * P.beta * (Tf - P.t_amb);
-}
-
-// divergence (sum of face differences, walls closed) of (u1, buoyant v1, w1)
+// divergence (sum of face differences, walls closed) of (u1, v1, w1), with BUOY
+// the buoyancy of the temperature T1 added to the y-faces (the adjoint's
+// velocity takes none); psi (the multigrid's first guess) is cleared where it
+// is given
+template <bool BUOY>
 __global__ __launch_bounds__(256) void k_gas_div(GP P, const float* __restrict__ u1, const float* __restrict__ v1,
                                                  const float* __restrict__ w1, const float* __restrict__ T1,
-                                                 float* __restrict__ f, float* __restrict__ psi) {
-  for (size_t g = blockIdx.x * (size_t)blockDim.x + threadIdx.x; g < P.nc; g += (size_t)gridDim.x * blockDim.x) {
-    int i, j, k;
-    cell_of(Dims{P.nx, P.ny, P.nz}, g, i, j, k);
-    const float ur = (i + 1 < P.nx) ? u1[gidx(i + 1, j, k, P.ny, P.nz)] : 0.f;
-    const float ul = (i > 0) ? u1[gidx(i, j, k, P.ny, P.nz)] : 0.f;
-    const float vt = (j + 1 < P.ny) ? buoyant_v(P, v1, T1, i, j + 1, k) : 0.f;
-    const float vb = (j > 0) ? buoyant_v(P, v1, T1, i, j, k) : 0.f;
-    const float wf = (k + 1 < P.nz) ? w1[gidx(i, j, k + 1, P.ny, P.nz + 1)] : 0.f;
-    const float wb = (k > 0) ? w1[gidx(i, j, k, P.ny, P.nz + 1)] : 0.f;
-    f[g] = (ur - ul) + (vt - vb) + (wf - wb);
-    psi[g] = 0.f;
+                                                 float* __restrict__ f, float* __restrict__ psi, PointGrid G) {
+  const PlaneBlock b = plane_block<DIV_U>(P, G);
+  if (b.i >= P.nx) return;
+  const int i = b.i;
+  const uint32_t z = (uint32_t)P.nz;
+  const size_t pu = (size_t)P.ny * P.nz, pv = pu + P.nz, pw = pu + P.ny;
+  const float *u0 = u1 + i * pu, *v0 = v1 + i * pv, *w0 = w1 + i * pw, *T0 = BUOY ? T1 + i * pu : nullptr;
+  const float bd = P.dt * P.beta;
+#pragma unroll
+  for (int u = 0; u < DIV_U; u++) {
+  const int r = b.r0 + 256 * u + (int)threadIdx.x;
+  if (r >= b.n) break;
+  const int j = row_of(r, P.mz), k = r - j * P.nz;
+  const uint32_t o = (uint32_t)r, ow = o + (uint32_t)j;
+  const float ur = (i + 1 < P.nx) ? ld32(u0 + pu, o) : 0.f;
+  const float ul = (i > 0) ? ld32(u0, o) : 0.f;
+  const float tc = BUOY ? ld32(T0, o) : 0.f;
+  float vt = (j + 1 < P.ny) ? ld32(v0, o + z) : 0.f, vb = (j > 0) ? ld32(v0, o) : 0.f;
+  if (BUOY) {
+    if (j + 1 < P.ny) vt += bd * (0.5f * (tc + ld32(T0, o + z)) - P.t_amb);
+    if (j > 0) vb += bd * (0.5f * (ld32(T0, o - z) + tc) - P.t_amb);
+  }
+  const float wf = (k + 1 < P.nz) ? ld32(w0, ow + 1) : 0.f;
+  const float wb = (k > 0) ? ld32(w0, ow) : 0.f;
+  (f + i * pu)[o] = (ur - ul) + (vt - vb) + (wf - wb);
+  if (psi) (psi + i * pu)[o] = 0.f;
   }
 }
 
-// u = u* - grad psi on the interior faces (v with its buoyancy), walls zero,
-// scalars copied
+// u = u* - grad psi on the interior faces (with BUOY, v with its buoyancy), walls zero
+template <bool BUOY>
 __global__ __launch_bounds__(256) void k_gas_final(GP P, const float* __restrict__ u1, const float* __restrict__ v1,
                                                    const float* __restrict__ w1, const float* __restrict__ s1,
                                                    const float* __restrict__ psi, float* __restrict__ u,
-                                                   float* __restrict__ v, float* __restrict__ w, float* __restrict__ s) {
-  const size_t total = P.nu + P.nv + P.nw + (size_t)P.K * P.nc;
-  for (size_t g0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x; g0 < total; g0 += (size_t)gridDim.x * blockDim.x) {
-    size_t g = g0;
-    const int q = split_points(P, g);
-    if (q == 3) {
-      s[g] = s1[g];
-      if (!isfinite(s1[g])) atomicOr(P.err, ERR_NONFINITE);
-      continue;
+                                                   float* __restrict__ v, float* __restrict__ w, PointGrid G) {
+  const PlaneBlock b = plane_block<FIN_U>(P, G);
+  const int i = b.i;
+  const uint32_t z = (uint32_t)P.nz;
+  const size_t pc = (size_t)P.ny * P.nz, pv = pc + P.nz, pw = pc + P.ny;
+  bool fin = true;
+  auto points = [&](float* O, auto&& value) {
+#pragma unroll
+    for (int t = 0; t < FIN_U; t++) {
+      const int r = b.r0 + 256 * t + (int)threadIdx.x;
+      if (r >= b.n) break;
+      const float val = value(r, (uint32_t)r);
+      fin = fin && isfinite(val);
+      O[(uint32_t)r] = val;
     }
-    int i, j, k;
-    float x[3];
-    point_of(P, q, g, i, j, k, x);
-    const int c = q == 0 ? i : (q == 1 ? j : k);
-    const int n = q == 0 ? P.nx : (q == 1 ? P.ny : P.nz);
-    float val = 0.f;
-    if (c > 0 && c < n) {
-      const size_t hi = gidx(i, j, k, P.ny, P.nz);
-      const size_t lo = gidx(i - (q == 0), j - (q == 1), k - (q == 2), P.ny, P.nz);
-      const float gp = psi[hi] - psi[lo];
-      if (q == 0) val = u1[g] - gp;
-      else if (q == 1) val = buoyant_v(P, v1, s1, i, j, k) - gp;
-      else val = w1[g] - gp;
-    }
-    if (!isfinite(val)) atomicOr(P.err, ERR_NONFINITE);
-    float* O = q == 0 ? u : (q == 1 ? v : w);
-    O[g] = val;
+  };
+  if (b.q == 0) {
+    const bool in = i > 0 && i < P.nx;
+    const float *p0 = psi + (in ? i : 1) * pc, *u0 = u1 + i * pc;
+    points(u + i * pc, [&](int, uint32_t o) { return in ? ld32(u0, o) - (ld32(p0, o) - ld32(p0 - pc, o)) : 0.f; });
+  } else if (b.q == 1) {
+    const float *p0 = psi + i * pc, *T0 = BUOY ? s1 + i * pc : nullptr, *v0 = v1 + i * pv;
+    points(v + i * pv, [&](int r, uint32_t o) {
+      const int j = row_of(r, P.mz);
+      if (!(j > 0 && j < P.ny)) return 0.f;
+      float val = ld32(v0, o);
+      if (BUOY) val += P.dt * P.beta * (0.5f * (ld32(T0, o - z) + ld32(T0, o)) - P.t_amb);
+      return val - (ld32(p0, o) - ld32(p0, o - z));
+    });
+  } else {
+    const float *p0 = psi + i * pc, *w0 = w1 + i * pw;
+    points(w + i * pw, [&](int r, uint32_t o) {
+      const int j = row_of(r, P.mz1), k = r - j * (P.nz + 1);
+      if (!(k > 0 && k < P.nz)) return 0.f;
+      const uint32_t c = o - (uint32_t)j;
+      return ld32(w0, o) - (ld32(p0, c) - ld32(p0, c - 1));
+    });
   }
+  if (!fin) atomicOr(P.err, ERR_NONFINITE);
 }
 
 // ---------------------------------------------------------------------------
@@ -904,52 +997,6 @@ __global__ void k_resnorm_final(const double* __restrict__ part, int nb, double*
 // ---------------------------------------------------------------------------
 // adjoint
 // ---------------------------------------------------------------------------
-// divergence of the wall-closed adjoint velocity (right-hand side of the
-// adjoint projection)
-__global__ __launch_bounds__(256) void k_gas_adj_div(GP P, const float* __restrict__ ub, const float* __restrict__ vb,
-                                                     const float* __restrict__ wb, float* __restrict__ f,
-                                                     float* __restrict__ psi) {
-  for (size_t g = blockIdx.x * (size_t)blockDim.x + threadIdx.x; g < P.nc; g += (size_t)gridDim.x * blockDim.x) {
-    int i, j, k;
-    cell_of(Dims{P.nx, P.ny, P.nz}, g, i, j, k);
-    const float ur = (i + 1 < P.nx) ? ub[gidx(i + 1, j, k, P.ny, P.nz)] : 0.f;
-    const float ul = (i > 0) ? ub[gidx(i, j, k, P.ny, P.nz)] : 0.f;
-    const float vt = (j + 1 < P.ny) ? vb[gidx(i, j + 1, k, P.ny + 1, P.nz)] : 0.f;
-    const float vl = (j > 0) ? vb[gidx(i, j, k, P.ny + 1, P.nz)] : 0.f;
-    const float wf = (k + 1 < P.nz) ? wb[gidx(i, j, k + 1, P.ny, P.nz + 1)] : 0.f;
-    const float wl = (k > 0) ? wb[gidx(i, j, k, P.ny, P.nz + 1)] : 0.f;
-    f[g] = (ur - ul) + (vt - vl) + (wf - wl);
-    psi[g] = 0.f;
-  }
-}
-
-// projected adjoint velocity: interior faces minus grad psi, walls zero
-__global__ __launch_bounds__(256) void k_gas_adj_sub(GP P, const float* __restrict__ ub, const float* __restrict__ vb,
-                                                     const float* __restrict__ wb, const float* __restrict__ psi,
-                                                     float* __restrict__ ub1, float* __restrict__ vb1,
-                                                     float* __restrict__ wb1) {
-  const size_t total = P.nu + P.nv + P.nw;
-  for (size_t g0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x; g0 < total; g0 += (size_t)gridDim.x * blockDim.x) {
-    size_t g = g0;
-    const int q = split_points(P, g);
-    int i, j, k;
-    float x[3];
-    point_of(P, q, g, i, j, k, x);
-    const int c = q == 0 ? i : (q == 1 ? j : k);
-    const int n = q == 0 ? P.nx : (q == 1 ? P.ny : P.nz);
-    const float* In = q == 0 ? ub : (q == 1 ? vb : wb);
-    float* O = q == 0 ? ub1 : (q == 1 ? vb1 : wb1);
-    float val = 0.f;
-    if (c > 0 && c < n) {
-      const size_t hi = gidx(i, j, k, P.ny, P.nz);
-      const size_t lo = gidx(i - (q == 0), j - (q == 1), k - (q == 2), P.ny, P.nz);
-      val = In[g] - (psi[hi] - psi[lo]);
-    }
-    if (!isfinite(val)) atomicOr(P.err, ERR_NONFINITE);
-    O[g] = val;
-  }
-}
-
 struct AdjOut {
   float* u;
   float* v;
@@ -957,152 +1004,231 @@ struct AdjOut {
   float* s;
 };
 
-// Scatter of val times the trilinear weights of L into F, called by every
-// lane of a wavefront together (on = false: no contribution).  Consecutive
-// lanes hold consecutive points along z, whose back-traced samples usually
-// share four of their eight corners: when the previous lane samples the same
-// array at the same (i0, j0) with k0 one less, its k0 + 1 corners are this
-// lane's k0 corners, so this lane adds them in and issues one atomic for
-// both (about 4 atomics per sample instead of 8).
-__device__ inline void scatter_lerp_wave(float* F, const Lerp& L, int d1, int d2, float val, bool on) {
-  float lo[4], hi[4];
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-    lo[c] = on ? lerp_weight(L, 2 * c) * val : 0.f;
-    hi[c] = on ? lerp_weight(L, 2 * c + 1) * val : 0.f;
-  }
-  const int lane = (int)__lane_id();
-  const unsigned long long fp = (unsigned long long)F;
-  const unsigned long long fprev = __shfl_up(fp, 1);
-  const int i0p = __shfl_up(L.i0, 1), j0p = __shfl_up(L.j0, 1), k0p = __shfl_up(L.k0, 1);
-  const int onp = __shfl_up(on ? 1 : 0, 1);
-  const bool take = on && lane > 0 && onp && fprev == fp && i0p == L.i0 && j0p == L.j0 && k0p + 1 == L.k0;
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-    const float h = __shfl_up(hi[c], 1);
-    if (take) lo[c] += h;
-  }
-  const int took = __shfl_down(take ? 1 : 0, 1);
-  const bool given = lane < 63 && took;     // the next lane issues this lane's k0 + 1 corners
-  if (!on) return;
-  float* base = F + gidx(L.i0, L.j0, L.k0, d1, d2);
-  const uint32_t sy = (uint32_t)d2, sx = (uint32_t)d1 * (uint32_t)d2;
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-    const uint32_t off = ((c >> 1) ? sx : 0u) + ((c & 1) ? sy : 0u);
-    if (lo[c] != 0.f) atomicAdd(base + off, lo[c]);
-    if (!given && hi[c] != 0.f) atomicAdd(base + off + 1, hi[c]);
-  }
-}
-
 // Adjoint of advection + emitter + buoyancy for every grid point of state s_t.
 // ub1/vb1/wb1: adjoint of the blended velocities (already projected, walls
 // zero); sb: adjoint of the output scalars; out: adjoint of s_t (cleared
-// before; accumulated with atomics); slots: pose partials.  The loop runs
-// wavefront-uniformly (the scatter exchanges corners between lanes).
-__global__ __launch_bounds__(256) void k_gas_adj_advect(GP P, VelPtrs vel, const float* __restrict__ s,
-                                                        const float* __restrict__ ub1, const float* __restrict__ vb1,
-                                                        const float* __restrict__ wb1, const float* __restrict__ sb,
-                                                        AdjOut out, const double* __restrict__ pose,
-                                                        double* __restrict__ slots, float* __restrict__ ub) {
-  const size_t total = P.nu + P.nv + P.nw + P.nc;
-  const Pose E = load_pose(pose);
-  double part[POSE_PARTIALS] = {0, 0, 0, 0, 0, 0};
-  for (size_t base = blockIdx.x * (size_t)blockDim.x; base < total; base += (size_t)gridDim.x * blockDim.x) {
-    const size_t g0 = base + threadIdx.x;
-    const bool live = g0 < total;
-    int q = 3;
+// before; accumulated with atomics); slots: pose partials.
+//
+// The atomics of the scatter at the back-traced points were 215 of its 392 us at
+// 128^3 (two scalars; four to eight a sample), and what they cost goes with the
+// cache lines they touch, so samples that share corners are merged first.
+// Neighbouring points' samples usually lie in neighbouring cells: a wavefront
+// holds 64 columns consecutive along z, whose lanes hand their k0 + 1 corners to
+// the next lane; a thread walks ADJ_J points along y and carries its j0 + 1
+// corners to the next one; and the workgroup's ADJ_I wavefronts hold consecutive
+// planes, each handing its i0 + 1 corners to the next through LDS.  The corners
+// at k0 + 1 that no lane took (mostly the last lane's) are carried and handed on
+// in the same way.  Each merge is taken only where the cells do adjoin (the
+// cell's packed index says so).  194 us, 65 of them still the atomics; 261 with
+// the last lane's corners issued as they come, 205 and 210 with 4 x 4 and 4 x 8
+// planes x points, 222 and 244 with 2 x 4 and 8 x 2.  (Columns, not points, are
+// dealt to the lanes, so that rows of any length fill the wavefronts.)
+constexpr int ADJ_J = 8, ADJ_I = 8;   // points a thread, planes (wavefronts) a workgroup
+
+__device__ __forceinline__ int lane_prev(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xF, 0xF, false); }   // wave_shr:1
+__device__ __forceinline__ int lane_next(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xF, 0xF, false); }   // wave_shl:1
+__device__ __forceinline__ float lane_prev(float x) { return __int_as_float(lane_prev(__float_as_int(x))); }
+
+// blocks of 64 columns (j group, k) of each grid, and groups of ADJ_I planes
+inline PointGrid column_grid(const GP& P) {
+  PointGrid G = {};
+  for (int q = 0; q < 4; q++) {
+    const uint32_t groups = (uint32_t)(P.ny + (q == 1) + ADJ_J - 1) / ADJ_J;
+    G.nb[q] = (groups * (uint32_t)(P.nz + (q == 2)) + 63u) / 64u;
+    G.per += G.nb[q];
+  }
+  G.blocks = G.per * (uint32_t)((P.nx + ADJ_I) / ADJ_I);
+  G.mper = (uint32_t)((0x100000000ull + G.per - 1) / G.per);
+  return G;
+}
+
+constexpr uint32_t CELL_I = 1u << 22, CELL_J = 1u << 11, NO_CELL = 0xffffffffu;   // packed cell: i0, j0, k0
+
+struct AdjLds {
+  uint32_t cell[2][ADJ_I][64];
+  float e[2][ADJ_I][MAXK][64], h[2][ADJ_I][MAXK][64];   // the rows at k0 and (where the next lane did not take it) k0 + 1
+};
+
+template <int Q>
+__device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, const float* __restrict__ s,
+                                            const float* __restrict__ ab_in, const float* __restrict__ vb1,
+                                            float* __restrict__ tgt, const Pose& E, float* __restrict__ ub, size_t total,
+                                            int i, int col0, AdjLds& S, double* part) {
+  constexpr int NV = Q < 3 ? 1 : MAXK;
+  const int K = Q < 3 ? 1 : P.K;
+  const int lane = (int)__lane_id(), wv = (int)(threadIdx.x >> 6);
+  const int d0 = P.nx + (Q == 0), d1 = P.ny + (Q == 1), d2 = P.nz + (Q == 2);
+  const int groups = (d1 + ADJ_J - 1) / ADJ_J;
+  const int col = col0 + lane, jg = row_of(col, Q == 2 ? P.mz1 : P.mz), k = col - jg * d2;
+  const bool lane_on = i < d0 && jg < groups;
+  const size_t sx = (size_t)d1 * d2;
+  const size_t plane = (size_t)i * sx;   // (uniform)
+  auto flush = [&](uint32_t c, int off1, int kk, float v) {   // v into corner off1 (x) of cell c, if any
+    if (v == 0.f) return;
+    const uint32_t at = ((c >> 22) * (uint32_t)d1 + ((c >> 11) & 2047u)) * (uint32_t)d2 + (c & 2047u);
+    atomicAdd(tgt + (Q < 3 ? 0 : kk * P.nc) + (off1 ? sx : 0) + at, v);
+  };
+  uint32_t pcell = NO_CELL;   // carried row: the cell whose (i0, j0, k0) and (i0 + 1, j0, k0) corners it holds
+  float pend[NV][2] = {}, hpend[NV][2] = {};
+#pragma unroll 1
+  for (int t = 0; t <= ADJ_J; t++) {
+    const int j = jg * ADJ_J + t;
+    const bool on = lane_on && t < ADJ_J && j < d1;
+    uint32_t cell = NO_CELL;
     Lerp L = {};
-    int d1 = P.ny, d2 = P.nz;
-    float* tgt = out.s;
-    bool on = false;                   // this lane scatters (face lanes: once; cell lanes: per scalar)
-    bool s_on[MAXK] = {false, false, false, false};
-    float sval[MAXK] = {0.f, 0.f, 0.f, 0.f};
-    float xbb[3] = {0.f, 0.f, 0.f};   // adjoint of the back-traced point
-    if (live) {
-      size_t g = g0;
-      q = split_points(P, g);
-      int i, j, k;
-      float x[3];
-      point_of(P, q, g, i, j, k, x);
-      float U[3];
-      node_velocity(P, vel, q, i, j, k, U);
-      const float xb[3] = {x[0] - P.dt * U[0], x[1] - P.dt * U[1], x[2] - P.dt * U[2]};
-      const float chi = emitter_chi(P, E, x);
-      const float dchi[3] = {chi * (x[0] - E.c[0]) * 2.f * P.s2inv, chi * (x[1] - E.c[1]) * 2.f * P.s2inv,
-                             chi * (x[2] - E.c[2]) * 2.f * P.s2inv};
-      if (q < 3) {
-        int d0;
-        gdims(P, q, d0, d1, d2);
-        const float* F = q == 0 ? vel.u : (q == 1 ? vel.v : vel.w);
-        const float* Ab = q == 0 ? ub1 : (q == 1 ? vb1 : wb1);
-        const float ab = Ab[g];
+    float sval[NV] = {};
+    if (on) {
+      const uint32_t r = (uint32_t)(j * d2 + k);
+      float d[3], U[3], xbb[3] = {0.f, 0.f, 0.f};   // xbb: adjoint of the back-traced point
+      plane_velocity<Q>(P, vel, i, j, k, U);
+      L = lerp_setup(P, Q, i, j, k, U);
+      cell = ((uint32_t)L.i0 << 22) | ((uint32_t)L.j0 << 11) | (uint32_t)L.k0;
+      const float chi = emitter_chi<Q>(P, E, i, j, k, d);
+      const float dchi[3] = {chi * d[0] * 2.f * P.s2inv, chi * d[1] * 2.f * P.s2inv, chi * d[2] * 2.f * P.s2inv};
+      auto sample = [&](const float* F, float ab, float target, int kk) {
+        ZPair z[4];
+        lerp_pairs(P.big, F, L, (uint32_t)d1, (uint32_t)d2, z);
+        const float val = lerp_pairs_eval(z, L);
+        // emitter: out = val + chi (target - val)
+#pragma unroll
+        for (int a = 0; a < 3; a++) part[a] += (double)(ab * (target - val) * dchi[a]);
+        const float vbar = (1.f - chi) * ab;
+        sval[kk] = vbar;
+        const float c[8] = {z[0].a, z[0].b, z[1].a, z[1].b, z[2].a, z[2].b, z[3].a, z[3].b};
+        float gr[3];
+        lerp_grad(c, L, gr);
+#pragma unroll
+        for (int a = 0; a < 3; a++) xbb[a] += L.cl[a] ? 0.f : vbar * gr[a] * P.inv_h;
+      };
+      if (Q < 3) {
+        const float ab = (ab_in + plane)[r];
         if (ab != 0.f) {
-          L = lerp_setup(P, q, xb);
-          float c[8];
-          lerp_load(F, L, d1, d2, c);
-          const float val = lerp_eval(c, L);
-          const float target = P.speed * E.a[q];
-          // emitter: out = val + chi (target - val)
-#pragma unroll
-          for (int a = 0; a < 3; a++) part[a] += (double)(ab * (target - val) * dchi[a]);
-          part[3 + q] += (double)(ab * chi * P.speed);
-          const float vbar = (1.f - chi) * ab;
-          tgt = q == 0 ? out.u : (q == 1 ? out.v : out.w);
-          on = true;
-          sval[0] = vbar;
-          float gr[3];
-          lerp_grad(c, L, gr);
-#pragma unroll
-          for (int a = 0; a < 3; a++) xbb[a] = L.cl[a] ? 0.f : vbar * gr[a] * P.inv_h;
+          part[3 + (Q < 3 ? Q : 0)] += (double)(ab * chi * P.speed);
+          sample(Q == 0 ? vel.u : (Q == 1 ? vel.v : vel.w), ab, P.speed * E.a[Q < 3 ? Q : 0], 0);
         }
       } else {
-        L = lerp_setup(P, 3, xb);
 #pragma unroll
-        for (int kk = 0; kk < MAXK; kk++) {
-          if (kk >= P.K) break;
-          float ab = sb[kk * P.nc + g];
+        for (int kk = 0; kk < NV; kk++) {
+          if (kk >= K) break;
+          float ab = (ab_in + kk * P.nc + plane)[r];
           if (kk == 0) {
             // buoyancy: each interior y-face of this cell took dt beta T / 2
+            const float* v0 = vb1 + (size_t)i * (sx + P.nz);
             float vs = 0.f;
-            if (j > 0) vs += vb1[gidx(i, j, k, P.ny + 1, P.nz)];
-            if (j + 1 < P.ny) vs += vb1[gidx(i, j + 1, k, P.ny + 1, P.nz)];
+            if (j > 0) vs += ld32(v0, r);
+            if (j + 1 < P.ny) vs += ld32(v0, r + (uint32_t)P.nz);
             ab += 0.5f * P.dt * P.beta * vs;
           }
-          if (ab == 0.f) continue;
-          float c[8];
-          lerp_load(s + kk * P.nc, L, P.ny, P.nz, c);
-          const float val = lerp_eval(c, L);
+          if (ab != 0.f) sample(s + kk * P.nc, ab, P.src[kk], kk);
+        }
+      }
+      // back-trace xb = x - dt U(x): U's adjoint -dt xbb is kept per point;
+      // k_gas_adj_ugather spreads it over the velocity grids
 #pragma unroll
-          for (int a = 0; a < 3; a++) part[a] += (double)(ab * (P.src[kk] - val) * dchi[a]);
-          const float sbar = (1.f - chi) * ab;
-          s_on[kk] = true;
-          sval[kk] = sbar;
-          float gr[3];
-          lerp_grad(c, L, gr);
+      for (int a = 0; a < 3; a++) (ub + (size_t)a * total + plane)[r] = -P.dt * xbb[a];
+    }
+    // along z: the previous lane's cell adjoins this one's, or the next lane's this one's
+    // (the lane moves run with every lane active: not behind a condition)
+    const uint32_t cell_p = (uint32_t)lane_prev((int)cell);
+    const bool take = lane > 0 && cell_p + 1u == cell;
+    const int take_n = lane_next(take ? 1 : 0);
+    const bool given = lane < 63 && take_n != 0;
+    // along y: the carried row is this cell's
+    const bool carried = pcell == cell;
+    const uint32_t ecell = t < ADJ_J ? cell : pcell;   // the row emitted now (after the last point, the carried one)
+    float e0[NV], e1[NV], h0[NV], h1[NV];
 #pragma unroll
-          for (int a = 0; a < 3; a++) xbb[a] += L.cl[a] ? 0.f : sbar * gr[a] * P.inv_h;
+    for (int kk = 0; kk < NV; kk++) {
+      e0[kk] = e1[kk] = h0[kk] = h1[kk] = 0.f;
+      if (kk >= K) continue;
+      if (t == ADJ_J) {
+        e0[kk] = pend[kk][0]; e1[kk] = pend[kk][1];
+        h0[kk] = hpend[kk][0]; h1[kk] = hpend[kk][1];
+        continue;
+      }
+      const float gz = (1.f - L.f[2]) * sval[kk], fz = L.f[2] * sval[kk];
+      float lo[2][2], hi[2][2];
+#pragma unroll
+      for (int cx = 0; cx < 2; cx++)
+#pragma unroll
+        for (int cy = 0; cy < 2; cy++) {
+          const float wxy = (cx ? L.f[0] : 1.f - L.f[0]) * (cy ? L.f[1] : 1.f - L.f[1]);
+          hi[cx][cy] = wxy * fz;
+          const float hp = lane_prev(hi[cx][cy]);
+          lo[cx][cy] = wxy * gz + (take ? hp : 0.f);
+          if (given) hi[cx][cy] = 0.f;
+        }
+      if (carried) {
+        lo[0][0] += pend[kk][0];
+        lo[1][0] += pend[kk][1];
+        hi[0][0] += hpend[kk][0];
+        hi[1][0] += hpend[kk][1];
+      } else if (pcell != NO_CELL) {
+        flush(pcell, 0, kk, pend[kk][0]);
+        flush(pcell, 1, kk, pend[kk][1]);
+        flush(pcell + 1u, 0, kk, hpend[kk][0]);
+        flush(pcell + 1u, 1, kk, hpend[kk][1]);
+      }
+      e0[kk] = lo[0][0];
+      e1[kk] = lo[1][0];
+      pend[kk][0] = lo[0][1];
+      pend[kk][1] = lo[1][1];
+      h0[kk] = hi[0][0];
+      h1[kk] = hi[1][0];
+      hpend[kk][0] = hi[0][1];
+      hpend[kk][1] = hi[1][1];
+    }
+    pcell = cell == NO_CELL ? NO_CELL : cell + CELL_J;
+    // along x: the next wavefront's cell adjoins this one's
+    const int buf = t & 1;
+    S.cell[buf][wv][lane] = ecell;
+#pragma unroll
+    for (int kk = 0; kk < NV; kk++)
+      if (kk < K) {
+        S.e[buf][wv][kk][lane] = e1[kk];
+        S.h[buf][wv][kk][lane] = h1[kk];
+      }
+    __syncthreads();
+    const uint32_t cp = wv > 0 ? S.cell[buf][wv - 1][lane] : NO_CELL, cn = wv < ADJ_I - 1 ? S.cell[buf][wv + 1][lane] : NO_CELL;
+    const bool xtake = ecell != NO_CELL && ecell >= CELL_I && cp + CELL_I == ecell;
+    const bool xgiven = ecell != NO_CELL && cn != NO_CELL && cn >= CELL_I && ecell + CELL_I == cn;
+    if (ecell != NO_CELL) {
+#pragma unroll
+      for (int kk = 0; kk < NV; kk++) {
+        if (kk >= K) break;
+        flush(ecell, 0, kk, e0[kk] + (xtake ? S.e[buf][wv - 1][kk][lane] : 0.f));
+        flush(ecell + 1u, 0, kk, h0[kk] + (xtake ? S.h[buf][wv - 1][kk][lane] : 0.f));
+        if (!xgiven) {
+          flush(ecell, 1, kk, e1[kk]);
+          flush(ecell + 1u, 1, kk, h1[kk]);
         }
       }
     }
-    // the scatters, every lane of the wavefront together
-#pragma unroll
-    for (int kk = 0; kk < MAXK; kk++) {
-      if (kk >= P.K) break;
-      // (one call for all lanes: the lanes of a wavefront may straddle two grids)
-      const bool face = q < 3;
-      float* F = face ? tgt : out.s + kk * P.nc;
-      const float val = face ? (kk == 0 ? sval[0] : 0.f) : sval[kk];
-      const bool lane_on = face ? (on && kk == 0) : s_on[kk];
-      scatter_lerp_wave(F, L, d1, d2, val, lane_on);
-    }
-    // back-trace xb = x - dt U(x): U's adjoint -dt xbb is kept per point;
-    // k_gas_adj_ugather spreads it over the velocity grids
-    if (live) {
-#pragma unroll
-      for (int a = 0; a < 3; a++) ub[(size_t)a * total + g0] = -P.dt * xbb[a];
-    }
   }
+}
+
+__global__ __launch_bounds__(64 * ADJ_I) void k_gas_adj_advect(GP P, VelPtrs vel, const float* __restrict__ s,
+                                                        const float* __restrict__ ub1, const float* __restrict__ vb1,
+                                                        const float* __restrict__ wb1, const float* __restrict__ sb,
+                                                        AdjOut out, const double* __restrict__ pose,
+                                                        double* __restrict__ slots, float* __restrict__ ub, PointGrid G) {
+  __shared__ AdjLds S;
+  const size_t total = P.nu + P.nv + P.nw + P.nc;
+  const Pose E = load_pose(pose);
+  double part[POSE_PARTIALS] = {0, 0, 0, 0, 0, 0};
+  uint32_t b = xcd_block();
+  int ig = G.per == 1u ? (int)b : (int)__umulhi(b, G.mper);
+  if ((uint32_t)ig * G.per > b) ig--;
+  b -= (uint32_t)ig * G.per;
+  int q = 0;
+#pragma unroll
+  for (int n = 0; n < 3; n++)
+    if (q == n && b >= G.nb[n]) { b -= G.nb[n]; q = n + 1; }
+  const int i = ADJ_I * ig + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), col0 = 64 * (int)b;
+  if (q == 0) adj_columns<0>(P, vel, s, ub1, nullptr, out.u, E, ub, total, i, col0, S, part);
+  else if (q == 1) adj_columns<1>(P, vel, s, vb1, nullptr, out.v, E, ub + P.nu, total, i, col0, S, part);
+  else if (q == 2) adj_columns<2>(P, vel, s, wb1, nullptr, out.w, E, ub + P.nu + P.nv, total, i, col0, S, part);
+  else adj_columns<3>(P, vel, s, sb, vb1, out.s, E, ub + P.nu + P.nv + P.nw, total, i, col0, S, part);
   // pose partials: wave sums, one FP64 atomic per component into the
   // wavefront's accumulator copy
   const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -1117,56 +1243,80 @@ __global__ __launch_bounds__(256) void k_gas_adj_advect(GP P, VelPtrs vel, const
 }
 
 // Adjoint of the velocity at every grid point (U of the back-traces, from
-// the stencils of node_velocity) as a gather: each velocity node of grid a
-// sums the U_a adjoints (ub, from k_gas_adj_advect) of the points whose
+// the stencils of plane_velocity) as a gather: each velocity node of grid A
+// sums the U_A adjoints (ub, from k_gas_adj_advect) of the points whose
 // stencil holds it, with the stencil's weights: its own point (1), the two
-// cells beside it along a (1/2 each), and on each other face grid b the
-// points beside it along a (1/2) whose clamped pair along b holds it (1/2
-// per hit).
-__global__ __launch_bounds__(256) void k_gas_adj_ugather(GP P, const float* __restrict__ ub, AdjOut out) {
-  const size_t total = P.nu + P.nv + P.nw + P.nc;
-  const size_t nvel = P.nu + P.nv + P.nw;
-  const size_t qoff[4] = {0, P.nu, P.nu + P.nv, nvel};
-  const int N[3] = {P.nx, P.ny, P.nz};
-  for (size_t g0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x; g0 < nvel; g0 += (size_t)gridDim.x * blockDim.x) {
-    size_t g = g0;
-    const int a = split_points(P, g);
-    int n[3];
-    float xn[3];
-    point_of(P, a, g, n[0], n[1], n[2], xn);
-    const float* U = ub + (size_t)a * total;
-    float acc = U[qoff[a] + g];
-    float cs = 0.f;
+// cells beside it along A (1/2 each), and on each other face grid B the points
+// beside it along A (1/2) whose clamped pair along B holds it (1/2 per hit: the
+// lower of the two is hit twice at the first node, the upper at the last).
+template <int A>
+__device__ __forceinline__ float ugather_point(const GP& P, const float* __restrict__ Uu, const float* __restrict__ Uv,
+                                               const float* __restrict__ Uw, const float* __restrict__ Uc, int i, int r) {
+  const int ny = P.ny, nz = P.nz;
+  const size_t pu = (size_t)ny * nz, pv = pu + nz, pw = pu + ny;
+  const uint32_t z = (uint32_t)nz;
+  const int j = row_of(r, A == 2 ? P.mz1 : P.mz), k = r - j * (nz + (A == 2));
+  auto hit = [](bool edge) { return edge ? 2.f : 1.f; };
+  float cs = 0.f, f0 = 0.f, f1 = 0.f;
+  if (A == 0) {
+    const uint32_t o = (uint32_t)r, ow = o + (uint32_t)j;
+    const float a0 = hit(j == 0), a1 = hit(j == ny - 1), b0 = hit(k == 0), b1 = hit(k == nz - 1);
 #pragma unroll
-    for (int t = 0; t < 2; t++) {
-      int c[3] = {n[0], n[1], n[2]};
-      c[a] = n[a] - 1 + t;
-      if (c[a] >= 0 && c[a] < N[a]) cs += U[qoff[3] + gidx(c[0], c[1], c[2], P.ny, P.nz)];
+    for (int ta = 0; ta < 2; ta++) {
+      const int pi = i - 1 + ta;
+      if (pi < 0 || pi >= P.nx) continue;   // (uniform)
+      const float *c = Uc + pi * pu, *v = Uv + pi * pv, *w = Uw + pi * pw;
+      cs += ld32(c, o);
+      f0 += a0 * ld32(v, o) + a1 * ld32(v, o + z);
+      f1 += b0 * ld32(w, ow) + b1 * ld32(w, ow + 1);
     }
-    acc += 0.5f * cs;
-#pragma unroll
-    for (int b = 0; b < 3; b++) {
-      if (b == a) continue;
-      int db0, db1, db2;
-      gdims(P, b, db0, db1, db2);
-      float fs = 0.f;
-#pragma unroll
-      for (int ta = 0; ta < 2; ta++) {
-#pragma unroll
-        for (int tb = 0; tb < 2; tb++) {
-          int p[3] = {n[0], n[1], n[2]};
-          p[a] = n[a] - 1 + ta;
-          p[b] = n[b] + tb;
-          if (p[a] < 0 || p[a] >= N[a] || p[b] > N[b]) continue;
-          const int hits = (max(p[b] - 1, 0) == n[b]) + (min(p[b], N[b] - 1) == n[b]);
-          if (hits) fs += (float)hits * U[qoff[b] + gidx(p[0], p[1], p[2], db1, db2)];
-        }
-      }
-      acc += 0.25f * fs;
-    }
-    float* O = a == 0 ? out.u : (a == 1 ? out.v : out.w);
-    O[g] += acc;
+    return ld32(Uu + i * pu, o) + 0.5f * cs + 0.25f * f0 + 0.25f * f1;
   }
+  if (A == 1) {
+    const float a0 = hit(i == 0), a1 = hit(i == P.nx - 1), b0 = hit(k == 0), b1 = hit(k == nz - 1);
+    const float *c = Uc + i * pu, *u0 = Uu + i * pu, *u1 = u0 + pu, *w = Uw + i * pw;
+#pragma unroll
+    for (int ta = 0; ta < 2; ta++) {
+      const int pj = j - 1 + ta;
+      if (pj < 0 || pj >= ny) continue;
+      const uint32_t o = (uint32_t)(pj * nz + k), ow = o + (uint32_t)pj;
+      cs += ld32(c, o);
+      f0 += a0 * ld32(u0, o) + a1 * ld32(u1, o);
+      f1 += b0 * ld32(w, ow) + b1 * ld32(w, ow + 1);
+    }
+    return ld32(Uv + i * pv, (uint32_t)r) + 0.5f * cs + 0.25f * f0 + 0.25f * f1;
+  }
+  const float a0 = hit(i == 0), a1 = hit(i == P.nx - 1), b0 = hit(j == 0), b1 = hit(j == ny - 1);
+  const float *c = Uc + i * pu, *u0 = Uu + i * pu, *u1 = u0 + pu, *v = Uv + i * pv;
+#pragma unroll
+  for (int ta = 0; ta < 2; ta++) {
+    const int pk = k - 1 + ta;
+    if (pk < 0 || pk >= nz) continue;
+    const uint32_t o = (uint32_t)(j * nz + pk);
+    cs += ld32(c, o);
+    f0 += a0 * ld32(u0, o) + a1 * ld32(u1, o);
+    f1 += b0 * ld32(v, o) + b1 * ld32(v, o + z);
+  }
+  return ld32(Uw + i * pw, (uint32_t)r) + 0.5f * cs + 0.25f * f0 + 0.25f * f1;
+}
+
+constexpr int UG_U = 2;
+__global__ __launch_bounds__(256) void k_gas_adj_ugather(GP P, const float* __restrict__ ub, AdjOut out, PointGrid G) {
+  const size_t total = P.nu + P.nv + P.nw + P.nc;
+  const PlaneBlock b = plane_block<UG_U>(P, G);
+  auto points = [&](auto a, float* O) {
+    constexpr int A = decltype(a)::value;
+    const float *Uu = ub + A * total, *Uv = Uu + P.nu, *Uw = Uv + P.nv, *Uc = Uw + P.nw;
+    O += (size_t)b.i * plane_points(A, P.ny, P.nz);
+#pragma unroll
+    for (int t = 0; t < UG_U; t++) {
+      const int r = b.r0 + 256 * t + (int)threadIdx.x;
+      if (r < b.n) O[(uint32_t)r] += ugather_point<A>(P, Uu, Uv, Uw, Uc, b.i, r);
+    }
+  };
+  if (b.q == 0) points(std::integral_constant<int, 0>{}, out.u);
+  else if (b.q == 1) points(std::integral_constant<int, 1>{}, out.v);
+  else points(std::integral_constant<int, 2>{}, out.w);
 }
 
 // sum of the accumulator copies into the step's pose partials (c at 6..8 and
@@ -1476,22 +1626,21 @@ void pressure_solve(gas_ctx* c, float* psi0, float* f0) {
   }
 }
 
-// one forward step from `in` to `out` (distinct), emitter at pose t
+// one forward step from `in` to `out` (their scalars distinct), emitter at pose t
 void gas_forward_step(gas_ctx* c, const gas_state& in, const gas_state& out, int t) {
   const GP& P = c->P;
   hipStream_t s = c->stream;
   gas_state tmp = packed(c, c->ws + c->L.tmp);
   float* psi0 = (float*)(c->ws + c->L.psi[0]);
   float* f0 = (float*)(c->ws + c->L.f[0]);
-  const size_t pts = P.nu + P.nv + P.nw + P.nc;
   c->t_adv.begin(s);
-  k_gas_advect<<<nblk(pts, 256), 256, 0, s>>>(P, VelPtrs{in.u, in.v, in.w}, in.s, tmp.u, tmp.v, tmp.w, tmp.s,
-                                             pose_at(c, t));
+  const PointGrid Ga = point_grid(P, 4, ADV_U), Gd = point_grid(P, 1, DIV_U), Gf = point_grid(P, 3, FIN_U);
+  k_gas_advect<<<Ga.blocks, 256, 0, s>>>(P, VelPtrs{in.u, in.v, in.w}, in.s, tmp.u, tmp.v, tmp.w, out.s,
+                                        pose_at(c, t), Ga);
   c->t_adv.end(s);
-  k_gas_div<<<nblk(P.nc, 256), 256, 0, s>>>(P, tmp.u, tmp.v, tmp.w, tmp.s, f0, psi0);
+  k_gas_div<true><<<Gd.blocks, 256, 0, s>>>(P, tmp.u, tmp.v, tmp.w, out.s, f0, c->d.pressure_solver ? psi0 : nullptr, Gd);
   pressure_solve(c, psi0, f0);
-  const size_t tot = P.nu + P.nv + P.nw + (size_t)P.K * P.nc;
-  k_gas_final<<<nblk(tot, 256), 256, 0, s>>>(P, tmp.u, tmp.v, tmp.w, tmp.s, psi0, out.u, out.v, out.w, out.s);
+  k_gas_final<true><<<Gf.blocks, 256, 0, s>>>(P, tmp.u, tmp.v, tmp.w, out.s, psi0, out.u, out.v, out.w, Gf);
 }
 
 // one adjoint step: abar_next (adjoint of s_{t+1}) -> abar (adjoint of s_t);
@@ -1502,16 +1651,15 @@ void gas_adjoint_step(gas_ctx* c, const gas_state& st, const gas_state& an, cons
   gas_state tmp = packed(c, c->ws + c->L.tmp);
   float* psi0 = (float*)(c->ws + c->L.psi[0]);
   float* f0 = (float*)(c->ws + c->L.f[0]);
-  k_gas_adj_div<<<nblk(P.nc, 256), 256, 0, s>>>(P, an.u, an.v, an.w, f0, psi0);
+  const PointGrid Gd = point_grid(P, 1, DIV_U), Gf = point_grid(P, 3, FIN_U), Ga = column_grid(P), Gu = point_grid(P, 3, UG_U);
+  k_gas_div<false><<<Gd.blocks, 256, 0, s>>>(P, an.u, an.v, an.w, nullptr, f0, c->d.pressure_solver ? psi0 : nullptr, Gd);
   pressure_solve(c, psi0, f0);
-  k_gas_adj_sub<<<nblk(P.nu + P.nv + P.nw, 256), 256, 0, s>>>(P, an.u, an.v, an.w, psi0, tmp.u, tmp.v, tmp.w);
+  k_gas_final<false><<<Gf.blocks, 256, 0, s>>>(P, an.u, an.v, an.w, nullptr, psi0, tmp.u, tmp.v, tmp.w, Gf);
   launch_zero(ab.u, c->L.state_floats * 4, s);
-  const size_t pts = P.nu + P.nv + P.nw + P.nc;
-  k_gas_adj_advect<<<nblk(pts, 256), 256, 0, s>>>(P, VelPtrs{st.u, st.v, st.w}, st.s, tmp.u, tmp.v, tmp.w, an.s,
-                                                 AdjOut{ab.u, ab.v, ab.w, ab.s}, pose_at(c, t),
-                                                 (double*)(c->ws + c->L.slots), (float*)(c->ws + c->L.ub));
-  k_gas_adj_ugather<<<nblk(P.nu + P.nv + P.nw, 256), 256, 0, s>>>(P, (const float*)(c->ws + c->L.ub),
-                                                                  AdjOut{ab.u, ab.v, ab.w, ab.s});
+  k_gas_adj_advect<<<Ga.blocks, 64 * ADJ_I, 0, s>>>(P, VelPtrs{st.u, st.v, st.w}, st.s, tmp.u, tmp.v, tmp.w, an.s,
+                                             AdjOut{ab.u, ab.v, ab.w, ab.s}, pose_at(c, t),
+                                             (double*)(c->ws + c->L.slots), (float*)(c->ws + c->L.ub), Ga);
+  k_gas_adj_ugather<<<Gu.blocks, 256, 0, s>>>(P, (const float*)(c->ws + c->L.ub), AdjOut{ab.u, ab.v, ab.w, ab.s}, Gu);
   k_gas_pose_acc<<<1, 64, 0, s>>>((double*)(c->ws + c->L.slots), acc_t);
 }
 
@@ -1579,6 +1727,9 @@ int gas_create(const gas_desc* d, void* workspace_dev, size_t ws_bytes, void* st
   P.nv = (size_t)d->nx * (d->ny + 1) * d->nz;
   P.nw = (size_t)d->nx * d->ny * (d->nz + 1);
   P.nc = (size_t)d->nx * d->ny * d->nz;
+  P.big = P.nu >= (1u << 30) || P.nv >= (1u << 30) || P.nw >= (1u << 30);
+  P.mz = (uint32_t)((0x100000000ull + d->nz - 1) / d->nz);
+  P.mz1 = (uint32_t)((0x100000000ull + d->nz) / (d->nz + 1));
   P.err = (int*)(c->ws + L.err);
   launch_zero(c->ws + L.slots, SLOTS * POSE_PARTIALS * sizeof(double), c->stream);
   launch_zero(c->ws + L.err, 64, c->stream);
@@ -1658,12 +1809,24 @@ int gas_step(gas_ctx* c, int32_t n_steps) {
   for (int t = c->t; t < c->t + n_steps; t++)
     if (!c->act_set[t]) return MPM_ESTATE;
   launch_pose(1, c->t, n_steps, c->d.dt, (const float*)(c->ws + c->L.act), (double*)(c->ws + c->L.pose), c->stream);
-  // the step reads the user arrays and writes them back through the
-  // temporaries; a checkpoint is taken before every k-th step
+  // the step reads the user's velocities and writes them back through the
+  // temporaries; the scalars, which advection finishes, alternate between the
+  // user array and the temporaries', so that the last step ends in the user's
+  // (an odd number of steps starts from a copy); a checkpoint is taken before
+  // every k-th step
+  gas_state from = c->user, to = c->user;
+  float* tmp_s = packed(c, c->ws + c->L.tmp).s;
+  if (n_steps & 1) {
+    hipMemcpyAsync(tmp_s, from.s, (size_t)c->P.K * c->P.nc * 4, hipMemcpyDeviceToDevice, c->stream);
+    from.s = tmp_s;
+  } else {
+    to.s = tmp_s;
+  }
   for (int t = c->t; t < c->t + n_steps; t++) {
     if (c->d.requires_grad && t % c->d.ckpt_every == 0)
-      copy_state(c, c->user, packed(c, c->ws + c->L.ckpt + (size_t)(t / c->d.ckpt_every) * state_stride(c)));
-    gas_forward_step(c, c->user, c->user, t);
+      copy_state(c, from, packed(c, c->ws + c->L.ckpt + (size_t)(t / c->d.ckpt_every) * state_stride(c)));
+    gas_forward_step(c, from, to, t);
+    float* sw = from.s; from.s = to.s; to.s = sw;
   }
   c->t += n_steps;
   if (hipGetLastError() != hipSuccess) return MPM_EHIP;

@@ -269,3 +269,27 @@ def test_gas_axis_tiles_vs_oracle(n):
     sim.step(2)
     say(f"  pressure residual {sim.residual():.2e}")
     compare(sim.state_numpy(), G.rollout_scene(sc, steps=2))
+
+
+@pytest.mark.parametrize("n,velocity,dt,scalars", [((12, 20, 28), 0.5, 5e-3, 1), ((20, 12, 68), 3.0, 0.05, 4)])
+def test_gas_gradient_merged_scatter_vs_oracle(n, velocity, dt, scalars):
+    """Ragged grids whose columns and planes do not fill the adjoint's
+    workgroups, with short back-traces (almost every sample merges with its
+    neighbours) and with ones of several cells that leave the grid (few do).
+    Tolerance: the gradient test's."""
+    sc = scenes.gas_room(n=n, steps=2, seed=12, n_scalars=scalars, velocity=velocity, dt=dt, translate=True)
+    sim = gas_sim(sc, requires_grad=True, ckpt_every=16)
+    sim.step(2)
+    wflat = _seeds(sim, 31)
+    ga, g0 = sim.backward(wflat.to(sim.device), want_grad0=True)
+    acts = torch.tensor(sc.actions, dtype=DT, requires_grad=True)
+    st0 = G.state_from_scene(sc, requires_grad=True)
+    st = G.rollout_scene(sc, actions=acts, state=st0, params=G.params_from_scene(sc))
+    wq = [t.double() for t in sim.split(wflat)]
+    L = sum((w * st[q]).sum() for w, q in zip(wq[:3], ("u", "v", "w"))) + (wq[3] * st["s"]).sum()
+    L.backward()
+    e = {"actions": rel(ga.double().cpu().numpy(), acts.grad.numpy())}
+    for q, g in zip(("u", "v", "w", "s"), sim.split(g0)):
+        e[q] = rel(g.double().cpu().numpy(), st0[q].grad.numpy())
+    say(f"gas {n}, velocity {velocity}: " + " ".join(f"{k} {v:.2e}" for k, v in e.items()))
+    assert max(e.values()) <= 2e-3
