@@ -480,9 +480,10 @@ static void rigid_tiled_run(mpm_ctx* c, const StepParams& P, const PState& us, i
     rigid_forward(c->rigid, P, rows, rigid_rec(c, 0), true, s);
     if (t + 1 == t0 + n) break;
     if (f.ck_k > 0 && (t + 1) % f.ck_k == 0)
-      fast_export(f, P, tmp, packed_state((float*)(f.ck_base + (size_t)((t + 1) / f.ck_k) * f.ck_stride), N), s);
+      fast_export(f, P, tmp, packed_state((float*)(f.ck_base + (size_t)((t + 1) / f.ck_k) * f.ck_stride), N), s,
+                  (float*)(c->ws + c->L.adj0));   // (R0's keys are still read: the adjoint's arrays are idle here)
     // (the G2P buffer's key row is free: it serves as the sort's row map)
-    fast_sort_next(f, P, R0, tmp, R0, tmp.key, s, true);
+    fast_sort_next(f, P, R0, tmp, R0, tmp.key, s, true, true);
   }
   if (f.do_export) fast_export(f, P, tmp, us, s);
 }
@@ -592,7 +593,7 @@ static int record_run(mpm_ctx* c, const StepParams& P, const PState& us, int t0,
   const size_t rb = c->L.rec.bytes;
   auto rec = [&](int t) { return sorted_state(c, c->L.seg + (size_t)t * rb); };
   SortedState R0 = rec(t0);
-  fast_sort_user(f, P, us, R0, s, true);
+  fast_sort_user(f, P, us, R0, s, true, true);
   if (t0 > 0) launch_row_map(rec(t0 - 1).b.id, R0.b.id, N, f.inv, sorted_map(c, c->L.seg + (size_t)(t0 - 1) * rb), s);
   uint32_t sid = fast_next_sid(f);
   fast_p2g(f, P, R0, sid, s);

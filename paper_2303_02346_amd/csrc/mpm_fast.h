@@ -187,7 +187,7 @@ uint32_t fast_next_sid(FastPath& f);
 void fast_sort_user(FastPath& f, const StepParams& P, const PState& user, SortedState& out, hipStream_t s,
                     bool touched = false, bool share = false);
 void fast_sort_next(FastPath& f, const StepParams& P, const SortedState& prev, const PBuf& next, SortedState& out,
-                    uint32_t* map, hipStream_t s, bool touched = false);
+                    uint32_t* map, hipStream_t s, bool touched = false, bool share = false);
 void fast_p2g(FastPath& f, const StepParams& P, const SortedState& st, uint32_t sid, hipStream_t s);
 void fast_grid(FastPath& f, const StepParams& P, const SortedState& st, uint32_t sid, int t, const double* pose_base,
                const float* act_base, hipStream_t s);
@@ -216,6 +216,8 @@ SortedState fast_own_state(FastPath& f, int b);
 // the buffer the last call left.  Returns 0, or -1 (nothing recorded yet).
 int fast_sort_snapshot(FastPath& f, const StepParams& P, const PState& user, int which, uint32_t* id_out,
                        uint32_t* key_out, int4* list_out, int* n_list_host, hipStream_t s);
-void fast_export(FastPath& f, const StepParams& P, const PBuf& X, const PState& user, hipStream_t s);
+// (scratch: 112 bytes a particle where the path's idle buffer is still needed)
+void fast_export(FastPath& f, const StepParams& P, const PBuf& X, const PState& user, hipStream_t s,
+                 float* scratch = nullptr);
 
 }  // namespace mpm

@@ -44,31 +44,66 @@ inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 // import: block key and rank of every particle (user order)
 // ---------------------------------------------------------------------------
 constexpr int IMPORT_PAD = 16;   // uint32 words between two keys' import counters
-__global__ __launch_bounds__(256) void k_import_keys(PState u, StepParams P, FastGeom g, uint32_t* __restrict__ counts,
-                                                     uint32_t* __restrict__ key_tmp, uint32_t* __restrict__ rank_tmp,
-                                                     uint32_t* __restrict__ touched, uint32_t* __restrict__ n_touched) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  bool has = p < u.N;
-  uint32_t key = 0;
+// Every key of a workgroup's particles is reserved with one global atomic: user
+// order is arbitrary, but a block holds hundreds of particles, and atomics on one
+// counter follow each other (208 blocks of 480 particles: 38.5 us with an atomic a
+// particle, now 5.3; 3.8M particles in 64 scenes 371, now 66).  The keys are
+// counted in an LDS hash table of twice as many entries as particles; the
+// counters stay padded to one per 64 bytes (packed, hundreds of keys' atomics
+// would fall on a few cache lines); the first reservation of a key appends it to
+// the touched list.
+constexpr int IMPORT_NT = 1024, IMPORT_HASH = 2 * IMPORT_NT;
+__global__ __launch_bounds__(IMPORT_NT) void k_import_keys(PState u, StepParams P, FastGeom g,
+                                                           uint32_t* __restrict__ counts,
+                                                           uint32_t* __restrict__ key_tmp,
+                                                           uint32_t* __restrict__ rank_tmp,
+                                                           uint32_t* __restrict__ touched,
+                                                           uint32_t* __restrict__ n_touched) {
+  constexpr uint32_t FREE = 0xffffffffu;
+  __shared__ uint32_t s_key[IMPORT_HASH], s_cnt[IMPORT_HASH];
+  const int tid = threadIdx.x, N = u.N;
+  const int p = blockIdx.x * IMPORT_NT + tid;
+  const bool has = p < N;
+  float x[3] = {0.f, 0.f, 0.f};
+  int sc = 0;
   if (has) {
-    const int N = u.N;
-    float x[3] = {u.x[p], u.x[N + p], u.x[2 * N + p]};
+#pragma unroll
+    for (int a = 0; a < 3; a++) x[a] = u.x[a * (size_t)N + p];
+    sc = P.pscene[p];
+  }
+#pragma unroll
+  for (int r = 0; r < 2; r++) { s_key[tid + r * IMPORT_NT] = FREE; s_cnt[tid + r * IMPORT_NT] = 0u; }
+  __syncthreads();
+  uint32_t key = 0, slot = 0, rank = 0;
+  if (has) {
     Stencil S;
-    if (!stencil_setup(x, P, S)) {
-      atomicOr(P.err, ERR_OUTSIDE);
-    } else {
-      key = block_key(g, P.pscene[p], S.base[0] >> 2, S.base[1] >> 2, S.base[2] >> 2);
+    if (!stencil_setup(x, P, S)) atomicOr(P.err, ERR_OUTSIDE);
+    else key = block_key(g, sc, S.base[0] >> 2, S.base[1] >> 2, S.base[2] >> 2);
+    // (at most half of the table is ever taken, so the probe ends)
+    slot = (key * 2654435761u) >> 21;
+    static_assert(IMPORT_HASH == 1 << 11, "hash bits");
+    for (;;) {
+      const uint32_t was = atomicCAS(&s_key[slot], FREE, key);
+      if (was == FREE || was == key) break;
+      slot = (slot + 1u) & (IMPORT_HASH - 1);
+    }
+    rank = atomicAdd(&s_cnt[slot], 1u);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 2; r++) {
+    const int q = tid + r * IMPORT_NT;
+    const uint32_t k = s_key[q];
+    if (k != FREE) {
+      const uint32_t base = atomicAdd(&counts[(size_t)k * IMPORT_PAD], s_cnt[q]);
+      if (base == 0u) touch_key(k, touched, n_touched, (uint32_t)g.n_keys);
+      s_cnt[q] = base;
     }
   }
-  // user order is arbitrary, so the lanes of a wavefront rarely share a key:
-  // one atomic per particle into counters padded to one per 64 bytes (packed
-  // counters would put hundreds of keys' atomics on a few cache lines); the
-  // first reservation of a key appends it to the touched list
+  __syncthreads();
   if (has) {
-    const uint32_t r = atomicAdd(&counts[(size_t)key * IMPORT_PAD], 1u);
-    if (r == 0u) touch_key(key, touched, n_touched, (uint32_t)g.n_keys);
     key_tmp[p] = key;
-    rank_tmp[p] = r;
+    rank_tmp[p] = s_cnt[slot] + rank;
   }
 }
 
@@ -369,37 +404,73 @@ __global__ __launch_bounds__(1024) void k_scan(uint32_t* __restrict__ counts, ui
 
 
 
-// The user-order particles to their sorted slots, as a gather: k_inv records
-// the user index of every slot (one scattered word per particle), k_gather_in
-// then reads each slot's particle (scattered reads) and writes the sorted rows
-// in order.
-__global__ __launch_bounds__(256) void k_inv(int N, const uint32_t* __restrict__ key_tmp,
-                                             const uint32_t* __restrict__ rank_tmp,
-                                             const uint32_t* __restrict__ offsets, uint32_t* __restrict__ inv) {
+// Between user order and sorted order a particle moves as one record of 28
+// words: x, v, C, then F (a solid) or J (a liquid), the material, the user
+// index, the key and the rank.  A row-wise gather or scatter touches a cache line
+// for every row of every particle (the gathers took 1010 and 555 us at 3.8M
+// particles; packed and unpacked they are 449 and 361 now); a record is two of them, and the passes
+// between records and rows are coalesced on both sides.  The records live in a
+// particle buffer that holds nothing at the time: its f, id, key and rank rows
+// are 112 bytes a particle.
+constexpr int REC_W = 28;
+struct Record {
+  float4 q[REC_W / 4];
+};
+static_assert(sizeof(Record) == 4 * (STATE_FLOATS + 3), "a record fits the rows f, id, key and rank");
+
+__global__ __launch_bounds__(256) void k_pack_in(PState u, const uint8_t* __restrict__ umat,
+                                                 const MatDev* __restrict__ mats, const uint32_t* __restrict__ key_tmp,
+                                                 const uint32_t* __restrict__ rank_tmp,
+                                                 const uint32_t* __restrict__ offsets, Record* __restrict__ rec) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int N = u.N;
   if (p >= N) return;
-  const uint32_t d = offsets[key_tmp[p]] + rank_tmp[p];
-  if (d < (uint32_t)N) inv[d] = (uint32_t)p;
+  const uint32_t key = key_tmp[p], rank = rank_tmp[p];
+  const uint32_t d = offsets[key] + rank;
+  if (d >= (uint32_t)N) return;
+  float w[REC_W];
+#pragma unroll
+  for (int a = 0; a < 3; a++) { w[a] = u.x[a * (size_t)N + p]; w[3 + a] = u.v[a * (size_t)N + p]; }
+#pragma unroll
+  for (int k = 0; k < 9; k++) { w[6 + k] = u.C[k * (size_t)N + p]; w[15 + k] = 0.f; }
+  const uint32_t m = umat[p];
+  if (mats[m].kind == KIND_LIQUID) {
+    w[15] = u.J[p];
+  } else {
+#pragma unroll
+    for (int k = 0; k < 9; k++) w[15 + k] = u.F[k * (size_t)N + p];
+  }
+  w[24] = __uint_as_float(m);
+  w[25] = __uint_as_float((uint32_t)p);
+  w[26] = __uint_as_float(key);
+  w[27] = __uint_as_float(rank);
+#pragma unroll
+  for (int q = 0; q < REC_W / 4; q++) rec[d].q[q] = make_float4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }
 
-__global__ __launch_bounds__(256) void k_gather_in(PState u, const uint8_t* __restrict__ umat, PBuf X,
-                                                   const uint32_t* __restrict__ inv,
-                                                   const uint32_t* __restrict__ key_tmp,
-                                                   const uint32_t* __restrict__ rank_tmp) {
+__global__ __launch_bounds__(256) void k_unpack_in(const Record* __restrict__ rec, const MatDev* __restrict__ mats, PBuf X,
+                                                   int N) {
   const int d = blockIdx.x * blockDim.x + threadIdx.x;
-  const int N = u.N;
   if (d >= N) return;
-  const uint32_t p = inv[d];
-  if (p >= (uint32_t)N) return;
+  float w[REC_W];
 #pragma unroll
-  for (int a = 0; a < 3; a++) { X.f[a * (size_t)N + d] = u.x[a * N + p]; X.f[(3 + a) * (size_t)N + d] = u.v[a * N + p]; }
+  for (int q = 0; q < REC_W / 4; q++) {
+    const float4 v = rec[d].q[q];
+    w[4 * q] = v.x; w[4 * q + 1] = v.y; w[4 * q + 2] = v.z; w[4 * q + 3] = v.w;
+  }
+  const uint32_t m = __float_as_uint(w[24]) & 0xffu;
 #pragma unroll
-  for (int k = 0; k < 9; k++) { X.f[(6 + k) * (size_t)N + d] = u.C[k * N + p]; X.f[(15 + k) * (size_t)N + d] = u.F[k * N + p]; }
-  X.f[24 * (size_t)N + d] = u.J[p];
-  X.id[d] = p;
-  X.key[d] = key_tmp[p];
-  X.rank[d] = rank_tmp[p];
-  X.mat[d] = umat[p];
+  for (int k = 0; k < 15; k++) X.f[k * (size_t)N + d] = w[k];
+  if (mats[m].kind == KIND_LIQUID) {
+    X.f[24 * (size_t)N + d] = w[15];
+  } else {
+#pragma unroll
+    for (int k = 0; k < 9; k++) X.f[(15 + k) * (size_t)N + d] = w[15 + k];
+  }
+  X.mat[d] = (uint8_t)m;
+  X.id[d] = __float_as_uint(w[25]);
+  X.key[d] = __float_as_uint(w[26]);
+  X.rank[d] = __float_as_uint(w[27]);
 }
 
 // block key and rank of the state produced from a sorted state (same rows);
@@ -440,33 +511,68 @@ __global__ __launch_bounds__(256) void k_sort_permute(PBuf in, PBuf out, int N, 
   map[p] = d;
 }
 
-// The sorted buffer back to the user arrays, as a gather: k_pos records the
-// sorted slot of every particle, k_gather_out reads each particle's slot and
-// writes the user rows in order.  Liquids keep the user's F and solids the
-// user's J (those rows are not carried by the kernels).
-__global__ __launch_bounds__(256) void k_pos(PBuf X, int N, uint32_t* __restrict__ pos) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
-  if (d >= N) return;
-  const uint32_t p = X.id[d];
-  if (p < (uint32_t)N) pos[p] = (uint32_t)d;
+// The sorted buffer back to the user arrays: k_pack_out packs the records and
+// notes the sorted slot of every particle, k_gather_out reads each particle's
+// record and writes the user rows in order.  Liquids keep the user's F and solids
+// the user's J (those rows are not carried by the kernels).  The records of a
+// wavefront leave through LDS as whole lines (a lane's own record in 16-byte
+// stores 112 bytes apart: 331 us at 3.8M particles).
+__global__ __launch_bounds__(256) void k_pack_out(PBuf X, int N, const MatDev* __restrict__ mats,
+                                                  uint32_t* __restrict__ pos, float4* __restrict__ rec) {
+  constexpr int Q = REC_W / 4;
+  __shared__ float4 s_rec[4][64 * Q];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int d = blockIdx.x * blockDim.x + threadIdx.x, d0 = d - lane;
+  if (d < N) {
+    const uint32_t p = X.id[d];
+    if (p < (uint32_t)N) pos[p] = (uint32_t)d;
+    float w[REC_W];
+#pragma unroll
+    for (int k = 0; k < 15; k++) w[k] = X.f[k * (size_t)N + d];
+#pragma unroll
+    for (int k = 15; k < REC_W; k++) w[k] = 0.f;
+    const uint32_t m = X.mat[d];
+    if (mats[m].kind == KIND_LIQUID) {
+      w[15] = X.f[24 * (size_t)N + d];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 9; k++) w[15 + k] = X.f[(15 + k) * (size_t)N + d];
+    }
+    w[24] = __uint_as_float(m);
+#pragma unroll
+    for (int q = 0; q < Q; q++) s_rec[wv][lane * Q + q] = make_float4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+  }
+  __syncthreads();
+  const int n = min(64, N - d0) * Q;
+#pragma unroll
+  for (int r = 0; r < Q; r++) {
+    const int q = lane + 64 * r;
+    if (q < n) rec[(size_t)d0 * Q + q] = s_rec[wv][q];
+  }
 }
 
-__global__ __launch_bounds__(256) void k_gather_out(PBuf X, PState u, const MatDev* __restrict__ mats,
-                                                    const uint32_t* __restrict__ pos) {
+__global__ __launch_bounds__(256) void k_gather_out(const Record* __restrict__ rec, PState u,
+                                                    const MatDev* __restrict__ mats, const uint32_t* __restrict__ pos) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   const int N = u.N;
   if (p >= N) return;
   const uint32_t j = pos[p];
   if (j >= (uint32_t)N) return;
+  float w[REC_W];
 #pragma unroll
-  for (int a = 0; a < 3; a++) { u.x[a * N + p] = X.f[a * (size_t)N + j]; u.v[a * N + p] = X.f[(3 + a) * (size_t)N + j]; }
+  for (int q = 0; q < REC_W / 4; q++) {
+    const float4 v = rec[j].q[q];
+    w[4 * q] = v.x; w[4 * q + 1] = v.y; w[4 * q + 2] = v.z; w[4 * q + 3] = v.w;
+  }
 #pragma unroll
-  for (int k = 0; k < 9; k++) u.C[k * N + p] = X.f[(6 + k) * (size_t)N + j];
-  if (mats[X.mat[j]].kind == KIND_LIQUID) {
-    u.J[p] = X.f[24 * (size_t)N + j];
+  for (int a = 0; a < 3; a++) { u.x[a * (size_t)N + p] = w[a]; u.v[a * (size_t)N + p] = w[3 + a]; }
+#pragma unroll
+  for (int k = 0; k < 9; k++) u.C[k * (size_t)N + p] = w[6 + k];
+  if (mats[__float_as_uint(w[24]) & 0xffu].kind == KIND_LIQUID) {
+    u.J[p] = w[15];
   } else {
 #pragma unroll
-    for (int k = 0; k < 9; k++) u.F[k * N + p] = X.f[(15 + k) * (size_t)N + j];
+    for (int k = 0; k < 9; k++) u.F[k * (size_t)N + p] = w[15 + k];
   }
 }
 
@@ -1186,15 +1292,26 @@ static inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1
 
 // the import's permutation (after its key count and scan) and the export,
 // both as a scattered word per particle plus a gather
-static void import_permute(FastPath& f, const PState& user, const uint8_t* umat, const PBuf& X, hipStream_t s) {
+// (tmp: a particle buffer that holds nothing, for the records)
+static void import_permute(FastPath& f, const PState& user, const StepParams& P, const PBuf& X, const PBuf& tmp,
+                           hipStream_t s) {
   const int N = f.N;
-  k_inv<<<nblk(N, 256), 256, 0, s>>>(N, f.key_tmp, f.rank_tmp, f.offsets, f.inv);
-  k_gather_in<<<nblk(N, 256), 256, 0, s>>>(user, umat, X, f.inv, f.key_tmp, f.rank_tmp);
+  Record* rec = reinterpret_cast<Record*>(tmp.f);
+  k_pack_in<<<nblk(N, 256), 256, 0, s>>>(user, P.mat, P.mats, f.key_tmp, f.rank_tmp, f.offsets, rec);
+  k_unpack_in<<<nblk(N, 256), 256, 0, s>>>(rec, P.mats, X, N);
 }
-static void export_state(FastPath& f, const PBuf& X, const PState& user, const MatDev* mats, hipStream_t s) {
+static void export_state(FastPath& f, const PBuf& X, const PBuf& tmp, const PState& user, const MatDev* mats, hipStream_t s) {
   const int N = f.N;
-  k_pos<<<nblk(N, 256), 256, 0, s>>>(X, N, f.inv);
-  k_gather_out<<<nblk(N, 256), 256, 0, s>>>(X, user, mats, f.inv);
+  Record* rec = reinterpret_cast<Record*>(tmp.f);
+  k_pack_out<<<nblk(N, 256), 256, 0, s>>>(X, N, mats, f.inv, reinterpret_cast<float4*>(rec));
+  k_gather_out<<<nblk(N, 256), 256, 0, s>>>(rec, user, mats, f.inv);
+}
+// One of the path's buffers that is neither X nor the one whose ids the last
+// call left (fast_sort_snapshot).
+static const PBuf& idle_buf(const FastPath& f, const PBuf& X) {
+  if (X.f == f.buf[0].f) return f.buf[1];
+  if (X.f == f.buf[1].f) return f.buf[0];
+  return f.buf[f.last_buf == 1 ? 0 : 1];
 }
 
 int fast_init(FastPath& f, char* ws, int n_grid, int n_scenes, int N, hipStream_t s) {
@@ -1293,11 +1410,11 @@ static void enqueue_call(FastPath& f, const StepParams& P, const PState& user, i
   // than the particle kernel has resident workgroups, in 256-thread
   // workgroups (three resident per CU) without the closure features
   const int fill_slots = (NT == 256 && FEAT == FEAT_NONE && f.share_chunks > 0) ? std::min(f.part_wgs, f.fused_slots) : 0;
-  k_import_keys<<<nblk(N, 256), 256, 0, s>>>(user, P, g, f.cpad, f.key_tmp, f.rank_tmp, f.touched, f.n_touched);
+  k_import_keys<<<nblk(N, IMPORT_NT), IMPORT_NT, 0, s>>>(user, P, g, f.cpad, f.key_tmp, f.rank_tmp, f.touched, f.n_touched);
   k_scan<<<1, 1024, 0, s>>>(f.cpad, f.offsets, f.touched, f.n_touched, f.list[0], f.list_n + 0, g.n_keys, f.gen,
                             f.cl_count, SCAN_TOUCHED, IMPORT_PAD, f.share_chunks > 0 ? NT : 0, f.share_chunks, NT,
                             fill_slots);
-  import_permute(f, user, P.mat, f.buf[0], s);
+  import_permute(f, user, P, f.buf[0], f.buf[1], s);
   PartArgs A;
   A.N = N;
   A.counts = f.counts;
@@ -1348,7 +1465,7 @@ static void enqueue_call(FastPath& f, const StepParams& P, const PState& user, i
       // the state at time t0 + step now sits in the output buffer
       if (ckpt) {
         PState ck = packed_state((float*)(f.ck_base + (size_t)((f.ck_t0 + step) / f.ck_k) * f.ck_stride), N);
-        export_state(f, A.out, ck, P.mats, s);
+        export_state(f, A.out, A.in, ck, P.mats, s);
       }
     }
     // grid update of this step; from step 1 on, workgroup 0 also scans the
@@ -1381,7 +1498,7 @@ static void enqueue_call(FastPath& f, const StepParams& P, const PState& user, i
       wr = nwr;
     }
   }
-  if (f.do_export) export_state(f, f.buf[cur], user, P.mats, s);
+  if (f.do_export) export_state(f, f.buf[cur], f.buf[cur ^ 1], user, P.mats, s);
   f.last_buf = cur;
 }
 
@@ -1462,22 +1579,23 @@ void fast_sort_user(FastPath& f, const StepParams& P, const PState& user, Sorted
   const int N = f.N;
   share = share && f.share_chunks > 0;
   new_epoch(f, s);
-  k_import_keys<<<nblk(N, 256), 256, 0, s>>>(user, P, f.g, f.cpad, f.key_tmp, f.rank_tmp, f.touched, f.n_touched);
+  k_import_keys<<<nblk(N, IMPORT_NT), IMPORT_NT, 0, s>>>(user, P, f.g, f.cpad, f.key_tmp, f.rank_tmp, f.touched, f.n_touched);
   k_scan<<<1, 1024, 0, s>>>(f.cpad, f.offsets, f.touched, f.n_touched, out.list, out.list_n, f.g.n_keys, f.gen,
                             out.cl_count ? out.cl_count : f.cl_count, touched ? SCAN_TOUCHED : SCAN_DENSE,
                             IMPORT_PAD, share ? SORTED_NT : 0, f.share_chunks, SORTED_NT, share ? sorted_slots(f) : 0);
-  import_permute(f, user, P.mat, out.b, s);
+  import_permute(f, user, P, out.b, idle_buf(f, out.b), s);
 }
 
 void fast_sort_next(FastPath& f, const StepParams& P, const SortedState& prev, const PBuf& next, SortedState& out,
-                    uint32_t* map, hipStream_t s, bool touched) {
+                    uint32_t* map, hipStream_t s, bool touched, bool share) {
   const int N = f.N;
+  share = share && f.share_chunks > 0;
   new_epoch(f, s);
   k_keys_next<<<nblk(N, 256), 256, 0, s>>>(next.f, prev.b.key, N, P, f.g, f.counts, f.key_tmp, f.rank_tmp,
                                            touched ? f.touched : nullptr, f.n_touched);
   k_scan<<<1, 1024, 0, s>>>(f.counts, f.offsets, f.touched, f.n_touched, out.list, out.list_n, f.g.n_keys, f.gen,
-                            out.cl_count ? out.cl_count : f.cl_count, touched ? SCAN_TOUCHED : SCAN_DENSE, 1, 0, 0,
-                            SORTED_NT, 0);
+                            out.cl_count ? out.cl_count : f.cl_count, touched ? SCAN_TOUCHED : SCAN_DENSE, 1,
+                            share ? SORTED_NT : 0, f.share_chunks, SORTED_NT, share ? sorted_slots(f) : 0);
   k_sort_permute<<<nblk(N, 256), 256, 0, s>>>(next, out.b, N, f.key_tmp, f.rank_tmp, f.offsets, map);
 }
 
@@ -1589,8 +1707,10 @@ int fast_sort_snapshot(FastPath& f, const StepParams& P, const PState& user, int
   return 0;
 }
 
-void fast_export(FastPath& f, const StepParams& P, const PBuf& X, const PState& user, hipStream_t s) {
-  export_state(f, X, user, P.mats, s);
+void fast_export(FastPath& f, const StepParams& P, const PBuf& X, const PState& user, hipStream_t s, float* scratch) {
+  PBuf tmp = idle_buf(f, X);
+  if (scratch) tmp.f = scratch;
+  export_state(f, X, tmp, user, P.mats, s);
 }
 
 void fast_destroy(FastPath& f) {

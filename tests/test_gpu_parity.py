@@ -554,3 +554,22 @@ def test_shared_blocks_vs_oracle(n, grid, dt, wgs, share, grad):
     ex = rel(g0[0:3].T.double().cpu().numpy(), st0["x"].grad.numpy())
     say(f"  shared blocks, {wgs} workgroups: actions {ea:.2e} dL/dx0 {ex:.2e}")
     assert ea <= 1e-4 and ex <= 1e-4
+
+
+@pytest.mark.parametrize("n", [3, 64, 65, 1023, 1024, 1025, 2050])
+def test_import_and_export_at_wavefront_and_table_edges_vs_oracle(n):
+    """Particle counts around a wavefront's records and the import's key
+    table (1024 particles a workgroup), three kinds; one call of two steps and
+    a second call from its result; the rows the kernels do not carry (a
+    liquid's F, a solid's J) stay the user's."""
+    sc = scenes.tiny(n_particles=n, n_grid=24, steps=4, seed=3)
+    liq = liquid_mask(sc)
+    sc.F[liq] += 0.25
+    sc.J[~liq] = 3.0
+    sim = sim_of(sc)
+    sim.step(2)
+    sim.step(2)
+    g = sim.state_numpy()
+    assert np.array_equal(g["F"][liq], np.asarray(sc.F, np.float32)[liq])
+    assert np.array_equal(g["J"][~liq], np.asarray(sc.J, np.float32)[~liq])
+    compare_states(g, oracle_state(sc, 4), liq, tol_x=1e-6, tol=1e-4, tol_FJ=1e-5, n_grid=sc.n_grid)
