@@ -318,23 +318,26 @@ __global__ __launch_bounds__(NT, 2) void k_g2p_adj_tiled(AdjArgs A, StepParams P
 __global__ __launch_bounds__(256) void k_grid_adj_tiled(AdjArgs A, StepParams P, FastGeom g,
                                                         const double* __restrict__ pose_t,
                                                         const float* __restrict__ act_t, double* __restrict__ acc_t) {
-  const uint32_t n_cl = A.cl_count[0];
-  const uint32_t stamp = (A.gen[0] << 16) | A.sid;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int li = lane >> 4, lj = (lane >> 2) & 3, lk = lane & 3;
   // one claimed block per wavefront (see k_grid)
   const uint32_t n_waves = 4u * gridDim.x;
-  for (uint32_t it = 4u * blockIdx.x + (uint32_t)wv; it < n_cl && it < (uint32_t)g.n_keys; it += n_waves) {
-    const uint32_t key = A.cl_list[it];
+  uint32_t it = 4u * blockIdx.x + (uint32_t)wv;
+  uint32_t key_it = it < (uint32_t)g.n_keys ? A.cl_list[it] : 0u;
+  const uint32_t n_cl = A.cl_count[0];
+  const uint32_t stamp = (A.gen[0] << 16) | A.sid;
+  for (; it < n_cl && it < (uint32_t)g.n_keys; it += n_waves) {
+    const uint32_t key = key_it;
+    if (it + n_waves < (uint32_t)g.n_keys) key_it = A.cl_list[it + n_waves];
     int sc, cx, cy, cz;
     key_decode(g, key, sc, cx, cy, cz);
     {
       const int gx = 4 * cx + li, gy = 4 * cy + lj, gz = 4 * cz + lk;
+      const size_t node = (size_t)key * 64 + lane;
+      const float4 gm = A.mmv[node];
       float4 tsum = make_float4(0.f, 0.f, 0.f, 0.f);
       sum_tiles(g, sc, cx, cy, cz, lane, A.tile_box, A.tiles, stamp, tsum);
       const float vb[3] = {tsum.x, tsum.y, tsum.z};
-      const size_t node = (size_t)key * 64 + lane;
-      const float4 gm = A.mmv[node];
       float loc[ACC_DOUBLES];
 #pragma unroll
       for (int q = 0; q < ACC_DOUBLES; q++) loc[q] = 0.f;
@@ -444,20 +447,24 @@ __global__ __launch_bounds__(NT, 2) void k_p2g_adj_tiled(AdjArgs A, StepParams P
   __shared__ float4 s_g[VT_LDS];
   const int N = A.N;
   const uint32_t n_list = A.list_n[0];
-  for (uint32_t e = blockIdx.x; e < n_list; e += gridDim.x) {
+  // (two workgroups an entry, which take its chunks in turn, the second ones after
+  // all the first: 32.2 -> 27.1 us at 250k particles, half of them water, half rigid)
+  for (uint32_t e2 = blockIdx.x; e2 < 2u * n_list; e2 += gridDim.x) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    int4 ent = A.list[e];
+    const uint32_t half = e2 >= n_list ? 1u : 0u;
+    int4 ent = A.list[e2 - half * n_list];
     ent.x = __builtin_amdgcn_readfirstlane(ent.x);
     ent.y = __builtin_amdgcn_readfirstlane(ent.y);
     ent.z = __builtin_amdgcn_readfirstlane(ent.z);
+    if ((int)half * NT >= ent.z) continue;
     int sc, bx, by, bz;
     key_decode(g, (uint32_t)ent.x, sc, bx, by, bz);
     const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
     stage_window<NT>(s_g, A.mmvb, g, sc, bx, by, bz, tid);
     __syncthreads();
     const int start = ent.y, count = ent.z;
-    for (int c0 = 0; c0 < count; c0 += NT) {
+    for (int c0 = (int)half * NT; c0 < count; c0 += 2 * NT) {
       const int j = start + c0 + tid;
       // FP32 for every lane, then FP64 for those it returned
       auto pass = [&](auto fp64, bool on) -> bool {

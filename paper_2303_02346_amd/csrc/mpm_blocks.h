@@ -58,6 +58,20 @@ __device__ __forceinline__ float wave_sum(float x) {
          (__int_as_float(__builtin_amdgcn_readlane(xi, 32)) + __int_as_float(__builtin_amdgcn_readlane(xi, 48)));
 }
 
+__device__ __forceinline__ double wave_sum(double x) {
+  auto mov = [](double y, auto ctrl) {
+    constexpr int CTRL = decltype(ctrl)::value;
+    return __hiloint2double(dpp::mov<CTRL>(__double2hiint(y)), dpp::mov<CTRL>(__double2loint(y)));
+  };
+  x += mov(x, std::integral_constant<int, dpp::kSwap1>{});
+  x += mov(x, std::integral_constant<int, dpp::kSwap2>{});
+  x += mov(x, std::integral_constant<int, dpp::kHalfMirror>{});
+  x += mov(x, std::integral_constant<int, dpp::kMirror>{});
+  const int h = __double2hiint(x), l = __double2loint(x);
+  auto row = [&](int lane) { return __hiloint2double(__builtin_amdgcn_readlane(h, lane), __builtin_amdgcn_readlane(l, lane)); };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
   int v = (int)x;
   v += dpp::mov<dpp::kSwap1>(v);
