@@ -50,7 +50,8 @@ __global__ __launch_bounds__(POSE_NT) void k_pose(int n_scenes, int t0, int n, f
 #pragma unroll
     for (int k = 0; k < 12; k++) sP[0][tid][k] = v[k];
     __syncthreads();
-    for (int off = 1; off < POSE_NT; off <<= 1) {
+    // (only as far as the chunk's steps reach: a call of 10 steps 7.1 -> 5.9 us, of one 6.7 -> 3.3)
+    for (int off = 1; off < m; off <<= 1) {
       if (tid >= off) {
         const double* L = sP[buf][tid - off];
         double w[12];
