@@ -132,7 +132,7 @@ __global__ __launch_bounds__(IMPORT_NT) void k_import_keys(PState u, StepParams 
 // one tile the keys and counts are read once, and before the number of keys is
 // known (two dependent round trips; three and three again for the second pass
 // before, when the scan set the length of that step's grid kernel: 13.4 us for
-// the 208 blocks above, now 9.5).
+// the 208 blocks above, now 9.4).
 template <int NT>
 __device__ void scan_touched(uint32_t* __restrict__ counts, uint32_t* __restrict__ offsets,
                              const uint32_t* __restrict__ touched, uint32_t* __restrict__ n_touched,

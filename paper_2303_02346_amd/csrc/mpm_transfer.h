@@ -182,7 +182,7 @@ __device__ __forceinline__ void weight_grad_sum(const float4* __restrict__ tile,
 // it covers; the tiles that cover any (about a third of the 27) are then added
 // eight loads at a time.  (All 27 neighbours in turn, box by box through LDS
 // permutes, cost about 800 vector instructions a block, and each second tile a
-// round trip of its own: k_grid 9.8 us at 250k particles on 128^3, now 7.4,
+// round trip of its own: k_grid 9.8 us at 250k particles on 128^3, now 6.7,
 // 35.9 at 1M on 256^3, now 22.0.)
 __device__ __forceinline__ void sum_tiles(const FastGeom& g, int sc, int cx, int cy, int cz, int lane,
                                           const int4* __restrict__ tile_box, const float* __restrict__ tiles,
@@ -242,19 +242,23 @@ __device__ __forceinline__ void sum_tiles(const FastGeom& g, int sc, int cx, int
   if (nb) b = boxes[half];
   const int c = cover(b, nb);
   const int slot = c ? b.z : 0;
-  // (entry 0 of every neighbour first)
-  add(half == 0 ? c : 0, slot);
   const int extra = (nb && (uint32_t)b.y == stamp) ? (b.x >> 24) & 7 : 0;
-  if (__ballot(extra > 0)) {
-    add(half == 1 ? c : 0, slot);
-    const int ex = max(extra, __shfl_xor(extra, 32));
-#pragma unroll 1
-    for (int s = 2; s < NSUB && __ballot(ex >= s); s += 2) {
-      const bool on = nb && ex >= s + half;
-      int4 b2 = make_int4(0, 0, 0, 0);
-      if (on) b2 = boxes[s + half];
-      const int c2 = cover(b2, on);
-      add(c2, c2 ? b2.z : 0);
+  const int ex = max(extra, __shfl_xor(extra, 32));
+  const bool more = __ballot(ex > 1) != 0ull;
+  // (the boxes of entries 2 and up are loaded together, ahead of the first sums)
+  constexpr int NP = NSUB / 2 - 1;
+  int4 b2[NP];
+#pragma unroll
+  for (int r = 0; r < NP; r++) {
+    b2[r] = make_int4(0, 0, 0, 0);
+    if (more && nb && ex >= 2 * r + 2 + half) b2[r] = boxes[2 * r + 2 + half];
+  }
+  add(c, slot);   // (lane order: entry 0 of every neighbour first, then their entries 1)
+  if (more) {
+#pragma unroll
+    for (int r = 0; r < NP; r++) {
+      const int c2 = cover(b2[r], nb && ex >= 2 * r + 2 + half);
+      add(c2, c2 ? b2[r].z : 0);
     }
   }
 }
