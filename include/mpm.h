@@ -237,7 +237,8 @@ enum {
   MPM_OPT_ADJOINT = 5,        /* 0: tiled (default), 1: plain */
   MPM_OPT_N_KEYS = 6,         /* read only: grid blocks of the context (rows of a sort snapshot list) */
   MPM_OPT_SHARE_CHUNKS = 7    /* a block holding more than this many chunks (of MPM_OPT_PART_THREADS
-                                 particles) is shared by two particle workgroups; 0 = never; default 2 */
+                                 particles) is shared by two particle workgroups, or by one per chunk while
+                                 all chunks fit the resident workgroups; 0 = never; default 2 */
 };
 int mpm_set_option(mpm_ctx* c, int32_t key, int32_t value);
 int mpm_get_option(const mpm_ctx* c, int32_t key, int32_t* value);
