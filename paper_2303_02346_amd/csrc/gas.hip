@@ -734,24 +734,26 @@ __global__ __launch_bounds__(BOTTOM_THREADS) void k_bottom(BottomArgs B) {
 // transforms.  Each axis transform is a dense contraction with an n x n
 // matrix: out[k] = sum_i M[i][k] in[i] along the axis.
 // ---------------------------------------------------------------------------
-// The basis is even or odd about the middle of the axis (column k has the
-// parity of k), so each transform is two contractions with half as many terms:
-// the even outputs from in[i] + in[n - 1 - i], the odd ones from the
-// differences (and the inverse from even and odd inputs, its outputs i and
-// n - 1 - i the sum and the difference of the two).  They run on the matrix
-// cores in FP32 (v_mfma_f32_16x16x4f32), 16 outputs of one parity x 16 lines a
-// tile.  A wavefront takes 16 C lines and a tile of outputs of both parities at
-// a time; the wavefronts of a workgroup share the lines.  Nothing goes through
-// LDS: the matrix is laid out once in the order in which lanes hold it, and the
-// terms are taken in an order (i = 16 s + 4 lr + t) in which a lane's terms are
-// contiguous in memory along z, and its lines along y and x, so that every load
-// and store moves 8 or 16 bytes a lane.  The last forward pass (x), the
-// division by the eigenvalues and the first inverse pass are one launch, the
-// coefficients in LDS between them.  At 128^3: 8.0 and 12.1 us forward and back along z, 8.0
-// and 7.5 along y, 12.4 for both along x (a pass's floor: 16.8 MB at the rate of a
-// large copy, 3.2 us; at two wavefronts per SIMD the latency of the loads ahead
-// of 64 products is the rest).  Full-length contractions staged through LDS,
-// every line chunk read eight times, took 14 us each.
+// The contractions run on the matrix cores in FP32 (v_mfma_f32_16x16x4f32),
+// 16 outputs x 16 lines a tile, two accumulators over alternate steps of four
+// terms, added at the end.  A wavefront takes 16 C lines and AXIS_MT tiles of
+// outputs at a time; the wavefronts of a workgroup share the lines.  Nothing
+// goes through LDS on the way in: the matrix is laid out once in the order in
+// which lanes hold it; along y and x a lane loads its C adjacent lines at once,
+// along z four adjacent terms, exchanged over the lanes that hold a line (with
+// 4-byte loads of the terms as they are needed 18.7 and 22.4 us).  The last forward pass (x), the division by the eigenvalues and the first
+// inverse pass are one launch, the coefficients in LDS between them.  At 128^3:
+// 10.6 and 14.1 us forward and back along z, 9.7 and 9.6 along y and 17.5 for both
+// along x (a pass's floor: 16.8 MB at the rate of a large copy, 3.2 us, and 537
+// MFLOP, 3.5 us on all matrix cores; at two wavefronts per SIMD the latency of the
+// loads ahead of each 32 products is the rest); 14 us each when 16 lines x 16
+// outputs a wavefront went through LDS and every line chunk was read eight times.
+// One output tile at a time takes 12 us along y and 20 along x, four 12 and 25.
+// Half-length contractions by the parity of the basis (sums and differences of the
+// two halves of a line) took 48 us a solve, not 61, but round differently:
+// gradients that hang on the far tail of the emitter moved by their own error, now
+// and then to twice it.  Here every sum is taken in the order of the terms, and
+// the results are the bits of the contractions staged through LDS.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct AxisArgs {
@@ -768,10 +770,11 @@ struct AxisArgs {
   int nz;
 };
 
-enum { AXIS_FWD = 0, AXIS_INV = 1, AXIS_BOTH = 2 };
+enum { AXIS_ONE = 0, AXIS_BOTH = 1 };
 
-// 16-term steps and 16-output tiles of one parity of an axis of n values
-__host__ __device__ inline int axis_steps(int n) { return (n / 2 + 15) / 16; }
+// 16-term steps, and 16-output tiles, of an axis of n values
+__host__ __device__ inline int axis_steps(int n) { return (n + 15) / 16; }
+constexpr int AXIS_MT = 2;   // output tiles a wavefront takes together
 
 template <int C> struct AxisVec;
 template <> struct AxisVec<2> { using T = float2; };
@@ -779,31 +782,53 @@ template <int C> __device__ __forceinline__ float axis_get(const typename AxisVe
   return reinterpret_cast<const float*>(&v)[c];
 }
 
-// Both parities of output tile m: acc[p][c] = 16 outputs x 16 lines (line tile
-// c).  load(i, t, a): the C values of term i = 16 s + 4 lr + t of the even and
-// the odd contraction.
+// 4 x 4 transpose over the four rows of 16 lanes: lane (lr, lc) gives v[t] to
+// element lr of lane (t, lc)
+__device__ __forceinline__ float4 axis_transpose(float4 v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const uint32_t x = __float_as_uint(v.x), y = __float_as_uint(v.y), z = __float_as_uint(v.z), w = __float_as_uint(v.w);
+  const u2 xz = __builtin_amdgcn_permlane32_swap(x, z, false, false);   // rows 2, 3 of x with rows 0, 1 of z
+  const u2 yw = __builtin_amdgcn_permlane32_swap(y, w, false, false);
+  const u2 xy = __builtin_amdgcn_permlane16_swap(xz[0], yw[0], false, false);   // rows 1, 3 of x with rows 0, 2 of y
+  const u2 zw = __builtin_amdgcn_permlane16_swap(xz[1], yw[1], false, false);
+  return make_float4(__uint_as_float(xy[0]), __uint_as_float(xy[1]), __uint_as_float(zw[0]), __uint_as_float(zw[1]));
+}
+
+// Output tiles m0 .. m0 + AXIS_MT - 1: res[q][c] = 16 outputs x 16 lines (line
+// tile c).  load(s, e): the C values of each of the terms 16 s + 4 t + lr, t < 4.
 template <int C, class Load>
-__device__ __forceinline__ void axis_contract(const float4* __restrict__ M, int S, int m, int lane, Load&& load,
-                                              floatx4 (&acc)[2][C]) {
+__device__ __forceinline__ void axis_contract(const float4* __restrict__ M, int S, int m0, int lane, Load&& load,
+                                              floatx4 (&res)[AXIS_MT][C]) {
+  floatx4 acc[2][AXIS_MT][C];
+  const float4* Mq[AXIS_MT];
 #pragma unroll
-  for (int p = 0; p < 2; p++)
+  for (int q = 0; q < AXIS_MT; q++) {
+    Mq[q] = M + (size_t)min(m0 + q, S - 1) * S * 64 + lane;   // (a tile past the last is not stored)
 #pragma unroll
-    for (int c = 0; c < C; c++) acc[p][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const float4* Me = M + (size_t)m * S * 64 + lane;
-  const float4* Mo = Me + (size_t)S * S * 64;
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+      for (int c = 0; c < C; c++) acc[u][q][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll 2
   for (int s = 0; s < S; s++) {
-    const float4 fe = Me[s * 64], fo = Mo[s * 64];
-    float e[4][C], o[4][C];
-    load(s, e, o);
+    float4 f[AXIS_MT];
+#pragma unroll
+    for (int q = 0; q < AXIS_MT; q++) f[q] = Mq[q][s * 64];
+    float e[4][C];
+    load(s, e);
 #pragma unroll
     for (int t = 0; t < 4; t++)
 #pragma unroll
-      for (int c = 0; c < C; c++) {
-        acc[0][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fe)[t], e[t][c], acc[0][c], 0, 0, 0);
-        acc[1][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fo)[t], o[t][c], acc[1][c], 0, 0, 0);
-      }
+      for (int q = 0; q < AXIS_MT; q++)
+#pragma unroll
+        for (int c = 0; c < C; c++)
+          acc[t & 1][q][c] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&f[q])[t], e[t][c], acc[t & 1][q][c], 0, 0, 0);
   }
+#pragma unroll
+  for (int q = 0; q < AXIS_MT; q++)
+#pragma unroll
+    for (int c = 0; c < C; c++) res[q][c] = acc[0][q][c] + acc[1][q][c];
 }
 
 template <bool INNER, int KIND, int C>
@@ -813,8 +838,9 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
   constexpr int LINES = 16 * C;
   const int lane = threadIdx.x & 63, lr = lane >> 4, lc = lane & 15;
   const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int n = X.n, h = n / 2, S = axis_steps(n);
+  const int n = X.n, S = axis_steps(n);
   const int line0 = blockIdx.x * LINES;
+  floatx4 res[AXIS_MT][C];
   if (INNER) {
     // line tile c of the lane: row line0 + 16 c + lc
     const float* in[C];
@@ -825,48 +851,24 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
       on[c] = line < X.A;
       in[c] = X.in + (size_t)(on[c] ? line : 0) * n;
     }
-    for (int m = wv; m < S; m += nw) {
-      floatx4 acc[2][C];
-      axis_contract<C>(X.M, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
-        const int i = 16 * s + 4 * lr;
-        const bool in_h = i < h;   // (past h the matrix is zero; the loads stay in the row)
-        const int ia = in_h ? (KIND == AXIS_FWD ? i : 2 * i) : 0;
+    for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+      axis_contract<C>(X.M, S, m0, lane, [&](int s, float (&e)[4][C]) {
+        const int i = min(16 * s + 4 * lr, n - 4);   // (past n the matrix is zero)
 #pragma unroll
         for (int c = 0; c < C; c++) {
-          const float4 a = *(const float4*)(in[c] + ia);
-          if (KIND == AXIS_FWD) {
-            const float4 b = *(const float4*)(in[c] + (n - 4 - ia));
-            e[0][c] = a.x + b.w; o[0][c] = a.x - b.w;
-            e[1][c] = a.y + b.z; o[1][c] = a.y - b.z;
-            e[2][c] = a.z + b.y; o[2][c] = a.z - b.y;
-            e[3][c] = a.w + b.x; o[3][c] = a.w - b.x;
-          } else {
-            // (an axis of n = 4 mod 8 ends between the two loads)
-            const float4 b = *(const float4*)(in[c] + (ia + 4 < n ? ia + 4 : ia));
-            e[0][c] = a.x; o[0][c] = a.y;
-            e[1][c] = a.z; o[1][c] = a.w;
-            e[2][c] = b.x; o[2][c] = b.y;
-            e[3][c] = b.z; o[3][c] = b.w;
-          }
+          const float4 a = axis_transpose(*(const float4*)(in[c] + i));
+          e[0][c] = a.x; e[1][c] = a.y; e[2][c] = a.z; e[3][c] = a.w;
         }
-      }, acc);
-      const int kk = 16 * m + 4 * lr;   // the lane's outputs kk .. kk + 3 of each parity (h is even: two or four of them)
-      if (kk >= h) continue;
-      const bool four = kk + 2 < h;
+      }, res);
 #pragma unroll
-      for (int c = 0; c < C; c++) {
-        if (!on[c]) continue;
-        float* o = X.out + (size_t)(line0 + 16 * c + lc) * n;
-        const floatx4 ev = acc[0][c], od = acc[1][c];
-        if (KIND == AXIS_FWD) {
-          *(float4*)(o + 2 * kk) = make_float4(ev[0], od[0], ev[1], od[1]);
-          if (four) *(float4*)(o + 2 * kk + 4) = make_float4(ev[2], od[2], ev[3], od[3]);
-        } else if (four) {
-          *(float4*)(o + kk) = make_float4(ev[0] + od[0], ev[1] + od[1], ev[2] + od[2], ev[3] + od[3]);
-          *(float4*)(o + n - 4 - kk) = make_float4(ev[3] - od[3], ev[2] - od[2], ev[1] - od[1], ev[0] - od[0]);
-        } else {
-          *(float4*)(o + kk) = make_float4(ev[0] + od[0], ev[1] + od[1], ev[1] - od[1], ev[0] - od[0]);
-        }
+      for (int q = 0; q < AXIS_MT; q++) {
+        const int k = 16 * (m0 + q) + 4 * lr;   // (n is a multiple of 4)
+        if (k >= n) continue;
+#pragma unroll
+        for (int c = 0; c < C; c++)
+          if (on[c])
+            *(float4*)(X.out + (size_t)(line0 + 16 * c + lc) * n + k) =
+                make_float4(res[q][c][0], res[q][c][1], res[q][c][2], res[q][c][3]);
       }
     }
     return;
@@ -878,90 +880,65 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
   const float* in = X.in + plane + (on ? line : 0);
   float* out = X.out + plane + line;
   const uint32_t B = (uint32_t)X.B;
-  // forward: terms from memory; outputs to memory (FWD) or to LDS (BOTH)
-  if (KIND != AXIS_INV) {
-    for (int m = wv; m < S; m += nw) {
-      floatx4 acc[2][C];
-      axis_contract<C>(X.M, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
+  float lyz[C];
+  const bool divide = X.lx != nullptr;
+  if (divide) {
+    const int l = on ? line : 0, ky = l / X.nz, kz = l - ky * X.nz;   // (C divides nz: the lines share ky)
+#pragma unroll
+    for (int c = 0; c < C; c++) { lyz[c] = X.lz[kz + c]; }
+    const float ly = X.ly[ky];
+    for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+      axis_contract<C>(X.M, S, m0, lane, [&](int s, float (&e)[4][C]) {
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-          const int i = 16 * s + 4 * lr + t, ia = i < h ? i : 0;   // (past h the matrix is zero)
-          const V a = *(const V*)(in + (uint32_t)ia * B), b = *(const V*)(in + (uint32_t)(n - 1 - ia) * B);
+          const V a = *(const V*)(in + (uint32_t)min(16 * s + 4 * t + lr, n - 1) * B);
 #pragma unroll
-          for (int c = 0; c < C; c++) {
-            e[t][c] = axis_get<C>(a, c) + axis_get<C>(b, c);
-            o[t][c] = axis_get<C>(a, c) - axis_get<C>(b, c);
-          }
+          for (int c = 0; c < C; c++) e[t][c] = axis_get<C>(a, c);
         }
-      }, acc);
-      float lyz[C];
-      const bool divide = KIND == AXIS_BOTH || X.lx;
-      if (divide) {
-        const int l = on ? line : 0, ky = l / X.nz, kz = l - ky * X.nz;   // (C divides nz: the lines share ky)
+      }, res);
 #pragma unroll
-        for (int c = 0; c < C; c++) lyz[c] = X.ly[ky] + X.lz[kz + c];
-      }
+      for (int q = 0; q < AXIS_MT; q++)
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int kk = 16 * m + 4 * lr + r;
-        if (kk >= h) continue;
-#pragma unroll
-        for (int p = 0; p < 2; p++) {
-          const int k = 2 * kk + p;
+        for (int r = 0; r < 4; r++) {
+          const int k = 16 * (m0 + q) + 4 * lr + r;
+          if (k >= n) continue;
           V v;
           float* f = reinterpret_cast<float*>(&v);
-          if (!divide) {
 #pragma unroll
-            for (int c = 0; c < C; c++) f[c] = acc[p][c][r];
-          } else {
-            const float lx = X.lx[k];
-#pragma unroll
-            for (int c = 0; c < C; c++) {
-              const float lam = lx + lyz[c];
-              f[c] = lam != 0.f ? acc[p][c][r] / lam : 0.f;
-            }
+          for (int c = 0; c < C; c++) {
+            const float lam = X.lx[k] + ly + lyz[c];
+            f[c] = lam != 0.f ? res[q][c][r] / lam : 0.f;
           }
           if (KIND == AXIS_BOTH) *(V*)(s_coef + k * LINES + C * lc) = v;
           else if (on) *(V*)(out + (uint32_t)k * B) = v;
         }
-      }
     }
+    if (KIND != AXIS_BOTH) return;
+    __syncthreads();
   }
-  if (KIND == AXIS_FWD) return;
-  if (KIND == AXIS_BOTH) __syncthreads();
   const float4* Mi = KIND == AXIS_BOTH ? X.M2 : X.M;
-  for (int m = wv; m < S; m += nw) {
-    floatx4 acc[2][C];
-    axis_contract<C>(Mi, S, m, lane, [&](int s, float (&e)[4][C], float (&o)[4][C]) {
+  for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+    axis_contract<C>(Mi, S, m0, lane, [&](int s, float (&e)[4][C]) {
 #pragma unroll
       for (int t = 0; t < 4; t++) {
-        const int i = 16 * s + 4 * lr + t, ia = i < h ? i : 0;
-        V a, b;
-        if (KIND == AXIS_BOTH) {
-          a = *(const V*)(s_coef + 2 * ia * LINES + C * lc);
-          b = *(const V*)(s_coef + (2 * ia + 1) * LINES + C * lc);
-        } else {
-          a = *(const V*)(in + (uint32_t)(2 * ia) * B);
-          b = *(const V*)(in + (uint32_t)(2 * ia + 1) * B);
-        }
+        const int i = min(16 * s + 4 * t + lr, n - 1);
+        const V a = KIND == AXIS_BOTH ? *(const V*)(s_coef + i * LINES + C * lc) : *(const V*)(in + (uint32_t)i * B);
 #pragma unroll
-        for (int c = 0; c < C; c++) { e[t][c] = axis_get<C>(a, c); o[t][c] = axis_get<C>(b, c); }
+        for (int c = 0; c < C; c++) e[t][c] = axis_get<C>(a, c);
       }
-    }, acc);
+    }, res);
     if (!on) continue;
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int i = 16 * m + 4 * lr + r;
-      if (i >= h) continue;
-      V a, b;
+    for (int q = 0; q < AXIS_MT; q++)
 #pragma unroll
-      for (int c = 0; c < C; c++) {
-        reinterpret_cast<float*>(&a)[c] = acc[0][c][r] + acc[1][c][r];
-        reinterpret_cast<float*>(&b)[c] = acc[0][c][r] - acc[1][c][r];
+      for (int r = 0; r < 4; r++) {
+        const int k = 16 * (m0 + q) + 4 * lr + r;
+        if (k >= n) continue;
+        V v;
+#pragma unroll
+        for (int c = 0; c < C; c++) reinterpret_cast<float*>(&v)[c] = res[q][c][r];
+        *(V*)(out + (uint32_t)k * B) = v;
       }
-      *(V*)(out + (uint32_t)i * B) = a;
-      *(V*)(out + (uint32_t)(n - 1 - i) * B) = b;
-    }
   }
 }
 
@@ -1418,8 +1395,8 @@ Layout plan(const gas_desc* d) {
     L.spec_tmp = take(nc * 4);
     for (int a = 0; a < 3; a++) {
       const size_t st = axis_steps(nn[a]);
-      L.dct[a] = take(2 * st * st * 64 * sizeof(float4));
-      L.idct[a] = take(2 * st * st * 64 * sizeof(float4));
+      L.dct[a] = take(st * st * 64 * sizeof(float4));
+      L.idct[a] = take(st * st * 64 * sizeof(float4));
       L.lam[a] = take((size_t)nn[a] * 4);
     }
   }
@@ -1560,12 +1537,11 @@ void mg_solve(gas_ctx* c, float* psi0, float* f0) {
   }
 }
 
-// one launch of transforms: 32 lines a workgroup (64 lines, with 16-byte loads
-// along y and x, leave one wavefront per SIMD at 128^3: 9.7 to 11.8 us a pass, 17.1
-// along x)
+// one launch of transforms: 32 lines a workgroup, two wavefronts per SIMD at 128^3
+// (16 lines along z: 11.2 and 15.1 us)
 template <bool INNER, int KIND, int C = 2>
 void launch_axis(const AxisArgs& X, int lines, int planes, hipStream_t s) {
-  const unsigned nt = 64u * (unsigned)min(4, axis_steps(X.n));
+  const unsigned nt = 64u * (unsigned)min(4, (axis_steps(X.n) + AXIS_MT - 1) / AXIS_MT);
   const size_t lds = KIND == AXIS_BOTH ? (size_t)X.n * 16 * C * 4 : 0;
   k_axis<INNER, KIND, C><<<dim3((lines + 16 * C - 1) / (16 * C), planes), nt, lds, s>>>(X);
 }
@@ -1589,8 +1565,8 @@ void spectral_solve(gas_ctx* c, float* psi0, const float* f0) {
   // one event pair around the back-to-back transforms (read as six): a pair
   // per launch would add its own overhead to each
   c->t_smooth.begin(s);
-  launch_axis<true, AXIS_FWD>(args(f0, T, Mf[2], nz, nx * ny, 1), nx * ny, 1, s);
-  launch_axis<false, AXIS_FWD>(args(T, psi0, Mf[1], ny, nx, nz), nz, nx, s);
+  launch_axis<true, AXIS_ONE>(args(f0, T, Mf[2], nz, nx * ny, 1), nx * ny, 1, s);
+  launch_axis<false, AXIS_ONE>(args(T, psi0, Mf[1], ny, nx, nz), nz, nx, s);
   // along x in place: every workgroup has read its lines when it writes them
   // (with more than 512 values an axis does not fit the 64 KB of a workgroup's
   // coefficients: two launches)
@@ -1604,11 +1580,11 @@ void spectral_solve(gas_ctx* c, float* psi0, const float* f0) {
   if (both) {
     launch_axis<false, AXIS_BOTH>(X, ny * nz, 1, s);
   } else {
-    launch_axis<false, AXIS_FWD>(X, ny * nz, 1, s);
-    launch_axis<false, AXIS_INV>(args(T, psi0, Mi[0], nx, 1, ny * nz), ny * nz, 1, s);
+    launch_axis<false, AXIS_ONE>(X, ny * nz, 1, s);
+    launch_axis<false, AXIS_ONE>(args(T, psi0, Mi[0], nx, 1, ny * nz), ny * nz, 1, s);
   }
-  launch_axis<false, AXIS_INV>(args(psi0, T, Mi[1], ny, nx, nz), nz, nx, s);
-  launch_axis<true, AXIS_INV>(args(T, psi0, Mi[2], nz, nx * ny, 1), nx * ny, 1, s);
+  launch_axis<false, AXIS_ONE>(args(psi0, T, Mi[1], ny, nx, nz), nz, nx, s);
+  launch_axis<true, AXIS_ONE>(args(T, psi0, Mi[2], nz, nx * ny, 1), nx * ny, 1, s);
   c->t_smooth.end(s);
 }
 
@@ -1740,23 +1716,22 @@ int gas_create(const gas_desc* d, void* workspace_dev, size_t ws_bytes, void* st
     const int nn[3] = {d->nx, d->ny, d->nz};
     for (int a = 0; a < 3; a++) {
       const int n = nn[a];
-      // as fragments [parity][output tile][step][lane (lr, lc)][t]: term
-      // 16 step + 4 lr + t, output 16 tile + lc of the parity (forward: rows i,
-      // outputs k = 2 kk + parity; inverse: rows k, outputs i); zero past n / 2
-      const int h = n / 2, st = axis_steps(n);
-      std::vector<float> C((size_t)2 * st * st * 256, 0.f), Ci(C.size(), 0.f), lam(n);
+      // as fragments [output tile][step][lane (lr, lc)][t]: term 16 step + 4 t + lr,
+      // output 16 tile + lc (forward: rows i, outputs k; inverse: rows k, outputs
+      // i); zero past n
+      const int st = axis_steps(n);
+      std::vector<float> C((size_t)st * st * 256, 0.f), Ci(C.size(), 0.f), lam(n);
       size_t q = 0;
-      for (int par = 0; par < 2; par++)
-        for (int m = 0; m < st; m++)
-          for (int sp = 0; sp < st; sp++)
-            for (int ln = 0; ln < 64; ln++)
-              for (int tt = 0; tt < 4; tt++, q++) {
-                const int term = 16 * sp + 4 * (ln >> 4) + tt, o = 16 * m + (ln & 15);
-                if (term >= h || o >= h) continue;
-                const int kf = 2 * o + par, ki = 2 * term + par;
-                C[q] = (float)cos(M_PI * kf * (term + 0.5) / n);
-                Ci[q] = (float)(cos(M_PI * ki * (o + 0.5) / n) * (ki == 0 ? 1.0 / n : 2.0 / n));
-              }
+      for (int m = 0; m < st; m++)
+        for (int sp = 0; sp < st; sp++)
+          for (int ln = 0; ln < 64; ln++)
+            for (int tt = 0; tt < 4; tt++, q++) {
+              const int term = 16 * sp + 4 * tt + (ln >> 4), o = 16 * m + (ln & 15);
+              if (term >= n || o >= n) continue;
+              const double vf = cos(M_PI * o * (term + 0.5) / n), vi = cos(M_PI * term * (o + 0.5) / n);
+              C[q] = (float)vf;
+              Ci[q] = (float)(vi * (term == 0 ? 1.0 / n : 2.0 / n));
+            }
       for (int k = 0; k < n; k++) {
         const double sk = sin(M_PI * k / (2.0 * n));
         lam[k] = (float)(-4.0 * sk * sk);

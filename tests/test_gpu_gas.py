@@ -259,8 +259,8 @@ def test_initial_states_are_loaded_again():
 
 @pytest.mark.parametrize("n", [(8, 12, 20), (20, 36, 8), (12, 68, 44), (516, 8, 12)])
 def test_gas_axis_tiles_vs_oracle(n):
-    """Axis lengths at the edges of the transform's tiles: halves below one
-    16-output tile, of 4 q + 2 outputs, one past a tile, and an x axis whose
+    """Axis lengths at the edges of the transform's tiles: below and just
+    past one 16-output tile, past a pair of tiles, and an x axis whose
     coefficients do not fit one workgroup (two launches)."""
     sc = scenes.gas_room(n=n, steps=2, seed=11, n_scalars=1, translate=True)
     say(f"gas {n}, 2 steps")
