@@ -15,7 +15,6 @@ import numpy as np
 import torch
 
 from . import _lib
-from . import scenes as scenes_mod
 from .scenes import Scene, concat_scenes
 
 STATE_ROWS = 25   # x(3) v(3) C(9) F(9) J(1), each row of length N
@@ -99,7 +98,6 @@ class Simulator:
         # converting the host arrays for every rollout took longer than the
         # rollout (6 ms at 250k particles)
         self._buf0 = torch.from_numpy(self._host_state(arrs)).to(self.device)
-        self._rigid = any(m.kind == scenes_mod.RIGID for m in mats)
         self.actions = torch.zeros(self.horizon, self.S, 6, dtype=torch.float32, device=self.device)
         acts = np.zeros((self.horizon, self.S, 6))
         for s, sc in enumerate(self.scenes):
@@ -201,8 +199,9 @@ class Simulator:
         self.set_actions(self.actions)
 
     def set_state(self):
-        if self._rigid:          # (rest shapes are taken from the state on the library's stream)
-            self._sync_in()
+        # (the state may have been written on this stream, and the step that
+        # reads it may be called under another)
+        self._sync_in()
         self._state = self.state_struct()
         _lib.check(_lib.lib().mpm_set_state(self.ctx, ctypes.byref(self._state)), "mpm_set_state", self.ctx)
 

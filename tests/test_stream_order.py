@@ -1,0 +1,69 @@
+"""Calls that hand over device memory keep their order with torch's streams.
+
+On the CPU the library and the streams are stand-ins that write down what is
+called; on the GPU the same calls are made from two streams."""
+import types
+
+import pytest
+import torch
+
+from paper_2303_02346_amd import _lib, scenes, sim as sim_mod
+
+
+class Recorder:
+    """A library, stream or tensor that notes every call on it."""
+
+    def __init__(self, log, name):
+        self._log, self._name = log, name
+
+    def __getattr__(self, what):
+        def call(*a, **k):
+            self._log.append(f"{self._name}.{what}")
+            return 0
+        return call
+
+
+def simulator_stub(monkeypatch):
+    log = []
+    sim = object.__new__(sim_mod.Simulator)
+    sim.ctx, sim.device = types.SimpleNamespace(value=0), torch.device("cpu")
+    sim.mat, sim.buf = torch.zeros(4, dtype=torch.uint8), torch.zeros(sim_mod.STATE_ROWS, 4)
+    sim.stream = Recorder(log, "library_stream")
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Recorder(log, "current_stream"))
+    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log, "lib"))
+    return sim, log
+
+
+def test_set_state_joins_the_current_stream(monkeypatch):
+    """The state may have been written on the stream that is current at the
+    call, and the step that reads it may follow under another one."""
+    sim, log = simulator_stub(monkeypatch)
+    sim.set_state()
+    assert log == ["library_stream.wait_stream", "lib.mpm_set_state"]
+
+
+def delayed(stream):
+    """About 0.1 s of work on the stream, for what follows on it to be late."""
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)
+
+
+@pytest.mark.gpu
+def test_state_written_on_another_stream_is_the_one_stepped():
+    sc = scenes.tiny(n_particles=300, steps=4, seed=3)
+    sim = sim_mod.Simulator(sc)
+    start = sim.buf.clone()
+    sim.step(4)
+    ref = sim.buf.clone()
+    sim.reset()
+    sim.buf.zero_()
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    delayed(other)
+    with torch.cuda.stream(other):
+        sim.buf.copy_(start)
+        sim.set_state()
+    sim.set_actions(sim.actions)
+    sim.step(4)
+    # (the sums' order differs from run to run)
+    assert torch.allclose(sim.buf, ref, rtol=0, atol=1e-5 * float(ref.abs().max()))
