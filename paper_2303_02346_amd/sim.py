@@ -190,8 +190,11 @@ class Simulator:
 
     def load(self, arrs=None):
         """Copy initial particle arrays (host, float64 from the scene
-        generator) into the device state, FP32; the scenes' own by default."""
+        generator) into the device state, FP32; the scenes' own by default.
+        The state is there when the call returns, for every stream."""
         self.buf.copy_(self._buf0 if arrs is None else torch.from_numpy(self._host_state(arrs)))
+        # (a copy within the device only waits for its own stream)
+        torch.cuda.current_stream(self.device).synchronize()
 
     def reset(self, arrs=None):
         self.load(arrs)
@@ -335,7 +338,7 @@ class MpmRollout(torch.autograd.Function):
     def forward(ctx, actions: torch.Tensor, sim: Simulator):
         if not sim.requires_grad:
             raise ValueError("MpmRollout needs a Simulator created with requires_grad=True")
-        sim.load()
+        sim.buf.copy_(sim._buf0)   # (load() without its wait: the step follows on the joined stream)
         sim.set_state()
         sim.set_actions(actions.detach())
         sim.step(actions.shape[0])

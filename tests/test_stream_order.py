@@ -42,6 +42,15 @@ def test_set_state_joins_the_current_stream(monkeypatch):
     assert log == ["library_stream.wait_stream", "lib.mpm_set_state"]
 
 
+def test_load_waits_for_its_copy(monkeypatch):
+    """The initial state is kept on the device, and a copy within the device
+    returns before it is done."""
+    sim, log = simulator_stub(monkeypatch)
+    sim._buf0 = torch.ones(sim_mod.STATE_ROWS, 4)
+    sim.load()
+    assert torch.equal(sim.buf, sim._buf0) and log == ["current_stream.synchronize"]
+
+
 def delayed(stream):
     """About 0.1 s of work on the stream, for what follows on it to be late."""
     with torch.cuda.stream(stream):
@@ -67,3 +76,17 @@ def test_state_written_on_another_stream_is_the_one_stepped():
     sim.step(4)
     # (the sums' order differs from run to run)
     assert torch.allclose(sim.buf, ref, rtol=0, atol=1e-5 * float(ref.abs().max()))
+
+
+@pytest.mark.gpu
+def test_loaded_state_is_there_for_every_stream():
+    sim = sim_mod.Simulator(scenes.tiny(n_particles=300, steps=4, seed=3))
+    start = sim.buf.clone()
+    for call in (sim.load, sim.reset):
+        sim.buf.zero_()
+        torch.cuda.synchronize()
+        other = torch.cuda.Stream()
+        delayed(other)
+        with torch.cuda.stream(other):
+            call()
+        assert torch.equal(sim.buf, start)
