@@ -124,11 +124,14 @@ class GasSim:
         self._staged.record(torch.cuda.current_stream(self.device))
 
     def reset(self):
+        """The scene's initial state (there for every stream when the call
+        returns), t = 0 and the scene's actions."""
         self.load()
         self._sync_in()
         self._state = self.struct(self.buf)
         self._check(_lib.lib().gas_set_state(self.ctx, ctypes.byref(self._state)), "gas_set_state")
         self.set_actions(self.actions)
+        torch.cuda.current_stream(self.device).synchronize()   # (load's transfers)
 
     def set_actions(self, actions: torch.Tensor, t0: int = 0):
         a = actions.to(self.device, torch.float32).reshape(-1, 6).contiguous()

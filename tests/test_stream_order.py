@@ -7,7 +7,7 @@ import types
 import pytest
 import torch
 
-from paper_2303_02346_amd import _lib, scenes, sim as sim_mod
+from paper_2303_02346_amd import _lib, gas as gas_mod, scenes, sim as sim_mod
 
 
 class Recorder:
@@ -51,6 +51,23 @@ def test_load_waits_for_its_copy(monkeypatch):
     assert torch.equal(sim.buf, sim._buf0) and log == ["current_stream.synchronize"]
 
 
+def test_gas_reset_waits_for_its_transfers(monkeypatch):
+    """The initial fields go through staging memory, in transfers that return
+    before they are done."""
+    log = []
+    sim = object.__new__(gas_mod.GasSim)
+    sim.ctx, sim.device = types.SimpleNamespace(value=0), torch.device("cpu")
+    sim.buf, sim.actions = torch.zeros(4), torch.zeros(2, 6)
+    sim.stream = Recorder(log, "library_stream")
+    for name in ("load", "set_actions"):
+        monkeypatch.setattr(sim, name, lambda *a, n=name: log.append(n), raising=False)
+    monkeypatch.setattr(sim, "struct", lambda buf: _lib.GasState(), raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Recorder(log, "current_stream"))
+    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log, "lib"))
+    sim.reset()
+    assert log.index("current_stream.synchronize") > log.index("load")
+
+
 def delayed(stream):
     """About 0.1 s of work on the stream, for what follows on it to be late."""
     with torch.cuda.stream(stream):
@@ -90,3 +107,16 @@ def test_loaded_state_is_there_for_every_stream():
         with torch.cuda.stream(other):
             call()
         assert torch.equal(sim.buf, start)
+
+
+@pytest.mark.gpu
+def test_gas_state_is_there_for_every_stream_after_a_reset():
+    sim = gas_mod.GasSim(scenes.gas_room(n=(16, 24, 32), steps=2))
+    start = sim.buf.clone()
+    sim.buf.zero_()
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    delayed(other)
+    with torch.cuda.stream(other):
+        sim.reset()
+    assert torch.equal(sim.buf, start)
