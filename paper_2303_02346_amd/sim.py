@@ -338,7 +338,7 @@ class MpmRollout(torch.autograd.Function):
     def forward(ctx, actions: torch.Tensor, sim: Simulator):
         if not sim.requires_grad:
             raise ValueError("MpmRollout needs a Simulator created with requires_grad=True")
-        sim.buf.copy_(sim._buf0)   # (load() without its wait: the step follows on the joined stream)
+        sim.load()
         sim.set_state()
         sim.set_actions(actions.detach())
         sim.step(actions.shape[0])

@@ -51,6 +51,18 @@ def test_load_waits_for_its_copy(monkeypatch):
     assert torch.equal(sim.buf, sim._buf0) and log == ["current_stream.synchronize"]
 
 
+def test_rollouts_restore_their_state_through_load_and_reset():
+    """(a program that starts its rollouts elsewhere overrides these)"""
+    for function, restore in ((sim_mod.MpmRollout, "load"), (gas_mod.GasRollout, "reset")):
+        log = []
+        state = types.SimpleNamespace(requires_grad=True, x=torch.zeros(3, 4), v=torch.zeros(3, 4), buf=torch.zeros(25, 4),
+                                      _buf0=torch.zeros(25, 4))
+        for name in ("load", "reset", "set_state", "set_actions", "step"):
+            setattr(state, name, lambda *a, n=name: log.append(n))
+        function.forward(types.SimpleNamespace(), torch.zeros(2, 1, 6), state)
+        assert log[0] == restore and log[-2:] == ["set_actions", "step"]
+
+
 def test_gas_reset_waits_for_its_transfers(monkeypatch):
     """The initial fields go through staging memory, in transfers that return
     before they are done."""
