@@ -106,22 +106,28 @@ class GasSim:
     # calls ------------------------------------------------------------------
     def load(self, u=None, v=None, w=None, s=None):
         sc = self.sc
-        parts = (sc.u if u is None else u, sc.v if v is None else v, sc.w if w is None else w, sc.s if s is None else s)
+        parts = [np.ascontiguousarray(a).reshape(-1)
+                 for a in (sc.u if u is None else u, sc.v if v is None else v,
+                           sc.w if w is None else w, sc.s if s is None else s)]
+        # (refused before anything of the state is written)
+        total = sum(a.size for a in parts)
+        if total != self.buf.numel():
+            raise RuntimeError(f"the fields hold {total} values, the state {self.buf.numel()}")
+        for a in parts:
+            torch.from_numpy(np.empty(0, a.dtype))   # TypeError for what is no number (text, objects, dates)
         self._staged.synchronize()       # the previous load's transfer has read the staging memory
         stage = self._stage.numpy()
         at = 0
-        for a in parts:
-            src = np.ascontiguousarray(a).reshape(-1)
-            end = at + src.size
-            if end > stage.size:
-                raise RuntimeError(f"the fields hold more than the state's {stage.size} values")
-            np.copyto(stage[at:end], src, casting="unsafe")
-            # (each field's transfer overlaps the next one's conversion)
-            self.buf[at:end].copy_(self._stage[at:end], non_blocking=True)
-            at = end
-        if at != stage.size:
-            raise RuntimeError(f"the fields hold {at} values, the state {stage.size}")
-        self._staged.record(torch.cuda.current_stream(self.device))
+        try:
+            for a in parts:
+                end = at + a.size
+                with np.errstate(over="ignore", invalid="ignore"):   # (beyond FP32's range: infinite)
+                    np.copyto(stage[at:end], a, casting="unsafe")
+                # (each field's transfer overlaps the next one's conversion)
+                self.buf[at:end].copy_(self._stage[at:end], non_blocking=True)
+                at = end
+        finally:
+            self._staged.record(torch.cuda.current_stream(self.device))
 
     def reset(self):
         """The scene's initial state (there for every stream when the call

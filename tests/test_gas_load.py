@@ -1,0 +1,73 @@
+"""GasSim.load: what it takes and refuses, and what a refused call leaves.
+
+On the CPU the staging memory and the state are ordinary host tensors."""
+import types
+import warnings
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2303_02346_amd import gas as gas_mod, scenes
+
+
+class Event:
+    def synchronize(self):
+        pass
+
+    def record(self, stream):
+        pass
+
+
+def gas_stub(monkeypatch, n=(8, 12, 8), scalars=2):
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(synchronize=lambda: None))
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    sim = object.__new__(gas_mod.GasSim)
+    sim.sc = scenes.gas_room(n=n, steps=1, n_scalars=scalars)
+    sim.device = torch.device("cpu")
+    total = sum(a.size for a in (sim.sc.u, sim.sc.v, sim.sc.w, sim.sc.s))
+    sim.buf = torch.full((total,), 7.0)
+    sim._stage, sim._staged = torch.empty(total), Event()
+    return sim
+
+
+def fields(sc):
+    return [np.asarray(a) for a in (sc.u, sc.v, sc.w, sc.s)]
+
+
+def packed(parts):
+    return torch.from_numpy(np.concatenate([np.asarray(a).reshape(-1).astype(np.float32) for a in parts]))
+
+
+@pytest.mark.parametrize("which", range(4))
+@pytest.mark.parametrize("what,error", [("short", RuntimeError), ("long", RuntimeError), ("text", TypeError),
+                                        ("object", TypeError), ("date", TypeError), ("wide", TypeError)])
+def test_a_refused_load_leaves_the_state(monkeypatch, which, what, error):
+    sim = gas_stub(monkeypatch)
+    parts = fields(sim.sc)
+    a = parts[which]
+    parts[which] = {"short": lambda: a[..., :-1], "long": lambda: np.concatenate([a, a]),
+                    "text": lambda: a.astype(str), "object": lambda: a.astype(object),
+                    "date": lambda: np.zeros(a.shape, "datetime64[s]"), "wide": lambda: a.astype(np.longdouble)}[what]()
+    with pytest.raises(error):
+        sim.load(*parts)
+    assert bool((sim.buf == 7.0).all())
+    sim.load()
+    assert torch.equal(sim.buf, packed(fields(sim.sc)))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32, np.float16, np.int64, np.uint8, bool])
+def test_number_types_and_orders_are_taken(monkeypatch, dtype):
+    sim = gas_stub(monkeypatch)
+    parts = [np.asfortranarray((4.0 * a).astype(dtype)) for a in fields(sim.sc)]
+    parts[0] = parts[0][::-1]
+    sim.load(*parts)
+    assert torch.equal(sim.buf, packed([np.ascontiguousarray(a) for a in parts]))
+
+
+def test_values_beyond_single_precision_become_infinite_without_a_warning(monkeypatch):
+    sim = gas_stub(monkeypatch)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        sim.load(u=np.full(sim.sc.u.shape, 1e300))
+    assert bool(torch.isinf(sim.buf[:sim.sc.u.size]).all())
