@@ -9,6 +9,7 @@ GasRollout   -- torch.autograd.Function: actions -> final packed state,
 from __future__ import annotations
 
 import ctypes
+import threading
 from typing import Optional
 
 import numpy as np
@@ -72,6 +73,7 @@ class GasSim:
         # on torch's threads, up to twice that)
         self._stage = torch.empty(sum(self.sizes), dtype=torch.float32, pin_memory=True)
         self._staged = torch.cuda.Event()
+        self._stage_lock = threading.Lock()   # (one load at a time uses it)
         self.actions = torch.zeros(self.horizon, 6, dtype=torch.float32, device=self.device)
         acts = np.zeros((self.horizon, 6))
         acts[: min(sc.horizon, self.horizon)] = sc.actions[: self.horizon]
@@ -115,19 +117,20 @@ class GasSim:
             raise RuntimeError(f"the fields hold {total} values, the state {self.buf.numel()}")
         for a in parts:
             torch.from_numpy(np.empty(0, a.dtype))   # TypeError for what is no number (text, objects, dates)
-        self._staged.synchronize()       # the previous load's transfer has read the staging memory
-        stage = self._stage.numpy()
-        at = 0
-        try:
-            for a in parts:
-                end = at + a.size
-                with np.errstate(over="ignore", invalid="ignore"):   # (beyond FP32's range: infinite)
-                    np.copyto(stage[at:end], a, casting="unsafe")
-                # (each field's transfer overlaps the next one's conversion)
-                self.buf[at:end].copy_(self._stage[at:end], non_blocking=True)
-                at = end
-        finally:
-            self._staged.record(torch.cuda.current_stream(self.device))
+        with self._stage_lock:
+            self._staged.synchronize()       # the previous load's transfer has read the staging memory
+            stage = self._stage.numpy()
+            at = 0
+            try:
+                for a in parts:
+                    end = at + a.size
+                    with np.errstate(over="ignore", invalid="ignore"):   # (beyond FP32's range: infinite)
+                        np.copyto(stage[at:end], a, casting="unsafe")
+                    # (each field's transfer overlaps the next one's conversion)
+                    self.buf[at:end].copy_(self._stage[at:end], non_blocking=True)
+                    at = end
+            finally:
+                self._staged.record(torch.cuda.current_stream(self.device))
 
     def reset(self):
         """The scene's initial state (there for every stream when the call

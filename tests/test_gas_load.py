@@ -1,6 +1,8 @@
 """GasSim.load: what it takes and refuses, and what a refused call leaves.
 
 On the CPU the staging memory and the state are ordinary host tensors."""
+import threading
+import time
 import types
 import warnings
 
@@ -27,7 +29,7 @@ def gas_stub(monkeypatch, n=(8, 12, 8), scalars=2):
     sim.device = torch.device("cpu")
     total = sum(a.size for a in (sim.sc.u, sim.sc.v, sim.sc.w, sim.sc.s))
     sim.buf = torch.full((total,), 7.0)
-    sim._stage, sim._staged = torch.empty(total), Event()
+    sim._stage, sim._staged, sim._stage_lock = torch.empty(total), Event(), threading.Lock()
     return sim
 
 
@@ -71,3 +73,23 @@ def test_values_beyond_single_precision_become_infinite_without_a_warning(monkey
         warnings.simplefilter("error")
         sim.load(u=np.full(sim.sc.u.shape, 1e300))
     assert bool(torch.isinf(sim.buf[:sim.sc.u.size]).all())
+
+
+def test_loads_from_two_threads_do_not_mix(monkeypatch):
+    """The conversions run without the interpreter's lock; the state is one
+    call's fields or the other's."""
+    sim = gas_stub(monkeypatch)
+    copyto = np.copyto
+
+    def slow(*a, **k):
+        copyto(*a, **k)
+        time.sleep(0.01)
+
+    monkeypatch.setattr(gas_mod.np, "copyto", slow)
+    calls = [[np.full(a.shape, float(k)) for a in fields(sim.sc)] for k in (1, 2)]
+    threads = [threading.Thread(target=sim.load, args=c) for c in calls]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert bool((sim.buf == sim.buf[0]).all())
