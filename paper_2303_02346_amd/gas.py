@@ -19,6 +19,12 @@ from . import _lib
 from .scenes import GasScene
 
 
+# values of one of the two pieces of pinned staging memory of a GasSim (4 MB each:
+# a 128^3 state is loaded in 2.8 ms, with pieces of 0.5 MB in 3.3, with the whole
+# state staged at once in 3.0)
+STAGE_VALUES = 1 << 20
+
+
 class GasSim:
     """A gas context for one GasScene.  The state lives in ``self.buf`` (one
     float32 vector: u, v, w, then the scalars); ``u``, ``v``, ``w``, ``s``
@@ -67,12 +73,12 @@ class GasSim:
         self.ctx = ctx
         self.sizes = [(nx + 1) * ny * nz, nx * (ny + 1) * nz, nx * ny * (nz + 1), self.K * nx * ny * nz]
         self.buf = torch.zeros(sum(self.sizes), dtype=torch.float32, device=self.device)
-        # pinned staging for load(): the host arrays are converted into it field
-        # by field, each copied while the next is converted (2.8 ms for a 128^3
-        # state; converted and concatenated in pageable memory it took 5 ms and,
-        # on torch's threads, up to twice that)
-        self._stage = torch.empty(sum(self.sizes), dtype=torch.float32, pin_memory=True)
-        self._staged = torch.cuda.Event()
+        # pinned staging for load(): the host arrays are converted into its two
+        # pieces in turn, one transferred while the other is filled (converted
+        # and concatenated in pageable memory a 128^3 state took 5 ms and, on
+        # torch's threads, up to twice that)
+        self._stage = torch.empty(2, min(STAGE_VALUES, sum(self.sizes)), dtype=torch.float32, pin_memory=True)
+        self._staged = (torch.cuda.Event(), torch.cuda.Event())
         self._stage_lock = threading.Lock()   # (one load at a time uses it)
         self.actions = torch.zeros(self.horizon, 6, dtype=torch.float32, device=self.device)
         acts = np.zeros((self.horizon, 6))
@@ -117,20 +123,22 @@ class GasSim:
             raise RuntimeError(f"the fields hold {total} values, the state {self.buf.numel()}")
         for a in parts:
             torch.from_numpy(np.empty(0, a.dtype))   # TypeError for what is no number (text, objects, dates)
+        stage = self._stage.numpy()
+        stream = torch.cuda.current_stream(self.device)
+        at = q = 0
         with self._stage_lock:
-            self._staged.synchronize()       # the previous load's transfer has read the staging memory
-            stage = self._stage.numpy()
-            at = 0
-            try:
-                for a in parts:
-                    end = at + a.size
+            for a in parts:
+                for i in range(0, a.size, stage.shape[1]):
+                    src = a[i:i + stage.shape[1]]
+                    self._staged[q].synchronize()      # the piece's last transfer has read it
                     with np.errstate(over="ignore", invalid="ignore"):   # (beyond FP32's range: infinite)
-                        np.copyto(stage[at:end], a, casting="unsafe")
-                    # (each field's transfer overlaps the next one's conversion)
-                    self.buf[at:end].copy_(self._stage[at:end], non_blocking=True)
-                    at = end
-            finally:
-                self._staged.record(torch.cuda.current_stream(self.device))
+                        np.copyto(stage[q, :src.size], src, casting="unsafe")
+                    try:
+                        self.buf[at:at + src.size].copy_(self._stage[q, :src.size], non_blocking=True)
+                    finally:
+                        self._staged[q].record(stream)
+                    at += src.size
+                    q ^= 1
 
     def reset(self):
         """The scene's initial state (there for every stream when the call

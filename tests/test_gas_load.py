@@ -14,22 +14,23 @@ from paper_2303_02346_amd import gas as gas_mod, scenes
 
 
 class Event:
+    pending = False
+
     def synchronize(self):
-        pass
+        self.pending = False
 
     def record(self, stream):
-        pass
+        self.pending = True
 
 
-def gas_stub(monkeypatch, n=(8, 12, 8), scalars=2):
+def gas_stub(monkeypatch, n=(8, 12, 8), scalars=2, piece=1000):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(synchronize=lambda: None))
-    monkeypatch.setattr(torch.cuda, "Event", Event)
     sim = object.__new__(gas_mod.GasSim)
     sim.sc = scenes.gas_room(n=n, steps=1, n_scalars=scalars)
     sim.device = torch.device("cpu")
     total = sum(a.size for a in (sim.sc.u, sim.sc.v, sim.sc.w, sim.sc.s))
     sim.buf = torch.full((total,), 7.0)
-    sim._stage, sim._staged, sim._stage_lock = torch.empty(total), Event(), threading.Lock()
+    sim._stage, sim._staged, sim._stage_lock = torch.empty(2, piece), (Event(), Event()), threading.Lock()
     return sim
 
 
@@ -93,3 +94,34 @@ def test_loads_from_two_threads_do_not_mix(monkeypatch):
     for t in threads:
         t.join()
     assert bool((sim.buf == sim.buf[0]).all())
+
+
+@pytest.mark.parametrize("piece", [1, 7, 864, 865, 5000])
+def test_a_piece_is_filled_again_only_after_its_transfer(monkeypatch, piece):
+    """Fields of 864 to 1536 values through pieces smaller than, as large as
+    and larger than one."""
+    sim = gas_stub(monkeypatch, piece=piece)
+    copyto = np.copyto
+
+    def checked(dst, *a, **k):
+        at = (dst.__array_interface__["data"][0] - sim._stage.data_ptr()) // 4
+        assert not sim._staged[at // piece].pending
+        copyto(dst, *a, **k)
+
+    monkeypatch.setattr(gas_mod.np, "copyto", checked)
+    for _ in range(2):
+        sim.buf.zero_()
+        sim.load()
+        assert torch.equal(sim.buf, packed(fields(sim.sc)))
+
+
+@pytest.mark.gpu
+def test_pinned_memory_of_a_large_state_is_bounded():
+    sc = scenes.gas_room(n=(64, 100, 128), steps=1)
+    sim = gas_mod.GasSim(sc)
+    assert sim.buf.numel() > 2 * gas_mod.STAGE_VALUES
+    assert sim._stage.is_pinned() and sim._stage.numel() <= 2 * gas_mod.STAGE_VALUES
+    for _ in range(2):
+        sim.buf.zero_()
+        sim.reset()
+        assert torch.equal(sim.buf.cpu(), packed(fields(sc)))
