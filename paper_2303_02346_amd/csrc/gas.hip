@@ -877,7 +877,8 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
   const int line = line0 + C * lc;
   const bool on = line < X.B;
   const size_t plane = (size_t)blockIdx.y * n * X.B;
-  const float* in = X.in + plane + (on ? line : 0);
+  // (a lane past the last line reads its workgroup's first one: in place, the others' lines may be being written)
+  const float* in = X.in + plane + (on ? line : line0);
   float* out = X.out + plane + line;
   const uint32_t B = (uint32_t)X.B;
   float lyz[C];

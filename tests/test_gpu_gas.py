@@ -293,3 +293,17 @@ def test_gas_gradient_merged_scatter_vs_oracle(n, velocity, dt, scalars):
         e[q] = rel(g.double().cpu().numpy(), st0[q].grad.numpy())
     say(f"gas {n}, velocity {velocity}: " + " ".join(f"{k} {v:.2e}" for k, v in e.items()))
     assert max(e.values()) <= 2e-3
+
+
+@pytest.mark.parametrize("n", [(36, 12, 12), (132, 20, 12), (512, 8, 12), (512, 12, 12)])
+def test_gas_x_transforms_in_one_launch_vs_oracle(n):
+    """The x transforms of one launch work in place on 32 lines a workgroup:
+    planes that leave the last workgroup 16 of them, and the longest axis
+    whose coefficients fit a workgroup (512 values, 64 KB of LDS)."""
+    sc = scenes.gas_room(n=n, steps=2, seed=13, n_scalars=1, translate=True)
+    say(f"gas {n}, 2 steps")
+    sim = gas_sim(sc)
+    sim.enable_stats(True)
+    sim.step(2)
+    say(f"  pressure residual {sim.residual():.2e}")
+    compare(sim.state_numpy(), G.rollout_scene(sc, steps=2))
