@@ -316,7 +316,9 @@ int mpm_mlp_init(void* state_dev, const float* samples_dev, int64_t n, const flo
 int mpm_mlp_train(void* state_dev, const float* samples_dev, int64_t n, int32_t batch, int32_t epochs, float lr,
                   uint64_t seed, void* scratch_dev, double* loss_hist_host, void* stream);
 /* Loss (host) and parameter gradient (device, 4803 floats) on the first
- * min(n, batch) records, without updating the weights. */
+ * min(n, batch) records, without updating the weights or the Adam moments.
+ * The Adam step count is cleared: the bias correction of a later
+ * mpm_mlp_train starts as for a first step. */
 int mpm_mlp_grad(void* state_dev, const float* samples_dev, int64_t n, int32_t batch, void* scratch_dev,
                  float* grad_out_dev, double* loss_out_host, void* stream);
 /* mpm_mlp_grad for callers that cannot allocate device memory (code under

@@ -498,7 +498,10 @@ __global__ __launch_bounds__(64 * SLICES) void k_mlp_update(void* scr, int nb, f
     for (int r = lane; r < (nb + 15) / 16; r += 64) l += S.loss[r];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
-    if (lane == 0) misc[0] = first ? l : misc[0] + l;
+    if (lane == 0) {
+      misc[0] = first ? l : misc[0] + l;
+      if (!ADAM) misc[1] = 0.0;   // (a gradient call ends a training run: its Adam step count starts anew)
+    }
   }
   __syncthreads();
   const int tid = threadIdx.x;
