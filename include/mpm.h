@@ -302,7 +302,8 @@ int mpm_set_closure(mpm_ctx* c, const void* mlp_state_dev, float residual_tol);
 int mpm_closure_stats(mpm_ctx* c, uint64_t* accepted, uint64_t* fallback);
 
 size_t mpm_mlp_state_bytes(void);
-/* Scratch (device) for mpm_mlp_train / mpm_mlp_grad with this batch size. */
+/* Scratch (device, of any alignment) for mpm_mlp_train / mpm_mlp_grad with
+ * this batch size. */
 size_t mpm_mlp_scratch_bytes(int32_t batch);
 /* Initialise: normalisation statistics from the n logged records in
  * samples_dev, weights from init_params (host, MLP parameter vector of 4803

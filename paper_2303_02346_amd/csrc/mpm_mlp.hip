@@ -282,8 +282,10 @@ constexpr int XS = 12;
 constexpr size_t SCR_BYTES = 2 * MLP_H * 4 + XS * 4 + 2 * MLP_H * 2;   // per sample, without the loss
 static_assert(SCR_BYTES % 16 == 0, "alignment of the arrays");
 __host__ __device__ constexpr size_t scratch_bytes(size_t nb) { return nb * SCR_BYTES + (nb + 15) / 16 * 8; }
+// (the arrays are read and written in 16-byte words; a caller's scratch may start anywhere)
+constexpr size_t SCR_ALIGN = 16;
 __host__ __device__ inline BatchScratch scratch_of(void* base, size_t nb) {
-  char* p = (char*)base;
+  char* p = (char*)(((uintptr_t)base + SCR_ALIGN - 1) & ~(uintptr_t)(SCR_ALIGN - 1));
   BatchScratch S;
   S.d1 = (float*)p; p += nb * MLP_H * 4;
   S.d2 = (float*)p; p += nb * MLP_H * 4;
@@ -565,7 +567,7 @@ size_t mpm_mlp_state_bytes(void) { return mlp_layout().total; }
 
 size_t mpm_mlp_scratch_bytes(int32_t batch) {
   if (batch < 1) return 0;
-  return al(scratch_bytes((size_t)batch));
+  return al(scratch_bytes((size_t)batch) + SCR_ALIGN);
 }
 
 int mpm_mlp_init(void* state_dev, const float* samples_dev, int64_t n, const float* init_params, uint64_t seed,
