@@ -93,7 +93,6 @@ class Simulator:
         self.ctx = ctx
         self.buf = torch.zeros(STATE_ROWS, self.N, dtype=torch.float32, device=self.device)
         self.mat = torch.from_numpy(arrs["mat"].astype(np.uint8)).to(self.device)
-        self._init_arrays = arrs
         # the scenes' initial state as the buffer holds it, uploaded once:
         # converting the host arrays for every rollout took longer than the
         # rollout (6 ms at 250k particles)
