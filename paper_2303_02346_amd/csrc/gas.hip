@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
+#include <algorithm>
 #include <type_traits>
 #include <new>
 #include <vector>
@@ -840,6 +841,8 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
   const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int n = X.n, S = axis_steps(n);
   const int line0 = blockIdx.x * LINES;
+  // output tiles: every wavefront of the line's workgroups (blockIdx.z) in turn
+  const int m_first = AXIS_MT * (wv + nw * (int)blockIdx.z), m_step = AXIS_MT * nw * (int)gridDim.z;
   floatx4 res[AXIS_MT][C];
   if (INNER) {
     // line tile c of the lane: row line0 + 16 c + lc
@@ -851,7 +854,7 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
       on[c] = line < X.A;
       in[c] = X.in + (size_t)(on[c] ? line : 0) * n;
     }
-    for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+    for (int m0 = m_first; m0 < S; m0 += m_step) {
       axis_contract<C>(X.M, S, m0, lane, [&](int s, float (&e)[4][C]) {
         const int i = min(16 * s + 4 * lr, n - 4);   // (past n the matrix is zero)
 #pragma unroll
@@ -888,7 +891,7 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
 #pragma unroll
     for (int c = 0; c < C; c++) { lyz[c] = X.lz[kz + c]; }
     const float ly = X.ly[ky];
-    for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+    for (int m0 = m_first; m0 < S; m0 += m_step) {
       axis_contract<C>(X.M, S, m0, lane, [&](int s, float (&e)[4][C]) {
 #pragma unroll
         for (int t = 0; t < 4; t++) {
@@ -918,7 +921,7 @@ __global__ __launch_bounds__(256) void k_axis(AxisArgs X) {
     __syncthreads();
   }
   const float4* Mi = KIND == AXIS_BOTH ? X.M2 : X.M;
-  for (int m0 = AXIS_MT * wv; m0 < S; m0 += AXIS_MT * nw) {
+  for (int m0 = m_first; m0 < S; m0 += m_step) {
     axis_contract<C>(Mi, S, m0, lane, [&](int s, float (&e)[4][C]) {
 #pragma unroll
       for (int t = 0; t < 4; t++) {
@@ -1538,13 +1541,36 @@ void mg_solve(gas_ctx* c, float* psi0, float* f0) {
   }
 }
 
-// one launch of transforms: 32 lines a workgroup, two wavefronts per SIMD at 128^3
-// (16 lines along z: 11.2 and 15.1 us)
+// One launch of transforms: 32 lines a workgroup, two wavefronts per SIMD at 128^3
+// (16 lines along z: 11.2 and 15.1 us).  A wavefront takes a pair of output tiles
+// at a time; where an axis has more pairs than a workgroup wavefronts and the lines
+// alone make fewer than AXIS_FILL workgroups, the pairs are dealt to several
+// workgroups of a line (six transforms, us, one workgroup a line and as dealt:
+// 8 x 8 x 1024 617 and 87, 64 x 64 x 512 183 and 85, 512 x 64 x 64 167 and 95,
+// 256 x 32 x 256 100 and 84, 1024 x 8 x 1024 1515 and 912; with a line at 256
+// workgroups 64 x 64 x 512 takes 111, at 1024 256 x 256 x 64 164 instead of 140).
+// Every output's sum keeps its order.
+constexpr unsigned AXIS_FILL = 512;
+struct AxisShape {
+  unsigned groups, nw, rounds, split;   // workgroups of lines, wavefronts, rounds of a wavefront, workgroups a line
+};
+template <int C = 2>
+AxisShape axis_shape(int n, int lines, int planes) {
+  AxisShape G;
+  const unsigned pairs = (unsigned)(axis_steps(n) + AXIS_MT - 1) / AXIS_MT;
+  G.groups = (unsigned)((lines + 16 * C - 1) / (16 * C)) * (unsigned)planes;
+  G.nw = pairs < 4u ? pairs : 4u;
+  G.rounds = (pairs + G.nw - 1) / G.nw;
+  const unsigned per = (unsigned)std::max<size_t>(1, (size_t)G.rounds * G.groups / AXIS_FILL);   // rounds a workgroup keeps
+  G.split = (G.rounds + per - 1) / per;
+  return G;
+}
 template <bool INNER, int KIND, int C = 2>
 void launch_axis(const AxisArgs& X, int lines, int planes, hipStream_t s) {
-  const unsigned nt = 64u * (unsigned)min(4, (axis_steps(X.n) + AXIS_MT - 1) / AXIS_MT);
+  const AxisShape G = axis_shape<C>(X.n, lines, planes);
   const size_t lds = KIND == AXIS_BOTH ? (size_t)X.n * 16 * C * 4 : 0;
-  k_axis<INNER, KIND, C><<<dim3((lines + 16 * C - 1) / (16 * C), planes), nt, lds, s>>>(X);
+  const dim3 grid((lines + 16 * C - 1) / (16 * C), planes, KIND == AXIS_BOTH ? 1u : G.split);
+  k_axis<INNER, KIND, C><<<grid, 64 * G.nw, lds, s>>>(X);
 }
 
 // A psi = f exactly by the axis transforms (psi0 receives the solution with
@@ -1570,8 +1596,9 @@ void spectral_solve(gas_ctx* c, float* psi0, const float* f0) {
   launch_axis<false, AXIS_ONE>(args(T, psi0, Mf[1], ny, nx, nz), nz, nx, s);
   // along x in place: every workgroup has read its lines when it writes them
   // (with more than 512 values an axis does not fit the 64 KB of a workgroup's
-  // coefficients: two launches)
-  const bool both = nx <= 512;
+  // coefficients, and where the output tiles have to be dealt to several workgroups
+  // none of them has all coefficients: two launches)
+  const bool both = nx <= 512 && axis_shape(nx, ny * nz, 1).split == 1u;
   AxisArgs X = args(psi0, both ? psi0 : T, Mf[0], nx, 1, ny * nz);
   X.M2 = Mi[0];
   X.lx = (const float*)(c->ws + c->L.lam[0]);
