@@ -1004,17 +1004,24 @@ struct AdjOut {
 // the last lane's corners issued as they come, 205 and 210 with 4 x 4 and 4 x 8
 // planes x points, 222 and 244 with 2 x 4 and 8 x 2.  (Columns, not points, are
 // dealt to the lanes, so that rows of any length fill the wavefronts.)
-constexpr int ADJ_J = 8, ADJ_I = 8;   // points a thread, planes (wavefronts) a workgroup
+//
+// ADJ_J points one after the other are a chain, which sets the time of a small
+// grid (12 x 20 x 28, four scalars: 63 us); there a thread takes one point.  The
+// line is at three workgroups a CU with one point a thread: backward of four steps
+// at 40^3 469 us against 534 with ADJ_J points, 48^3 505 and 540, 64^3 700 and 675,
+// 8 x 1024 x 8 1000 and 950.
+constexpr int ADJ_J = 8, ADJ_I = 8;   // points a thread (or one), planes (wavefronts) a workgroup
+constexpr uint32_t ADJ_SHORT_BLOCKS = 3 * 256;
 
 __device__ __forceinline__ int lane_prev(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xF, 0xF, false); }   // wave_shr:1
 __device__ __forceinline__ int lane_next(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xF, 0xF, false); }   // wave_shl:1
 __device__ __forceinline__ float lane_prev(float x) { return __int_as_float(lane_prev(__float_as_int(x))); }
 
 // blocks of 64 columns (j group, k) of each grid, and groups of ADJ_I planes
-inline PointGrid column_grid(const GP& P) {
+inline PointGrid column_grid(const GP& P, int J) {
   PointGrid G = {};
   for (int q = 0; q < 4; q++) {
-    const uint32_t groups = (uint32_t)(P.ny + (q == 1) + ADJ_J - 1) / ADJ_J;
+    const uint32_t groups = (uint32_t)(P.ny + (q == 1) + J - 1) / J;
     G.nb[q] = (groups * (uint32_t)(P.nz + (q == 2)) + 63u) / 64u;
     G.per += G.nb[q];
   }
@@ -1030,7 +1037,7 @@ struct AdjLds {
   float e[2][ADJ_I][MAXK][64], h[2][ADJ_I][MAXK][64];   // the rows at k0 and (where the next lane did not take it) k0 + 1
 };
 
-template <int Q>
+template <int Q, int J>
 __device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, const float* __restrict__ s,
                                             const float* __restrict__ ab_in, const float* __restrict__ vb1,
                                             float* __restrict__ tgt, const Pose& E, float* __restrict__ ub, size_t total,
@@ -1039,7 +1046,7 @@ __device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, con
   const int K = Q < 3 ? 1 : P.K;
   const int lane = (int)__lane_id(), wv = (int)(threadIdx.x >> 6);
   const int d0 = P.nx + (Q == 0), d1 = P.ny + (Q == 1), d2 = P.nz + (Q == 2);
-  const int groups = (d1 + ADJ_J - 1) / ADJ_J;
+  const int groups = (d1 + J - 1) / J;
   const int col = col0 + lane, jg = row_of(col, Q == 2 ? P.mz1 : P.mz), k = col - jg * d2;
   const bool lane_on = i < d0 && jg < groups;
   const size_t sx = (size_t)d1 * d2;
@@ -1052,9 +1059,9 @@ __device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, con
   uint32_t pcell = NO_CELL;   // carried row: the cell whose (i0, j0, k0) and (i0 + 1, j0, k0) corners it holds
   float pend[NV][2] = {}, hpend[NV][2] = {};
 #pragma unroll 1
-  for (int t = 0; t <= ADJ_J; t++) {
-    const int j = jg * ADJ_J + t;
-    const bool on = lane_on && t < ADJ_J && j < d1;
+  for (int t = 0; t <= J; t++) {
+    const int j = jg * J + t;
+    const bool on = lane_on && t < J && j < d1;
     uint32_t cell = NO_CELL;
     Lerp L = {};
     float sval[NV] = {};
@@ -1116,13 +1123,13 @@ __device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, con
     const bool given = lane < 63 && take_n != 0;
     // along y: the carried row is this cell's
     const bool carried = pcell == cell;
-    const uint32_t ecell = t < ADJ_J ? cell : pcell;   // the row emitted now (after the last point, the carried one)
+    const uint32_t ecell = t < J ? cell : pcell;   // the row emitted now (after the last point, the carried one)
     float e0[NV], e1[NV], h0[NV], h1[NV];
 #pragma unroll
     for (int kk = 0; kk < NV; kk++) {
       e0[kk] = e1[kk] = h0[kk] = h1[kk] = 0.f;
       if (kk >= K) continue;
-      if (t == ADJ_J) {
+      if (t == J) {
         e0[kk] = pend[kk][0]; e1[kk] = pend[kk][1];
         h0[kk] = hpend[kk][0]; h1[kk] = hpend[kk][1];
         continue;
@@ -1188,6 +1195,7 @@ __device__ __forceinline__ void adj_columns(const GP& P, const VelPtrs& vel, con
   }
 }
 
+template <int J>
 __global__ __launch_bounds__(64 * ADJ_I) void k_gas_adj_advect(GP P, VelPtrs vel, const float* __restrict__ s,
                                                         const float* __restrict__ ub1, const float* __restrict__ vb1,
                                                         const float* __restrict__ wb1, const float* __restrict__ sb,
@@ -1206,10 +1214,10 @@ __global__ __launch_bounds__(64 * ADJ_I) void k_gas_adj_advect(GP P, VelPtrs vel
   for (int n = 0; n < 3; n++)
     if (q == n && b >= G.nb[n]) { b -= G.nb[n]; q = n + 1; }
   const int i = ADJ_I * ig + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), col0 = 64 * (int)b;
-  if (q == 0) adj_columns<0>(P, vel, s, ub1, nullptr, out.u, E, ub, total, i, col0, S, part);
-  else if (q == 1) adj_columns<1>(P, vel, s, vb1, nullptr, out.v, E, ub + P.nu, total, i, col0, S, part);
-  else if (q == 2) adj_columns<2>(P, vel, s, wb1, nullptr, out.w, E, ub + P.nu + P.nv, total, i, col0, S, part);
-  else adj_columns<3>(P, vel, s, sb, vb1, out.s, E, ub + P.nu + P.nv + P.nw, total, i, col0, S, part);
+  if (q == 0) adj_columns<0, J>(P, vel, s, ub1, nullptr, out.u, E, ub, total, i, col0, S, part);
+  else if (q == 1) adj_columns<1, J>(P, vel, s, vb1, nullptr, out.v, E, ub + P.nu, total, i, col0, S, part);
+  else if (q == 2) adj_columns<2, J>(P, vel, s, wb1, nullptr, out.w, E, ub + P.nu + P.nv, total, i, col0, S, part);
+  else adj_columns<3, J>(P, vel, s, sb, vb1, out.s, E, ub + P.nu + P.nv + P.nw, total, i, col0, S, part);
   // pose partials: wave sums, one FP64 atomic per component into the
   // wavefront's accumulator copy
   const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -1655,14 +1663,16 @@ void gas_adjoint_step(gas_ctx* c, const gas_state& st, const gas_state& an, cons
   gas_state tmp = packed(c, c->ws + c->L.tmp);
   float* psi0 = (float*)(c->ws + c->L.psi[0]);
   float* f0 = (float*)(c->ws + c->L.f[0]);
-  const PointGrid Gd = point_grid(P, 1, DIV_U), Gf = point_grid(P, 3, FIN_U), Ga = column_grid(P), Gu = point_grid(P, 3, UG_U);
+  const PointGrid Gd = point_grid(P, 1, DIV_U), Gf = point_grid(P, 3, FIN_U), G1 = column_grid(P, 1), Gu = point_grid(P, 3, UG_U);
   k_gas_div<false><<<Gd.blocks, 256, 0, s>>>(P, an.u, an.v, an.w, nullptr, f0, c->d.pressure_solver ? psi0 : nullptr, Gd);
   pressure_solve(c, psi0, f0);
   k_gas_final<false><<<Gf.blocks, 256, 0, s>>>(P, an.u, an.v, an.w, nullptr, psi0, tmp.u, tmp.v, tmp.w, Gf);
   launch_zero(ab.u, c->L.state_floats * 4, s);
-  k_gas_adj_advect<<<Ga.blocks, 64 * ADJ_I, 0, s>>>(P, VelPtrs{st.u, st.v, st.w}, st.s, tmp.u, tmp.v, tmp.w, an.s,
-                                             AdjOut{ab.u, ab.v, ab.w, ab.s}, pose_at(c, t),
-                                             (double*)(c->ws + c->L.slots), (float*)(c->ws + c->L.ub), Ga);
+  const bool one = G1.blocks <= ADJ_SHORT_BLOCKS;
+  const PointGrid Ga = one ? G1 : column_grid(P, ADJ_J);
+  (one ? k_gas_adj_advect<1> : k_gas_adj_advect<ADJ_J>)<<<Ga.blocks, 64 * ADJ_I, 0, s>>>(
+      P, VelPtrs{st.u, st.v, st.w}, st.s, tmp.u, tmp.v, tmp.w, an.s, AdjOut{ab.u, ab.v, ab.w, ab.s}, pose_at(c, t),
+      (double*)(c->ws + c->L.slots), (float*)(c->ws + c->L.ub), Ga);
   k_gas_adj_ugather<<<Gu.blocks, 256, 0, s>>>(P, (const float*)(c->ws + c->L.ub), AdjOut{ab.u, ab.v, ab.w, ab.s}, Gu);
   k_gas_pose_acc<<<1, 64, 0, s>>>((double*)(c->ws + c->L.slots), acc_t);
 }

@@ -338,3 +338,27 @@ def test_gas_longest_x_axis_of_one_launch():
     sim.step(1)
     say(f"gas {sc.n}: pressure residual {sim.residual():.2e}")
     assert 0.0 < sim.residual() <= 1e-4
+
+
+@pytest.mark.parametrize("n,velocity,dt,scalars", [((8, 12, 8), 0.5, 5e-3, 2), ((52, 36, 44), 0.5, 5e-3, 2),
+                                                   ((44, 68, 52), 0.5, 5e-3, 2), ((20, 100, 76), 3.0, 0.05, 3)])
+def test_gas_gradient_points_a_thread_vs_oracle(n, velocity, dt, scalars):
+    """The adjoint scatter with one point a thread (small grids: 16 and 714
+    workgroups, of at most 768) and with eight, the columns of both ragged in
+    every direction.  Tolerance: the gradient test's."""
+    sc = scenes.gas_room(n=n, steps=2, seed=15, n_scalars=scalars, velocity=velocity, dt=dt, translate=True)
+    sim = gas_sim(sc, requires_grad=True, ckpt_every=16)
+    sim.step(2)
+    wflat = _seeds(sim, 32)
+    ga, g0 = sim.backward(wflat.to(sim.device), want_grad0=True)
+    acts = torch.tensor(sc.actions, dtype=DT, requires_grad=True)
+    st0 = G.state_from_scene(sc, requires_grad=True)
+    st = G.rollout_scene(sc, actions=acts, state=st0, params=G.params_from_scene(sc))
+    wq = [t.double() for t in sim.split(wflat)]
+    L = sum((w * st[q]).sum() for w, q in zip(wq[:3], ("u", "v", "w"))) + (wq[3] * st["s"]).sum()
+    L.backward()
+    e = {"actions": rel(ga.double().cpu().numpy(), acts.grad.numpy())}
+    for q, g in zip(("u", "v", "w", "s"), sim.split(g0)):
+        e[q] = rel(g.double().cpu().numpy(), st0[q].grad.numpy())
+    say(f"gas {n}, velocity {velocity}: " + " ".join(f"{k} {v:.2e}" for k, v in e.items()))
+    assert max(e.values()) <= 2e-3
