@@ -232,13 +232,19 @@ enum {
                                  without rigid bodies, including those that keep every step's record;
                                  tiled backward calls without rigid bodies) */
   MPM_OPT_PART_THREADS = 2,   /* 128, 256 or 512 threads per particle workgroup */
-  MPM_OPT_PART_WGS = 3,       /* particle workgroups per launch (persistent, 64..65536) */
+  MPM_OPT_PART_WGS = 3,       /* particle workgroups per launch (persistent, 64..65536).  In launches of
+                                 256-thread workgroups without closure or logging, the fused kernel works
+                                 off a list of more than two entries per resident workgroup with the
+                                 resident workgroups alone: a value above their number (compute units times
+                                 occupancy) then makes no difference */
   MPM_OPT_GRID_WGS = 4,       /* grid-update workgroups per launch (64..65536) */
   MPM_OPT_ADJOINT = 5,        /* 0: tiled (default), 1: plain */
   MPM_OPT_N_KEYS = 6,         /* read only: grid blocks of the context (rows of a sort snapshot list) */
   MPM_OPT_SHARE_CHUNKS = 7    /* a block holding more than this many chunks (of MPM_OPT_PART_THREADS
-                                 particles) is shared by two particle workgroups, or by one per chunk while
-                                 all chunks fit the resident workgroups; 0 = never; default 2 */
+                                 particles) is shared by two particle workgroups; in launches of 256-thread
+                                 workgroups without closure or logging it is shared by one per chunk, at
+                                 most six, while the entries of all blocks so shared are no more than the
+                                 resident workgroups; 0 = never; default 2 */
 };
 int mpm_set_option(mpm_ctx* c, int32_t key, int32_t value);
 int mpm_get_option(const mpm_ctx* c, int32_t key, int32_t* value);
@@ -266,7 +272,10 @@ int mpm_sort_snapshot(mpm_ctx* c, int32_t which, uint32_t* id_dev, uint32_t* key
  * set) for every launch shape in a fixed candidate set (particles per
  * chunk, workgroup counts, and the chunk count above which a block is
  * shared by two workgroups), keeps the fastest and returns it in best[5] =
- * {part_threads, part_wgs, grid_wgs, microseconds per step, share_chunks}. */
+ * {part_threads, part_wgs, grid_wgs, microseconds per step, share_chunks}.
+ * (On long lists the candidates for part_wgs above the resident workgroups
+ * are the same launch, see MPM_OPT_PART_WGS: which of them is returned is
+ * then a matter of their run-to-run spread.) */
 int mpm_autotune(mpm_ctx* c, int32_t n_steps, int32_t* best);
 
 /* ---- learned closure of the Drucker-Prager cone return (sand) ----------

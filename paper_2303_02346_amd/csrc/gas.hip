@@ -407,22 +407,22 @@ __global__ __launch_bounds__(256) void k_gas_div(GP P, const float* __restrict__
   const float bd = P.dt * P.beta;
 #pragma unroll
   for (int u = 0; u < DIV_U; u++) {
-  const int r = b.r0 + 256 * u + (int)threadIdx.x;
-  if (r >= b.n) break;
-  const int j = row_of(r, P.mz), k = r - j * P.nz;
-  const uint32_t o = (uint32_t)r, ow = o + (uint32_t)j;
-  const float ur = (i + 1 < P.nx) ? ld32(u0 + pu, o) : 0.f;
-  const float ul = (i > 0) ? ld32(u0, o) : 0.f;
-  const float tc = BUOY ? ld32(T0, o) : 0.f;
-  float vt = (j + 1 < P.ny) ? ld32(v0, o + z) : 0.f, vb = (j > 0) ? ld32(v0, o) : 0.f;
-  if (BUOY) {
-    if (j + 1 < P.ny) vt += bd * (0.5f * (tc + ld32(T0, o + z)) - P.t_amb);
-    if (j > 0) vb += bd * (0.5f * (ld32(T0, o - z) + tc) - P.t_amb);
-  }
-  const float wf = (k + 1 < P.nz) ? ld32(w0, ow + 1) : 0.f;
-  const float wb = (k > 0) ? ld32(w0, ow) : 0.f;
-  (f + i * pu)[o] = (ur - ul) + (vt - vb) + (wf - wb);
-  if (psi) (psi + i * pu)[o] = 0.f;
+    const int r = b.r0 + 256 * u + (int)threadIdx.x;
+    if (r >= b.n) break;
+    const int j = row_of(r, P.mz), k = r - j * P.nz;
+    const uint32_t o = (uint32_t)r, ow = o + (uint32_t)j;
+    const float ur = (i + 1 < P.nx) ? ld32(u0 + pu, o) : 0.f;
+    const float ul = (i > 0) ? ld32(u0, o) : 0.f;
+    const float tc = BUOY ? ld32(T0, o) : 0.f;
+    float vt = (j + 1 < P.ny) ? ld32(v0, o + z) : 0.f, vb = (j > 0) ? ld32(v0, o) : 0.f;
+    if (BUOY) {
+      if (j + 1 < P.ny) vt += bd * (0.5f * (tc + ld32(T0, o + z)) - P.t_amb);
+      if (j > 0) vb += bd * (0.5f * (ld32(T0, o - z) + tc) - P.t_amb);
+    }
+    const float wf = (k + 1 < P.nz) ? ld32(w0, ow + 1) : 0.f;
+    const float wb = (k > 0) ? ld32(w0, ow) : 0.f;
+    (f + i * pu)[o] = (ur - ul) + (vt - vb) + (wf - wb);
+    if (psi) (psi + i * pu)[o] = 0.f;
   }
 }
 
@@ -1000,10 +1000,13 @@ struct AdjOut {
 // planes, each handing its i0 + 1 corners to the next through LDS.  The corners
 // at k0 + 1 that no lane took (mostly the last lane's) are carried and handed on
 // in the same way.  Each merge is taken only where the cells do adjoin (the
-// cell's packed index says so).  194 us, 65 of them still the atomics; 261 with
-// the last lane's corners issued as they come, 205 and 210 with 4 x 4 and 4 x 8
-// planes x points, 222 and 244 with 2 x 4 and 8 x 2.  (Columns, not points, are
-// dealt to the lanes, so that rows of any length fill the wavefronts.)
+// cell's packed index says so).  With an adjoint that is non-zero everywhere 506 ->
+// 240 us; over the eight steps back from a loss of 27 cells, where much of it is
+// still zero, 392 -> 197 on average (113 in the first, 215 in the last), 65 of them
+// the atomics, and there 261 with the last lane's corners issued as they come, 205
+// and 210 with 4 x 4 and 4 x 8 planes x points, 222 and 244 with 2 x 4 and 8 x 2.
+// (Columns, not points, are dealt to the lanes, so that rows of any length fill the
+// wavefronts.)
 //
 // ADJ_J points one after the other are a chain, which sets the time of a small
 // grid (12 x 20 x 28, four scalars: 63 us); there a thread takes one point.  The

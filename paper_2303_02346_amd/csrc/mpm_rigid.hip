@@ -16,7 +16,7 @@ namespace {
 inline unsigned nblk(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b); }
 
 // Adds the K values of every row's body into base[body * stride + q].  Each
-// wavefront takes `rows` runs of 64 rows; row(j, v) gives row j's body (or -1)
+// wavefront takes `runs` runs of 64 rows; row(j, v) gives row j's body (or -1)
 // and its values.  Runs that hold one body are summed per lane, and the wavefront
 // is reduced and its atomics issued when the body changes and at the end; of a
 // run that holds several, each is reduced by itself.  (A reduction through LDS
@@ -134,26 +134,26 @@ __global__ __launch_bounds__(256) void k_rigid_rest(PState u, const uint8_t* __r
                                                     double* __restrict__ rest_acc, float* __restrict__ rest) {
   const int N = u.N;
   body_sums<12>(SETUP_RUNS, rest_acc + 4, 16, [&](int j, double* v) {
-  const int b = j < N ? body_of[mat[j]] : -1;
-  if (b >= 0) {
-    const double* S = rest_acc + (size_t)b * 16;
-    const double m = (double)mats[mat[j]].mass;
-    double r[3];
+    const int b = j < N ? body_of[mat[j]] : -1;
+    if (b >= 0) {
+      const double* S = rest_acc + (size_t)b * 16;
+      const double m = (double)mats[mat[j]].mass;
+      double r[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-      const float rf = (float)((double)u.x[a * N + j] - S[1 + a] / S[0]);
-      rest[a * (size_t)N + j] = rf;
-      r[a] = (double)rf;
+      for (int a = 0; a < 3; a++) {
+        const float rf = (float)((double)u.x[a * N + j] - S[1 + a] / S[0]);
+        rest[a * (size_t)N + j] = rf;
+        r[a] = (double)rf;
+      }
+      const double rr = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+#pragma unroll
+      for (int a = 0; a < 3; a++) v[a] = m * r[a];
+#pragma unroll
+      for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) v[3 + a * 3 + c] = m * ((a == c ? rr : 0.0) - r[a] * r[c]);
     }
-    const double rr = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-#pragma unroll
-    for (int a = 0; a < 3; a++) v[a] = m * r[a];
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-      for (int c = 0; c < 3; c++) v[3 + a * 3 + c] = m * ((a == c ? rr : 0.0) - r[a] * r[c]);
-  }
-  return b;
+    return b;
   });
 }
 
@@ -187,29 +187,29 @@ __global__ __launch_bounds__(256) void k_rigid_sum(RigidRows rows, int n_bodies,
                                                    double* __restrict__ acc) {
   const int N = rows.st.N;
   body_sums<RIGID_ACC>(SUM_RUNS, wave_slot(acc, n_bodies), RIGID_ACC, [&](int j, double* v) {
-  uint32_t pid = 0;
-  const int b = row_body(rows, body_of, j, N, pid);
-  if (b >= 0) {
-    const double m = (double)mats[rows.mat[j]].mass;
-    double x[3], vv[3], r[3];
+    uint32_t pid = 0;
+    const int b = row_body(rows, body_of, j, N, pid);
+    if (b >= 0) {
+      const double m = (double)mats[rows.mat[j]].mass;
+      double x[3], vv[3], r[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-      x[a] = (double)rows.st.x[a * (size_t)N + j];
-      vv[a] = (double)rows.st.v[a * (size_t)N + j];
-      r[a] = (double)rest[a * (size_t)N + pid];
+      for (int a = 0; a < 3; a++) {
+        x[a] = (double)rows.st.x[a * (size_t)N + j];
+        vv[a] = (double)rows.st.v[a * (size_t)N + j];
+        r[a] = (double)rest[a * (size_t)N + pid];
+      }
+#pragma unroll
+      for (int a = 0; a < 3; a++) { v[a] = m * x[a]; v[3 + a] = m * vv[a]; }
+#pragma unroll
+      for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) v[6 + a * 3 + c] = m * x[a] * r[c];
+      double xv[3];
+      cross3(x, vv, xv);
+#pragma unroll
+      for (int a = 0; a < 3; a++) v[15 + a] = m * xv[a];
     }
-#pragma unroll
-    for (int a = 0; a < 3; a++) { v[a] = m * x[a]; v[3 + a] = m * vv[a]; }
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-      for (int c = 0; c < 3; c++) v[6 + a * 3 + c] = m * x[a] * r[c];
-    double xv[3];
-    cross3(x, vv, xv);
-#pragma unroll
-    for (int a = 0; a < 3; a++) v[15 + a] = m * xv[a];
-  }
-  return b;
+    return b;
   });
 }
 
@@ -304,39 +304,39 @@ __global__ __launch_bounds__(256) void k_rigid_adj_sum(RigidRows rows, int n_bod
                                                        double* __restrict__ acc) {
   const int N = rows.st.N;
   body_sums<RIGID_ACC>(SUM_RUNS, wave_slot(acc, n_bodies), RIGID_ACC, [&](int j, double* v) {
-  uint32_t pid = 0;
-  int b = row_body(rows, body_of, j, N, pid);
-  const uint32_t jn = (b >= 0 && map) ? map[j] : (uint32_t)j;
-  if (jn >= (uint32_t)N) b = -1;
-  if (b >= 0) {
-    const double* O = rec + (size_t)b * RIGID_REC;
-    double r[3], q[3], xb[3], vb[3];
+    uint32_t pid = 0;
+    int b = row_body(rows, body_of, j, N, pid);
+    const uint32_t jn = (b >= 0 && map) ? map[j] : (uint32_t)j;
+    if (jn >= (uint32_t)N) b = -1;
+    if (b >= 0) {
+      const double* O = rec + (size_t)b * RIGID_REC;
+      double r[3], q[3], xb[3], vb[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-      r[a] = (double)rest[a * (size_t)N + pid];
-      xb[a] = (double)abar[a * (size_t)N + jn];
-      vb[a] = (double)abar[(3 + a) * (size_t)N + jn];
+      for (int a = 0; a < 3; a++) {
+        r[a] = (double)rest[a * (size_t)N + pid];
+        xb[a] = (double)abar[a * (size_t)N + jn];
+        vb[a] = (double)abar[(3 + a) * (size_t)N + jn];
+      }
+#pragma unroll
+      for (int a = 0; a < 3; a++) q[a] = O[RR_R + a * 3] * r[0] + O[RR_R + a * 3 + 1] * r[1] + O[RR_R + a * 3 + 2] * r[2];
+      double Cb[9];
+#pragma unroll
+      for (int k = 0; k < 9; k++) Cb[k] = (double)abar[(6 + k) * (size_t)N + jn];
+      double qv[3], vw[3];
+      cross3(q, vb, qv);
+      cross3(vb, O + RR_W, vw);
+      v[0] = xb[0]; v[1] = xb[1]; v[2] = xb[2];
+      v[3] = vb[0]; v[4] = vb[1]; v[5] = vb[2];
+      v[6] = qv[0] + Cb[7] - Cb[5];
+      v[7] = qv[1] + Cb[2] - Cb[6];
+      v[8] = qv[2] + Cb[3] - Cb[1];
+#pragma unroll
+      for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+          v[9 + a * 3 + c] = (xb[a] + vw[a]) * r[c] + (double)abar[(15 + a * 3 + c) * (size_t)N + jn];
     }
-#pragma unroll
-    for (int a = 0; a < 3; a++) q[a] = O[RR_R + a * 3] * r[0] + O[RR_R + a * 3 + 1] * r[1] + O[RR_R + a * 3 + 2] * r[2];
-    double Cb[9];
-#pragma unroll
-    for (int k = 0; k < 9; k++) Cb[k] = (double)abar[(6 + k) * (size_t)N + jn];
-    double qv[3], vw[3];
-    cross3(q, vb, qv);
-    cross3(vb, O + RR_W, vw);
-    v[0] = xb[0]; v[1] = xb[1]; v[2] = xb[2];
-    v[3] = vb[0]; v[4] = vb[1]; v[5] = vb[2];
-    v[6] = qv[0] + Cb[7] - Cb[5];
-    v[7] = qv[1] + Cb[2] - Cb[6];
-    v[8] = qv[2] + Cb[3] - Cb[1];
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-      for (int c = 0; c < 3; c++)
-        v[9 + a * 3 + c] = (xb[a] + vw[a]) * r[c] + (double)abar[(15 + a * 3 + c) * (size_t)N + jn];
-  }
-  return b;
+    return b;
   });
 }
 

@@ -85,7 +85,8 @@ class Simulator:
         base = self.workspace.data_ptr()
         self._ws_ptr = (base + 255) // 256 * 256
         # the library works on a stream of its own (default priority); every
-        # call first waits for torch's current stream and returns synchronised
+        # call first makes it wait for torch's current stream, and the calls
+        # that compute return synchronised
         self.stream = torch.cuda.Stream(self.device)
         ctx = ctypes.c_void_p()
         _lib.check(L.mpm_create(ctypes.byref(d), ctypes.c_void_p(self._ws_ptr), ctypes.c_size_t(self.ws_bytes),
@@ -93,9 +94,9 @@ class Simulator:
         self.ctx = ctx
         self.buf = torch.zeros(STATE_ROWS, self.N, dtype=torch.float32, device=self.device)
         self.mat = torch.from_numpy(arrs["mat"].astype(np.uint8)).to(self.device)
-        # the scenes' initial state as the buffer holds it, uploaded once:
-        # converting the host arrays for every rollout took longer than the
-        # rollout (6 ms at 250k particles)
+        # the scenes' initial state as the buffer holds it, uploaded once (100
+        # bytes a particle of device memory): converting the host arrays for
+        # every rollout took longer than the rollout (6 ms at 250k particles)
         self._buf0 = torch.from_numpy(self._host_state(arrs)).to(self.device)
         self.actions = torch.zeros(self.horizon, self.S, 6, dtype=torch.float32, device=self.device)
         acts = np.zeros((self.horizon, self.S, 6))
