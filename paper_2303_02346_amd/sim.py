@@ -15,7 +15,7 @@ import numpy as np
 import torch
 
 from . import _lib
-from .scenes import Scene, concat_scenes
+from .scenes import RIGID, Scene, concat_scenes
 
 STATE_ROWS = 25   # x(3) v(3) C(9) F(9) J(1), each row of length N
 
@@ -88,6 +88,8 @@ class Simulator:
         # call first makes it wait for torch's current stream, and the calls
         # that compute return synchronised
         self.stream = torch.cuda.Stream(self.device)
+        self._written = []      # streams of set_state calls that the library's stream has yet to wait for
+        self._rigid = any(m.kind == RIGID for m in mats)
         ctx = ctypes.c_void_p()
         _lib.check(L.mpm_create(ctypes.byref(d), ctypes.c_void_p(self._ws_ptr), ctypes.c_size_t(self.ws_bytes),
                                 ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(ctx)), "mpm_create")
@@ -111,7 +113,12 @@ class Simulator:
         self.set_option(_lib.MPM_OPT_ADJOINT, 1 if adjoint == "plain" else 0)
 
     def _sync_in(self):
-        self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        current = torch.cuda.current_stream(self.device)
+        self.stream.wait_stream(current)
+        for s in self._written:
+            if s != current:
+                self.stream.wait_stream(s)
+        self._written.clear()
 
     def set_option(self, key: int, value: int):
         _lib.check(_lib.lib().mpm_set_option(self.ctx, int(key), int(value)), "mpm_set_option")
@@ -202,9 +209,16 @@ class Simulator:
         self.set_actions(self.actions)
 
     def set_state(self):
-        # (the state may have been written on this stream, and the step that
-        # reads it may be called under another)
-        self._sync_in()
+        # the state may have been written on this stream and the next call be
+        # made under another one: that call waits for both (a wait here cost
+        # 25 us of a one-step call's 140).  At once where this call reads the
+        # state (rigid bodies' rest shapes), or where the stream is the
+        # caller's own (its id is its handle) and may be gone by then
+        s = torch.cuda.current_stream(self.device)
+        if self._rigid or s.stream_id == s.cuda_stream != 0:
+            self._sync_in()
+        elif s not in self._written:
+            self._written.append(s)
         self._state = self.state_struct()
         _lib.check(_lib.lib().mpm_set_state(self.ctx, ctypes.byref(self._state)), "mpm_set_state", self.ctx)
 

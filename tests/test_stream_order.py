@@ -11,44 +11,88 @@ from paper_2303_02346_amd import _lib, gas as gas_mod, scenes, sim as sim_mod
 
 
 class Recorder:
-    """A library, stream or tensor that notes every call on it."""
+    """A library that notes every call on it."""
 
-    def __init__(self, log, name):
-        self._log, self._name = log, name
+    def __init__(self, log):
+        self._log = log
 
     def __getattr__(self, what):
         def call(*a, **k):
-            self._log.append(f"{self._name}.{what}")
+            self._log.append(what)
             return 0
         return call
 
 
-def simulator_stub(monkeypatch):
+class Stream:
+    """A stream that notes what it waits for and when the host waits for it."""
+
+    def __init__(self, log, name, stream_id=33, cuda_stream=0x1000):
+        self._log, self._name, self.stream_id, self.cuda_stream = log, name, stream_id, cuda_stream
+
+    def wait_stream(self, other):
+        self._log.append(f"{self._name} waits for {other._name}")
+
+    def synchronize(self):
+        self._log.append(f"host waits for {self._name}")
+
+
+def simulator_stub(monkeypatch, rigid=False):
+    """A simulator on stand-ins, its log, and a function that makes a stream
+    current."""
     log = []
     sim = object.__new__(sim_mod.Simulator)
     sim.ctx, sim.device = types.SimpleNamespace(value=0), torch.device("cpu")
     sim.mat, sim.buf = torch.zeros(4, dtype=torch.uint8), torch.zeros(sim_mod.STATE_ROWS, 4)
-    sim.stream = Recorder(log, "library_stream")
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Recorder(log, "current_stream"))
-    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log, "lib"))
-    return sim, log
+    sim.stream, sim._written, sim._rigid = Stream(log, "library"), [], rigid
+    current = [Stream(log, "a")]
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: current[0])
+    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log))
+
+    def use(stream):
+        current[0] = stream
+    return sim, log, use
 
 
-def test_set_state_joins_the_current_stream(monkeypatch):
-    """The state may have been written on the stream that is current at the
-    call, and the step that reads it may follow under another one."""
-    sim, log = simulator_stub(monkeypatch)
+def test_state_set_under_another_stream_is_waited_for(monkeypatch):
+    """The state may have been written on the stream that is current at
+    set_state, and the step that reads it follow under another one."""
+    sim, log, use = simulator_stub(monkeypatch)
     sim.set_state()
-    assert log == ["library_stream.wait_stream", "lib.mpm_set_state"]
+    use(Stream(log, "b"))
+    sim.set_state()
+    use(Stream(log, "c"))
+    sim.step(1)
+    assert log[:2] == ["mpm_set_state"] * 2 and log[-1] == "mpm_step"
+    assert sorted(log[2:-1]) == [f"library waits for {s}" for s in "abc"]
+    del log[:]
+    sim.step(1)                  # (once)
+    assert log == ["library waits for c", "mpm_step"]
+
+
+def test_state_set_under_the_stream_of_the_step_is_waited_for_once(monkeypatch):
+    sim, log, use = simulator_stub(monkeypatch)
+    sim.set_state()
+    sim.step(1)
+    assert log == ["mpm_set_state", "library waits for a", "mpm_step"]
+
+
+@pytest.mark.parametrize("rigid,stream", [(True, {}), (False, {"stream_id": 0x1000})])
+def test_state_is_waited_for_at_once(monkeypatch, rigid, stream):
+    """Rest shapes are taken from the state by set_state itself; a stream of
+    the caller's own may be destroyed before the step."""
+    sim, log, use = simulator_stub(monkeypatch, rigid)
+    use(Stream(log, "own", **stream))
+    sim.set_state()
+    assert log == ["library waits for own", "mpm_set_state"]
 
 
 def test_load_waits_for_its_copy(monkeypatch):
     """The initial state is kept on the device, and a copy within the device
     returns before it is done."""
-    sim, log = simulator_stub(monkeypatch)
+    sim, log, _ = simulator_stub(monkeypatch)
     sim._buf0 = torch.ones(sim_mod.STATE_ROWS, 4)
     sim.load()
-    assert torch.equal(sim.buf, sim._buf0) and log == ["current_stream.synchronize"]
+    assert torch.equal(sim.buf, sim._buf0) and log == ["host waits for a"]
 
 
 def test_rollouts_restore_their_state_through_load_and_reset():
@@ -70,14 +114,14 @@ def test_gas_reset_waits_for_its_transfers(monkeypatch):
     sim = object.__new__(gas_mod.GasSim)
     sim.ctx, sim.device = types.SimpleNamespace(value=0), torch.device("cpu")
     sim.buf, sim.actions = torch.zeros(4), torch.zeros(2, 6)
-    sim.stream = Recorder(log, "library_stream")
+    sim.stream = Stream(log, "library")
     for name in ("load", "set_actions"):
         monkeypatch.setattr(sim, name, lambda *a, n=name: log.append(n), raising=False)
     monkeypatch.setattr(sim, "struct", lambda buf: _lib.GasState(), raising=False)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Recorder(log, "current_stream"))
-    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log, "lib"))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream(log, "a"))
+    monkeypatch.setattr(_lib, "lib", lambda: Recorder(log))
     sim.reset()
-    assert log.index("current_stream.synchronize") > log.index("load")
+    assert log.index("host waits for a") > log.index("load")
 
 
 def delayed(stream):
@@ -101,7 +145,6 @@ def test_state_written_on_another_stream_is_the_one_stepped():
     with torch.cuda.stream(other):
         sim.buf.copy_(start)
         sim.set_state()
-    sim.set_actions(sim.actions)
     sim.step(4)
     # (the sums' order differs from run to run)
     assert torch.allclose(sim.buf, ref, rtol=0, atol=1e-5 * float(ref.abs().max()))
