@@ -282,10 +282,8 @@ constexpr int XS = 12;
 constexpr size_t SCR_BYTES = 2 * MLP_H * 4 + XS * 4 + 2 * MLP_H * 2;   // per sample, without the loss
 static_assert(SCR_BYTES % 16 == 0, "alignment of the arrays");
 __host__ __device__ constexpr size_t scratch_bytes(size_t nb) { return nb * SCR_BYTES + (nb + 15) / 16 * 8; }
-// (the arrays are read and written in 16-byte words; a caller's scratch may start anywhere)
-constexpr size_t SCR_ALIGN = 16;
 __host__ __device__ inline BatchScratch scratch_of(void* base, size_t nb) {
-  char* p = (char*)(((uintptr_t)base + SCR_ALIGN - 1) & ~(uintptr_t)(SCR_ALIGN - 1));
+  char* p = (char*)base;
   BatchScratch S;
   S.d1 = (float*)p; p += nb * MLP_H * 4;
   S.d2 = (float*)p; p += nb * MLP_H * 4;
@@ -563,6 +561,12 @@ static void* noalloc_scratch(int dev) {
 
 extern "C" {
 
+// The arrays are read and written in 16-byte words, but a caller's scratch may
+// start anywhere.  (Aligned here and not in the kernels: a pointer made from an
+// integer there is no longer known to be global, and its loads become flat ones.)
+constexpr size_t SCR_ALIGN = 16;
+static void* aligned_scratch(void* p) { return (void*)(((uintptr_t)p + SCR_ALIGN - 1) & ~(uintptr_t)(SCR_ALIGN - 1)); }
+
 size_t mpm_mlp_state_bytes(void) { return mlp_layout().total; }
 
 size_t mpm_mlp_scratch_bytes(int32_t batch) {
@@ -635,7 +639,8 @@ int mpm_mlp_grad(void* state_dev, const float* samples_dev, int64_t n, int32_t b
                  float* grad_out_dev, double* loss_out_host, void* stream) {
   if (!state_dev || !samples_dev || n < 1 || batch < 1 || !scratch_dev || !grad_out_dev) return MPM_EINVAL;
   const int nb = (int)(n < batch ? n : batch);
-  return grad_impl(state_dev, samples_dev, n, nb, scratch_dev, grad_out_dev, loss_out_host, (hipStream_t)stream);
+  return grad_impl(state_dev, samples_dev, n, nb, aligned_scratch(scratch_dev), grad_out_dev, loss_out_host,
+                   (hipStream_t)stream);
 }
 
 int mpm_mlp_grad_noalloc(void* state_dev, const float* samples_dev, int64_t n, int32_t batch, float* grad_out_dev,
@@ -654,6 +659,7 @@ int mpm_mlp_train(void* state_dev, const float* samples_dev, int64_t n, int32_t 
                   uint64_t seed, void* scratch_dev, double* loss_hist_host, void* stream) {
   if (!state_dev || !samples_dev || n < 1 || batch < 1 || epochs < 1 || !scratch_dev || !(lr > 0.f)) return MPM_EINVAL;
   hipStream_t s = (hipStream_t)stream;
+  scratch_dev = aligned_scratch(scratch_dev);
   MlpLayout L = mlp_layout();
   char* st = (char*)state_dev;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
