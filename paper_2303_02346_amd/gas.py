@@ -140,6 +140,8 @@ class GasSim:
                     at += src.size
                     q ^= 1
 
+    _step_follows = False      # in a rollout, whose step waits for what reset() left to do
+
     def reset(self):
         """The scene's initial state (there for every stream when the call
         returns), t = 0 and the scene's actions."""
@@ -148,7 +150,8 @@ class GasSim:
         self._state = self.struct(self.buf)
         self._check(_lib.lib().gas_set_state(self.ctx, ctypes.byref(self._state)), "gas_set_state")
         self.set_actions(self.actions)
-        torch.cuda.current_stream(self.device).synchronize()   # (load's transfers)
+        if not self._step_follows:
+            torch.cuda.current_stream(self.device).synchronize()   # (load's transfers)
 
     def set_actions(self, actions: torch.Tensor, t0: int = 0):
         a = actions.to(self.device, torch.float32).reshape(-1, 6).contiguous()
@@ -233,7 +236,11 @@ class GasRollout(torch.autograd.Function):
     def forward(ctx, actions: torch.Tensor, sim: GasSim):
         if not sim.requires_grad:
             raise ValueError("GasRollout needs a GasSim created with requires_grad=True")
-        sim.reset()
+        sim._step_follows = True
+        try:
+            sim.reset()
+        finally:
+            sim._step_follows = False
         sim.set_actions(actions.detach())
         sim.step(actions.shape[0])
         ctx.sim = sim

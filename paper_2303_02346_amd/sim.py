@@ -185,6 +185,8 @@ class Simulator:
                              self.mat.data_ptr() if with_mat else None)
 
     # ---- calls -------------------------------------------------------------
+    _step_follows = False      # in a rollout, whose step waits for what load() left to do
+
     def _host_state(self, a) -> np.ndarray:
         N = self.N
         host = np.empty((STATE_ROWS, N), np.float32)
@@ -201,7 +203,8 @@ class Simulator:
         The state is there when the call returns, for every stream."""
         self.buf.copy_(self._buf0 if arrs is None else torch.from_numpy(self._host_state(arrs)))
         # (a copy within the device only waits for its own stream)
-        torch.cuda.current_stream(self.device).synchronize()
+        if not self._step_follows:
+            torch.cuda.current_stream(self.device).synchronize()
 
     def reset(self, arrs=None):
         self.load(arrs)
@@ -352,7 +355,11 @@ class MpmRollout(torch.autograd.Function):
     def forward(ctx, actions: torch.Tensor, sim: Simulator):
         if not sim.requires_grad:
             raise ValueError("MpmRollout needs a Simulator created with requires_grad=True")
-        sim.load()
+        sim._step_follows = True
+        try:
+            sim.load()
+        finally:
+            sim._step_follows = False
         sim.set_state()
         sim.set_actions(actions.detach())
         sim.step(actions.shape[0])

@@ -95,16 +95,29 @@ def test_load_waits_for_its_copy(monkeypatch):
     assert torch.equal(sim.buf, sim._buf0) and log == ["host waits for a"]
 
 
-def test_rollouts_restore_their_state_through_load_and_reset():
-    """(a program that starts its rollouts elsewhere overrides these)"""
-    for function, restore in ((sim_mod.MpmRollout, "load"), (gas_mod.GasRollout, "reset")):
-        log = []
-        state = types.SimpleNamespace(requires_grad=True, x=torch.zeros(3, 4), v=torch.zeros(3, 4), buf=torch.zeros(25, 4),
-                                      _buf0=torch.zeros(25, 4))
-        for name in ("load", "reset", "set_state", "set_actions", "step"):
-            setattr(state, name, lambda *a, n=name: log.append(n))
+@pytest.mark.parametrize("function,restore", [(sim_mod.MpmRollout, "load"), (gas_mod.GasRollout, "reset")])
+def test_rollouts_restore_their_state_through_load_and_reset(function, restore):
+    """(a program that starts its rollouts elsewhere overrides these)  Their
+    wait is left out there, and only there: the step waits."""
+    log = []
+    state = types.SimpleNamespace(requires_grad=True, x=torch.zeros(3, 4), v=torch.zeros(3, 4), buf=torch.zeros(25, 4),
+                                  _buf0=torch.zeros(25, 4), _step_follows=False)
+
+    def note(name, fail=False):
+        def call(*a):
+            log.append((name, state._step_follows))
+            if fail:
+                raise RuntimeError(name)
+        return call
+
+    for name in ("load", "reset", "set_state", "set_actions", "step"):
+        setattr(state, name, note(name))
+    function.forward(types.SimpleNamespace(), torch.zeros(2, 1, 6), state)
+    assert log[0] == (restore, True) and log[-2:] == [("set_actions", False), ("step", False)]
+    setattr(state, restore, note(restore, fail=True))
+    with pytest.raises(RuntimeError):
         function.forward(types.SimpleNamespace(), torch.zeros(2, 1, 6), state)
-        assert log[0] == restore and log[-2:] == ["set_actions", "step"]
+    assert not state._step_follows
 
 
 def test_gas_reset_waits_for_its_transfers(monkeypatch):
