@@ -1758,21 +1758,24 @@ int gas_create(const gas_desc* d, void* workspace_dev, size_t ws_bytes, void* st
     for (int a = 0; a < 3; a++) {
       const int n = nn[a];
       // as fragments [output tile][step][lane (lr, lc)][t]: term 16 step + 4 t + lr,
-      // output 16 tile + lc (forward: rows i, outputs k; inverse: rows k, outputs
-      // i); zero past n
+      // output 16 tile + lc (forward: terms i, outputs k; inverse: terms k, outputs
+      // i); zero past n.  Every cosine is computed once, for its place in both
+      // (computed for each, a room with an axis of 1024 took 20 ms to create, not 11).
       const int st = axis_steps(n);
+      auto place = [](int o, int term) { return ((term & 3) * 16 + o) * 4 + (term >> 2); };
       std::vector<float> C((size_t)st * st * 256, 0.f), Ci(C.size(), 0.f), lam(n);
-      size_t q = 0;
-      for (int m = 0; m < st; m++)
-        for (int sp = 0; sp < st; sp++)
-          for (int ln = 0; ln < 64; ln++)
-            for (int tt = 0; tt < 4; tt++, q++) {
-              const int term = 16 * sp + 4 * tt + (ln >> 4), o = 16 * m + (ln & 15);
-              if (term >= n || o >= n) continue;
-              const double vf = cos(M_PI * o * (term + 0.5) / n), vi = cos(M_PI * term * (o + 0.5) / n);
-              C[q] = (float)vf;
-              Ci[q] = (float)(vi * (term == 0 ? 1.0 / n : 2.0 / n));
+      for (int kt = 0; kt < st; kt++)
+        for (int it = 0; it < st; it++) {
+          float* f = C.data() + ((size_t)kt * st + it) * 256;
+          float* fi = Ci.data() + ((size_t)it * st + kt) * 256;
+          for (int dk = 0; dk < 16 && 16 * kt + dk < n; dk++)
+            for (int di = 0; di < 16 && 16 * it + di < n; di++) {
+              const int k = 16 * kt + dk, i = 16 * it + di;
+              const double v = cos(M_PI * k * (i + 0.5) / n);
+              f[place(dk, di)] = (float)v;
+              fi[place(di, dk)] = (float)(v * (k == 0 ? 1.0 / n : 2.0 / n));
             }
+        }
       for (int k = 0; k < n; k++) {
         const double sk = sin(M_PI * k / (2.0 * n));
         lam[k] = (float)(-4.0 * sk * sk);
