@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <mutex>
 #include <vector>
 
 namespace mpm {
@@ -119,13 +120,59 @@ struct KernelTimer {
   }
 };
 
+// Pinned host words for contexts, 64 of them (one a cache line) per page.  Words
+// come back when a context is destroyed and pages are kept: freeing pinned memory
+// waits for the device and breaks a graph capture that is under way anywhere in the
+// process, and contexts may be destroyed at any time.  The pool holds as many pages
+// as the most contexts alive at once needed, and lives as long as the process.
+class HostWords {
+ public:
+  int* take() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (free_.empty()) {
+      char* page = nullptr;
+      free_.reserve(words_ + PER_PAGE);   // (so that give() never allocates)
+      if (hipHostMalloc((void**)&page, PER_PAGE * STRIDE, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();   // (the caller reports it)
+        return nullptr;
+      }
+      words_ += PER_PAGE;
+      for (size_t w = 0; w < PER_PAGE; w++) free_.push_back((int*)(page + w * STRIDE));
+    }
+    int* p = free_.back();
+    free_.pop_back();
+    return p;
+  }
+  void give(int* p) {
+    std::lock_guard<std::mutex> lock(mu_);
+    free_.push_back(p);
+  }
+  static HostWords& pool() {
+    static HostWords* w = new HostWords;
+    return *w;
+  }
+
+ private:
+  static constexpr size_t PER_PAGE = 64, STRIDE = 64;
+  std::mutex mu_;
+  std::vector<int*> free_;
+  size_t words_ = 0;
+};
+
 // A device error word's copy in pinned host memory: read after a stream has been
 // waited for, without the staged (and blocking) copy that pageable memory takes.
 struct HostWord {
   int* p = nullptr;
-  bool create() { return hipHostMalloc((void**)&p, sizeof(int), hipHostMallocDefault) == hipSuccess; }
+  bool create() {
+    try {
+      p = HostWords::pool().take();
+    } catch (...) {   // (nothing is thrown across the C boundary)
+      p = nullptr;
+    }
+    return p != nullptr;
+  }
   void destroy() {
-    if (p) (void)hipHostFree(p);
+    if (p) HostWords::pool().give(p);
     p = nullptr;
   }
 };
